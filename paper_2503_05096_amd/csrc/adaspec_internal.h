@@ -54,7 +54,11 @@ inline int attn_row_groups(int max_rows)
     return max_rows > r ? (max_rows + r - 1) / r : 1;
 }
 
-AttnPlan make_attn_plan(const adaspec_attn_dims &d, bool fast_path);
+// Which kernel family a call takes.  ADASPEC_PATH_FAST names the head_dim 128 form; AUTO also reaches the others.
+enum class AttnKind { kVector, kMfma128, kMfma64 };
+constexpr int kAttnD64Block = 64;   // tokens per block of the head_dim 64 form (attn_d64.hip)
+AttnKind attn_kind(const adaspec_attn_dims &d);
+AttnPlan make_attn_plan(const adaspec_attn_dims &d, AttnKind kind);
 bool attn_fast_path_supported(const adaspec_attn_dims &d);
 
 struct AttnArgs {
@@ -79,7 +83,7 @@ constexpr int kMaxSchedW = 1024;
 constexpr int64_t kMaxAttnItems = (int64_t)1 << 24;   // (request, split) work items of one attention call
 
 // Fills sched_w / n_row_groups / rows_per_group for the matrix-core kernel's launch of a.dims.
-void attn_mfma_shape(AttnArgs &a);
+void attn_mfma_shape(AttnArgs &a, AttnKind kind);
 
 hipError_t launch_attn_plan(const AttnArgs &a);
 // tree verification: ancestor masks of all query rows (after the plan kernel: it reads cu_q)
@@ -89,6 +93,9 @@ hipError_t launch_attn_mfma(const AttnArgs &a);
 // row-split form for units of more than 32 rows (attn_rows.hip); launch_attn_mfma forwards to it
 hipError_t launch_attn_rows(const AttnArgs &a);
 int attn_rows_grid_slots(const AttnArgs &a, int cus);   // resident workgroups = columns of the schedule table
+// head_dim 64 (attn_d64.hip)
+hipError_t launch_attn_d64(const AttnArgs &a);
+int attn_d64_grid_slots(const AttnArgs &a, int cus);
 hipError_t launch_attn_combine(const AttnArgs &a);
 
 // ---- accept workspace ------------------------------------------------------

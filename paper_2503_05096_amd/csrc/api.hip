@@ -92,23 +92,28 @@ static int validate_attn_dims(const adaspec_attn_dims *d)
     return ADASPEC_OK;
 }
 
-static bool attn_use_fast(const adaspec_attn_dims &d)
+AttnKind attn_kind(const adaspec_attn_dims &d)
 {
-    if (d.path == ADASPEC_PATH_VECTOR) return false;
-    return attn_fast_path_supported(d);
+    if (d.path == ADASPEC_PATH_VECTOR) return AttnKind::kVector;
+    if (attn_fast_path_supported(d)) return AttnKind::kMfma128;
+    // head_dim 64 in 16 bits: the vector kernel is never ahead (MI355X, whole call, bf16, 32/8 heads: 64 requests of
+    // 256-4096 tokens 1024 us against 65 us) and its fp32 accumulator is further from 64 bits (3.4e-7 against 2.4e-7)
+    if (d.dtype != ADASPEC_F32 && d.head_dim == 64) return AttnKind::kMfma64;
+    return AttnKind::kVector;
 }
 
-AttnPlan make_attn_plan(const adaspec_attn_dims &d, bool fast_path)
+AttnPlan make_attn_plan(const adaspec_attn_dims &d, AttnKind kind)
 {
     AttnPlan p;
     const int G = d.n_q_heads / d.n_kv_heads;
+    const bool scheduled = kind != AttnKind::kVector;      // units handed out by the schedule table
     // The matrix-core kernel runs 4 wavefronts per work item, each over up to 256
     // tokens, and merges them on chip; the vector kernel runs one wavefront per
     // item.  With few (request, kv head) pairs the splits are shortened so that
     // the chip still sees enough independent items.
     const int64_t pairs = (int64_t)d.batch * d.n_kv_heads;
-    if (fast_path) {
-        p.block_tokens = 32;
+    if (scheduled) {
+        p.block_tokens = kind == AttnKind::kMfma64 ? kAttnD64Block : 32;
         p.split_tokens = pairs >= 512 ? 2048 : (pairs >= 256 ? 2048 : (pairs >= 128 ? 1024 : (pairs >= 32 ? 512 : 256)));
     } else {
         p.block_tokens = 64;
@@ -128,7 +133,7 @@ AttnPlan make_attn_plan(const adaspec_attn_dims &d, bool fast_path)
     p.off_row_rec = off;    off = align_up(off + (size_t)(d.total_q > 0 ? d.total_q : 1) * 16, 256);
     {   // schedule table: every unit appears once, every round is W <= kMaxSchedW wide
         const size_t units = (size_t)p.max_items * d.n_kv_heads * attn_row_groups(p.max_rows);
-        p.off_sched = off;  off = align_up(off + (fast_path ? units + kMaxSchedW : 1) * 4, 256);
+        p.off_sched = off;  off = align_up(off + (scheduled ? units + kMaxSchedW : 1) * 4, 256);
     }
     p.off_anc = off;        off = align_up(off + (size_t)(d.total_q > 0 ? d.total_q : 1) * 8, 256);
     p.off_part_ml = off;
@@ -184,7 +189,7 @@ extern "C" {
 size_t adaspec_verify_attn_workspace_bytes(const adaspec_attn_dims *dims)
 {
     if (validate_attn_dims(dims) != ADASPEC_OK) return 0;
-    return make_attn_plan(*dims, attn_use_fast(*dims)).total_bytes;
+    return make_attn_plan(*dims, attn_kind(*dims)).total_bytes;
 }
 
 // chain (parents == NULL, tree == false) and tree verification share everything but the mask
@@ -206,8 +211,8 @@ static int verify_attn_impl(const void *q, const void *k_pages, const void *v_pa
     if (!plan_only && (!aligned16(q) || !aligned16(k_pages) || !aligned16(v_pages) || !aligned16(out)))
         return ADASPEC_ERR_ALIGN;
     AttnArgs a;
-    const bool fast = attn_use_fast(*dims);
-    a.plan = make_attn_plan(*dims, fast);
+    const AttnKind kind = attn_kind(*dims);
+    a.plan = make_attn_plan(*dims, kind);
     if (workspace_bytes < a.plan.total_bytes) return ADASPEC_ERR_WORKSPACE;
     a.q = q; a.k_pages = k_pages; a.v_pages = v_pages;
     a.block_table = block_table; a.ctx_lens = ctx_lens; a.spec_lens = spec_lens;
@@ -217,14 +222,15 @@ static int verify_attn_impl(const void *q, const void *k_pages, const void *v_pa
     const float scale = dims->scale > 0.0f ? dims->scale : 1.0f / sqrtf((float)dims->head_dim);
     a.scale_log2 = scale * 1.4426950408889634f;
 
-    if (fast) attn_mfma_shape(a);
+    if (kind != AttnKind::kVector) attn_mfma_shape(a, kind);
     if (dims->plan_mode != ADASPEC_PLAN_REUSE) {
         if (launch_attn_plan(a) != hipSuccess) return ADASPEC_ERR_HIP;
         if (tree && launch_tree_masks(a) != hipSuccess) return ADASPEC_ERR_HIP;
     }
     if (plan_only) return ADASPEC_OK;
     if (!record_event(dims->timing_start, dims->timing_stop, true, a.stream)) return ADASPEC_ERR_HIP;
-    hipError_t e = fast ? launch_attn_mfma(a) : launch_attn_vector(a);
+    hipError_t e = kind == AttnKind::kVector ? launch_attn_vector(a)
+                   : kind == AttnKind::kMfma64 ? launch_attn_d64(a) : launch_attn_mfma(a);
     if (e != hipSuccess) return ADASPEC_ERR_HIP;
     if (!record_event(dims->timing_start, dims->timing_stop, false, a.stream)) return ADASPEC_ERR_HIP;
     if (launch_attn_combine(a) != hipSuccess) return ADASPEC_ERR_HIP;

@@ -456,7 +456,7 @@ static void with_instance(int dtype, int rt, bool tree, F &&f)
     else with_tree(BF16{});
 }
 
-void attn_mfma_shape(AttnArgs &a)
+void attn_mfma_shape(AttnArgs &a, AttnKind kind)
 {
     const AttnPlan &p = a.plan;
     const int rt = attn_row_tiles(p.max_rows);
@@ -464,7 +464,9 @@ void attn_mfma_shape(AttnArgs &a)
     a.rows_per_group = 16 * rt;
     const int64_t max_units = (int64_t)p.max_items * a.dims.n_kv_heads * a.n_row_groups;
     int slots = 1;
-    if (rt > 2) {
+    if (kind == AttnKind::kMfma64) {
+        slots = attn_d64_grid_slots(a, device_cus());
+    } else if (rt > 2) {
         slots = attn_rows_grid_slots(a, device_cus());               // more than 32 rows: the row-split kernel
         if (slots <= 0) slots = device_cus();
     } else {
