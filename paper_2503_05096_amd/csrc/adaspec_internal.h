@@ -32,6 +32,14 @@ struct AttnPlan {
     size_t off_part_ml;     // float[max_items][Hkv][max_rows][2]  (m in log2 units, l)
     size_t off_part_o;      // float[max_items][Hkv][max_rows][d]
     size_t total_bytes;
+    bool direct;            // small chain calls: one workgroup per possible unit, no metadata kernel (attn_mfma_common.h)
+    int per_req;            // possible splits per request: ceil(max_pages_per_req * page_size / split_tokens)
+};
+
+// What a kernel of a direct call needs to find its unit by itself.
+struct DirectArgs {
+    const int32_t *ctx_lens, *spec_lens;
+    int batch, max_spec_len, total_q, per_req, split_tokens;
 };
 
 // Length of every split of a request with L cached tokens cut into ns splits.
@@ -55,7 +63,7 @@ inline int attn_row_groups(int max_rows)
 }
 
 // Which kernel family a call takes.  ADASPEC_PATH_FAST names the head_dim 128 form; AUTO also reaches the others.
-enum class AttnKind { kVector, kMfma128, kMfma64 };
+enum class AttnKind { kVector, kMfma128, kMfma64, kMfmaF32 };
 constexpr int kAttnD64Block = 64;   // tokens per block of the head_dim 64 form (attn_d64.hip)
 AttnKind attn_kind(const adaspec_attn_dims &d);
 AttnPlan make_attn_plan(const adaspec_attn_dims &d, AttnKind kind);
@@ -76,7 +84,13 @@ struct AttnArgs {
     int sched_cus = 1;        // compute units of the device
     int n_row_groups = 1;     // units per (item, kv head)
     int rows_per_group = 16;  // query rows (times G) one unit covers
+    bool direct = false;      // plan.direct and a chain call
 };
+
+inline DirectArgs direct_args(const AttnArgs &a)
+{
+    return DirectArgs{a.ctx_lens, a.spec_lens, a.dims.batch, a.dims.max_spec_len, a.dims.total_q, a.plan.per_req, a.plan.split_tokens};
+}
 
 // Upper bound on W for which the workspace holds a schedule table.
 constexpr int kMaxSchedW = 1024;
@@ -96,6 +110,9 @@ int attn_rows_grid_slots(const AttnArgs &a, int cus);   // resident workgroups =
 // head_dim 64 (attn_d64.hip)
 hipError_t launch_attn_d64(const AttnArgs &a);
 int attn_d64_grid_slots(const AttnArgs &a, int cus);
+// fp32, head_dim 64 or 128 (attn_f32.hip)
+hipError_t launch_attn_f32(const AttnArgs &a);
+int attn_f32_grid_slots(const AttnArgs &a, int cus);
 hipError_t launch_attn_combine(const AttnArgs &a);
 
 // ---- accept workspace ------------------------------------------------------

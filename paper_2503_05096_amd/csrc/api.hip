@@ -92,6 +92,12 @@ static int validate_attn_dims(const adaspec_attn_dims *d)
     return ADASPEC_OK;
 }
 
+// Direct calls (no metadata kernel): at most this many requests (the combine kernel finds a row's request with one scan
+// of four per lane) and possible units (two workgroups per compute unit: all resident at once, nothing to balance).
+constexpr int kDirectMaxBatch = 256;
+constexpr int kDirectMaxUnits = 512;
+constexpr int kWavesPerUnit = 4;
+
 AttnKind attn_kind(const adaspec_attn_dims &d)
 {
     if (d.path == ADASPEC_PATH_VECTOR) return AttnKind::kVector;
@@ -99,6 +105,9 @@ AttnKind attn_kind(const adaspec_attn_dims &d)
     // head_dim 64 in 16 bits: the vector kernel is never ahead (MI355X, whole call, bf16, 32/8 heads: 64 requests of
     // 256-4096 tokens 1024 us against 65 us) and its fp32 accumulator is further from 64 bits (3.4e-7 against 2.4e-7)
     if (d.dtype != ADASPEC_F32 && d.head_dim == 64) return AttnKind::kMfma64;
+    // fp32 at these head dims: likewise (4 requests of 128-512 tokens, 8 heads of 64: 109 us against 19 us, of which
+    // the GPU works 10; error against 64 bits 3.7e-7 against 2.1e-7)
+    if (d.dtype == ADASPEC_F32 && (d.head_dim == 64 || d.head_dim == 128)) return AttnKind::kMfmaF32;
     return AttnKind::kVector;
 }
 
@@ -113,14 +122,26 @@ AttnPlan make_attn_plan(const adaspec_attn_dims &d, AttnKind kind)
     // the chip still sees enough independent items.
     const int64_t pairs = (int64_t)d.batch * d.n_kv_heads;
     if (scheduled) {
-        p.block_tokens = kind == AttnKind::kMfma64 ? kAttnD64Block : 32;
+        p.block_tokens = kind == AttnKind::kMfma64 ? kAttnD64Block : (kind == AttnKind::kMfmaF32 ? 16 : 32);
         p.split_tokens = pairs >= 512 ? 2048 : (pairs >= 256 ? 2048 : (pairs >= 128 ? 1024 : (pairs >= 32 ? 512 : 256)));
     } else {
         p.block_tokens = 64;
         p.split_tokens = 256;
     }
     const int64_t max_ctx = (int64_t)d.max_pages_per_req * d.page_size;
+    p.direct = false;
+    if (kind == AttnKind::kMfmaF32 && d.batch <= kDirectMaxBatch) {
+        // Small batches: the shortest split (one block per wavefront or more) with which all possible units are
+        // resident at once; such a call needs no metadata kernel.
+        const int64_t per_item = (int64_t)d.n_kv_heads * attn_row_groups((d.max_spec_len + 1) * G);
+        for (int s = kWavesPerUnit * p.block_tokens; s <= 2048 && !p.direct; s *= 2)
+            if (d.batch * ((max_ctx + s - 1) / s) * per_item <= kDirectMaxUnits) {
+                p.direct = true;
+                p.split_tokens = s;
+            }
+    }
     const int64_t per_req = (max_ctx + p.split_tokens - 1) / p.split_tokens;
+    p.per_req = (int)per_req;
     p.max_items = (int)((int64_t)d.batch * per_req);
     p.max_rows = (d.max_spec_len + 1) * G;
     size_t off = 0;
@@ -222,15 +243,17 @@ static int verify_attn_impl(const void *q, const void *k_pages, const void *v_pa
     const float scale = dims->scale > 0.0f ? dims->scale : 1.0f / sqrtf((float)dims->head_dim);
     a.scale_log2 = scale * 1.4426950408889634f;
 
+    a.direct = a.plan.direct && !tree;
     if (kind != AttnKind::kVector) attn_mfma_shape(a, kind);
-    if (dims->plan_mode != ADASPEC_PLAN_REUSE) {
+    if (dims->plan_mode != ADASPEC_PLAN_REUSE && !a.direct) {
         if (launch_attn_plan(a) != hipSuccess) return ADASPEC_ERR_HIP;
         if (tree && launch_tree_masks(a) != hipSuccess) return ADASPEC_ERR_HIP;
     }
     if (plan_only) return ADASPEC_OK;
     if (!record_event(dims->timing_start, dims->timing_stop, true, a.stream)) return ADASPEC_ERR_HIP;
     hipError_t e = kind == AttnKind::kVector ? launch_attn_vector(a)
-                   : kind == AttnKind::kMfma64 ? launch_attn_d64(a) : launch_attn_mfma(a);
+                   : kind == AttnKind::kMfma64 ? launch_attn_d64(a)
+                   : kind == AttnKind::kMfmaF32 ? launch_attn_f32(a) : launch_attn_mfma(a);
     if (e != hipSuccess) return ADASPEC_ERR_HIP;
     if (!record_event(dims->timing_start, dims->timing_stop, false, a.stream)) return ADASPEC_ERR_HIP;
     if (launch_attn_combine(a) != hipSuccess) return ADASPEC_ERR_HIP;

@@ -463,8 +463,15 @@ void attn_mfma_shape(AttnArgs &a, AttnKind kind)
     a.n_row_groups = attn_row_groups(p.max_rows);
     a.rows_per_group = 16 * rt;
     const int64_t max_units = (int64_t)p.max_items * a.dims.n_kv_heads * a.n_row_groups;
+    a.sched_cus = device_cus();
+    if (a.direct) {                                                  // one workgroup per possible unit
+        a.sched_w = (int)max_units;
+        return;
+    }
     int slots = 1;
-    if (kind == AttnKind::kMfma64) {
+    if (kind == AttnKind::kMfmaF32) {
+        slots = attn_f32_grid_slots(a, device_cus());
+    } else if (kind == AttnKind::kMfma64) {
         slots = attn_d64_grid_slots(a, device_cus());
     } else if (rt > 2) {
         slots = attn_rows_grid_slots(a, device_cus());               // more than 32 rows: the row-split kernel
@@ -475,7 +482,6 @@ void attn_mfma_shape(AttnArgs &a, AttnKind kind)
         });
     }
     a.sched_w = (int)(max_units < slots ? max_units : slots);
-    a.sched_cus = device_cus();
 }
 
 hipError_t launch_attn_mfma(const AttnArgs &a)

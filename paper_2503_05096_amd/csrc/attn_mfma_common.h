@@ -90,4 +90,34 @@ struct Unit {
     int64_t qrow0, bt_off;      // first query row; offset of the request's row in block_table
 };
 
+// ---- direct calls ---------------------------------------------------------------------------------------------------
+// The metadata kernel and the schedule table balance a large ragged batch; a small one only waits for them (4.7 us, and
+// two more dependent loads at the head of every workgroup). A direct call launches one workgroup per (request, possible
+// split, kv head, row group): the numbering follows from the host-side bounds, the splits of a request all have
+// plan.split_tokens tokens, and the workgroup reads its request's lengths (and adds up the rows before them) itself.
+// false: the request is shorter than this split, or has fewer rows than this group.
+__device__ __forceinline__ bool direct_unit(Unit &u, const DirectArgs &a, int G, int Hkv, int n_row_groups, int rows_per_group,
+                                            int block_tokens, int max_pages_per_req, int lane)
+{
+    const int idx = blockIdx.x;
+    const int rg = idx % n_row_groups;
+    u.gkv = (idx / n_row_groups) % Hkv;
+    u.item = idx / (n_row_groups * Hkv);
+    u.i = u.item / a.per_req;
+    const int s = u.item - u.i * a.per_req;
+    int part = 0;
+    for (int j = lane; j < u.i; j += kWave) part += min(max(a.spec_lens[j], 0), a.max_spec_len) + 1;
+    u.L = max(a.ctx_lens[u.i], 1);
+    u.n = min(max(a.spec_lens[u.i], 0), a.max_spec_len) + 1;
+    u.qrow0 = __builtin_amdgcn_readlane(wave_scan_incl_dpp(part), 63);
+    u.ns = min((u.L + a.split_tokens - 1) / a.split_tokens, a.per_req);
+    u.rows = u.n * G;
+    u.r0 = rg * rows_per_group;
+    u.t0 = s * a.split_tokens;
+    u.t1 = min(u.L, u.t0 + a.split_tokens);
+    u.nblk = (u.t1 - u.t0 + block_tokens - 1) / block_tokens;
+    u.bt_off = (int64_t)u.i * max_pages_per_req;
+    return s < u.ns && u.r0 < u.rows && u.qrow0 + u.n <= a.total_q;
+}
+
 }  // namespace adaspec

@@ -261,15 +261,44 @@ hipError_t launch_attn_plan(const AttnArgs &a)
 //   m* = max_s m_s,  out = sum_s 2^(m_s - m*) O_s / sum_s 2^(m_s - m*) l_s.
 // One wavefront per (row, head); rows whose request has a single split were
 // already finalised by the main kernel and are skipped.
+//
+// kDirect: no metadata kernel has run; the wavefront finds its row's request from the lengths (up to 256 requests, four
+// per lane), and the splits of request i are the items i * per_req, i * per_req + 1, ...
+template <bool kDirect>
 __global__ __launch_bounds__(256) void attn_combine_kernel(
     const int32_t *__restrict__ row_rec, const float *__restrict__ part_ml,
     const float *__restrict__ part_o, void *__restrict__ out, int total_q, int Hq, int Hkv, int d,
-    int max_rows, int out_dtype)
+    int max_rows, int out_dtype, DirectArgs direct)
 {
     const int unit = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (unit >= total_q * Hq) return;
     const int r = unit / Hq, h = unit % Hq;
-    const int4 rec = *reinterpret_cast<const int4 *>(row_rec + 4 * (int64_t)r);   // (request, ns, first split, row base)
+    int4 rec;                                                       // (request, ns, first split, row base)
+    if constexpr (kDirect) {
+        int n[4], sum = 0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int i = 4 * lane + u;
+            n[u] = i < direct.batch ? min(max(direct.spec_lens[i], 0), direct.max_spec_len) + 1 : 0;
+            sum += n[u];
+        }
+        const int incl = wave_scan_incl_dpp(sum);
+        const unsigned long long past = __ballot(incl > r);
+        if (!past) return;                                          // inconsistent lengths
+        const int owner = (int)__builtin_ctzll(past);
+        int first = incl - sum, i = 4 * lane, u = 0;
+#pragma unroll
+        for (; u < 3; ++u)
+            if (first + n[u] <= r) { first += n[u]; ++i; }
+            else break;
+        first = __shfl(first, owner, kWave);
+        i = __builtin_amdgcn_readfirstlane(__shfl(i, owner, kWave));
+        const int L = max(direct.ctx_lens[i], 1);
+        rec = make_int4(i, min((L + direct.split_tokens - 1) / direct.split_tokens, direct.per_req), i * direct.per_req,
+                        (r - first) * (Hq / Hkv));
+    } else {
+        rec = *reinterpret_cast<const int4 *>(row_rec + 4 * (int64_t)r);
+    }
     const int ns = rec.y, s0 = rec.z;
     if (ns <= 1) return;
     const int G = Hq / Hkv, g = h / G, rr = rec.w + (h % G);
@@ -331,10 +360,14 @@ hipError_t launch_attn_combine(const AttnArgs &a)
     if (units == 0) return hipSuccess;
     // no request can have more than one split: every row was finalised by the main kernel
     if ((int64_t)a.dims.max_pages_per_req * a.dims.page_size <= p.split_tokens) return hipSuccess;
-    hipLaunchKernelGGL(attn_combine_kernel, dim3(ceil_div(units, 4)), dim3(256), 0, a.stream,
-                       (const int32_t *)(a.ws + p.off_row_rec), (const float *)(a.ws + p.off_part_ml),
-                       (const float *)(a.ws + p.off_part_o), a.out, a.dims.total_q, a.dims.n_q_heads,
-                       a.dims.n_kv_heads, a.dims.head_dim, p.max_rows, a.dims.out_dtype);
+    auto launch = [&](auto direct) {
+        hipLaunchKernelGGL(attn_combine_kernel<decltype(direct)::value>, dim3(ceil_div(units, 4)), dim3(256), 0, a.stream,
+                           (const int32_t *)(a.ws + p.off_row_rec), (const float *)(a.ws + p.off_part_ml),
+                           (const float *)(a.ws + p.off_part_o), a.out, a.dims.total_q, a.dims.n_q_heads,
+                           a.dims.n_kv_heads, a.dims.head_dim, p.max_rows, a.dims.out_dtype, direct_args(a));
+    };
+    if (a.direct) launch(std::true_type{});
+    else launch(std::false_type{});
     return hipGetLastError();
 }
 

@@ -1,8 +1,8 @@
 // Portable vector-ALU verification attention: any of the three storage types,
 // any head_dim that is a multiple of 8 up to 256.  One wavefront per
-// (work item, kv head, chunk of 8 query rows).  It is the path for fp32 inputs
-// and for shapes the matrix-core kernel does not take; speed is secondary here,
-// clarity and generality come first.
+// (work item, kv head, chunk of 8 query rows).  It is the path for head dims the
+// matrix-core kernels do not take (they take 64 and 128); speed is secondary
+// here, clarity and generality come first.
 //
 // Per 64-token block:  lane <-> token for the scores (each lane walks its key
 // row, the query rows are broadcast from LDS), wavefront reductions for the

@@ -7,17 +7,10 @@ carry 24 (bf16) or 22 (f16) bits, so both types are held to the fp32 guard of th
 import pytest
 
 import workloads as W
-from tests.test_gpu_parity import check_attention
+from tests.test_gpu_parity import check_attention, pkg  # noqa: F401  (fixture)
 from tests.test_gpu_tree import _check_tree_attention
 
 pytestmark = pytest.mark.gpu
-
-
-@pytest.fixture(scope="module")
-def pkg():
-    import paper_2503_05096_amd as p
-    return p
-
 
 SHAPES = [
     # ctx_lens, spec_lens, Hq, Hkv
@@ -32,7 +25,7 @@ SHAPES = [
 
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("shape", SHAPES, ids=lambda s: f"B{len(s[0])}-L{max(s[0])}-k{max(s[1])}-{s[2]}x{s[3]}")
-def test_attention_d64_edges(shape, dtype, oracle_mod, pkg):
+def test_attention_d64_edges(shape, dtype, oracle_mod, pkg):  # noqa: F811
     ctx, spec, hq, hkv = shape
     st = W.make_custom_step(640, ctx_lens=ctx, spec_lens=spec, n_q_heads=hq, n_kv_heads=hkv, head_dim=64, dtype=dtype,
                             acceptance=False, name=f"d64-{dtype}")
@@ -40,7 +33,7 @@ def test_attention_d64_edges(shape, dtype, oracle_mod, pkg):
 
 
 @pytest.mark.parametrize("dtype,hq,hkv", [("bf16", 2, 2), ("f16", 8, 2)])
-def test_tree_attention_d64_edges(dtype, hq, hkv, oracle_mod, pkg):
+def test_tree_attention_d64_edges(dtype, hq, hkv, oracle_mod, pkg):  # noqa: F811
     ctx = [1, 64, 65, 40, 300, 2100, 33, 16, 700, 17]
     spec = [0, 63, 63, 39, 7, 30, 32, 15, 1, 5]
     st = W.make_custom_step(641, ctx_lens=ctx, spec_lens=spec, n_q_heads=hq, n_kv_heads=hkv, head_dim=64, dtype=dtype,
