@@ -206,7 +206,10 @@ size_t adaspec_accept_workspace_bytes(const adaspec_accept_dims *dims);
  * same up to V <= 524288 (it reads the logits row twice, the second time from the caches);
  * anything else runs on the vector path.  AUTO: two-pass when it fits (batches above 1024 requests:
  * only with more logits rows than compute units or V >= 65536), register-resident when it fits,
- * streaming for larger vocabularies, else vector.
+ * streaming for larger vocabularies, else vector.  Where AUTO names the streaming or the vector path
+ * (larger vocabularies up to 524288, fp32 rows, rows of two types) and V, strides and base pointers are
+ * aligned as above, up to 1024 requests run with the two-pass form's kernels instead (as long as the
+ * workspace stays within ADASPEC_NOALLOC_SCRATCH_BYTES).
  */
 int adaspec_accept(const void *target_logits, const void *draft_probs,
                    const int32_t *draft_tokens, const float *uniforms,
@@ -241,7 +244,8 @@ int adaspec_accept_noalloc(const void *target_logits, const void *draft_probs,
  * looked at for their alignment): ADASPEC_PATH_VECTOR, _FAST, _STREAM or _TWO_PASS; dims->path
  * itself unless it is ADASPEC_PATH_AUTO; a negative adaspec_status if dims are invalid or a
  * forced path does not fit.  Host-only, launches nothing.  For callers that account for the bytes
- * a call reads: the two-pass path skips rows (see above). */
+ * a call reads: the two-pass path skips rows (see above).  ADASPEC_PATH_STREAM and _VECTOR as the
+ * answer to AUTO are upper bounds: such a call may run with the two-pass form's kernels. */
 int adaspec_accept_resolved_path(const void *target_logits, const void *draft_probs,
                                  const adaspec_accept_dims *dims);
 

@@ -1,13 +1,16 @@
-// Two-pass acceptance in row PARTS for gfx950: 16-bit logits and draft probabilities of one type,
-// V % 8 == 0, V <= 131072, up to 1024 requests.
+// Two-pass acceptance in row PARTS for gfx950: logits and draft probabilities of any storage types, V % 8 == 0,
+// V <= 524288, 16-byte aligned rows, up to 1024 requests.
 //
 // The sequential rule (accept drafts in order, recover one token at the first rejection, else take the
 // bonus token) needs two things: the accept test on draft rows, for which the row's softmax statistics
 // (m, Z) suffice, and the residual distribution with a draw from it on ONE row per request.  Both are
-// sweeps over vocabulary rows of 256 KB that a single compute unit takes 7-12 us for; handing whole rows
+// sweeps over vocabulary rows of 256 KB and more that a single compute unit takes 7-12 us for; handing whole rows
 // to workgroups leaves the chip unevenly loaded (382 rows on 256 compute units) and every row a serial
 // chain.  Here every row is cut into parts, one small workgroup (256 threads) each, a few per compute
 // unit, all resident at once.
+//
+// A row is a sequence of CHUNKS of 16 bytes of logits (8 elements of 16 bits, 4 of fp32) with as many draft
+// probabilities beside them.
 //
 //   accept_rowparts_kernel   workgroup = (draft row, part).  Finds the row's request from spec_lens itself
 //       (block scan, up to 1024 requests), streams its part of the logits row once (part h = steps h,
@@ -17,22 +20,25 @@
 //       Records are stored per SLOT (request, draft position), so the second pass reads them without
 //       knowing where the request's rows start.  Workgroup 0 also writes cu_q and clears the tickets of
 //       the second pass.
-//   accept_decide_kernel     workgroup = (request, part of <= 1024 chunks of 16 bytes).  Merges the part
+//   accept_decide_kernel     workgroup = (request, part of <= 1024 chunks).  Merges the part
 //       statistics of the request's draft rows, applies the accept test to each (one lane per draft), finds
 //       the first rejection -> the deciding row; part 0 writes the accepted drafts, the padding and the
 //       length.  A greedy rejection is decided by the merged arg-max.  Otherwise the workgroup loads its
-//       part of the deciding row (and of its draft-probability row) and publishes the residual and
-//       probability mass per (step, wavefront, 16-lane row); the workgroup that finishes LAST for its
-//       request (an integer ticket per request, one atomic add at the exit, no waiting) puts the parts on
-//       one scale, finds the (part, step, wavefront) that holds tau = u1 * R, recomputes that wavefront's
-//       64 chunks with the same expressions and picks the element.
+//       part of the deciding row (and of its draft-probability row; each wavefront 256 contiguous chunks) and
+//       publishes the residual and probability mass of each of its wavefronts; the workgroup that finishes LAST
+//       for its request (an integer ticket per request, one atomic add at the exit, no waiting) puts the parts
+//       on one scale, finds the (part, wavefront) that holds tau = u1 * R, recomputes that wavefront's
+//       256 chunks with the same expressions and picks the element.
 // Per-element arithmetic is fp32, sums across lanes and workgroups fp64, in a fixed order: outputs do
 // not depend on which workgroup arrives last.
 //
 // What the time goes to (MI355X, 510 rows of V = 128256, time stamps): a dependent memory access costs
 // 1.2-1.7 us and the chain has six of them (first pass: lengths -> row; second pass: slot records -> row,
-// then stores acknowledged -> ticket -> partial sums -> the 64 chunks of the draw), the two launches add
-// 1.7 us each, and the rows themselves stream at 5.0-5.5 TB/s.
+// then stores acknowledged -> ticket -> partial sums -> the chunks of the draw), the two launches add
+// 1.7 us each, and the rows themselves stream at 5.0-5.5 TB/s.  Whole calls: 510 rows of V = 128256 bf16 40 us, 256 rows
+// of it in fp32 43 us, 192 rows of V = 262144 bf16 36 us.  Masses are published per wavefront (16 bytes per 256 chunks) and
+// not per step and 16-lane row, so that a row of any length fits the final search of one workgroup with two pairs per
+// thread; the four steps of the winning pair are recomputed by one wavefront each.
 #include "adaspec_internal.h"
 #include "device_utils.h"
 #include "row_registers.h"
@@ -44,13 +50,16 @@ constexpr int kQW = kQT / kWave;            // 4 wavefronts
 constexpr int kStatSteps = 8;               // first pass: steps of kQT chunks per part (32 KB of logits)
 constexpr int kStatWgsPerCu = 6;           // first pass: workgroups that fit a compute unit (80 registers each)
 constexpr int kStatTargetWgsPerCu = 3;     // ... and how many the launch aims for: few long streams read faster than many short ones
-constexpr int kStatParts = 8;               // parts per row at most: V <= 8 * 8 * 256 * 8 = 131072
-constexpr int kSumSteps = 4;                // second pass: steps per part (16 KB of logits + 16 KB of probabilities)
-constexpr int kSumParts = 16;               // parts per row at most
+constexpr int kStatParts = 8;               // parts per row at most, of up to 64 steps: V <= 8 * 64 * 256 * 4 = 524288
+constexpr int kSumSteps = 4;                // second pass: steps of kQT chunks per part
+constexpr int kSumChunks = kSumSteps * kQT; // chunks per part (16 KB of logits)
+constexpr int kSumParts = 128;              // parts per row at most
+constexpr int kPartsMaxVocab = 524288;
 constexpr int kPartsMaxBatch = 1024;        // requests the in-kernel scan covers (4 per thread)
 constexpr int kPartsMaxSlots = 32768;       // batch * max_spec_len slots the workspace is laid out for
-static_assert(kSumParts * kSumSteps == 64, "one lane per step of the row in the final search");
-static_assert(kSumParts * kSumSteps * kQW == kQT, "one thread per (part, step, wavefront) in the final search");
+static_assert(kSumSteps == kQW, "one wavefront per step in the final search");
+static_assert(kSumParts * kQW == 2 * kQT, "two (part, wavefront) pairs per thread in the final search");
+static_assert(kPartsMaxVocab <= kSumParts * kSumChunks * 4 && kPartsMaxVocab <= kStatParts * 64 * kQT * 4, "fp32 rows fit");
 
 // Phase time stamps for tuning builds (-DADASPEC_STAMPS): thread 0 of every workgroup leaves the 100 MHz
 // wall clock at up to 8 points of each kernel; adaspec_debug_read_stamps copies them out.  Product builds
@@ -102,100 +111,183 @@ __device__ __forceinline__ HalfStat fetch_stat(const HalfStat *p)
     return s;
 }
 
-// sums of the second pass: float[B][kSumParts][kSumSteps][kQW][2 kinds (residual, p)][4 rows of 16 lanes]
-__device__ __forceinline__ size_t sum_index(int i, int h, int it, int w, int kind)
-{
-    return ((((size_t)(i * kSumParts + h) * kSumSteps + it) * kQW + w) * 2 + kind) * 4;
-}
-
-// One 16-byte chunk (8 elements): residual r_v = max(0, e_v / Z - q_v) and p_v = e_v / Z with
-// e_v = 2^(l_v c - m c).  The sums and the final search both call this, so they see the same numbers.
-template <class P>
-__device__ __forceinline__ void part_chunk_masses(const uint4 &lv, const uint4 &qv, float c, float mc, float invZ,
-                                                  float (&rv)[8], float (&pv)[8])
-{
-    const uint32_t w[4] = {lv.x, lv.y, lv.z, lv.w}, qw[4] = {qv.x, qv.y, qv.z, qv.w};
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const float ea = __builtin_amdgcn_exp2f(fmaf(P::lo(w[e]), c, -mc));
-        const float eb = __builtin_amdgcn_exp2f(fmaf(P::hi(w[e]), c, -mc));
-        rv[2 * e] = fmaxf(0.f, fmaf(ea, invZ, -P::lo(qw[e])));
-        rv[2 * e + 1] = fmaxf(0.f, fmaf(eb, invZ, -P::hi(qw[e])));
-        pv[2 * e] = ea * invZ;
-        pv[2 * e + 1] = eb * invZ;
-    }
-}
+// mass of one wavefront's 256 chunks of a part: [B][n_parts][kQW]
+struct WaveMass { double residual, prob; };
 
 // 16 bytes per lane through a buffer descriptor (past the end of the buffer: zeros); AUX = cache policy bits
 // of the instruction (0 = default, 2 = non-temporal: data that is read once)
 constexpr int kAuxDefault = 0, kAuxStream = 2;
 template <int AUX>
-__device__ __forceinline__ uint4 part_load16(__amdgpu_buffer_rsrc_t rs, uint32_t lane_offset, int step)
+__device__ __forceinline__ uint4 part_load16(__amdgpu_buffer_rsrc_t rs, uint32_t lane_offset, int step_offset)
 {
-    const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)lane_offset, step * (kQT * 16), AUX);
+    const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)lane_offset, step_offset, AUX);
     return make_uint4(v.x, v.y, v.z, v.w);
 }
 
-// exact maximum of the 8 values of a chunk
-template <class P>
+// ---- chunks of logits -------------------------------------------------------------------------------
+template <class LT> struct Chunk {                    // 16-bit types
+    using P = Pair16<LT>;
+    static constexpr int kN = 8;
+    static __device__ __forceinline__ void unpack(const uint4 &v, float (&x)[kN])
+    {
+        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { x[2 * e] = P::lo(w[e]); x[2 * e + 1] = P::hi(w[e]); }
+    }
+    // chunks past the end of the row arrive as zeros (range check of the buffer) and become -inf in place
+    static __device__ __forceinline__ void blank(uint4 &v, bool past)
+    {
+        const uint32_t ninf = past ? P::kNegInf2 : 0u;
+        v.x |= ninf; v.y |= ninf; v.z |= ninf; v.w |= ninf;
+    }
+};
+template <> struct Chunk<F32> {
+    static constexpr int kN = 4;
+    static __device__ __forceinline__ void unpack(const uint4 &v, float (&x)[kN])
+    {
+        x[0] = __uint_as_float(v.x); x[1] = __uint_as_float(v.y); x[2] = __uint_as_float(v.z); x[3] = __uint_as_float(v.w);
+    }
+    static __device__ __forceinline__ void blank(uint4 &v, bool past)
+    {
+        constexpr uint32_t kNegInf = 0xff800000u;
+        v.x = past ? kNegInf : v.x; v.y = past ? kNegInf : v.y; v.z = past ? kNegInf : v.z; v.w = past ? kNegInf : v.w;
+    }
+};
+
+// ---- the draft probabilities beside a chunk of N logits: 8, 16 or 32 bytes ----------------------------
+template <int N, class PT> struct ProbChunk {
+    static constexpr int kBytes = N * (int)sizeof(typename PT::storage);
+    uint32_t w[kBytes / 4];
+    __device__ __forceinline__ void zero()
+    {
+#pragma unroll
+        for (int k = 0; k < kBytes / 4; ++k) w[k] = 0u;
+    }
+    __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t rs, uint32_t lane_offset, int step_offset)
+    {
+        typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+        if constexpr (kBytes == 8) {
+            const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rs, (int)lane_offset, step_offset, kAuxDefault);
+            w[0] = v.x; w[1] = v.y;
+        } else {
+#pragma unroll
+            for (int k = 0; k < kBytes / 16; ++k) {
+                const uint4 v = part_load16<kAuxDefault>(rs, lane_offset + 16 * k, step_offset);
+                w[4 * k] = v.x; w[4 * k + 1] = v.y; w[4 * k + 2] = v.z; w[4 * k + 3] = v.w;
+            }
+        }
+    }
+    __device__ __forceinline__ void unpack(float (&x)[N]) const
+    {
+        if constexpr (sizeof(typename PT::storage) == 4) {
+#pragma unroll
+            for (int e = 0; e < N; ++e) x[e] = __uint_as_float(w[e]);
+        } else {
+#pragma unroll
+            for (int e = 0; e < N / 2; ++e) { x[2 * e] = Pair16<PT>::lo(w[e]); x[2 * e + 1] = Pair16<PT>::hi(w[e]); }
+        }
+    }
+    __device__ __forceinline__ void keep()            // opaque to the optimiser (see keep_packed)
+    {
+#pragma unroll
+        for (int k = 0; k < kBytes / 4; ++k) asm volatile("" : "+v"(w[k]));
+    }
+};
+
+// 2^((l - m) c).  16-bit logits: one fused operation with mc = m * c (the rounding of mc is far below that of
+// the logits' storage type).  fp32 logits: the difference first, as the portable kernel does it: for large
+// logits the rounding of mc would be visible in how the parts of a row are put together.
+template <class LT>
+__device__ __forceinline__ float exp_weight(float l, float m, float c, float mc)
+{
+    if constexpr (sizeof(typename LT::storage) == 4) return __builtin_amdgcn_exp2f((l - m) * c);
+    else return __builtin_amdgcn_exp2f(fmaf(l, c, -mc));
+}
+
+// One chunk: residual r_v = max(0, e_v / Z - q_v) and p_v = e_v / Z with e_v = 2^((l_v - m) c).
+// The sums and the final search both call this, so they see the same numbers.
+template <class LT, class PT>
+__device__ __forceinline__ void part_chunk_masses(const uint4 &lv, const ProbChunk<Chunk<LT>::kN, PT> &qv, float m, float c,
+                                                  float mc, float invZ, float (&rv)[Chunk<LT>::kN], float (&pv)[Chunk<LT>::kN])
+{
+    constexpr int N = Chunk<LT>::kN;
+    float x[N], q[N];
+    Chunk<LT>::unpack(lv, x);
+    qv.unpack(q);
+#pragma unroll
+    for (int e = 0; e < N; ++e) {
+        const float w = exp_weight<LT>(x[e], m, c, mc);
+        rv[e] = fmaxf(0.f, fmaf(w, invZ, -q[e]));
+        pv[e] = w * invZ;
+    }
+}
+
+// exact maximum of the values of a chunk
+template <class LT>
 __device__ __forceinline__ float chunk_max(const uint4 &v, float m)
 {
-    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+    float x[Chunk<LT>::kN];
+    Chunk<LT>::unpack(v, x);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) m = fmaxf(m, fmaxf(P::lo(w[e]), P::hi(w[e])));
+    for (int e = 0; e < Chunk<LT>::kN; ++e) m = fmaxf(m, x[e]);
     return m;
 }
 
-// Exact maximum of a thread's STEPS chunks, on the bit patterns.  Both 16-bit formats are sign-magnitude:
+// Exact maximum of a thread's STEPS chunks.  16-bit types: on the bit patterns.  Both are sign-magnitude:
 // among non-negative values the order of the patterns as SIGNED 16-bit integers is the order of the
 // values, and every negative value is a negative integer, so a packed signed maximum (one instruction per
 // two elements) is exact as soon as one value is >= +0.  A thread that holds nothing but negative values
 // (masked vocabularies) wants the smallest magnitude instead: the packed UNSIGNED minimum.
 typedef unsigned short ushort2v __attribute__((ext_vector_type(2)));
-template <class P, int STEPS>
+template <class LT, int STEPS>
 __device__ __forceinline__ float thread_max(const uint4 (&lg)[STEPS])
 {
-    short2v pm = {(short)0x8000, (short)0x8000};
+    if constexpr (sizeof(typename LT::storage) == 4) {
+        float m = -INFINITY;
 #pragma unroll
-    for (int it = 0; it < STEPS; ++it) {
-        const uint32_t w[4] = {lg[it].x, lg[it].y, lg[it].z, lg[it].w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) pm = __builtin_elementwise_max(pm, __builtin_bit_cast(short2v, w[e]));
-    }
-    int top = max((int)pm.x, (int)pm.y);
-    if (top < 0) {
-        ushort2v pn = {(unsigned short)0xffff, (unsigned short)0xffff};
+        for (int it = 0; it < STEPS; ++it) m = chunk_max<LT>(lg[it], m);
+        return m;
+    } else {
+        short2v pm = {(short)0x8000, (short)0x8000};
 #pragma unroll
         for (int it = 0; it < STEPS; ++it) {
             const uint32_t w[4] = {lg[it].x, lg[it].y, lg[it].z, lg[it].w};
 #pragma unroll
-            for (int e = 0; e < 4; ++e) pn = __builtin_elementwise_min(pn, __builtin_bit_cast(ushort2v, w[e]));
+            for (int e = 0; e < 4; ++e) pm = __builtin_elementwise_max(pm, __builtin_bit_cast(short2v, w[e]));
         }
-        top = min((int)pn.x, (int)pn.y);
+        int top = max((int)pm.x, (int)pm.y);
+        if (top < 0) {
+            ushort2v pn = {(unsigned short)0xffff, (unsigned short)0xffff};
+#pragma unroll
+            for (int it = 0; it < STEPS; ++it) {
+                const uint32_t w[4] = {lg[it].x, lg[it].y, lg[it].z, lg[it].w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) pn = __builtin_elementwise_min(pn, __builtin_bit_cast(ushort2v, w[e]));
+            }
+            top = min((int)pn.x, (int)pn.y);
+        }
+        return Pair16<LT>::lo((uint32_t)top & 0xffffu);
     }
-    return P::lo((uint32_t)top & 0xffffu);
 }
 
 // (maximum, normaliser) of STEPS chunks per thread over the whole workgroup, relative to the workgroup's
 // maximum: every thread sums against its own maximum (no barrier between the two sweeps), the pairs are
 // merged over the wavefront and, through LDS, over the workgroup.  Returns false if no finite value exists.
-template <class P, int STEPS>
+template <class LT, int STEPS>
 __device__ __forceinline__ bool part_max_and_norm(uint4 (&lg)[STEPS], float c, float *s_m, double *s_z,
                                                   int lane, int wv, float &m_out, double &z_out)
 {
-    const float mt = thread_max<P, STEPS>(lg);
+    const float mt = thread_max<LT, STEPS>(lg);
     float zt = 0.f;
     if (mt > -INFINITY) {
         const float mtc = mt * c;
 #pragma unroll
         for (int it = 0; it < STEPS; ++it) {
             keep_packed(lg[it]);
-            const uint32_t w[4] = {lg[it].x, lg[it].y, lg[it].z, lg[it].w};
+            float x[Chunk<LT>::kN];
+            Chunk<LT>::unpack(lg[it], x);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                zt += __builtin_amdgcn_exp2f(fmaf(P::lo(w[e]), c, -mtc));
-                zt += __builtin_amdgcn_exp2f(fmaf(P::hi(w[e]), c, -mtc));
-            }
+            for (int e = 0; e < Chunk<LT>::kN; ++e) zt += exp_weight<LT>(x[e], mt, c, mtc);
         }
     }
     const float mw = wave_max(mt);
@@ -213,23 +305,22 @@ __device__ __forceinline__ bool part_max_and_norm(uint4 (&lg)[STEPS], float c, f
     return m > -INFINITY;
 }
 
-// arg-max (lowest index on ties) of STEPS chunks per thread over the workgroup; chunk0 = first chunk of the part
-template <class P, int STEPS>
+// arg-max (lowest index on ties) of STEPS chunks per thread over the workgroup; chunk0 = first chunk of this lane
+template <class LT, int STEPS>
 __device__ __forceinline__ ArgMax part_argmax(uint4 (&lg)[STEPS], int chunk0, int V, float *s_m, int *s_i,
-                                              int tid, int lane, int wv)
+                                              int lane, int wv)
 {
+    constexpr int N = Chunk<LT>::kN;
     ArgMax best{-INFINITY, V};
 #pragma unroll
     for (int it = 0; it < STEPS; ++it) {
         keep_packed(lg[it]);
-        const uint32_t w[4] = {lg[it].x, lg[it].y, lg[it].z, lg[it].w};
-        const int base = (chunk0 + it * kQT + tid) * 8;
+        float x[N];
+        Chunk<LT>::unpack(lg[it], x);
+        const int base = (chunk0 + it * kWave) * N;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const float x0 = P::lo(w[e]), x1 = P::hi(w[e]);
-            if (x0 > best.v) best = ArgMax{x0, base + 2 * e};
-            if (x1 > best.v) best = ArgMax{x1, base + 2 * e + 1};
-        }
+        for (int e = 0; e < N; ++e)
+            if (x[e] > best.v) best = ArgMax{x[e], base + e};
     }
     best = wave_argmax(best);
     if (lane == 0) { s_m[wv] = best.v; s_i[wv] = best.i; }
@@ -242,16 +333,16 @@ __device__ __forceinline__ ArgMax part_argmax(uint4 (&lg)[STEPS], int chunk0, in
 
 // ---------------------------------------------------------------------------------------------------
 // First pass: statistics of every draft row, in parts.
-template <class DT>
+template <class LT>
 __global__ __launch_bounds__(kQT, kStatWgsPerCu) void accept_rowparts_kernel(
     const char *__restrict__ logits, const char *__restrict__ probs,
     const int32_t *__restrict__ draft_tokens, const float *__restrict__ uniforms,
     const int32_t *__restrict__ spec_lens, const float *__restrict__ temperature, int B, int V, int total_q,
-    int total_draft, int max_spec_len, int n_parts, int64_t lstride, int64_t pstride,
+    int total_draft, int max_spec_len, int n_parts, int64_t lstride, int64_t pstride, int probs_dtype,
     int32_t *__restrict__ cu_q, int32_t *__restrict__ req_ticket, SlotRec *__restrict__ slot_rec,
     HalfStat *__restrict__ part_stat)
 {
-    using P = Pair16<DT>;
+    constexpr int kN = Chunk<LT>::kN, kSize = (int)sizeof(typename LT::storage);
     __shared__ int s_tot[kQW];
     __shared__ int s_row[5];                 // request, position, k, temperature bits, logits row
     __shared__ float s_m[kQW];
@@ -315,8 +406,8 @@ __global__ __launch_bounds__(kQT, kStatWgsPerCu) void accept_rowparts_kernel(
     // ---- the part of the row, streamed once: kStatSteps steps in flight, each consumed as it lands -------
     // (a compute unit needs about as long for the exponentials of a row as the memory system needs to
     // deliver it: only a stream whose arithmetic runs under its own loads gets both done in the time of one)
-    const int row_chunks = V >> 3;
-    const char *lrow = logits + (int64_t)r * lstride * 2;
+    const int row_chunks = V / kN;
+    const char *lrow = logits + (int64_t)r * lstride * kSize;
     // Part h takes the steps h, h + n_parts, h + 2 n_parts, ... of the row, so that the workgroups of a row
     // sweep it together (neighbouring addresses are in flight at the same time), and reads them past the
     // caches: a draft row is read once, here.
@@ -324,25 +415,25 @@ __global__ __launch_bounds__(kQT, kStatWgsPerCu) void accept_rowparts_kernel(
     const int steps = (row_steps - h + n_parts - 1) / n_parts;
     const __amdgpu_buffer_rsrc_t rl = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(lrow), 0, row_chunks * 16, 0x00020000);
 #define ADASPEC_ROW_STEP(s) ((s) * n_parts + h)
+#define ADASPEC_STEP_OFFSET(s) (ADASPEC_ROW_STEP(s) * (kQT * 16))
 #define ADASPEC_STEP_CHUNK(s) (ADASPEC_ROW_STEP(s) * kQT + tid)
 #define ADASPEC_STEP_PAST_END(s) (ADASPEC_STEP_CHUNK(s) >= row_chunks)
     const uint32_t tid16 = (uint32_t)tid * 16u;
     uint4 lg[kStatSteps];
 #pragma unroll
-    for (int u = 0; u < kStatSteps; ++u) lg[u] = part_load16<kAuxStream>(rl, tid16, ADASPEC_ROW_STEP(u));
+    for (int u = 0; u < kStatSteps; ++u) lg[u] = part_load16<kAuxStream>(rl, tid16, ADASPEC_STEP_OFFSET(u));
 
     const int64_t slot = (int64_t)ri * max_spec_len + j;
     if (h == 0 && tid == 0) {
-        // what the accept test needs besides (m, Z): scalar loads, they travel with the row
+        // what the accept test needs besides (m, Z): these loads travel with the row
         const int x = draft_tokens[dr];
         const int xa = min(max(x, 0), V - 1);            // (address only: an out-of-range token must not fault)
-        const char *prow = probs + (int64_t)dr * pstride * 2;
-        const uint32_t lw = reinterpret_cast<const uint32_t *>(lrow)[xa >> 1];
-        const uint32_t qw = reinterpret_cast<const uint32_t *>(prow)[xa >> 1];
+        const int64_t px = (int64_t)dr * pstride + xa;
         SlotRec rec;
         rec.x = x;
-        rec.lx_bits = __float_as_uint((xa & 1) ? P::hi(lw) : P::lo(lw));
-        rec.qx_bits = __float_as_uint((xa & 1) ? P::hi(qw) : P::lo(qw));
+        rec.lx_bits = __float_as_uint(load_as_float<LT>(lrow, xa));
+        rec.qx_bits = __float_as_uint(probs_dtype == ADASPEC_F32 ? load_as_float<F32>(probs, px)
+                                      : probs_dtype == ADASPEC_F16 ? load_as_float<F16>(probs, px) : load_as_float<BF16>(probs, px));
         rec.u0_bits = __float_as_uint(uniforms[2 * (int64_t)r]);
         slot_rec[slot] = rec;
     }
@@ -352,11 +443,8 @@ __global__ __launch_bounds__(kQT, kStatWgsPerCu) void accept_rowparts_kernel(
     // it has been consumed the request for the step that takes its place in the window (past the part:
     // zeros, no traffic) into the same registers.  Macros, not lambdas: an array captured by reference
     // would be given a home in scratch memory.
-#define ADASPEC_STEP_WORDS(w, s, u)                                                                   \
-    const uint32_t ninf_##w = ADASPEC_STEP_PAST_END(s) ? P::kNegInf2 : 0u;                             \
-    const uint32_t w[4] = {lg[u].x | ninf_##w, lg[u].y | ninf_##w, lg[u].z | ninf_##w, lg[u].w | ninf_##w};
 #define ADASPEC_STEP_REFILL(s, u)                                                                     \
-    lg[u] = part_load16<kAuxStream>(rl, tid16, ADASPEC_ROW_STEP((s) + kStatSteps));        \
+    lg[u] = part_load16<kAuxStream>(rl, tid16, ADASPEC_STEP_OFFSET((s) + kStatSteps));                 \
     __builtin_amdgcn_sched_barrier(0);       /* one step at a time: nothing unpacked ahead of its turn */
     if (T == 0.0f) {
         // greedy: arg-max, lowest index on ties (a thread meets its elements in index order)
@@ -364,14 +452,14 @@ __global__ __launch_bounds__(kQT, kStatWgsPerCu) void accept_rowparts_kernel(
         for (int s0 = 0; s0 < steps; s0 += kStatSteps) {
 #pragma unroll
             for (int u = 0; u < kStatSteps; ++u) {
-                ADASPEC_STEP_WORDS(w, s0 + u, u)
-                const int base = ADASPEC_STEP_CHUNK(s0 + u) * 8;
+                uint4 v = lg[u];
+                Chunk<LT>::blank(v, ADASPEC_STEP_PAST_END(s0 + u));
+                float x[kN];
+                Chunk<LT>::unpack(v, x);
+                const int base = ADASPEC_STEP_CHUNK(s0 + u) * kN;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const float x0 = P::lo(w[e]), x1 = P::hi(w[e]);
-                    if (x0 > best.v) best = ArgMax{x0, base + 2 * e};
-                    if (x1 > best.v) best = ArgMax{x1, base + 2 * e + 1};
-                }
+                for (int e = 0; e < kN; ++e)
+                    if (x[e] > best.v) best = ArgMax{x[e], base + e};
                 ADASPEC_STEP_REFILL(s0 + u, u)
             }
         }
@@ -391,35 +479,42 @@ __global__ __launch_bounds__(kQT, kStatWgsPerCu) void accept_rowparts_kernel(
     // the order of the values and every negative value is a negative integer, so a running packed signed
     // maximum (one instruction per two elements) is the exact maximum as soon as the thread has seen one
     // value >= +0; until then (masked vocabularies) the chunk's float maximum is taken the slow way.
+    // fp32 chunks (half as many elements per byte) take the float maximum throughout.
     const float c = 1.4426950408889634f / T;
     short2v pm = {(short)0x8000, (short)0x8000};
     float m_run = -INFINITY, zt = 0.f;
     for (int s0 = 0; s0 < steps; s0 += kStatSteps) {
 #pragma unroll
         for (int u = 0; u < kStatSteps; ++u) {
-            ADASPEC_STEP_WORDS(w, s0 + u, u)
+            uint4 v = lg[u];
+            Chunk<LT>::blank(v, ADASPEC_STEP_PAST_END(s0 + u));
+            float mn;
+            if constexpr (kN == 4) {
+                mn = chunk_max<LT>(v, m_run);
+            } else {
+                const uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-            for (int e = 0; e < 4; ++e) pm = __builtin_elementwise_max(pm, __builtin_bit_cast(short2v, w[e]));
-            const int top = max((int)pm.x, (int)pm.y);
-            const float mn = top >= 0 ? P::lo((uint32_t)top & 0xffffu) : chunk_max<P>(make_uint4(w[0], w[1], w[2], w[3]), m_run);
+                for (int e = 0; e < 4; ++e) pm = __builtin_elementwise_max(pm, __builtin_bit_cast(short2v, w[e]));
+                const int top = max((int)pm.x, (int)pm.y);
+                mn = top >= 0 ? Pair16<LT>::lo((uint32_t)top & 0xffffu) : chunk_max<LT>(v, m_run);
+            }
             if (mn > m_run) {
                 zt *= __builtin_amdgcn_exp2f((m_run - mn) * c);          // (-inf - finite) -> 0
                 m_run = mn;
             }
             if (m_run > -INFINITY) {
                 const float mnc = m_run * c;
+                float x[kN];
+                Chunk<LT>::unpack(v, x);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    zt += __builtin_amdgcn_exp2f(fmaf(P::lo(w[e]), c, -mnc));
-                    zt += __builtin_amdgcn_exp2f(fmaf(P::hi(w[e]), c, -mnc));
-                }
+                for (int e = 0; e < kN; ++e) zt += exp_weight<LT>(x[e], m_run, c, mnc);
             }
             ADASPEC_STEP_REFILL(s0 + u, u)
         }
     }
-#undef ADASPEC_STEP_WORDS
 #undef ADASPEC_STEP_REFILL
 #undef ADASPEC_ROW_STEP
+#undef ADASPEC_STEP_OFFSET
 #undef ADASPEC_STEP_CHUNK
 #undef ADASPEC_STEP_PAST_END
     const float mw = wave_max(m_run);
@@ -474,24 +569,25 @@ __device__ __forceinline__ RowMerge merge_row_parts(const HalfStat (&s)[kStatPar
 
 // ---------------------------------------------------------------------------------------------------
 // Second pass: the deciding row of every request, in parts, and the draw.
-template <class DT>
-__global__ __launch_bounds__(kQT, 8) void accept_decide_kernel(
+template <class LT, class PT>
+__global__ __launch_bounds__(kQT, sizeof(typename PT::storage) > sizeof(typename LT::storage) ? 6 : 8) void accept_decide_kernel(
     const char *__restrict__ logits, const char *__restrict__ probs,
     const int32_t *__restrict__ draft_tokens, const float *__restrict__ uniforms,
     const int32_t *__restrict__ spec_lens, const float *__restrict__ temperature, int V, int total_q,
     int total_draft, int max_spec_len, int n_stat_parts, int n_parts, int64_t lstride, int64_t pstride,
     const int32_t *__restrict__ cu_q, int32_t *__restrict__ req_ticket, const SlotRec *__restrict__ slot_rec,
     const HalfStat *__restrict__ part_stat, int out_stride, int32_t *__restrict__ out_tokens,
-    int32_t *__restrict__ out_accept_len, float *__restrict__ sums, HalfStat *__restrict__ sum_stat)
+    int32_t *__restrict__ out_accept_len, WaveMass *__restrict__ sums, HalfStat *__restrict__ sum_stat)
 {
-    using P = Pair16<DT>;
-    __shared__ float s_m[kSumParts > kQW ? kSumParts : kQW];
-    __shared__ double s_z[kSumParts > kQW ? kSumParts : kQW];
+    constexpr int kN = Chunk<LT>::kN, kLSize = (int)sizeof(typename LT::storage), kPSize = (int)sizeof(typename PT::storage);
+    using Probs = ProbChunk<kN, PT>;
+    __shared__ float s_m[kSumParts];
+    __shared__ double s_z[kSumParts];
     __shared__ int s_i[kQW];
     __shared__ int s_last;
-    __shared__ double mass[kSumParts][kSumSteps][kQW];
-    __shared__ double s_tau, s_before;
-    __shared__ int s_step, s_retry;
+    __shared__ double s_wave[kQW];
+    __shared__ double s_before;
+    __shared__ int s_pick[2], s_lastpos;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int i = blockIdx.x / n_parts, h = blockIdx.x % n_parts;
     ADASPEC_STAMP(1, 0);
@@ -534,7 +630,7 @@ __global__ __launch_bounds__(kQT, 8) void accept_decide_kernel(
                 mine = merge_row_parts(parts, c, !sampled);
                 if (sampled) {
                     const float lx = __uint_as_float(rec.lx_bits), qx = __uint_as_float(rec.qx_bits);
-                    const float px = __builtin_amdgcn_exp2f(fmaf(lx, c, -(mine.m * c))) * (float)(1.0 / mine.Z);
+                    const float px = exp_weight<LT>(lx, mine.m, c, mine.m * c) * (float)(1.0 / mine.Z);
                     flag = (qx > 0.f) ? (__uint_as_float(rec.u0_bits) < px / qx) : 1;
                 } else {
                     flag = rec.x == mine.arg;
@@ -575,35 +671,34 @@ __global__ __launch_bounds__(kQT, 8) void accept_decide_kernel(
 
     ADASPEC_STAMP(1, 1);
     // ---- this workgroup's part of the deciding row (and of its draft probabilities) -------------------
-    const int row_chunks = V >> 3;
-    const int chunk0 = h * (kSumSteps * kQT);
-    const int nchunks = min(row_chunks - chunk0, kSumSteps * kQT);   // >= 1 by the choice of n_parts
-    const char *lrow = logits + (int64_t)r * lstride * 2;
-    const char *prow = probs + (int64_t)(r - i) * pstride * 2;
+    // wavefront w owns the part's chunks 256 w .. 256 w + 255, lane l of its step it the chunk 64 it + l of those
+    const int row_chunks = V / kN;
+    const int chunk0 = h * kSumChunks;
+    const int nchunks = min(row_chunks - chunk0, kSumChunks);        // >= 1 by the choice of n_parts
+    const char *lrow = logits + (int64_t)r * lstride * kLSize;
+    const char *prow = probs + (int64_t)(r - i) * pstride * kPSize;
     const bool has_q = sampled && !bonus;
     const __amdgpu_buffer_rsrc_t rl =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(lrow) + (int64_t)chunk0 * 16, 0, nchunks * 16, 0x00020000);
     // (a bonus row has no draft probabilities: descriptor of size zero, the loads return zeros)
-    const __amdgpu_buffer_rsrc_t rq =
-        __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(prow) + (int64_t)chunk0 * 16, 0, has_q ? nchunks * 16 : 0, 0x00020000);
-    const uint32_t tid16 = (uint32_t)tid * 16u;
-    uint4 lg[kSumSteps], qg[kSumSteps];
+    const __amdgpu_buffer_rsrc_t rq = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<char *>(prow) + (int64_t)chunk0 * Probs::kBytes, 0, has_q ? nchunks * Probs::kBytes : 0, 0x00020000);
+    const int my_chunk = wv * (kSumSteps * kWave) + lane;            // of step 0, inside the part
+    uint4 lg[kSumSteps];
+    Probs qg[kSumSteps];
 #pragma unroll
-    for (int it = 0; it < kSumSteps; ++it) lg[it] = part_load16<kAuxDefault>(rl, tid16, it);
+    for (int it = 0; it < kSumSteps; ++it) lg[it] = part_load16<kAuxDefault>(rl, (uint32_t)my_chunk * 16u, it * (kWave * 16));
 #pragma unroll
-    for (int it = 0; it < kSumSteps; ++it) qg[it] = part_load16<kAuxDefault>(rq, tid16, it);
+    for (int it = 0; it < kSumSteps; ++it) qg[it].load(rq, (uint32_t)(my_chunk * Probs::kBytes), it * (kWave * Probs::kBytes));
     const float u_draw = uniforms[2 * (int64_t)r + 1];
 #pragma unroll
-    for (int it = 0; it < kSumSteps; ++it) {
-        const uint32_t ninf = (it * kQT + tid >= nchunks) ? P::kNegInf2 : 0u;
-        lg[it].x |= ninf; lg[it].y |= ninf; lg[it].z |= ninf; lg[it].w |= ninf;
-    }
-    HalfStat *my_stat = sum_stat + i * kSumParts + h;
-    float *my_sums = sums + sum_index(i, h, 0, 0, 0);
+    for (int it = 0; it < kSumSteps; ++it) Chunk<LT>::blank(lg[it], my_chunk + it * kWave >= nchunks);
+    HalfStat *my_stat = sum_stat + (int64_t)i * n_parts + h;
+    WaveMass *my_sum = sums + ((int64_t)i * n_parts + h) * kQW + wv;
     ADASPEC_STAMP(1, 2);
     if (!sampled) {
         // greedy bonus row: arg-max of the part; the last workgroup merges the parts
-        const ArgMax b = part_argmax<P, kSumSteps>(lg, chunk0, V, s_m, s_i, tid, lane, wv);
+        const ArgMax b = part_argmax<LT, kSumSteps>(lg, chunk0 + my_chunk, V, s_m, s_i, lane, wv);
         if (tid == 0) publish_stat(my_stat, b.v, b.i < V ? b.i : -1, 0.0);
     } else {
         float m = row.m;
@@ -611,29 +706,29 @@ __global__ __launch_bounds__(kQT, 8) void accept_decide_kernel(
         bool any = true;
         // a bonus row was not seen by the first pass: maximum and normaliser of this part alone (the last
         // workgroup puts the parts on one scale)
-        if (bonus) any = part_max_and_norm<P, kSumSteps>(lg, c, s_m, s_z, lane, wv, m, Zd);
-        if (!any) {
-            for (int t = tid; t < kSumSteps * kQW * 8; t += kQT) publish_f32(my_sums + t, 0.f);
-            if (tid == 0) publish_stat(my_stat, -INFINITY, -1, 1.0);
-        } else {
+        if (bonus) any = part_max_and_norm<LT, kSumSteps>(lg, c, s_m, s_z, lane, wv, m, Zd);
+        double res = 0.0, prob = 0.0;
+        if (any) {
             const float mc = m * c, invZ = (float)(1.0 / Zd);
 #pragma unroll
             for (int it = 0; it < kSumSteps; ++it) {
-                float rv[8], pv[8], acc_r = 0.f, acc_p = 0.f;
+                float rv[kN], pv[kN], acc_r = 0.f, acc_p = 0.f;
                 keep_packed(lg[it]);
-                keep_packed(qg[it]);
-                part_chunk_masses<P>(lg[it], qg[it], c, mc, invZ, rv, pv);
+                qg[it].keep();
+                part_chunk_masses<LT, PT>(lg[it], qg[it], m, c, mc, invZ, rv, pv);
 #pragma unroll
-                for (int e = 0; e < 8; ++e) { acc_r += rv[e]; acc_p += pv[e]; }
-                acc_r = row16_sum(acc_r);
-                acc_p = row16_sum(acc_p);
-                if ((lane & 15) == 0) {
-                    publish_f32(sums + sum_index(i, h, it, wv, 0) + (lane >> 4), acc_r);
-                    publish_f32(sums + sum_index(i, h, it, wv, 1) + (lane >> 4), acc_p);
-                }
+                for (int e = 0; e < kN; ++e) { acc_r += rv[e]; acc_p += pv[e]; }
+                res += (double)acc_r;
+                prob += (double)acc_p;
             }
-            if (tid == 0) publish_stat(my_stat, m, 0, Zd);
+            res = wave_sum(res);
+            prob = wave_sum(prob);
         }
+        if (lane == 0) {
+            publish_u64(&my_sum->residual, (unsigned long long)__double_as_longlong(res));
+            publish_u64(&my_sum->prob, (unsigned long long)__double_as_longlong(prob));
+        }
+        if (tid == 0) publish_stat(my_stat, any ? m : -INFINITY, any ? 0 : -1, any ? Zd : 1.0);
     }
 
     // ---- ticket: the workgroup that finishes last for this request does the draw ----------------------
@@ -649,120 +744,136 @@ __global__ __launch_bounds__(kQT, 8) void accept_decide_kernel(
     if (!sampled) {
         if (wv == 0) {
             ArgMax b{-INFINITY, V};
-            if (lane < n_parts) {
-                const HalfStat st = fetch_stat(sum_stat + i * kSumParts + lane);
-                if (st.arg >= 0) b = ArgMax{st.m, st.arg};
+            for (int p = lane; p < n_parts; p += kWave) {
+                const HalfStat st = fetch_stat(sum_stat + (int64_t)i * n_parts + p);
+                if (st.arg >= 0) b = argmax_merge(b, ArgMax{st.m, st.arg});
             }
             b = wave_argmax(b);
             if (lane == 0) o[a] = b.i < V ? b.i : 0;
         }
         return;
     }
-    // thread (part, step, wavefront): its residual and probability mass, all parts on one scale
-    const int ph = tid >> 4, pit = (tid >> 2) & 3, pw = tid & 3;
+    // thread t: the (part, wavefront) pairs 2t and 2t + 1 (of one part), all parts on one scale
+    const int n_pairs = n_parts * kQW;
     HalfStat st;
     st.m = -INFINITY; st.arg = -1; st.Z = 1.0;
-    float4 pr = make_float4(0.f, 0.f, 0.f, 0.f), pp = pr;
-    if (ph < n_parts) {
-        st = fetch_stat(sum_stat + i * kSumParts + ph);
-        const float *src = sums + sum_index(i, ph, pit, pw, 0);
-        const unsigned long long r0 = fetch_u64(src), r1 = fetch_u64(src + 2), p0 = fetch_u64(src + 4), p1 = fetch_u64(src + 6);
-        pr = make_float4(__uint_as_float((uint32_t)r0), __uint_as_float((uint32_t)(r0 >> 32)),
-                         __uint_as_float((uint32_t)r1), __uint_as_float((uint32_t)(r1 >> 32)));
-        pp = make_float4(__uint_as_float((uint32_t)p0), __uint_as_float((uint32_t)(p0 >> 32)),
-                         __uint_as_float((uint32_t)p1), __uint_as_float((uint32_t)(p1 >> 32)));
-    }
-    if ((tid & 15) == 0) { s_m[ph] = st.m; s_z[ph] = st.Z; }
-    __syncthreads();
-    float M = s_m[0];
+    double res[2] = {0.0, 0.0}, pm[2] = {0.0, 0.0};
+    if (2 * tid < n_pairs) {
+        const WaveMass *src = sums + (int64_t)i * n_pairs + 2 * tid;
+        st = fetch_stat(sum_stat + (int64_t)i * n_parts + (tid >> 1));
 #pragma unroll
-    for (int p = 1; p < kSumParts; ++p) M = fmaxf(M, s_m[p]);
+        for (int u = 0; u < 2; ++u) {
+            res[u] = __longlong_as_double((long long)fetch_u64(&src[u].residual));
+            pm[u] = __longlong_as_double((long long)fetch_u64(&src[u].prob));
+        }
+    }
+    if ((tid & 1) == 0) { s_m[tid >> 1] = st.m; s_z[tid >> 1] = st.Z; }
+    if (tid == 0) { s_pick[0] = s_pick[1] = 0x7fffffff; s_lastpos = -1; }
+    float M = wave_max(st.m);
+    if (lane == 0) s_wave[wv] = (double)M;
+    __syncthreads();
+    M = (float)s_wave[0];
+#pragma unroll
+    for (int w = 1; w < kQW; ++w) M = fmaxf(M, (float)s_wave[w]);
     // p_v of part h was computed as 2^((l_v - m_h) c) / Z_h: times Z_h 2^((m_h - M) c) it is relative to M in
     // every part (a rejected draft row has the same (m, Z) in all parts: a common factor, which tau absorbs)
     const double my_sc = st.m > -INFINITY ? st.Z * (double)__builtin_amdgcn_exp2f((st.m - M) * c) : 0.0;
-    const double res = (((double)pr.x + (double)pr.y) + ((double)pr.z + (double)pr.w)) * my_sc;
-    const double pm = (((double)pp.x + (double)pp.y) + ((double)pp.z + (double)pp.w)) * my_sc;
-    const int steps = ceil_div(row_chunks, kQT);             // steps of kQT chunks in the row (<= 64)
-    bool use_p = bonus;                                       // (for a bonus row the two sums are the same numbers)
-    for (int attempt = 0; attempt < 2; ++attempt) {
-        mass[ph][pit][pw] = use_p ? pm : res;
-        __syncthreads();
-        if (wv == 0) {
-            // lane L owns step L of the row: total over its wavefronts, running totals over the steps, R,
-            // and the step whose running total first exceeds tau
-            double t = 0.0;
-            if (lane < steps) {
 #pragma unroll
-                for (int ww = 0; ww < kQW; ++ww) t = t + mass[lane >> 2][lane & 3][ww];
-            }
-            const double incl = wave_scan_incl(t, lane);
-            const double R = __shfl(incl, steps - 1, kWave);
-            const double tq = (double)u_draw * R;
-            const unsigned long long hits = __ballot(lane < steps && incl > tq);
-            const int pick = hits ? (int)__builtin_ctzll(hits) : steps - 1;
-            const double bef = __shfl(incl - t, pick, kWave);
-            if (lane == 0) { s_tau = tq; s_before = bef; s_step = pick; s_retry = !(R > 0.0) && !use_p; }
+    for (int u = 0; u < 2; ++u) { res[u] *= my_sc; pm[u] *= my_sc; }
+    bool use_p = bonus;                                       // (for a bonus row the two sums are the same numbers)
+    double tau = 0.0;
+    for (int attempt = 0; attempt < 2; ++attempt) {
+        const double w0 = use_p ? pm[0] : res[0], w1 = use_p ? pm[1] : res[1];
+        const double incl = wave_scan_incl(w0 + w1, lane);
+        __syncthreads();                                      // s_wave is free again
+        if (lane == 63) s_wave[wv] = incl;
+        __syncthreads();
+        double before = 0.0, R = 0.0;
+#pragma unroll
+        for (int w = 0; w < kQW; ++w) {
+            if (w < wv) before += s_wave[w];
+            R += s_wave[w];
         }
+        if (!(R > 0.0) && !use_p) { use_p = true; continue; }  // p == q everywhere (R == 0): draw from p instead
+        tau = (double)u_draw * R;
+        // the first pair whose running total exceeds tau (rounding may leave none: then the last with mass).
+        // Every thread's claim goes through a minimum / maximum over pair numbers; the winner leaves its prefix.
+        const double at1 = before + incl, at0 = at1 - w1;     // running totals after the two pairs
+        int claim = 0x7fffffff, pos = -1;
+        if (w1 > 0.0) { pos = 2 * tid + 1; if (at1 > tau) claim = 2 * tid + 1; }
+        if (w0 > 0.0) { pos = max(pos, 2 * tid); if (at0 > tau) claim = 2 * tid; }
+        if (claim != 0x7fffffff) atomicMin(&s_pick[0], claim);
+        if (pos >= 0) atomicMax(&s_lastpos, pos);
         __syncthreads();
-        if (!s_retry) break;
-        use_p = true;                         // p == q everywhere (R == 0): draw from p instead
+        const int pick = s_pick[0] != 0x7fffffff ? s_pick[0] : s_lastpos;
+        if (pick >= 0 && (pick >> 1) == tid) s_before = (pick & 1) ? at0 : at0 - w0;
+        if (tid == 0) s_pick[1] = pick;
         __syncthreads();
+        break;
     }
-    if (wv != 0) return;
     ADASPEC_STAMP(1, 6);
 
-    // ---- inside the step: the wavefront, then the lane, then the element (one wavefront works) -----
-    const double tau = s_tau;
-    const int sstep = s_step;
-    const int hh = sstep >> 2, ii = sstep & 3;
-    const double ws = lane < kQW ? mass[hh][ii][lane] : 0.0;
-    const double wincl = s_before + wave_scan_incl(ws, lane);
-    const unsigned long long whit = __ballot(lane < kQW && ws > 0.0 && wincl > tau);
-    const unsigned long long wpos = __ballot(lane < kQW && ws > 0.0);
-    if (!wpos) {                              // no mass anywhere (non-finite input): stay defined
-        if (lane == 0) o[a] = 0;
+    // ---- inside the pair: the step (one wavefront each), then the lane, then the element ------------------
+    const int pair = s_pick[1];
+    if (pair < 0 || pair >= n_pairs) {        // no mass anywhere (non-finite input): stay defined
+        if (tid == 0) o[a] = 0;
         return;
     }
-    const int wstar = whit ? (int)__builtin_ctzll(whit) : 63 - (int)__builtin_clzll(wpos);
-    const double base = __shfl(wincl - ws, wstar, kWave);
-    // statistics and scale of the part that holds the step
+    const int hh = pair / kQW;
     HalfStat sth;
-    sth.m = s_m[hh]; sth.arg = 0; sth.Z = s_z[hh];
+    sth.m = s_m[hh]; sth.Z = s_z[hh];
     const double sch = sth.m > -INFINITY ? sth.Z * (double)__builtin_amdgcn_exp2f((sth.m - M) * c) : 0.0;
-    const int chunk = hh * (kSumSteps * kQT) + ii * kQT + wstar * kWave + lane;   // this lane's 16 bytes of the row
+    const int chunk = hh * kSumChunks + ((pair % kQW) * kSumSteps + wv) * kWave + lane;   // this lane's chunk of the row
     const bool with_q = has_q && !use_p;
-    uint4 lv = make_uint4(P::kNegInf2, P::kNegInf2, P::kNegInf2, P::kNegInf2), qv = make_uint4(0, 0, 0, 0);
+    uint4 lv = make_uint4(0, 0, 0, 0);
+    Probs qv;
+    qv.zero();
     if (chunk < row_chunks) {
         lv = *reinterpret_cast<const uint4 *>(lrow + (int64_t)chunk * 16);
-        if (with_q) qv = *reinterpret_cast<const uint4 *>(prow + (int64_t)chunk * 16);
+        if (with_q) __builtin_memcpy(qv.w, __builtin_assume_aligned(prow + (int64_t)chunk * Probs::kBytes, Probs::kBytes < 16 ? 8 : 16), Probs::kBytes);
     }
-    float rv[8], pv[8], sstar = 0.f;
-    part_chunk_masses<P>(lv, qv, c, sth.m * c, (float)(1.0 / sth.Z), rv, pv);   // same expressions as the sums
+    Chunk<LT>::blank(lv, chunk >= row_chunks);
+    float rv[kN], pv[kN], mine32 = 0.f;
+    part_chunk_masses<LT, PT>(lv, qv, sth.m, c, sth.m * c, (float)(1.0 / sth.Z), rv, pv);   // same expressions as the sums
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
+    for (int e = 0; e < kN; ++e) {
         if (use_p) rv[e] = pv[e];
-        sstar += rv[e];
+        mine32 += rv[e];
     }
-    const double mine = (double)sstar * sch;
-    const double li = base + wave_scan_incl(mine, lane);
-    const unsigned long long lhit = __ballot(sstar > 0.f && li > tau);
-    const unsigned long long lpos = __ballot(sstar > 0.f);
-    if (!lpos) {                              // the sums said there was mass here, the recomputation finds none
-        if (lane == 0) o[a] = 0;
-        return;
+    const double mine = (double)mine32 * sch;
+    const double incl = wave_scan_incl(mine, lane);
+    if (lane == 63) s_wave[wv] = incl;                        // (last read behind the barriers above)
+    __syncthreads();
+    // the step: first whose running total exceeds tau, else the last with mass
+    double at = s_before, base = 0.0;
+    int step = -1;
+    bool found = false;
+#pragma unroll
+    for (int it = 0; it < kSumSteps; ++it) {
+        const double tot = s_wave[it];
+        if (!found && tot > 0.0) {
+            step = it; base = at;
+            found = at + tot > tau;
+        }
+        at += tot;
     }
-    const int owner = lhit ? (int)__builtin_ctzll(lhit) : 63 - (int)__builtin_clzll(lpos);
+    if (step < 0 && tid == 0) o[a] = 0;       // the sums said there was mass here, the recomputation finds none
+    if (step != wv) return;
+    const double li = base + incl;
+    const unsigned long long lhit = __ballot(mine32 > 0.f && li > tau);
+    const unsigned long long lpos = __ballot(mine32 > 0.f);
+    const int owner = lhit ? (int)__builtin_ctzll(lhit) : 63 - (int)__builtin_clzll(lpos);   // lpos != 0: the step has mass
     if (lane == owner) {
         double cum = li - mine;
         int pick = -1, lastpos = -1;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
+        for (int e = 0; e < kN; ++e) {
             cum += (double)rv[e] * sch;
             if (rv[e] > 0.f) lastpos = e;
             if (pick < 0 && rv[e] > 0.f && cum > tau) pick = e;
         }
         if (pick < 0) pick = lastpos < 0 ? 0 : lastpos;
-        o[a] = chunk * 8 + pick;
+        o[a] = chunk * kN + pick;
     }
     ADASPEC_STAMP(1, 7);
 }
@@ -778,67 +889,78 @@ static int parts_compute_units()
     return cus;
 }
 
-bool accept_parts_supported(const adaspec_accept_dims &d)
+// elements per 16-byte chunk of logits
+static int chunk_elems(const adaspec_accept_dims &d) { return d.logits_dtype == ADASPEC_F32 ? 4 : 8; }
+static int sum_parts(const adaspec_accept_dims &d) { return ceil_div(d.vocab / chunk_elems(d), kSumChunks); }
+
+bool accept_parts_dims_fit(const adaspec_accept_dims &d)
 {
-    return d.batch <= kPartsMaxBatch && (int64_t)d.batch * d.max_spec_len <= kPartsMaxSlots &&
-           d.vocab <= kStatParts * kStatSteps * kQT * 8;
+    return d.batch <= kPartsMaxBatch && (int64_t)d.batch * d.max_spec_len <= kPartsMaxSlots && d.vocab <= kPartsMaxVocab &&
+           d.vocab % 8 == 0 && d.logits_row_stride % 8 == 0 && d.probs_row_stride % 8 == 0;
 }
 
 size_t accept_parts_slot_bytes(const adaspec_accept_dims &d)
 {
-    if (!accept_parts_supported(d)) return 0;
     return (size_t)d.batch * (d.max_spec_len > 0 ? d.max_spec_len : 1) * sizeof(SlotRec);
 }
 size_t accept_parts_stat_bytes(const adaspec_accept_dims &d)
 {
-    if (!accept_parts_supported(d)) return 0;
     return (size_t)d.batch * (d.max_spec_len > 0 ? d.max_spec_len : 1) * kStatParts * sizeof(HalfStat);
 }
 size_t accept_parts_sum_bytes(const adaspec_accept_dims &d)
 {
-    if (!accept_parts_supported(d)) return 0;
-    return (size_t)(d.batch > 0 ? d.batch : 1) * kSumParts * kSumSteps * kQW * 8 * sizeof(float);
+    return (size_t)(d.batch > 0 ? d.batch : 1) * sum_parts(d) * kQW * sizeof(WaveMass);
 }
 size_t accept_parts_sum_stat_bytes(const adaspec_accept_dims &d)
 {
-    if (!accept_parts_supported(d)) return 0;
-    return (size_t)(d.batch > 0 ? d.batch : 1) * kSumParts * sizeof(HalfStat);
+    return (size_t)(d.batch > 0 ? d.batch : 1) * sum_parts(d) * sizeof(HalfStat);
 }
 
 hipError_t launch_accept_parts(const AcceptArgs &a)
 {
     const adaspec_accept_dims &d = a.dims;
     if (d.batch == 0) return hipSuccess;
-    const int row_chunks = d.vocab >> 3, row_steps = ceil_div(row_chunks, kQT);
+    const int row_chunks = d.vocab / chunk_elems(d), row_steps = ceil_div(row_chunks, kQT);
     // First pass: a part is a stream of 8, 16, 32 or 64 steps.  Short streams spread a row over more compute
     // units; long ones read faster (measured on MI355X, config 3: 8 steps 48 us for the whole call, 16 steps
-    // 44 us, 32 steps 42 us).  Aim: about three workgroups per compute unit, all resident at once.
+    // 44 us, 32 steps 42 us).  Aim: about three workgroups per compute unit, all resident at once; and a row
+    // has kStatParts parts at most.
     int stat_steps = kStatSteps;
-    while (stat_steps < 64 && (int64_t)d.total_draft * ceil_div(row_steps, stat_steps) > (int64_t)kStatTargetWgsPerCu * parts_compute_units())
+    while (stat_steps < 64 &&
+           (row_steps > kStatParts * stat_steps ||
+            (int64_t)d.total_draft * ceil_div(row_steps, stat_steps) > (int64_t)kStatTargetWgsPerCu * parts_compute_units()))
         stat_steps *= 2;
     const int n_stat_parts = ceil_div(row_steps, stat_steps);
-    const int n_sum_parts = ceil_div(row_chunks, kSumSteps * kQT);
-    auto launch = [&](auto tag) {
-        using DT = decltype(tag);
-        int32_t *cu_q = (int32_t *)(a.ws + a.plan.off_cu_q);
-        int32_t *ticket = (int32_t *)(a.ws + a.plan.off_req_ticket);
-        SlotRec *slot_rec = (SlotRec *)(a.ws + a.plan.off_slot_rec);
-        HalfStat *part_stat = (HalfStat *)(a.ws + a.plan.off_part_stat);
+    const int n_sum_parts = sum_parts(d);
+    int32_t *cu_q = (int32_t *)(a.ws + a.plan.off_cu_q);
+    int32_t *ticket = (int32_t *)(a.ws + a.plan.off_req_ticket);
+    SlotRec *slot_rec = (SlotRec *)(a.ws + a.plan.off_slot_rec);
+    HalfStat *part_stat = (HalfStat *)(a.ws + a.plan.off_part_stat);
+    auto first = [&](auto lt) {
         // (the first pass always runs, at least with one workgroup: it also clears the tickets)
-        const int grid1 = d.total_draft > 0 ? d.total_draft * n_stat_parts : 1;
-        hipLaunchKernelGGL((accept_rowparts_kernel<DT>), dim3(grid1), dim3(kQT), 0, a.stream,
+        const int grid = d.total_draft > 0 ? d.total_draft * n_stat_parts : 1;
+        hipLaunchKernelGGL((accept_rowparts_kernel<decltype(lt)>), dim3(grid), dim3(kQT), 0, a.stream,
                            (const char *)a.logits, (const char *)a.probs, a.draft_tokens, a.uniforms, a.spec_lens,
                            a.temperature, d.batch, d.vocab, d.total_q, d.total_draft, d.max_spec_len, n_stat_parts,
-                           d.logits_row_stride, d.probs_row_stride, cu_q, ticket, slot_rec, part_stat);
-        hipLaunchKernelGGL((accept_decide_kernel<DT>), dim3(d.batch * n_sum_parts), dim3(kQT), 0, a.stream,
+                           d.logits_row_stride, d.probs_row_stride, d.probs_dtype, cu_q, ticket, slot_rec, part_stat);
+    };
+    auto second = [&](auto lt, auto pt) {
+        hipLaunchKernelGGL((accept_decide_kernel<decltype(lt), decltype(pt)>), dim3(d.batch * n_sum_parts), dim3(kQT), 0, a.stream,
                            (const char *)a.logits, (const char *)a.probs, a.draft_tokens, a.uniforms, a.spec_lens,
                            a.temperature, d.vocab, d.total_q, d.total_draft, d.max_spec_len, n_stat_parts, n_sum_parts,
                            d.logits_row_stride, d.probs_row_stride, cu_q, ticket, slot_rec, part_stat, d.out_stride,
-                           a.out_tokens, a.out_accept_len, (float *)(a.ws + a.plan.off_part),
+                           a.out_tokens, a.out_accept_len, (WaveMass *)(a.ws + a.plan.off_part),
                            (HalfStat *)(a.ws + a.plan.off_half_stat));
     };
-    if (d.logits_dtype == ADASPEC_F16) launch(F16{});
-    else launch(BF16{});
+    auto with_logits = [&](auto lt) {
+        first(lt);
+        if (d.probs_dtype == ADASPEC_F32) second(lt, F32{});
+        else if (d.probs_dtype == ADASPEC_F16) second(lt, F16{});
+        else second(lt, BF16{});
+    };
+    if (d.logits_dtype == ADASPEC_F32) with_logits(F32{});
+    else if (d.logits_dtype == ADASPEC_F16) with_logits(F16{});
+    else with_logits(BF16{});
     return hipGetLastError();
 }
 

@@ -1,8 +1,9 @@
 // Portable acceptance kernel: any vocabulary size, any of the three storage
 // types for logits and draft probabilities, arbitrary row strides.  One
 // workgroup of 256 threads per logits row, several sweeps over the row (the
-// later ones served by the caches).  It is the path for fp32 inputs and for
-// shapes the register-resident kernel does not take.
+// later ones served by the caches).  It is the path for rows that are not
+// aligned to 16 bytes or not a multiple of 8 long, and for batches of fp32 rows
+// that are too large for the form in parts.
 //
 // Per row:  sweep 1  max / argmax (lowest index wins ties)      -> greedy rows end here
 //           sweep 2  Z = sum 2^((l - m) * log2(e)/T)

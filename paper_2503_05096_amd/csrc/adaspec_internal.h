@@ -128,8 +128,9 @@ struct AcceptPlan {
     size_t off_slot_rec;    // int32[B * max_spec_len][4] per (request, draft position): token, its logit, its draft
                             // probability, the accept uniform (form in parts)
     size_t off_part_stat;   // HalfStat[B * max_spec_len][8]: (maximum, normaliser | arg-max) of each part of a draft row
-    size_t off_half_stat;   // HalfStat[B][16]: per part of the deciding row
-    size_t off_part;        // float[B][16 parts][4 steps][4][2][4]: partial sums of the deciding rows
+    size_t off_half_stat;   // HalfStat[B][parts]: per part of the deciding row
+    size_t off_part;        // WaveMass[B][parts][4]: masses of the deciding rows, per wavefront of a part
+    bool parts;             // the workspace holds what the form in parts needs
     size_t off_tree_stat;   // tree acceptance: per-node statistics (tree_node_stat_bytes() each)
     size_t total_bytes;
 };
@@ -162,8 +163,9 @@ hipError_t launch_accept_stream(const AcceptArgs &a);
 // two-pass form: flags of the draft rows, then one workgroup per request (sampling + outputs)
 hipError_t launch_accept_test(const AcceptArgs &a);
 hipError_t launch_accept_resolve(const AcceptArgs &a);
-// two-pass form with every row cut into parts (accept_parts.hip): up to 1024 requests
-bool accept_parts_supported(const adaspec_accept_dims &d);
+// two-pass form with every row cut into parts (accept_parts.hip): up to 1024 requests.  Whether a call can take it is
+// decided by its dims alone (plan.parts) and the alignment of its rows.
+bool accept_parts_dims_fit(const adaspec_accept_dims &d);
 size_t accept_parts_slot_bytes(const adaspec_accept_dims &d);
 size_t accept_parts_stat_bytes(const adaspec_accept_dims &d);
 size_t accept_parts_sum_bytes(const adaspec_accept_dims &d);

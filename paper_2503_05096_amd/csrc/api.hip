@@ -192,11 +192,22 @@ AcceptPlan make_accept_plan(const adaspec_accept_dims &d)
     const size_t nb = (size_t)(d.batch > 0 ? d.batch : 1);
     p.off_row_stat = off;   off = align_up(off + tq * sizeof(RowStat), 256);
     p.off_req_ticket = off; off = align_up(off + nb * 4, 256);
-    p.off_slot_rec = off;   off = align_up(off + accept_parts_slot_bytes(d), 256);
-    p.off_part_stat = off;  off = align_up(off + accept_parts_stat_bytes(d), 256);
-    p.off_half_stat = off;  off = align_up(off + accept_parts_sum_stat_bytes(d), 256);
-    p.off_part = off;       off = align_up(off + accept_parts_sum_bytes(d), 256);
     p.off_tree_stat = off; off = align_up(off + tq * tree_node_stat_bytes(), 256);
+    // What the form in parts needs comes last.  16-bit rows of one type up to V = 131072 always have it; for the others
+    // it is laid out only where the whole workspace still fits adaspec_accept_noalloc's built-in scratch, so that no
+    // call outgrows that array because of it.
+    p.parts = accept_parts_dims_fit(d);
+    p.off_slot_rec = p.off_part_stat = p.off_half_stat = p.off_part = off;
+    if (p.parts) {
+        size_t end = off;
+        p.off_slot_rec = end;   end = align_up(end + accept_parts_slot_bytes(d), 256);
+        p.off_part_stat = end;  end = align_up(end + accept_parts_stat_bytes(d), 256);
+        p.off_half_stat = end;  end = align_up(end + accept_parts_sum_stat_bytes(d), 256);
+        p.off_part = end;       end = align_up(end + accept_parts_sum_bytes(d), 256);
+        const bool narrow = d.logits_dtype != ADASPEC_F32 && d.logits_dtype == d.probs_dtype && d.vocab <= 131072;
+        p.parts = narrow || end <= kNoallocScratchBytes;
+        if (p.parts) off = end;
+    }
     p.total_bytes = off;
     return p;
 }
@@ -304,7 +315,7 @@ static int resolve_accept_path(const adaspec_accept_dims &d, const void *logits,
     // use the older two-pass pair when there are more rows than compute units or the vocabulary is large; a
     // row that does not fit the registers of one workgroup (V > 131072) goes to the streaming kernel, anything
     // else to the vector kernel.
-    if (two_pass_ok && accept_parts_supported(d)) return ADASPEC_PATH_TWO_PASS;
+    if (two_pass_ok && make_accept_plan(d).parts) return ADASPEC_PATH_TWO_PASS;
     if (two_pass_ok && (d.total_q > compute_units() || d.vocab >= 65536)) return ADASPEC_PATH_TWO_PASS;
     if (fast_ok) return ADASPEC_PATH_FAST;
     if (stream_ok) return ADASPEC_PATH_STREAM;
@@ -355,12 +366,18 @@ static int accept_impl(const void *target_logits, const void *draft_probs,
     a.dims = *dims; a.ws = static_cast<char *>(workspace);
     a.stream = static_cast<hipStream_t>(stream);
 
-    if (two_pass) {
+    // AUTO: rows that the two-pass form in parts can read (any storage types, V up to 524288, aligned) take it in place of
+    // the streaming and vector kernels too, which evaluate every row in one workgroup (MI355X, whole call: V = 128256
+    // in fp32, 256 rows: vector kernel 746 us, in parts 43 us; V = 262144 in bf16, 192 rows: streaming kernel 65 us, in
+    // parts 36 us).  Forced paths keep their kernels, and so do AUTO calls with other rows or too many requests.
+    const bool aligned = aligned16(target_logits) && (dims->total_draft == 0 || aligned16(draft_probs));
+    const bool in_parts = a.plan.parts && aligned && (two_pass || (dims->path == ADASPEC_PATH_AUTO && !fast));
+    if (two_pass || in_parts) {
         // the statistics of the draft rows, then per request the accept tests, the sampling on the one row
         // that decides its token, and the request's outputs (no emit kernel); both in row parts for up to
         // 1024 requests, larger batches with one workgroup per row and then per request
         if (!record_event(dims->timing_start, dims->timing_stop, true, a.stream)) return ADASPEC_ERR_HIP;
-        if (accept_parts_supported(*dims)) {
+        if (in_parts) {
             if (launch_accept_parts(a) != hipSuccess) return ADASPEC_ERR_HIP;
         } else {
             if (launch_accept_test(a) != hipSuccess) return ADASPEC_ERR_HIP;
