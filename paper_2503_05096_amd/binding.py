@@ -68,6 +68,31 @@ class AdaspecError(RuntimeError):
 
 
 _lib = None
+_fast = None        # the _fastcall module once the library is loaded
+
+# entry points the native call path uses, in the order it expects their addresses
+_FAST_ENTRIES = ("adaspec_verify_attn_workspace_bytes", "adaspec_verify_attn", "adaspec_verify_attn_tree",
+                 "adaspec_accept_workspace_bytes", "adaspec_accept", "adaspec_accept_tree", "adaspec_kv_append",
+                 "adaspec_kv_compact_path", "adaspec_commit", "adaspec_draft_sample_workspace_bytes",
+                 "adaspec_draft_sample")
+
+
+def _native():
+    """The native call path (csrc_python/fastcall.cpp): its functions make an ordinary call in full, or return
+    NotImplemented without having done anything, and the wrapper goes on in Python."""
+    global _fast
+    if _fast is None:
+        L = lib()
+        import torch
+        try:
+            from . import _fastcall
+        except ImportError as e:
+            raise ImportError(f"{os.path.join(_HERE, '_fastcall.so')} is missing or does not fit this torch: build it "
+                              "together with the library (python paper_2503_05096_amd/build.py)") from e
+        _fastcall.setup(tuple(C.cast(getattr(L, n), C.c_void_p).value for n in _FAST_ENTRIES), _workspace,
+                        torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice)
+        _fast = _fastcall
+    return _fast
 
 
 def lib() -> C.CDLL:
@@ -216,6 +241,11 @@ def verify_attn(q, k_pages, v_pages, block_table, ctx_lens, spec_lens, out=None,
     require `workspace`: a tensor of at least adaspec_verify_attn_workspace_bytes that the caller owns
     and that no other call touches between the build and the last reuse.
     parents [TQ] int32 (a draft tree): adaspec_verify_attn_tree instead."""
+    if path == "auto" and timing is None:
+        r = (_fast or _native()).verify_attn(q, k_pages, v_pages, block_table, ctx_lens, spec_lens, out, max_spec_len,
+                                             scale, out_dtype, plan, workspace, stream, parents)
+        if r is not NotImplemented:
+            return r
     import torch
     dims = _with_timing(attn_dims(q, k_pages, block_table, max_spec_len=max_spec_len, scale=scale,
                                   out_dtype=out_dtype, path=path, plan=plan), timing)
@@ -290,6 +320,11 @@ def accept(target_logits, draft_probs, draft_tokens, uniforms, spec_lens, temper
            max_spec_len: int, out_tokens=None, out_accept_len=None, out_stride: Optional[int] = None,
            path: str = "auto", workspace=None, stream=None, timing=None) -> Tuple[object, object]:
     """adaspec_accept on device tensors; returns (out_tokens [B][out_stride], out_accept_len [B])."""
+    if path == "auto" and timing is None:
+        r = (_fast or _native()).accept(target_logits, draft_probs, draft_tokens, uniforms, spec_lens, temperature,
+                                        max_spec_len, out_tokens, out_accept_len, out_stride, workspace, stream)
+        if r is not NotImplemented:
+            return r
     import torch
     for t in (uniforms, temperature):
         assert t.is_cuda
@@ -339,6 +374,12 @@ def accept_tree(target_logits, draft_probs, draft_tokens, parents, uniforms, spe
                 out_stride: Optional[int] = None, path: str = "auto", workspace=None, stream=None, timing=None):
     """adaspec_accept_tree; returns (out_tokens [B][out_stride], out_accept_len [B], out_path [B][out_stride]).
     path: "auto", "vector" (portable per-node kernel) or "fast" (1024-thread per-node kernel)."""
+    if path == "auto" and timing is None:
+        r = (_fast or _native()).accept_tree(target_logits, draft_probs, draft_tokens, parents, uniforms, spec_lens,
+                                             temperature, max_spec_len, out_tokens, out_accept_len, out_path, out_stride,
+                                             workspace, stream)
+        if r is not NotImplemented:
+            return r
     import torch
     for t in (uniforms, temperature, parents):
         assert t.is_cuda and t.is_contiguous()
@@ -369,6 +410,9 @@ def accept_tree(target_logits, draft_probs, draft_tokens, parents, uniforms, spe
 def kv_compact_path(k_pages, v_pages, block_table, ctx_lens, spec_lens, out_path, out_accept_len, *,
                     max_spec_len: int, stream=None) -> None:
     """adaspec_kv_compact_path: moves the accepted nodes' K/V rows to chain positions, in place."""
+    if (_fast or _native()).kv_compact_path(k_pages, v_pages, block_table, ctx_lens, spec_lens, out_path, out_accept_len,
+                                            max_spec_len, stream) is not NotImplemented:
+        return
     import torch
     num_pages, Hkv, P, d = k_pages.shape
     B, max_pages = block_table.shape
@@ -431,6 +475,9 @@ def check_ragged_inputs(block_table, ctx_lens, spec_lens, dims: AttnDims, stream
 def kv_append(k_new, v_new, k_pages, v_pages, block_table, ctx_lens, spec_lens, *, max_spec_len: int,
               stream=None) -> None:
     """adaspec_kv_append: writes the new tokens' K/V rows [TQ][Hkv][d] into the pages, in place."""
+    if (_fast or _native()).kv_append(k_new, v_new, k_pages, v_pages, block_table, ctx_lens, spec_lens, max_spec_len,
+                                      stream) is not NotImplemented:
+        return
     import torch
     TQ, Hkv, d = k_new.shape
     num_pages, Hkv2, P, d2 = k_pages.shape
@@ -453,6 +500,10 @@ def commit(out_tokens, out_accept_len, spec_lens, ctx_lens, *, max_spec_len: int
            committed_lens=None, next_ctx_lens=None, last_token=None, seq_tokens=None, seq_lens=None,
            stream=None):
     """adaspec_commit; returns (committed_lens, next_ctx_lens or None, last_token)."""
+    r = (_fast or _native()).commit(out_tokens, out_accept_len, spec_lens, ctx_lens, max_spec_len, next_spec_lens,
+                                    committed_lens, next_ctx_lens, last_token, seq_tokens, seq_lens, stream)
+    if r is not NotImplemented:
+        return r
     import torch
     B, out_stride = out_tokens.shape
     dev = out_tokens.device
@@ -484,6 +535,11 @@ def draft_sample(draft_logits, temperature, uniforms, *, probs_dtype=None, draft
                  draft_tokens=None, confidence=None, path: str = "auto", workspace=None, stream=None, timing=None):
     """adaspec_draft_sample; returns (draft_probs, draft_tokens [R] int32, confidence [R] float32).
     path "split" (ADASPEC_PATH_TWO_PASS for this call) cuts every row into four parts."""
+    if path == "auto" and timing is None:
+        r = (_fast or _native()).draft_sample(draft_logits, temperature, uniforms, probs_dtype, draft_probs, out_rows,
+                                              draft_tokens, confidence, workspace, stream)
+        if r is not NotImplemented:
+            return r
     import torch
     R, V = draft_logits.shape
     dev = draft_logits.device

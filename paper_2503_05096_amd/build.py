@@ -1,5 +1,5 @@
 """Builds libadaspec.so (the C-ABI library) from csrc/*.hip (device + host code) and csrc/*.cpp
-(host-only code) for gfx950 with hipcc."""
+(host-only code) for gfx950 with hipcc, and _fastcall.so (the Python binding's native call path) with g++."""
 from __future__ import annotations
 
 import glob
@@ -13,6 +13,8 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 BUILD_DIR = os.path.join(HERE, "_build")
 LIB_PATH = os.path.join(HERE, "libadaspec.so")
+FASTCALL_SOURCE = os.path.join(HERE, "csrc_python", "fastcall.cpp")
+FASTCALL_PATH = os.path.join(HERE, "_fastcall.so")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -20,6 +22,25 @@ FLAGS = [
     # packed-FP32 instructions stay off (scalar fp32 code only)
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
 ]
+
+
+def build_fastcall(verbose: bool = False) -> str:
+    """The extension module uses torch's and Python's headers only (no HIP), so the host compiler builds it."""
+    import sysconfig
+
+    import torch
+    root = os.path.dirname(torch.__file__)
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-I", os.path.join(root, "include"), "-I", os.path.join(root, "include", "torch", "csrc", "api", "include"),
+           "-I", sysconfig.get_paths()["include"], FASTCALL_SOURCE, "-o", FASTCALL_PATH,
+           "-L", os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"g++ failed on {FASTCALL_SOURCE}:\n{r.stderr}")
+    return FASTCALL_PATH
 
 
 def build_library(verbose: bool = False, jobs: int = 8) -> str:
@@ -38,7 +59,9 @@ def build_library(verbose: bool = False, jobs: int = 8) -> str:
         return r.stderr
 
     with ThreadPoolExecutor(jobs) as ex:
+        fastcall = ex.submit(build_fastcall, verbose)
         logs = list(ex.map(compile_one, zip(sources, objects)))
+        fastcall.result()
     if verbose:
         for log in logs:
             # hipcc's host pass does not know the device-only feature flag: harmless
