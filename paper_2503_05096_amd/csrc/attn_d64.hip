@@ -58,21 +58,21 @@ __device__ __forceinline__ void split_weights(const float *p, uint4 (&w)[WeightS
     }
 }
 
-template <class T, int RT, bool kTree>
+template <class T, int RT, bool kTree, bool kDirect>
 __global__ __launch_bounds__(256, (RT <= 2 ? 2 : 1)) void attn_d64_kernel(
     const char *__restrict__ q, const char *__restrict__ k_pages, const char *__restrict__ v_pages,
     const int32_t *__restrict__ block_table, void *__restrict__ out, const int32_t *__restrict__ header,
     const int32_t *__restrict__ unit_meta, const int32_t *__restrict__ sched,
     const unsigned long long *__restrict__ anc, float *__restrict__ part_ml, float *__restrict__ part_o,
-    int Hq, int Hkv, int max_pages_per_req, int max_rows, int n_row_groups, float scale_log2, int out_dtype)
+    int Hq, int Hkv, int max_pages_per_req, int max_rows, int n_row_groups, float scale_log2, int out_dtype, DirectArgs direct)
 {
     constexpr int kRows = 16 * RT;
-    constexpr int kMerge = kRows * kORow64 * 4;
-    constexpr int kSmem = kWaves * kVtBytes > kMerge ? kWaves * kVtBytes : kMerge;
+    // per wavefront: its V^T tile, later its [rows][d] fp32 state for the merge
+    constexpr int kSlab = kRows * kORow64 * 4 > kVtBytes ? kRows * kORow64 * 4 : kVtBytes;
     constexpr int kQLoads = (RT * 2 * 64 + 255) / 256;              // Q^T operand entries per thread
-    __shared__ __attribute__((aligned(16))) char smem[kSmem];
+    __shared__ __attribute__((aligned(16))) char smem[kWaves * kSlab];
     __shared__ __attribute__((aligned(16))) uint4 q_lds[RT * 2 * 64];   // Q^T operands, MFMA lane order
-    __shared__ float s_m[kWaves][kRows], s_l[kWaves][kRows], s_mstar[kRows];
+    __shared__ float s_m[kWaves][kRows], s_l[kWaves][kRows];
     __shared__ unsigned long long s_anc[kTree ? kRows : 1];         // ancestor mask of each row of the unit
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -80,13 +80,13 @@ __global__ __launch_bounds__(256, (RT <= 2 ? 2 : 1)) void attn_d64_kernel(
     const int g = lane >> 4, n16 = lane & 15;
     const int v_half = (lane >> 3) & 1, v_c = lane & 7;             // V loads: half-block and 8-channel chunk of the lane
     const int G = Hq / Hkv;
-    const int total_units = header[0] * Hkv * n_row_groups;
+    const int total_units = kDirect ? 0 : header[0] * Hkv * n_row_groups;
     const int64_t head_bytes = (int64_t)16 * kD64 * 2;              // one (page, head) block
-    char *my_lds = smem + wv * kVtBytes;
+    char *my_lds = smem + wv * kSlab;
     // V^T tile unit of (half, channel 8c + dd, group): 66 dd + 16 grp + 8 half + c
     char *vt_wr = my_lds + 16 * lane;
     const char *vt_rd = my_lds + 16 * (66 * (n16 & 7) + 16 * g + (n16 >> 3));
-    float *obuf = reinterpret_cast<float *>(smem);
+    float *my_state = reinterpret_cast<float *>(my_lds);
 
     // K operand: lane (g, m) <- token 16 mt + m, channels 32 s + 8 g .. +7
     // V raw:     lane (tq = g, half, c) <- token 32 half + 16 pg + 4 tq + i, channels 8 c .. 8 c + 7
@@ -95,7 +95,7 @@ __global__ __launch_bounds__(256, (RT <= 2 ? 2 : 1)) void attn_d64_kernel(
     const uint32_t v_lane_off = (4 * g) * (kD64 * 2) + 16 * v_c;
 
     const int W = gridDim.x, wg = blockIdx.x;
-    const int n_rounds = header[2];
+    const int n_rounds = kDirect ? 0 : header[2];
     int round = 0;
     int idx_ahead = wg;                                             // round 0 is the identity
     auto next_unit = [&](Unit &u) -> bool {
@@ -172,9 +172,11 @@ __global__ __launch_bounds__(256, (RT <= 2 ? 2 : 1)) void attn_d64_kernel(
     };
 
     Unit cur, nxt;
-    bool have = next_unit(cur);
+    bool have;
     uint4 qv[kQLoads];
     unsigned long long av = 0ull;
+    if constexpr (kDirect) have = direct_unit(cur, direct, block_table, G, Hkv, n_row_groups, kRows, kBlk64, max_pages_per_req, wv, lane);
+    else have = next_unit(cur);
     if (have) {
         load_q(cur, qv);
         if constexpr (kTree) av = load_anc(cur);
@@ -183,7 +185,7 @@ __global__ __launch_bounds__(256, (RT <= 2 ? 2 : 1)) void attn_d64_kernel(
 
     while (have) {
         const Unit u = cur;
-        const bool have_next = next_unit(nxt);
+        const bool have_next = kDirect ? false : next_unit(nxt);
         const int first_masked = u.L - u.n + 1;                    // tokens >= this are hidden from some row
 #pragma unroll
         for (int k = 0; k < kQLoads; ++k)
@@ -195,7 +197,7 @@ __global__ __launch_bounds__(256, (RT <= 2 ? 2 : 1)) void attn_d64_kernel(
             const int row = u.r0 + 16 * nt + n16;
             pos[nt] = row < u.rows ? (u.L - u.n + row / G) : -1;
         }
-        __syncthreads();
+        lds_barrier();
 
         float m[RT], lsum[RT];
         f32x4 o[RT][4];
@@ -331,48 +333,22 @@ __global__ __launch_bounds__(256, (RT <= 2 ? 2 : 1)) void attn_d64_kernel(
         }
 
         // ---- next unit: its first K/V block and Q rows travel while this unit's states are merged
-#pragma unroll
-        for (int nt = 0; nt < RT; ++nt) {
-            lsum[nt] += __shfl_xor(lsum[nt], 16, kWave);
-            lsum[nt] += __shfl_xor(lsum[nt], 32, kWave);
-            if (g == 0) s_m[wv][16 * nt + n16] = m[nt];
-        }
         if (have_next) {
             load_q(nxt, qv);
             if constexpr (kTree) av = load_anc(nxt);
             first_loads(nxt);
         }
-        __syncthreads();            // s_m complete; every wavefront is done with its V^T tile and q_lds
-
         // ---- merge the four wavefronts' states through LDS (as in attn_mfma.hip) ----------
-        float fsc[RT];
 #pragma unroll
         for (int nt = 0; nt < RT; ++nt) {
-            const int rl = 16 * nt + n16;
-            float ms = s_m[0][rl];
+            lsum[nt] += __shfl_xor(lsum[nt], 16, kWave);
+            lsum[nt] += __shfl_xor(lsum[nt], 32, kWave);
+            if (g == 0) { s_m[wv][16 * nt + n16] = m[nt]; s_l[wv][16 * nt + n16] = lsum[nt]; }
 #pragma unroll
-            for (int w = 1; w < kWaves; ++w) ms = fmaxf(ms, s_m[w][rl]);
-            fsc[nt] = __builtin_amdgcn_exp2f(m[nt] - ms);
-            if (g == 0) {
-                s_l[wv][rl] = lsum[nt] * fsc[nt];
-                if (wv == 0) s_mstar[rl] = ms;
-            }
+            for (int dt = 0; dt < 4; ++dt)
+                *reinterpret_cast<f32x4 *>(my_state + (16 * nt + n16) * kORow64 + 16 * dt + 4 * g) = o[nt][dt];
         }
-#pragma unroll
-        for (int w = 0; w < kWaves; ++w) {
-            if (wv == w) {
-#pragma unroll
-                for (int nt = 0; nt < RT; ++nt)
-#pragma unroll
-                    for (int dt = 0; dt < 4; ++dt) {
-                        f32x4 *dst = reinterpret_cast<f32x4 *>(obuf + (16 * nt + n16) * kORow64 + 16 * dt + 4 * g);
-                        f32x4 v = o[nt][dt] * fsc[nt];
-                        if (w > 0) v += *dst;
-                        *dst = v;
-                    }
-            }
-            __syncthreads();
-        }
+        lds_barrier();
         // 256 threads: 16*RT rows x 16 float4 columns
 #pragma unroll
         for (int it = 0; it < RT; ++it) {
@@ -380,8 +356,16 @@ __global__ __launch_bounds__(256, (RT <= 2 ? 2 : 1)) void attn_d64_kernel(
             const int rl = idx >> 4, c4 = idx & 15;
             const int row = u.r0 + rl;
             if (row >= u.rows) continue;
-            const f32x4 acc = *reinterpret_cast<const f32x4 *>(obuf + rl * kORow64 + 4 * c4);
-            const float ltot = (s_l[0][rl] + s_l[1][rl]) + (s_l[2][rl] + s_l[3][rl]);
+            float ms = s_m[0][rl], ltot = 0.f;
+#pragma unroll
+            for (int w = 1; w < kWaves; ++w) ms = fmaxf(ms, s_m[w][rl]);
+            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) {
+                const float sc = __builtin_amdgcn_exp2f(s_m[w][rl] - ms);
+                ltot += sc * s_l[w][rl];
+                acc += sc * *reinterpret_cast<const f32x4 *>(smem + w * kSlab + 4 * (rl * kORow64 + 4 * c4));
+            }
             if (u.ns == 1) {
                 const float inv = 1.0f / ltot;
                 const int64_t obase = ((u.qrow0 + row / G) * Hq + u.gkv * G + row % G) * (int64_t)kD64 + 4 * c4;
@@ -396,13 +380,14 @@ __global__ __launch_bounds__(256, (RT <= 2 ? 2 : 1)) void attn_d64_kernel(
                 const int64_t idx_row = ((int64_t)u.item * Hkv + u.gkv) * max_rows + row;
                 *reinterpret_cast<f32x4 *>(part_o + idx_row * kD64 + 4 * c4) = acc;
                 if (c4 == 0) {
-                    part_ml[idx_row * 2] = s_mstar[rl];
+                    part_ml[idx_row * 2] = ms;
                     part_ml[idx_row * 2 + 1] = ltot;
                 }
             }
         }
-        // the next loop iteration overwrites q_lds and the V^T tiles: everyone must be done reading obuf
-        __syncthreads();
+        if constexpr (kDirect) break;
+        // the next loop iteration overwrites q_lds, the V^T tiles and s_m: everyone must be done reading the states
+        lds_barrier();
         cur = nxt;
         have = have_next;
     }
@@ -410,28 +395,30 @@ __global__ __launch_bounds__(256, (RT <= 2 ? 2 : 1)) void attn_d64_kernel(
 
 // ---- host side -----------------------------------------------------------------------------------------------
 template <typename F>
-static void with_d64_instance(int dtype, int rt, bool tree, F &&f)
+static void with_d64_instance(const AttnArgs &a, F &&f)
 {
-    auto with_rt = [&](auto tag, auto tree_tag) {
-        if (rt == 1) f(tag, std::integral_constant<int, 1>{}, tree_tag);
-        else if (rt == 2) f(tag, std::integral_constant<int, 2>{}, tree_tag);
-        else f(tag, std::integral_constant<int, 4>{}, tree_tag);
+    const int rt = attn_row_tiles(a.plan.max_rows);
+    auto with_mode = [&](auto tag, auto rt_tag) {
+        if (a.direct) f(tag, rt_tag, std::false_type{}, std::true_type{});
+        else if (a.parents) f(tag, rt_tag, std::true_type{}, std::false_type{});
+        else f(tag, rt_tag, std::false_type{}, std::false_type{});
     };
-    auto with_tree = [&](auto tag) {
-        if (tree) with_rt(tag, std::true_type{});
-        else with_rt(tag, std::false_type{});
+    auto with_rt = [&](auto tag) {
+        if (rt == 1) with_mode(tag, std::integral_constant<int, 1>{});
+        else if (rt == 2) with_mode(tag, std::integral_constant<int, 2>{});
+        else with_mode(tag, std::integral_constant<int, 4>{});
     };
-    if (dtype == ADASPEC_F16) with_tree(F16{});
-    else with_tree(BF16{});
+    if (a.dims.dtype == ADASPEC_F16) with_rt(F16{});
+    else with_rt(BF16{});
 }
 
-template <typename T, int RT, bool kTree>
+template <typename T, int RT, bool kTree, bool kDirect>
 static int attn_d64_slots(int cus)
 {
     static int slots = 0;
     if (slots == 0) {
         int per_cu = 1;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, attn_d64_kernel<T, RT, kTree>, 256, 0) != hipSuccess)
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, attn_d64_kernel<T, RT, kTree, kDirect>, 256, 0) != hipSuccess)
             per_cu = 1;
         const int n = cus * (per_cu > 0 ? per_cu : 1);
         slots = n < kMaxSchedW ? n : kMaxSchedW;
@@ -442,8 +429,8 @@ static int attn_d64_slots(int cus)
 int attn_d64_grid_slots(const AttnArgs &a, int cus)
 {
     int slots = 1;
-    with_d64_instance(a.dims.dtype, attn_row_tiles(a.plan.max_rows), a.parents != nullptr, [&](auto tag, auto rt_tag, auto tree_tag) {
-        slots = attn_d64_slots<decltype(tag), decltype(rt_tag)::value, decltype(tree_tag)::value>(cus);
+    with_d64_instance(a, [&](auto tag, auto rt, auto tree, auto direct) {
+        slots = attn_d64_slots<decltype(tag), decltype(rt)::value, decltype(tree)::value, decltype(direct)::value>(cus);
     });
     return slots;
 }
@@ -453,15 +440,14 @@ hipError_t launch_attn_d64(const AttnArgs &a)
     const AttnPlan &p = a.plan;
     const adaspec_attn_dims &d = a.dims;
     if (a.sched_w <= 0) return hipSuccess;                          // no work item can exist
-    with_d64_instance(d.dtype, attn_row_tiles(p.max_rows), a.parents != nullptr, [&](auto tag, auto rt_tag, auto tree_tag) {
-        using T = decltype(tag);
-        hipLaunchKernelGGL((attn_d64_kernel<T, decltype(rt_tag)::value, decltype(tree_tag)::value>), dim3(a.sched_w),
-                           dim3(256), 0, a.stream, (const char *)a.q, (const char *)a.k_pages, (const char *)a.v_pages,
-                           a.block_table, a.out, (const int32_t *)(a.ws + p.off_header),
+    with_d64_instance(a, [&](auto tag, auto rt, auto tree, auto direct) {
+        hipLaunchKernelGGL((attn_d64_kernel<decltype(tag), decltype(rt)::value, decltype(tree)::value, decltype(direct)::value>),
+                           dim3(a.sched_w), dim3(256), 0, a.stream, (const char *)a.q, (const char *)a.k_pages,
+                           (const char *)a.v_pages, a.block_table, a.out, (const int32_t *)(a.ws + p.off_header),
                            (const int32_t *)(a.ws + p.off_unit_meta), (const int32_t *)(a.ws + p.off_sched),
                            (const unsigned long long *)(a.ws + p.off_anc), (float *)(a.ws + p.off_part_ml),
                            (float *)(a.ws + p.off_part_o), d.n_q_heads, d.n_kv_heads, d.max_pages_per_req, p.max_rows,
-                           a.n_row_groups, a.scale_log2, d.out_dtype);
+                           a.n_row_groups, a.scale_log2, d.out_dtype, direct_args(a));
     });
     return hipGetLastError();
 }

@@ -42,9 +42,12 @@ __global__ __launch_bounds__(256, (RT <= 2 ? 2 : 1)) void attn_f32_kernel(
 {
     constexpr int kRows = 16 * RT, kJ = D / 16, kH = D / 64, kORow = D + 4;
     constexpr int kQLoads = RT * kJ * 64 / 256;
-    __shared__ __attribute__((aligned(16))) float obuf[kRows * kORow];
+    constexpr int kState = kRows * kORow;                                  // floats of one wavefront's state
+    // merge buffer: one state per wavefront, or (four tiles of 128 channels: too large) one that they add into in turn
+    constexpr bool kSlabs = kState * kWaves * 4 <= 96 * 1024;
+    __shared__ __attribute__((aligned(16))) float obuf[kSlabs ? kWaves * kState : kState];
     __shared__ __attribute__((aligned(16))) f32x4 q_lds[RT * kJ * 64];     // Q^T operands, MFMA lane order
-    __shared__ float s_m[kWaves][kRows], s_l[kWaves][kRows], s_mstar[kRows];
+    __shared__ float s_m[kWaves][kRows], s_l[kWaves][kRows];
     __shared__ unsigned long long s_anc[kTree ? kRows : 1];
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -123,7 +126,7 @@ __global__ __launch_bounds__(256, (RT <= 2 ? 2 : 1)) void attn_f32_kernel(
     bool have;
     f32x4 qv[kQLoads];
     unsigned long long av = 0ull;
-    if constexpr (kDirect) have = direct_unit(cur, direct, G, Hkv, n_row_groups, kRows, kPage, max_pages_per_req, lane);
+    if constexpr (kDirect) have = direct_unit(cur, direct, block_table, G, Hkv, n_row_groups, kRows, kPage, max_pages_per_req, wv, lane);
     else have = next_unit(cur);
     if (have) {
         first_loads(cur);
@@ -248,50 +251,54 @@ __global__ __launch_bounds__(256, (RT <= 2 ? 2 : 1)) void attn_f32_kernel(
         }
 
         // ---- next unit: its first page and Q rows travel while this unit's states are merged
-#pragma unroll
-        for (int nt = 0; nt < RT; ++nt) {
-            lsum[nt] += __shfl_xor(lsum[nt], 16, kWave);
-            lsum[nt] += __shfl_xor(lsum[nt], 32, kWave);
-            if (g == 0) s_m[wv][16 * nt + n16] = m[nt];
-        }
         if (have_next) {
             first_loads(nxt);
             load_q(nxt, qv);
             if constexpr (kTree) av = load_anc(nxt);
         }
-        lds_barrier();              // s_m complete; every wavefront is done with q_lds
-
         // ---- merge the four wavefronts' states through LDS (as in attn_mfma.hip) ----------
-        float fsc[RT];
 #pragma unroll
         for (int nt = 0; nt < RT; ++nt) {
-            const int rl = 16 * nt + n16;
-            float ms = s_m[0][rl];
-#pragma unroll
-            for (int w = 1; w < kWaves; ++w) ms = fmaxf(ms, s_m[w][rl]);
-            fsc[nt] = __builtin_amdgcn_exp2f(m[nt] - ms);
-            if (g == 0) {
-                s_l[wv][rl] = lsum[nt] * fsc[nt];
-                if (wv == 0) s_mstar[rl] = ms;
-            }
+            lsum[nt] += __shfl_xor(lsum[nt], 16, kWave);
+            lsum[nt] += __shfl_xor(lsum[nt], 32, kWave);
+            if (g == 0) { s_m[wv][16 * nt + n16] = m[nt]; s_l[wv][16 * nt + n16] = lsum[nt]; }
         }
+        auto leave_state = [&](float *buf, float (&sc)[RT], bool add) {
 #pragma unroll
-        for (int w = 0; w < kWaves; ++w) {
-            if (wv == w) {
+            for (int nt = 0; nt < RT; ++nt)
 #pragma unroll
-                for (int nt = 0; nt < RT; ++nt)
+                for (int h = 0; h < kH; ++h)
 #pragma unroll
-                    for (int h = 0; h < kH; ++h)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) {
-                            // lane (g, n16), register r of tile (h, e): channel 64 h + 16 g + 4 r + e
-                            f32x4 *dst = reinterpret_cast<f32x4 *>(obuf + (16 * nt + n16) * kORow + 64 * h + 16 * g + 4 * r);
-                            f32x4 v = f32x4{o[nt][h][0][r], o[nt][h][1][r], o[nt][h][2][r], o[nt][h][3][r]} * fsc[nt];
-                            if (w > 0) v += *dst;
-                            *dst = v;
+                    for (int r = 0; r < 4; ++r) {
+                        // lane (g, n16), register r of tile (h, e): channel 64 h + 16 g + 4 r + e
+                        f32x4 *dst = reinterpret_cast<f32x4 *>(buf + (16 * nt + n16) * kORow + 64 * h + 16 * g + 4 * r);
+                        f32x4 v = f32x4{o[nt][h][0][r], o[nt][h][1][r], o[nt][h][2][r], o[nt][h][3][r]};
+                        if constexpr (!kSlabs) {
+                            v *= sc[nt];
+                            if (add) v += *dst;
                         }
-            }
+                        *dst = v;
+                    }
+        };
+        float fsc[RT] = {};
+        if constexpr (kSlabs) {
+            leave_state(obuf + wv * kState, fsc, false);
             lds_barrier();
+        } else {
+            lds_barrier();          // s_m complete
+#pragma unroll
+            for (int nt = 0; nt < RT; ++nt) {
+                const int rl = 16 * nt + n16;
+                float ms = s_m[0][rl];
+#pragma unroll
+                for (int w = 1; w < kWaves; ++w) ms = fmaxf(ms, s_m[w][rl]);
+                fsc[nt] = __builtin_amdgcn_exp2f(m[nt] - ms);
+            }
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) {
+                if (wv == w) leave_state(obuf, fsc, w > 0);
+                lds_barrier();
+            }
         }
         // 256 threads: 16*RT rows x D/4 float4 columns
 #pragma unroll
@@ -300,8 +307,17 @@ __global__ __launch_bounds__(256, (RT <= 2 ? 2 : 1)) void attn_f32_kernel(
             const int rl = idx / (D / 4), c4 = idx % (D / 4);
             const int row = u.r0 + rl;
             if (row >= u.rows) continue;
-            const f32x4 acc = *reinterpret_cast<const f32x4 *>(obuf + rl * kORow + 4 * c4);
-            const float ltot = (s_l[0][rl] + s_l[1][rl]) + (s_l[2][rl] + s_l[3][rl]);
+            float ms = s_m[0][rl], ltot = 0.f;
+#pragma unroll
+            for (int w = 1; w < kWaves; ++w) ms = fmaxf(ms, s_m[w][rl]);
+            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) {
+                const float sc = __builtin_amdgcn_exp2f(s_m[w][rl] - ms);
+                ltot += sc * s_l[w][rl];
+                if constexpr (kSlabs) acc += sc * *reinterpret_cast<const f32x4 *>(obuf + w * kState + rl * kORow + 4 * c4);
+            }
+            if constexpr (!kSlabs) acc = *reinterpret_cast<const f32x4 *>(obuf + rl * kORow + 4 * c4);
             if (u.ns == 1) {
                 const int64_t obase = ((u.qrow0 + row / G) * Hq + u.gkv * G + row % G) * (int64_t)D + 4 * c4;
                 *reinterpret_cast<f32x4 *>(out + obase) = acc * (1.0f / ltot);
@@ -309,7 +325,7 @@ __global__ __launch_bounds__(256, (RT <= 2 ? 2 : 1)) void attn_f32_kernel(
                 const int64_t idx_row = ((int64_t)u.item * Hkv + u.gkv) * max_rows + row;
                 *reinterpret_cast<f32x4 *>(part_o + idx_row * D + 4 * c4) = acc;
                 if (c4 == 0) {
-                    part_ml[idx_row * 2] = s_mstar[rl];
+                    part_ml[idx_row * 2] = ms;
                     part_ml[idx_row * 2 + 1] = ltot;
                 }
             }

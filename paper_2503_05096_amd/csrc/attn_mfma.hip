@@ -29,33 +29,33 @@
 
 namespace adaspec {
 
-template <class T, int RT, bool kTree>
+template <class T, int RT, bool kTree, bool kDirect>
 __global__ __launch_bounds__(256, (RT <= 2 ? 2 : 1)) void attn_mfma_kernel(
     const char *__restrict__ q, const char *__restrict__ k_pages, const char *__restrict__ v_pages,
     const int32_t *__restrict__ block_table, void *__restrict__ out, int32_t *__restrict__ header,
     const int32_t *__restrict__ unit_meta, const int32_t *__restrict__ sched,
     const unsigned long long *__restrict__ anc, float *__restrict__ part_ml, float *__restrict__ part_o,
     int Hq, int Hkv, int max_pages_per_req, int max_rows, int n_row_groups, float scale_log2,
-    int out_dtype)
+    int out_dtype, DirectArgs direct)
 {
     constexpr int kRows = 16 * RT;
-    constexpr int kMerge = kRows * kORowStride * 4;                 // the [rows][d] fp32 merge buffer
-    constexpr int kSmem = kWaves * kVtBytes > kMerge ? kWaves * kVtBytes : kMerge;
-    __shared__ __attribute__((aligned(16))) char smem[kSmem];
+    // per wavefront: its V^T tile, later its [rows][d] fp32 state for the merge
+    constexpr int kSlab = kRows * kORowStride * 4 > kVtBytes ? kRows * kORowStride * 4 : kVtBytes;
+    __shared__ __attribute__((aligned(16))) char smem[kWaves * kSlab];
     __shared__ __attribute__((aligned(16))) uint4 q_lds[RT * 4 * 64];   // Q^T operands, MFMA lane order
-    __shared__ float s_m[kWaves][kRows], s_l[kWaves][kRows], s_mstar[kRows];
+    __shared__ float s_m[kWaves][kRows], s_l[kWaves][kRows];
     __shared__ unsigned long long s_anc[kTree ? kRows : 1];         // ancestor mask of each row of the unit
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);        // wave-uniform by construction
     const int g = lane >> 4, n16 = lane & 15;
     const int G = Hq / Hkv;
-    const int total_units = header[0] * Hkv * n_row_groups;
+    const int total_units = kDirect ? 0 : header[0] * Hkv * n_row_groups;
     const int64_t head_bytes = (int64_t)16 * kD * 2;                // one (page, head) block
-    char *my_lds = smem + wv * kVtBytes;
+    char *my_lds = smem + wv * kSlab;
     char *vt_wr = my_lds + 16 * (16 * g + n16);
     const char *vt_rd = my_lds + 16 * (66 * (n16 & 7) + 16 * g + (n16 >> 3));
-    float *obuf = reinterpret_cast<float *>(smem);
+    float *my_state = reinterpret_cast<float *>(my_lds);
 
     // K operand: lane (g, m) <- token 16 mt + m, channels 32 s + 8 g .. +7
     // V raw:     lane (tq = g, c = n16) <- token 16 pg + 4 tq + i, channels 8 c .. 8 c + 7
@@ -69,7 +69,7 @@ __global__ __launch_bounds__(256, (RT <= 2 ? 2 : 1)) void attn_mfma_kernel(
     // the longest unit of the round to the workgroup with the least work so far.  No atomic is
     // needed and the next unit is known ahead of time, so its data can be requested early.
     const int W = gridDim.x, wg = blockIdx.x;
-    const int n_rounds = header[2];
+    const int n_rounds = kDirect ? 0 : header[2];
     int round = 0;
     int idx_ahead = wg;                                             // round 0 is the identity
     auto next_unit = [&](Unit &u) -> bool {
@@ -149,9 +149,11 @@ __global__ __launch_bounds__(256, (RT <= 2 ? 2 : 1)) void attn_mfma_kernel(
     };
 
     Unit cur, nxt;
-    bool have = next_unit(cur);
+    bool have;
     uint4 qv[RT];
     unsigned long long av = 0ull;
+    if constexpr (kDirect) have = direct_unit(cur, direct, block_table, G, Hkv, n_row_groups, kRows, kBlk, max_pages_per_req, wv, lane);
+    else have = next_unit(cur);
     if (have) {
         load_q(cur, qv);
         if constexpr (kTree) av = load_anc(cur);
@@ -160,7 +162,7 @@ __global__ __launch_bounds__(256, (RT <= 2 ? 2 : 1)) void attn_mfma_kernel(
 
     while (have) {
         const Unit u = cur;
-        const bool have_next = next_unit(nxt);
+        const bool have_next = kDirect ? false : next_unit(nxt);
         const int first_masked = u.L - u.n + 1;                    // tokens >= this are hidden from some row
 #pragma unroll
         for (int k = 0; k < RT; ++k) q_lds[tid + 256 * k] = qv[k];
@@ -171,7 +173,7 @@ __global__ __launch_bounds__(256, (RT <= 2 ? 2 : 1)) void attn_mfma_kernel(
             const int row = u.r0 + 16 * nt + n16;
             pos[nt] = row < u.rows ? (u.L - u.n + row / G) : -1;
         }
-        __syncthreads();
+        lds_barrier();              // (LDS only: a full barrier would wait for the unit's first block as well)
 
         float m[RT], lsum[RT];
         f32x4 o[RT][8];
@@ -327,51 +329,26 @@ __global__ __launch_bounds__(256, (RT <= 2 ? 2 : 1)) void attn_mfma_kernel(
 
         // ---- next unit: request its first K/V block and its Q rows now, so that they travel while
         // this unit's states are merged and written out.
-#pragma unroll
-        for (int nt = 0; nt < RT; ++nt) {
-            lsum[nt] += __shfl_xor(lsum[nt], 16, kWave);
-            lsum[nt] += __shfl_xor(lsum[nt], 32, kWave);
-            if (g == 0) s_m[wv][16 * nt + n16] = m[nt];
-        }
         if (have_next) {
             load_q(nxt, qv);
             if constexpr (kTree) av = load_anc(nxt);
             first_loads(nxt);
         }
-        __syncthreads();            // s_m complete; every wavefront is done with its V^T tile and q_lds
-
-        // ---- merge the four wavefronts' states through LDS --------------------------------
-        // m* = max over wavefronts, each state rescaled by 2^(m - m*); the O tiles are summed
-        // into one [rows][d] fp32 buffer (aliasing the V^T tiles) one wavefront after another.
-        float fsc[RT];
+        // ---- merge the four wavefronts' states through LDS: each leaves its own (over its V^T tile, which nobody
+        // else reads), one barrier, then every output element is put together from the four,
+        //   O = sum_w 2^(m_w - m*) O_w, m* = max over wavefronts.
+        // (Adding into one buffer, wavefront after wavefront, took four more barriers: MI355X, one request of 1500
+        // tokens, 2.0 us of a 9.7 us kernel.)
 #pragma unroll
         for (int nt = 0; nt < RT; ++nt) {
-            const int rl = 16 * nt + n16;
-            float ms = s_m[0][rl];
+            lsum[nt] += __shfl_xor(lsum[nt], 16, kWave);
+            lsum[nt] += __shfl_xor(lsum[nt], 32, kWave);
+            if (g == 0) { s_m[wv][16 * nt + n16] = m[nt]; s_l[wv][16 * nt + n16] = lsum[nt]; }
 #pragma unroll
-            for (int w = 1; w < kWaves; ++w) ms = fmaxf(ms, s_m[w][rl]);
-            fsc[nt] = __builtin_amdgcn_exp2f(m[nt] - ms);
-            if (g == 0) {
-                s_l[wv][rl] = lsum[nt] * fsc[nt];
-                if (wv == 0) s_mstar[rl] = ms;
-            }
+            for (int dt = 0; dt < 8; ++dt)
+                *reinterpret_cast<f32x4 *>(my_state + (16 * nt + n16) * kORowStride + 16 * dt + 4 * g) = o[nt][dt];
         }
-#pragma unroll
-        for (int w = 0; w < kWaves; ++w) {
-            if (wv == w) {
-#pragma unroll
-                for (int nt = 0; nt < RT; ++nt)
-#pragma unroll
-                    for (int dt = 0; dt < 8; ++dt) {
-                        f32x4 *dst = reinterpret_cast<f32x4 *>(obuf + (16 * nt + n16) * kORowStride +
-                                                               16 * dt + 4 * g);
-                        f32x4 v = o[nt][dt] * fsc[nt];
-                        if (w > 0) v += *dst;
-                        *dst = v;
-                    }
-            }
-            __syncthreads();
-        }
+        lds_barrier();
         // 256 threads: 16*RT rows x 32 float4 columns
 #pragma unroll
         for (int it = 0; it < 2 * RT; ++it) {
@@ -379,8 +356,16 @@ __global__ __launch_bounds__(256, (RT <= 2 ? 2 : 1)) void attn_mfma_kernel(
             const int rl = idx >> 5, c4 = idx & 31;
             const int row = u.r0 + rl;
             if (row >= u.rows) continue;
-            const f32x4 acc = *reinterpret_cast<const f32x4 *>(obuf + rl * kORowStride + 4 * c4);
-            const float ltot = (s_l[0][rl] + s_l[1][rl]) + (s_l[2][rl] + s_l[3][rl]);
+            float ms = s_m[0][rl], ltot = 0.f;
+#pragma unroll
+            for (int w = 1; w < kWaves; ++w) ms = fmaxf(ms, s_m[w][rl]);
+            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) {
+                const float sc = __builtin_amdgcn_exp2f(s_m[w][rl] - ms);
+                ltot += sc * s_l[w][rl];
+                acc += sc * *reinterpret_cast<const f32x4 *>(smem + w * kSlab + 4 * (rl * kORowStride + 4 * c4));
+            }
             if (u.ns == 1) {
                 const float inv = 1.0f / ltot;
                 const int64_t obase = ((u.qrow0 + row / G) * Hq + u.gkv * G + row % G) * (int64_t)kD + 4 * c4;
@@ -395,13 +380,14 @@ __global__ __launch_bounds__(256, (RT <= 2 ? 2 : 1)) void attn_mfma_kernel(
                 const int64_t idx_row = ((int64_t)u.item * Hkv + u.gkv) * max_rows + row;
                 *reinterpret_cast<f32x4 *>(part_o + idx_row * kD + 4 * c4) = acc;
                 if (c4 == 0) {
-                    part_ml[idx_row * 2] = s_mstar[rl];
+                    part_ml[idx_row * 2] = ms;
                     part_ml[idx_row * 2 + 1] = ltot;
                 }
             }
         }
-        // the next loop iteration overwrites q_lds and the V^T tiles: everyone must be done reading obuf
-        __syncthreads();
+        if constexpr (kDirect) break;
+        // the next loop iteration overwrites q_lds, the V^T tiles and s_m: everyone must be done reading the states
+        lds_barrier();
         cur = nxt;
         have = have_next;
     }
@@ -427,13 +413,13 @@ static int device_cus()
     return cus;
 }
 
-template <typename T, int RT, bool kTree>
+template <typename T, int RT, bool kTree, bool kDirect>
 static int attn_mfma_slots()
 {
     static int slots = 0;
     if (slots == 0) {
         int per_cu = 1;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, attn_mfma_kernel<T, RT, kTree>, 256, 0) != hipSuccess)
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, attn_mfma_kernel<T, RT, kTree, kDirect>, 256, 0) != hipSuccess)
             per_cu = 1;
         const int n = device_cus() * (per_cu > 0 ? per_cu : 1);
         slots = n < kMaxSchedW ? n : kMaxSchedW;
@@ -442,18 +428,20 @@ static int attn_mfma_slots()
 }
 
 template <typename F>
-static void with_instance(int dtype, int rt, bool tree, F &&f)
+static void with_instance(const AttnArgs &a, F &&f)
 {
-    auto with_rt = [&](auto tag, auto tree_tag) {
-        if (rt == 1) f(tag, std::integral_constant<int, 1>{}, tree_tag);
-        else f(tag, std::integral_constant<int, 2>{}, tree_tag);
+    const int rt = attn_row_tiles(a.plan.max_rows);
+    auto with_mode = [&](auto tag, auto rt_tag) {
+        if (a.direct) f(tag, rt_tag, std::false_type{}, std::true_type{});
+        else if (a.parents) f(tag, rt_tag, std::true_type{}, std::false_type{});
+        else f(tag, rt_tag, std::false_type{}, std::false_type{});
     };
-    auto with_tree = [&](auto tag) {
-        if (tree) with_rt(tag, std::true_type{});
-        else with_rt(tag, std::false_type{});
+    auto with_rt = [&](auto tag) {
+        if (rt == 1) with_mode(tag, std::integral_constant<int, 1>{});
+        else with_mode(tag, std::integral_constant<int, 2>{});
     };
-    if (dtype == ADASPEC_F16) with_tree(F16{});
-    else with_tree(BF16{});
+    if (a.dims.dtype == ADASPEC_F16) with_rt(F16{});
+    else with_rt(BF16{});
 }
 
 void attn_mfma_shape(AttnArgs &a, AttnKind kind)
@@ -465,6 +453,7 @@ void attn_mfma_shape(AttnArgs &a, AttnKind kind)
     const int64_t max_units = (int64_t)p.max_items * a.dims.n_kv_heads * a.n_row_groups;
     a.sched_cus = device_cus();
     if (a.direct) {                                                  // one workgroup per possible unit
+        if (kind == AttnKind::kMfma128 && rt > 2) attn_rows_grid_slots(a, a.sched_cus);   // (raises its LDS limit once)
         a.sched_w = (int)max_units;
         return;
     }
@@ -477,8 +466,8 @@ void attn_mfma_shape(AttnArgs &a, AttnKind kind)
         slots = attn_rows_grid_slots(a, device_cus());               // more than 32 rows: the row-split kernel
         if (slots <= 0) slots = device_cus();
     } else {
-        with_instance(a.dims.dtype, rt, a.parents != nullptr, [&](auto tag, auto rt_tag, auto tree_tag) {
-            slots = attn_mfma_slots<decltype(tag), decltype(rt_tag)::value, decltype(tree_tag)::value>();
+        with_instance(a, [&](auto tag, auto rt_tag, auto tree, auto direct) {
+            slots = attn_mfma_slots<decltype(tag), decltype(rt_tag)::value, decltype(tree)::value, decltype(direct)::value>();
         });
     }
     a.sched_w = (int)(max_units < slots ? max_units : slots);
@@ -490,17 +479,14 @@ hipError_t launch_attn_mfma(const AttnArgs &a)
     const adaspec_attn_dims &d = a.dims;
     if (a.sched_w <= 0) return hipSuccess;                          // no work item can exist
     if (attn_row_tiles(p.max_rows) > 2) return launch_attn_rows(a);
-    with_instance(d.dtype, attn_row_tiles(p.max_rows), a.parents != nullptr, [&](auto tag, auto rt_tag, auto tree_tag) {
-        using T = decltype(tag);
-        constexpr int RT = decltype(rt_tag)::value;
-        constexpr bool kTree = decltype(tree_tag)::value;
-        hipLaunchKernelGGL((attn_mfma_kernel<T, RT, kTree>), dim3(a.sched_w), dim3(256), 0, a.stream,
-                           (const char *)a.q, (const char *)a.k_pages, (const char *)a.v_pages,
-                           a.block_table, a.out, (int32_t *)(a.ws + p.off_header),
+    with_instance(a, [&](auto tag, auto rt, auto tree, auto direct) {
+        hipLaunchKernelGGL((attn_mfma_kernel<decltype(tag), decltype(rt)::value, decltype(tree)::value, decltype(direct)::value>),
+                           dim3(a.sched_w), dim3(256), 0, a.stream, (const char *)a.q, (const char *)a.k_pages,
+                           (const char *)a.v_pages, a.block_table, a.out, (int32_t *)(a.ws + p.off_header),
                            (const int32_t *)(a.ws + p.off_unit_meta), (const int32_t *)(a.ws + p.off_sched),
-                           (const unsigned long long *)(a.ws + p.off_anc), (float *)(a.ws + p.off_part_ml), (float *)(a.ws + p.off_part_o), d.n_q_heads,
-                           d.n_kv_heads, d.max_pages_per_req, p.max_rows, a.n_row_groups, a.scale_log2,
-                           d.out_dtype);
+                           (const unsigned long long *)(a.ws + p.off_anc), (float *)(a.ws + p.off_part_ml),
+                           (float *)(a.ws + p.off_part_o), d.n_q_heads, d.n_kv_heads, d.max_pages_per_req, p.max_rows,
+                           a.n_row_groups, a.scale_log2, d.out_dtype, direct_args(a));
     });
     return hipGetLastError();
 }

@@ -93,11 +93,15 @@ struct Unit {
 // ---- direct calls ---------------------------------------------------------------------------------------------------
 // The metadata kernel and the schedule table balance a large ragged batch; a small one only waits for them (4.7 us, and
 // two more dependent loads at the head of every workgroup). A direct call launches one workgroup per (request, possible
-// split, kv head, row group): the numbering follows from the host-side bounds, the splits of a request all have
-// plan.split_tokens tokens, and the workgroup reads its request's lengths (and adds up the rows before them) itself.
+// split, kv head, row group): the numbering follows from the host-side bounds, and the workgroup reads its request's
+// lengths (and adds up the rows before them) itself.  The splits are the ones the metadata kernel would have cut.
 // false: the request is shorter than this split, or has fewer rows than this group.
-__device__ __forceinline__ bool direct_unit(Unit &u, const DirectArgs &a, int G, int Hkv, int n_row_groups, int rows_per_group,
-                                            int block_tokens, int max_pages_per_req, int lane)
+// About where the wavefront's first page ids stand follows from the numbering alone: that place is looked at together with
+// the lengths, so that the loads which need them mostly find them in the scalar cache instead of one more memory round
+// trip away.
+__device__ __forceinline__ bool direct_unit(Unit &u, const DirectArgs &a, const int32_t *__restrict__ block_table, int G, int Hkv,
+                                            int n_row_groups, int rows_per_group, int block_tokens, int max_pages_per_req, int wv,
+                                            int lane)
 {
     const int idx = blockIdx.x;
     const int rg = idx % n_row_groups;
@@ -105,6 +109,9 @@ __device__ __forceinline__ bool direct_unit(Unit &u, const DirectArgs &a, int G,
     u.item = idx / (n_row_groups * Hkv);
     u.i = u.item / a.per_req;
     const int s = u.item - u.i * a.per_req;
+    u.bt_off = (int64_t)u.i * max_pages_per_req;
+    const int first_page = (s * a.split_tokens + wv * block_tokens) >> 4;
+    const int warm = block_table[u.bt_off + min(first_page, max_pages_per_req - 1)];
     int part = 0;
     for (int j = lane; j < u.i; j += kWave) part += min(max(a.spec_lens[j], 0), a.max_spec_len) + 1;
     u.L = max(a.ctx_lens[u.i], 1);
@@ -113,10 +120,11 @@ __device__ __forceinline__ bool direct_unit(Unit &u, const DirectArgs &a, int G,
     u.ns = min((u.L + a.split_tokens - 1) / a.split_tokens, a.per_req);
     u.rows = u.n * G;
     u.r0 = rg * rows_per_group;
-    u.t0 = s * a.split_tokens;
-    u.t1 = min(u.L, u.t0 + a.split_tokens);
+    const int slen = split_len_of(u.L, u.ns, block_tokens);
+    u.t0 = s * slen;
+    u.t1 = min(u.L, u.t0 + slen);
     u.nblk = (u.t1 - u.t0 + block_tokens - 1) / block_tokens;
-    u.bt_off = (int64_t)u.i * max_pages_per_req;
+    asm volatile("" :: "s"(warm), "s"(u.L));
     return s < u.ns && u.r0 < u.rows && u.qrow0 + u.n <= a.total_q;
 }
 

@@ -67,13 +67,14 @@ __device__ __forceinline__ void load_pair_to_lds(const v4i32 &rsrc, uint32_t lan
                  :: "s"(lds_addr), "v"(lane_offset0), "v"(lane_offset1_minus_1024), "s"(rsrc) : "memory", "m0");
 }
 
-template <class T, bool kTree>
+template <class T, bool kTree, bool kDirect>
 __global__ __launch_bounds__(256, 2) void attn_rows_kernel(
     const char *__restrict__ q, const char *__restrict__ k_pages, const char *__restrict__ v_pages,
     const int32_t *__restrict__ block_table, void *__restrict__ out, const int32_t *__restrict__ header,
     const int32_t *__restrict__ unit_meta, const int32_t *__restrict__ sched,
     const unsigned long long *__restrict__ anc, float *__restrict__ part_ml, float *__restrict__ part_o,
-    int Hq, int Hkv, int max_pages_per_req, int max_rows, int n_row_groups, float scale_log2, int out_dtype)
+    int Hq, int Hkv, int max_pages_per_req, int max_rows, int n_row_groups, float scale_log2, int out_dtype,
+    DirectArgs direct)
 {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     char *vt_tile = smem + kSlots * kSlotBytes;
@@ -83,13 +84,15 @@ __global__ __launch_bounds__(256, 2) void attn_rows_kernel(
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g = lane >> 4, n16 = lane & 15;
     const int G = Hq / Hkv;
-    const int total_units = header[0] * Hkv * n_row_groups;
-    const int n_rounds = header[2];
+    const int total_units = kDirect ? 0 : header[0] * Hkv * n_row_groups;
+    const int n_rounds = kDirect ? 0 : header[2];
     const int W = gridDim.x, wg = blockIdx.x;
 
     // ---- work units of this workgroup, in schedule order; two cursors walk them: the loader runs kAhead
     // blocks ahead of the arithmetic, across unit boundaries
     auto next_unit = [&](int &round, Unit &u) -> bool {
+        if constexpr (kDirect)                                      // one unit per workgroup
+            return round++ == 0 && direct_unit(u, direct, block_table, G, Hkv, n_row_groups, kRowsPerGroup, kBlk, max_pages_per_req, 0, lane);
         for (; round < n_rounds; ++round) {
             const int idx = sched[(int64_t)round * W + wg];
             if (idx < 0 || idx >= total_units) continue;
@@ -379,16 +382,16 @@ __global__ __launch_bounds__(256, 2) void attn_rows_kernel(
 }
 
 // ---- host side -----------------------------------------------------------------------------------------------
-template <typename T, bool kTree>
+template <typename T, bool kTree, bool kDirect>
 static int attn_rows_slots(int cus)
 {
     static int slots = 0;
     if (slots == 0) {
-        if (hipFuncSetAttribute((const void *)attn_rows_kernel<T, kTree>, hipFuncAttributeMaxDynamicSharedMemorySize,
+        if (hipFuncSetAttribute((const void *)attn_rows_kernel<T, kTree, kDirect>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 kRowsSmem) != hipSuccess)
             return 0;
         int per_cu = 1;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, attn_rows_kernel<T, kTree>, 256, kRowsSmem) != hipSuccess)
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, attn_rows_kernel<T, kTree, kDirect>, 256, kRowsSmem) != hipSuccess)
             per_cu = 1;
         const int n = cus * (per_cu > 0 ? per_cu : 1);
         slots = n < kMaxSchedW ? n : kMaxSchedW;
@@ -397,21 +400,22 @@ static int attn_rows_slots(int cus)
 }
 
 template <typename F>
-static void with_rows_instance(int dtype, bool tree, F &&f)
+static void with_rows_instance(const AttnArgs &a, F &&f)
 {
-    auto with_tree = [&](auto tag) {
-        if (tree) f(tag, std::true_type{});
-        else f(tag, std::false_type{});
+    auto with_mode = [&](auto tag) {
+        if (a.direct) f(tag, std::false_type{}, std::true_type{});
+        else if (a.parents) f(tag, std::true_type{}, std::false_type{});
+        else f(tag, std::false_type{}, std::false_type{});
     };
-    if (dtype == ADASPEC_F16) with_tree(F16{});
-    else with_tree(BF16{});
+    if (a.dims.dtype == ADASPEC_F16) with_mode(F16{});
+    else with_mode(BF16{});
 }
 
 int attn_rows_grid_slots(const AttnArgs &a, int cus)
 {
     int slots = 0;
-    with_rows_instance(a.dims.dtype, a.parents != nullptr, [&](auto tag, auto tree_tag) {
-        slots = attn_rows_slots<decltype(tag), decltype(tree_tag)::value>(cus);
+    with_rows_instance(a, [&](auto tag, auto tree, auto direct) {
+        slots = attn_rows_slots<decltype(tag), decltype(tree)::value, decltype(direct)::value>(cus);
     });
     return slots;
 }
@@ -421,15 +425,14 @@ hipError_t launch_attn_rows(const AttnArgs &a)
     const AttnPlan &p = a.plan;
     const adaspec_attn_dims &d = a.dims;
     if (a.sched_w <= 0) return hipSuccess;                          // no work item can exist
-    with_rows_instance(d.dtype, a.parents != nullptr, [&](auto tag, auto tree_tag) {
-        using T = decltype(tag);
-        constexpr bool kTree = decltype(tree_tag)::value;
-        hipLaunchKernelGGL((attn_rows_kernel<T, kTree>), dim3(a.sched_w), dim3(256), kRowsSmem, a.stream,
-                           (const char *)a.q, (const char *)a.k_pages, (const char *)a.v_pages, a.block_table, a.out,
-                           (const int32_t *)(a.ws + p.off_header), (const int32_t *)(a.ws + p.off_unit_meta),
-                           (const int32_t *)(a.ws + p.off_sched), (const unsigned long long *)(a.ws + p.off_anc),
-                           (float *)(a.ws + p.off_part_ml), (float *)(a.ws + p.off_part_o), d.n_q_heads, d.n_kv_heads,
-                           d.max_pages_per_req, p.max_rows, a.n_row_groups, a.scale_log2, d.out_dtype);
+    with_rows_instance(a, [&](auto tag, auto tree, auto direct) {
+        hipLaunchKernelGGL((attn_rows_kernel<decltype(tag), decltype(tree)::value, decltype(direct)::value>), dim3(a.sched_w),
+                           dim3(256), kRowsSmem, a.stream, (const char *)a.q, (const char *)a.k_pages, (const char *)a.v_pages,
+                           a.block_table, a.out, (const int32_t *)(a.ws + p.off_header),
+                           (const int32_t *)(a.ws + p.off_unit_meta), (const int32_t *)(a.ws + p.off_sched),
+                           (const unsigned long long *)(a.ws + p.off_anc), (float *)(a.ws + p.off_part_ml),
+                           (float *)(a.ws + p.off_part_o), d.n_q_heads, d.n_kv_heads, d.max_pages_per_req, p.max_rows,
+                           a.n_row_groups, a.scale_log2, d.out_dtype, direct_args(a));
     });
     return hipGetLastError();
 }

@@ -1,0 +1,53 @@
+"""Attention calls with and without a metadata kernel, at the same edges: small batches find their units themselves
+(direct), the same requests among more than 256 others go through the schedule. Contexts around the page, the block, the
+turn of a workgroup and the shortest splits; one, two and more row tiles; enough splits for every form of the combine
+kernel. Bar: the guards of the other attention tests."""
+import numpy as np
+import pytest
+
+import workloads as W
+from tests.test_gpu_parity import check_attention, pkg  # noqa: F401  (fixture)
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [
+    # ctx_lens, spec_lens, Hq, Hkv
+    ([1, 2, 16, 17, 31, 32, 33], [0, 1, 0, 2, 1, 3, 0], 4, 4),                 # one block and less
+    ([127, 128, 129, 511, 513], [3, 0, 7, 3, 8], 8, 2),                        # splits of 128 tokens, up to 36 rows
+    ([1500], [5], 32, 8),                                                      # 12 splits: four wavefronts per row combine
+    ([9000, 40], [3, 0], 16, 2),                                               # many splits beside a single one
+    ([700, 90], [10, 7], 64, 8),                                               # 88 rows: two row groups
+    ([4097, 4096, 4095], [0, 1, 2], 8, 1),
+]
+
+
+@pytest.mark.parametrize("d,dtype", [(128, "bf16"), (128, "f16"), (64, "bf16"), (64, "f32"), (128, "f32")])
+@pytest.mark.parametrize("crowd", [0, 260], ids=["direct", "scheduled"])
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: f"B{len(s[0])}-L{max(s[0])}-k{max(s[1])}-{s[2]}x{s[3]}")
+def test_attention_direct_and_scheduled(shape, crowd, d, dtype, oracle_mod, pkg):  # noqa: F811
+    ctx, spec, hq, hkv = shape
+    rng = np.random.default_rng(crowd + d)
+    more = rng.integers(1, 40, crowd)
+    at = crowd // 2
+    st = W.make_custom_step(128 + d, ctx_lens=[*more[:at], *ctx, *more[at:]], spec_lens=[*[0] * at, *spec, *[0] * (crowd - at)],
+                            n_q_heads=hq, n_kv_heads=hkv, head_dim=d, dtype=dtype, acceptance=False, name=f"direct-{crowd}-{dtype}")
+    check_attention(st, oracle_mod, pkg)
+
+
+def test_attention_direct_with_a_wide_block_table(oracle_mod, pkg):  # noqa: F811
+    """A block table far wider than the contexts: most possible splits do not exist, and the entries behind a request's
+    pages are not page ids."""
+    import torch
+    from tests.harness import compare_attention, to_device
+    st = W.make_custom_step(5, ctx_lens=[300, 33], spec_lens=[2, 1], n_q_heads=8, n_kv_heads=2, head_dim=128, dtype="bf16",
+                            acceptance=False)
+    dev = to_device(st, acceptance=False)
+    ref, _ = oracle_mod.verify_attn(st.q, st.k_pages, st.v_pages, st.block_table, st.ctx_lens, st.spec_lens, dtype=st.dtype)
+    wide = torch.full((2, 1024), -1, dtype=torch.int32, device="cuda")
+    wide[:, :dev.block_table.shape[1]] = dev.block_table
+    for plan in ("run", "reuse"):                      # a direct call needs no metadata in the workspace
+        ws = torch.full((64 << 20,), 255, dtype=torch.uint8, device="cuda")
+        out = pkg.verify_attn(dev.q, dev.k_pages, dev.v_pages, wide, dev.ctx_lens, dev.spec_lens, max_spec_len=2, out_dtype=0,
+                              workspace=ws, plan=plan)
+        torch.cuda.synchronize()
+        assert compare_attention(out, ref, None, "bf16")["max_abs_vs_f64"] <= 2e-5
