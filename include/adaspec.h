@@ -457,11 +457,11 @@ typedef struct {
                                    (16-bit logits, V <= 131072), VECTOR = the
                                    three-sweep kernel, TWO_PASS = the split form
                                    (same shapes as FAST, needs the workspace):
-                                   every row cut into four parts over three small
-                                   kernels, for steps with fewer rows than the
-                                   device has compute units; AUTO = the split
-                                   form when it fits, a workspace is given and
-                                   V >= 32768, else FAST when it fits, else VECTOR */
+                                   every row cut into parts over three small
+                                   kernels; AUTO = the split form, of any storage
+                                   types, when a workspace is given and V >= 8192;
+                                   else FAST when it fits and V >= 32768, else
+                                   VECTOR */
     int32_t reserved;
     void   *timing_start;       /* optional pair of hipEvent_t (both or neither, NULL = none), recorded */
     void   *timing_stop;        /* on `stream` around the call's kernels                                */

@@ -41,25 +41,12 @@
 // thread; the four steps of the winning pair are recomputed by one wavefront each.
 #include "adaspec_internal.h"
 #include "device_utils.h"
-#include "row_registers.h"
+#include "row_parts.h"
 
 namespace adaspec {
 
-constexpr int kQT = 256;                    // threads per workgroup
-constexpr int kQW = kQT / kWave;            // 4 wavefronts
-constexpr int kStatSteps = 8;               // first pass: steps of kQT chunks per part (32 KB of logits)
-constexpr int kStatWgsPerCu = 6;           // first pass: workgroups that fit a compute unit (80 registers each)
-constexpr int kStatTargetWgsPerCu = 3;     // ... and how many the launch aims for: few long streams read faster than many short ones
-constexpr int kStatParts = 8;               // parts per row at most, of up to 64 steps: V <= 8 * 64 * 256 * 4 = 524288
-constexpr int kSumSteps = 4;                // second pass: steps of kQT chunks per part
-constexpr int kSumChunks = kSumSteps * kQT; // chunks per part (16 KB of logits)
-constexpr int kSumParts = 128;              // parts per row at most
-constexpr int kPartsMaxVocab = 524288;
 constexpr int kPartsMaxBatch = 1024;        // requests the in-kernel scan covers (4 per thread)
 constexpr int kPartsMaxSlots = 32768;       // batch * max_spec_len slots the workspace is laid out for
-static_assert(kSumSteps == kQW, "one wavefront per step in the final search");
-static_assert(kSumParts * kQW == 2 * kQT, "two (part, wavefront) pairs per thread in the final search");
-static_assert(kPartsMaxVocab <= kSumParts * kSumChunks * 4 && kPartsMaxVocab <= kStatParts * 64 * kQT * 4, "fp32 rows fit");
 
 // Phase time stamps for tuning builds (-DADASPEC_STAMPS): thread 0 of every workgroup leaves the 100 MHz
 // wall clock at up to 8 points of each kernel; adaspec_debug_read_stamps copies them out.  Product builds
@@ -114,96 +101,6 @@ __device__ __forceinline__ HalfStat fetch_stat(const HalfStat *p)
 // mass of one wavefront's 256 chunks of a part: [B][n_parts][kQW]
 struct WaveMass { double residual, prob; };
 
-// 16 bytes per lane through a buffer descriptor (past the end of the buffer: zeros); AUX = cache policy bits
-// of the instruction (0 = default, 2 = non-temporal: data that is read once)
-constexpr int kAuxDefault = 0, kAuxStream = 2;
-template <int AUX>
-__device__ __forceinline__ uint4 part_load16(__amdgpu_buffer_rsrc_t rs, uint32_t lane_offset, int step_offset)
-{
-    const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)lane_offset, step_offset, AUX);
-    return make_uint4(v.x, v.y, v.z, v.w);
-}
-
-// ---- chunks of logits -------------------------------------------------------------------------------
-template <class LT> struct Chunk {                    // 16-bit types
-    using P = Pair16<LT>;
-    static constexpr int kN = 8;
-    static __device__ __forceinline__ void unpack(const uint4 &v, float (&x)[kN])
-    {
-        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) { x[2 * e] = P::lo(w[e]); x[2 * e + 1] = P::hi(w[e]); }
-    }
-    // chunks past the end of the row arrive as zeros (range check of the buffer) and become -inf in place
-    static __device__ __forceinline__ void blank(uint4 &v, bool past)
-    {
-        const uint32_t ninf = past ? P::kNegInf2 : 0u;
-        v.x |= ninf; v.y |= ninf; v.z |= ninf; v.w |= ninf;
-    }
-};
-template <> struct Chunk<F32> {
-    static constexpr int kN = 4;
-    static __device__ __forceinline__ void unpack(const uint4 &v, float (&x)[kN])
-    {
-        x[0] = __uint_as_float(v.x); x[1] = __uint_as_float(v.y); x[2] = __uint_as_float(v.z); x[3] = __uint_as_float(v.w);
-    }
-    static __device__ __forceinline__ void blank(uint4 &v, bool past)
-    {
-        constexpr uint32_t kNegInf = 0xff800000u;
-        v.x = past ? kNegInf : v.x; v.y = past ? kNegInf : v.y; v.z = past ? kNegInf : v.z; v.w = past ? kNegInf : v.w;
-    }
-};
-
-// ---- the draft probabilities beside a chunk of N logits: 8, 16 or 32 bytes ----------------------------
-template <int N, class PT> struct ProbChunk {
-    static constexpr int kBytes = N * (int)sizeof(typename PT::storage);
-    uint32_t w[kBytes / 4];
-    __device__ __forceinline__ void zero()
-    {
-#pragma unroll
-        for (int k = 0; k < kBytes / 4; ++k) w[k] = 0u;
-    }
-    __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t rs, uint32_t lane_offset, int step_offset)
-    {
-        typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-        if constexpr (kBytes == 8) {
-            const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rs, (int)lane_offset, step_offset, kAuxDefault);
-            w[0] = v.x; w[1] = v.y;
-        } else {
-#pragma unroll
-            for (int k = 0; k < kBytes / 16; ++k) {
-                const uint4 v = part_load16<kAuxDefault>(rs, lane_offset + 16 * k, step_offset);
-                w[4 * k] = v.x; w[4 * k + 1] = v.y; w[4 * k + 2] = v.z; w[4 * k + 3] = v.w;
-            }
-        }
-    }
-    __device__ __forceinline__ void unpack(float (&x)[N]) const
-    {
-        if constexpr (sizeof(typename PT::storage) == 4) {
-#pragma unroll
-            for (int e = 0; e < N; ++e) x[e] = __uint_as_float(w[e]);
-        } else {
-#pragma unroll
-            for (int e = 0; e < N / 2; ++e) { x[2 * e] = Pair16<PT>::lo(w[e]); x[2 * e + 1] = Pair16<PT>::hi(w[e]); }
-        }
-    }
-    __device__ __forceinline__ void keep()            // opaque to the optimiser (see keep_packed)
-    {
-#pragma unroll
-        for (int k = 0; k < kBytes / 4; ++k) asm volatile("" : "+v"(w[k]));
-    }
-};
-
-// 2^((l - m) c).  16-bit logits: one fused operation with mc = m * c (the rounding of mc is far below that of
-// the logits' storage type).  fp32 logits: the difference first, as the portable kernel does it: for large
-// logits the rounding of mc would be visible in how the parts of a row are put together.
-template <class LT>
-__device__ __forceinline__ float exp_weight(float l, float m, float c, float mc)
-{
-    if constexpr (sizeof(typename LT::storage) == 4) return __builtin_amdgcn_exp2f((l - m) * c);
-    else return __builtin_amdgcn_exp2f(fmaf(l, c, -mc));
-}
-
 // One chunk: residual r_v = max(0, e_v / Z - q_v) and p_v = e_v / Z with e_v = 2^((l_v - m) c).
 // The sums and the final search both call this, so they see the same numbers.
 template <class LT, class PT>
@@ -219,54 +116,6 @@ __device__ __forceinline__ void part_chunk_masses(const uint4 &lv, const ProbChu
         const float w = exp_weight<LT>(x[e], m, c, mc);
         rv[e] = fmaxf(0.f, fmaf(w, invZ, -q[e]));
         pv[e] = w * invZ;
-    }
-}
-
-// exact maximum of the values of a chunk
-template <class LT>
-__device__ __forceinline__ float chunk_max(const uint4 &v, float m)
-{
-    float x[Chunk<LT>::kN];
-    Chunk<LT>::unpack(v, x);
-#pragma unroll
-    for (int e = 0; e < Chunk<LT>::kN; ++e) m = fmaxf(m, x[e]);
-    return m;
-}
-
-// Exact maximum of a thread's STEPS chunks.  16-bit types: on the bit patterns.  Both are sign-magnitude:
-// among non-negative values the order of the patterns as SIGNED 16-bit integers is the order of the
-// values, and every negative value is a negative integer, so a packed signed maximum (one instruction per
-// two elements) is exact as soon as one value is >= +0.  A thread that holds nothing but negative values
-// (masked vocabularies) wants the smallest magnitude instead: the packed UNSIGNED minimum.
-typedef unsigned short ushort2v __attribute__((ext_vector_type(2)));
-template <class LT, int STEPS>
-__device__ __forceinline__ float thread_max(const uint4 (&lg)[STEPS])
-{
-    if constexpr (sizeof(typename LT::storage) == 4) {
-        float m = -INFINITY;
-#pragma unroll
-        for (int it = 0; it < STEPS; ++it) m = chunk_max<LT>(lg[it], m);
-        return m;
-    } else {
-        short2v pm = {(short)0x8000, (short)0x8000};
-#pragma unroll
-        for (int it = 0; it < STEPS; ++it) {
-            const uint32_t w[4] = {lg[it].x, lg[it].y, lg[it].z, lg[it].w};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) pm = __builtin_elementwise_max(pm, __builtin_bit_cast(short2v, w[e]));
-        }
-        int top = max((int)pm.x, (int)pm.y);
-        if (top < 0) {
-            ushort2v pn = {(unsigned short)0xffff, (unsigned short)0xffff};
-#pragma unroll
-            for (int it = 0; it < STEPS; ++it) {
-                const uint32_t w[4] = {lg[it].x, lg[it].y, lg[it].z, lg[it].w};
-#pragma unroll
-                for (int e = 0; e < 4; ++e) pn = __builtin_elementwise_min(pn, __builtin_bit_cast(ushort2v, w[e]));
-            }
-            top = min((int)pn.x, (int)pn.y);
-        }
-        return Pair16<LT>::lo((uint32_t)top & 0xffffu);
     }
 }
 
@@ -322,13 +171,7 @@ __device__ __forceinline__ ArgMax part_argmax(uint4 (&lg)[STEPS], int chunk0, in
         for (int e = 0; e < N; ++e)
             if (x[e] > best.v) best = ArgMax{x[e], base + e};
     }
-    best = wave_argmax(best);
-    if (lane == 0) { s_m[wv] = best.v; s_i[wv] = best.i; }
-    lds_barrier();
-    ArgMax b{s_m[0], s_i[0]};
-#pragma unroll
-    for (int w = 1; w < kQW; ++w) b = argmax_merge(b, ArgMax{s_m[w], s_i[w]});
-    return b;
+    return reduce_argmax(best, s_m, s_i, lane, wv);
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -403,28 +246,14 @@ __global__ __launch_bounds__(kQT, kStatWgsPerCu) void accept_rowparts_kernel(
     if (r >= total_q) return;
     ADASPEC_STAMP(0, 1);
 
-    // ---- the part of the row, streamed once: kStatSteps steps in flight, each consumed as it lands -------
-    // (a compute unit needs about as long for the exponentials of a row as the memory system needs to
-    // deliver it: only a stream whose arithmetic runs under its own loads gets both done in the time of one)
+    // ---- the part of the row, streamed once (a draft row is read only here: past the caches) -----------
     const int row_chunks = V / kN;
     const char *lrow = logits + (int64_t)r * lstride * kSize;
-    // Part h takes the steps h, h + n_parts, h + 2 n_parts, ... of the row, so that the workgroups of a row
-    // sweep it together (neighbouring addresses are in flight at the same time), and reads them past the
-    // caches: a draft row is read once, here.
-    const int row_steps = ceil_div(row_chunks, kQT);
-    const int steps = (row_steps - h + n_parts - 1) / n_parts;
     const __amdgpu_buffer_rsrc_t rl = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(lrow), 0, row_chunks * 16, 0x00020000);
-#define ADASPEC_ROW_STEP(s) ((s) * n_parts + h)
-#define ADASPEC_STEP_OFFSET(s) (ADASPEC_ROW_STEP(s) * (kQT * 16))
-#define ADASPEC_STEP_CHUNK(s) (ADASPEC_ROW_STEP(s) * kQT + tid)
-#define ADASPEC_STEP_PAST_END(s) (ADASPEC_STEP_CHUNK(s) >= row_chunks)
-    const uint32_t tid16 = (uint32_t)tid * 16u;
-    uint4 lg[kStatSteps];
-#pragma unroll
-    for (int u = 0; u < kStatSteps; ++u) lg[u] = part_load16<kAuxStream>(rl, tid16, ADASPEC_STEP_OFFSET(u));
-
     const int64_t slot = (int64_t)ri * max_spec_len + j;
-    if (h == 0 && tid == 0) {
+    HalfStat *my_stat = part_stat + slot * kStatParts + h;
+    auto leave_slot = [&]() {
+        if (h != 0 || tid != 0) return;
         // what the accept test needs besides (m, Z): these loads travel with the row
         const int x = draft_tokens[dr];
         const int xa = min(max(x, 0), V - 1);            // (address only: an out-of-range token must not fault)
@@ -436,101 +265,20 @@ __global__ __launch_bounds__(kQT, kStatWgsPerCu) void accept_rowparts_kernel(
                                       : probs_dtype == ADASPEC_F16 ? load_as_float<F16>(probs, px) : load_as_float<BF16>(probs, px));
         rec.u0_bits = __float_as_uint(uniforms[2 * (int64_t)r]);
         slot_rec[slot] = rec;
-    }
-    HalfStat *my_stat = part_stat + slot * kStatParts + h;
+    };
     ADASPEC_STAMP(0, 2);
-    // One step of the stream: the chunk of step s (past the end of the part: -inf), used in place, and once
-    // it has been consumed the request for the step that takes its place in the window (past the part:
-    // zeros, no traffic) into the same registers.  Macros, not lambdas: an array captured by reference
-    // would be given a home in scratch memory.
-#define ADASPEC_STEP_REFILL(s, u)                                                                     \
-    lg[u] = part_load16<kAuxStream>(rl, tid16, ADASPEC_STEP_OFFSET((s) + kStatSteps));                 \
-    __builtin_amdgcn_sched_barrier(0);       /* one step at a time: nothing unpacked ahead of its turn */
     if (T == 0.0f) {
-        // greedy: arg-max, lowest index on ties (a thread meets its elements in index order)
-        ArgMax best{-INFINITY, V};
-        for (int s0 = 0; s0 < steps; s0 += kStatSteps) {
-#pragma unroll
-            for (int u = 0; u < kStatSteps; ++u) {
-                uint4 v = lg[u];
-                Chunk<LT>::blank(v, ADASPEC_STEP_PAST_END(s0 + u));
-                float x[kN];
-                Chunk<LT>::unpack(v, x);
-                const int base = ADASPEC_STEP_CHUNK(s0 + u) * kN;
-#pragma unroll
-                for (int e = 0; e < kN; ++e)
-                    if (x[e] > best.v) best = ArgMax{x[e], base + e};
-                ADASPEC_STEP_REFILL(s0 + u, u)
-            }
-        }
-        best = wave_argmax(best);
-        if (lane == 0) { s_m[wv] = best.v; s_i[wv] = best.i; }
-        lds_barrier();
+        const PartStream st = stream_part<LT, false, true, kAuxStream>(rl, row_chunks, n_parts, h, V, 0.f, tid, leave_slot);
+        const ArgMax b = reduce_argmax(st.best, s_m, s_i, lane, wv);
         if (tid == 0) {
-            ArgMax b{s_m[0], s_i[0]};
-#pragma unroll
-            for (int w = 1; w < kQW; ++w) b = argmax_merge(b, ArgMax{s_m[w], s_i[w]});
-            HalfStat st; st.m = b.v; st.arg = b.i < V ? b.i : -1; st.Z = 0.0; *my_stat = st;
+            HalfStat out; out.m = b.v; out.arg = b.i < V ? b.i : -1; out.Z = 0.0; *my_stat = out;
         }
         return;
     }
-    // Maximum and normaliser on line, against a running per-thread reference m_run.  Both 16-bit formats are
-    // sign-magnitude: among non-negative values the order of the bit patterns as SIGNED 16-bit integers is
-    // the order of the values and every negative value is a negative integer, so a running packed signed
-    // maximum (one instruction per two elements) is the exact maximum as soon as the thread has seen one
-    // value >= +0; until then (masked vocabularies) the chunk's float maximum is taken the slow way.
-    // fp32 chunks (half as many elements per byte) take the float maximum throughout.
     const float c = 1.4426950408889634f / T;
-    short2v pm = {(short)0x8000, (short)0x8000};
-    float m_run = -INFINITY, zt = 0.f;
-    for (int s0 = 0; s0 < steps; s0 += kStatSteps) {
-#pragma unroll
-        for (int u = 0; u < kStatSteps; ++u) {
-            uint4 v = lg[u];
-            Chunk<LT>::blank(v, ADASPEC_STEP_PAST_END(s0 + u));
-            float mn;
-            if constexpr (kN == 4) {
-                mn = chunk_max<LT>(v, m_run);
-            } else {
-                const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-                for (int e = 0; e < 4; ++e) pm = __builtin_elementwise_max(pm, __builtin_bit_cast(short2v, w[e]));
-                const int top = max((int)pm.x, (int)pm.y);
-                mn = top >= 0 ? Pair16<LT>::lo((uint32_t)top & 0xffffu) : chunk_max<LT>(v, m_run);
-            }
-            if (mn > m_run) {
-                zt *= __builtin_amdgcn_exp2f((m_run - mn) * c);          // (-inf - finite) -> 0
-                m_run = mn;
-            }
-            if (m_run > -INFINITY) {
-                const float mnc = m_run * c;
-                float x[kN];
-                Chunk<LT>::unpack(v, x);
-#pragma unroll
-                for (int e = 0; e < kN; ++e) zt += exp_weight<LT>(x[e], m_run, c, mnc);
-            }
-            ADASPEC_STEP_REFILL(s0 + u, u)
-        }
-    }
-#undef ADASPEC_STEP_REFILL
-#undef ADASPEC_ROW_STEP
-#undef ADASPEC_STEP_OFFSET
-#undef ADASPEC_STEP_CHUNK
-#undef ADASPEC_STEP_PAST_END
-    const float mw = wave_max(m_run);
-    const double zw = wave_sum(m_run > -INFINITY ? (double)(zt * __builtin_amdgcn_exp2f((m_run - mw) * c)) : 0.0);
-    if (lane == 0) { s_m[wv] = mw; s_z[wv] = zw; }
-    lds_barrier();
-    if (tid == 0) {
-        float m = s_m[0];
-#pragma unroll
-        for (int w = 1; w < kQW; ++w) m = fmaxf(m, s_m[w]);
-        double z = 0.0;
-#pragma unroll
-        for (int w = 0; w < kQW; ++w)
-            z += s_m[w] > -INFINITY ? s_z[w] * (double)__builtin_amdgcn_exp2f((s_m[w] - m) * c) : 0.0;
-        HalfStat st; st.m = m; st.arg = 0; st.Z = z; *my_stat = st;
-    }
+    const PartStream st = stream_part<LT, true, false, kAuxStream>(rl, row_chunks, n_parts, h, V, c, tid, leave_slot);
+    const HalfStat out = reduce_norm(st, c, s_m, s_z, lane, wv);
+    if (tid == 0) *my_stat = out;
     ADASPEC_STAMP(0, 3);
 }
 
@@ -585,9 +333,7 @@ __global__ __launch_bounds__(kQT, sizeof(typename PT::storage) > sizeof(typename
     __shared__ double s_z[kSumParts];
     __shared__ int s_i[kQW];
     __shared__ int s_last;
-    __shared__ double s_wave[kQW];
-    __shared__ double s_before;
-    __shared__ int s_pick[2], s_lastpos;
+    __shared__ PairScratch s_pair;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int i = blockIdx.x / n_parts, h = blockIdx.x % n_parts;
     ADASPEC_STAMP(1, 0);
@@ -768,53 +514,28 @@ __global__ __launch_bounds__(kQT, sizeof(typename PT::storage) > sizeof(typename
         }
     }
     if ((tid & 1) == 0) { s_m[tid >> 1] = st.m; s_z[tid >> 1] = st.Z; }
-    if (tid == 0) { s_pick[0] = s_pick[1] = 0x7fffffff; s_lastpos = -1; }
     float M = wave_max(st.m);
-    if (lane == 0) s_wave[wv] = (double)M;
+    if (lane == 0) s_pair.wave[wv] = (double)M;
     __syncthreads();
-    M = (float)s_wave[0];
+    M = (float)s_pair.wave[0];
 #pragma unroll
-    for (int w = 1; w < kQW; ++w) M = fmaxf(M, (float)s_wave[w]);
+    for (int w = 1; w < kQW; ++w) M = fmaxf(M, (float)s_pair.wave[w]);
     // p_v of part h was computed as 2^((l_v - m_h) c) / Z_h: times Z_h 2^((m_h - M) c) it is relative to M in
     // every part (a rejected draft row has the same (m, Z) in all parts: a common factor, which tau absorbs)
     const double my_sc = st.m > -INFINITY ? st.Z * (double)__builtin_amdgcn_exp2f((st.m - M) * c) : 0.0;
 #pragma unroll
     for (int u = 0; u < 2; ++u) { res[u] *= my_sc; pm[u] *= my_sc; }
     bool use_p = bonus;                                       // (for a bonus row the two sums are the same numbers)
-    double tau = 0.0;
-    for (int attempt = 0; attempt < 2; ++attempt) {
-        const double w0 = use_p ? pm[0] : res[0], w1 = use_p ? pm[1] : res[1];
-        const double incl = wave_scan_incl(w0 + w1, lane);
-        __syncthreads();                                      // s_wave is free again
-        if (lane == 63) s_wave[wv] = incl;
-        __syncthreads();
-        double before = 0.0, R = 0.0;
-#pragma unroll
-        for (int w = 0; w < kQW; ++w) {
-            if (w < wv) before += s_wave[w];
-            R += s_wave[w];
-        }
-        if (!(R > 0.0) && !use_p) { use_p = true; continue; }  // p == q everywhere (R == 0): draw from p instead
-        tau = (double)u_draw * R;
-        // the first pair whose running total exceeds tau (rounding may leave none: then the last with mass).
-        // Every thread's claim goes through a minimum / maximum over pair numbers; the winner leaves its prefix.
-        const double at1 = before + incl, at0 = at1 - w1;     // running totals after the two pairs
-        int claim = 0x7fffffff, pos = -1;
-        if (w1 > 0.0) { pos = 2 * tid + 1; if (at1 > tau) claim = 2 * tid + 1; }
-        if (w0 > 0.0) { pos = max(pos, 2 * tid); if (at0 > tau) claim = 2 * tid; }
-        if (claim != 0x7fffffff) atomicMin(&s_pick[0], claim);
-        if (pos >= 0) atomicMax(&s_lastpos, pos);
-        __syncthreads();
-        const int pick = s_pick[0] != 0x7fffffff ? s_pick[0] : s_lastpos;
-        if (pick >= 0 && (pick >> 1) == tid) s_before = (pick & 1) ? at0 : at0 - w0;
-        if (tid == 0) s_pick[1] = pick;
-        __syncthreads();
-        break;
+    double R, at1 = pair_totals(s_pair, use_p ? pm[0] + pm[1] : res[0] + res[1], tid, lane, wv, R);
+    if (!(R > 0.0) && !use_p) {                               // p == q everywhere (R == 0): draw from p instead
+        use_p = true;
+        at1 = pair_totals(s_pair, pm[0] + pm[1], tid, lane, wv, R);
     }
+    const double tau = (double)u_draw * R;
+    const int pair = pick_pair(s_pair, use_p ? pm[0] : res[0], use_p ? pm[1] : res[1], at1, tau, tid);
     ADASPEC_STAMP(1, 6);
 
     // ---- inside the pair: the step (one wavefront each), then the lane, then the element ------------------
-    const int pair = s_pick[1];
     if (pair < 0 || pair >= n_pairs) {        // no mass anywhere (non-finite input): stay defined
         if (tid == 0) o[a] = 0;
         return;
@@ -841,40 +562,11 @@ __global__ __launch_bounds__(kQT, sizeof(typename PT::storage) > sizeof(typename
         mine32 += rv[e];
     }
     const double mine = (double)mine32 * sch;
-    const double incl = wave_scan_incl(mine, lane);
-    if (lane == 63) s_wave[wv] = incl;                        // (last read behind the barriers above)
-    __syncthreads();
-    // the step: first whose running total exceeds tau, else the last with mass
-    double at = s_before, base = 0.0;
-    int step = -1;
-    bool found = false;
-#pragma unroll
-    for (int it = 0; it < kSumSteps; ++it) {
-        const double tot = s_wave[it];
-        if (!found && tot > 0.0) {
-            step = it; base = at;
-            found = at + tot > tau;
-        }
-        at += tot;
-    }
-    if (step < 0 && tid == 0) o[a] = 0;       // the sums said there was mass here, the recomputation finds none
-    if (step != wv) return;
-    const double li = base + incl;
-    const unsigned long long lhit = __ballot(mine32 > 0.f && li > tau);
-    const unsigned long long lpos = __ballot(mine32 > 0.f);
-    const int owner = lhit ? (int)__builtin_ctzll(lhit) : 63 - (int)__builtin_clzll(lpos);   // lpos != 0: the step has mass
-    if (lane == owner) {
-        double cum = li - mine;
-        int pick = -1, lastpos = -1;
-#pragma unroll
-        for (int e = 0; e < kN; ++e) {
-            cum += (double)rv[e] * sch;
-            if (rv[e] > 0.f) lastpos = e;
-            if (pick < 0 && rv[e] > 0.f && cum > tau) pick = e;
-        }
-        if (pick < 0) pick = lastpos < 0 ? 0 : lastpos;
-        o[a] = chunk * kN + pick;
-    }
+    double li;
+    bool none;
+    const bool owner = own_point(s_pair, mine, tau, lane, wv, li, none);
+    if (none && tid == 0) o[a] = 0;           // the sums said there was mass here, the recomputation finds none
+    if (owner) o[a] = chunk * kN + pick_element<kN>(rv, li - mine, sch, tau);
     ADASPEC_STAMP(1, 7);
 }
 
@@ -889,9 +581,7 @@ static int parts_compute_units()
     return cus;
 }
 
-// elements per 16-byte chunk of logits
-static int chunk_elems(const adaspec_accept_dims &d) { return d.logits_dtype == ADASPEC_F32 ? 4 : 8; }
-static int sum_parts(const adaspec_accept_dims &d) { return ceil_div(d.vocab / chunk_elems(d), kSumChunks); }
+static int sum_parts(const adaspec_accept_dims &d) { return parts_sum_parts(d.vocab, d.logits_dtype); }
 
 bool accept_parts_dims_fit(const adaspec_accept_dims &d)
 {
@@ -920,17 +610,7 @@ hipError_t launch_accept_parts(const AcceptArgs &a)
 {
     const adaspec_accept_dims &d = a.dims;
     if (d.batch == 0) return hipSuccess;
-    const int row_chunks = d.vocab / chunk_elems(d), row_steps = ceil_div(row_chunks, kQT);
-    // First pass: a part is a stream of 8, 16, 32 or 64 steps.  Short streams spread a row over more compute
-    // units; long ones read faster (measured on MI355X, config 3: 8 steps 48 us for the whole call, 16 steps
-    // 44 us, 32 steps 42 us).  Aim: about three workgroups per compute unit, all resident at once; and a row
-    // has kStatParts parts at most.
-    int stat_steps = kStatSteps;
-    while (stat_steps < 64 &&
-           (row_steps > kStatParts * stat_steps ||
-            (int64_t)d.total_draft * ceil_div(row_steps, stat_steps) > (int64_t)kStatTargetWgsPerCu * parts_compute_units()))
-        stat_steps *= 2;
-    const int n_stat_parts = ceil_div(row_steps, stat_steps);
+    const int n_stat_parts = parts_stat_parts(d.total_draft, d.vocab, d.logits_dtype, parts_compute_units());
     const int n_sum_parts = sum_parts(d);
     int32_t *cu_q = (int32_t *)(a.ws + a.plan.off_cu_q);
     int32_t *ticket = (int32_t *)(a.ws + a.plan.off_req_ticket);

@@ -580,12 +580,27 @@ static int validate_draft_dims(const adaspec_draft_dims *d)
     return ADASPEC_OK;
 }
 
+// AUTO of draft sampling (MI355X, us per call, 128 rows): the form in parts from V = 8192 on (three launches: 12.1 whatever
+// the type; the three-sweep kernel 12-13 at V = 8192, 15 at 16384), the three-sweep kernel below (V = 4096: 10.0, in parts
+// 12.1, register-resident 14.0).  Without a workspace the register-resident kernel is ahead of the three sweeps from
+// V = 32768 on (V = 24576: 17.2 against 17.4; V = 128256: 36 against 46).
+constexpr int kDraftPartsFrom = 8192, kDraftFastFrom = 32768;
+
+// Whether dims may take the form in parts: forced (ADASPEC_PATH_TWO_PASS) for 16-bit logits up to V = 131072; AUTO also
+// for fp32 logits and larger vocabularies.
+static bool draft_parts_fit(const adaspec_draft_dims &d)
+{
+    if (!draft_parts_supported(d)) return false;
+    const bool small16 = d.logits_dtype != ADASPEC_F32 && d.vocab <= 131072;
+    return small16 || (d.path == ADASPEC_PATH_AUTO && d.vocab >= kDraftPartsFrom);
+}
+
 size_t adaspec_draft_sample_workspace_bytes(const adaspec_draft_dims *d)
 {
     if (validate_draft_dims(d) != ADASPEC_OK || d->rows == 0) return 0;
-    if (d->vocab % 8 || d->logits_row_stride % 8 || d->probs_row_stride % 8 || !draft_split_supported(*d)) return 0;
+    if (d->vocab % 8 || d->logits_row_stride % 8 || d->probs_row_stride % 8 || !draft_parts_fit(*d)) return 0;
     if (d->path == ADASPEC_PATH_VECTOR || d->path == ADASPEC_PATH_FAST) return 0;
-    return draft_split_workspace_bytes(d->rows);
+    return draft_parts_workspace_bytes(*d);
 }
 
 int adaspec_draft_sample(const void *draft_logits, const float *temperature, const float *uniforms,
@@ -601,28 +616,27 @@ int adaspec_draft_sample(const void *draft_logits, const float *temperature, con
     if (!aligned16(draft_logits) || !aligned16(draft_probs)) return ADASPEC_ERR_ALIGN;
     if (!draft_sample_supported(*d, draft_logits, draft_probs)) return ADASPEC_ERR_UNSUPPORTED;
     const bool fast_ok = draft_fast_supported(*d);
-    const bool split_ok = draft_split_supported(*d);
+    const bool split_ok = draft_parts_fit(*d);
     if (d->path == ADASPEC_PATH_FAST && !fast_ok) return ADASPEC_ERR_UNSUPPORTED;
     bool split = false;
     if (d->path == ADASPEC_PATH_TWO_PASS) {
         if (!split_ok) return ADASPEC_ERR_UNSUPPORTED;
         if (!workspace) return ADASPEC_ERR_NULL;
         if (reinterpret_cast<uintptr_t>(workspace) & 255u) return ADASPEC_ERR_ALIGN;
-        if (workspace_bytes < draft_split_workspace_bytes(d->rows)) return ADASPEC_ERR_WORKSPACE;
+        if (workspace_bytes < draft_parts_workspace_bytes(*d)) return ADASPEC_ERR_WORKSPACE;
         split = true;
     } else if (d->path == ADASPEC_PATH_AUTO) {
-        // three small kernels against one long one: worth it once a row is long (measured on MI355X, 128 rows:
-        // V = 128256 24 against 36 us)
-        split = split_ok && d->vocab >= 32768 && workspace && !(reinterpret_cast<uintptr_t>(workspace) & 255u) &&
-                workspace_bytes >= draft_split_workspace_bytes(d->rows);
+        split = split_ok && d->vocab >= kDraftPartsFrom && workspace && !(reinterpret_cast<uintptr_t>(workspace) & 255u) &&
+                workspace_bytes >= draft_parts_workspace_bytes(*d);
     }
-    const bool fast = !split && fast_ok && d->path != ADASPEC_PATH_VECTOR;
+    const bool fast = !split && fast_ok &&
+                      (d->path == ADASPEC_PATH_FAST || (d->path == ADASPEC_PATH_AUTO && d->vocab >= kDraftFastFrom));
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (!record_event(d->timing_start, d->timing_stop, true, st)) return ADASPEC_ERR_HIP;
     hipError_t e;
     if (split)
-        e = launch_draft_split(draft_logits, temperature, uniforms, out_rows, draft_probs, draft_tokens, confidence, *d,
-                               static_cast<char *>(workspace), st);
+        e = launch_draft_parts(draft_logits, temperature, uniforms, out_rows, draft_probs, draft_tokens, confidence, *d,
+                               static_cast<char *>(workspace), compute_units(), st);
     else if (fast)
         e = launch_draft_fast(draft_logits, temperature, uniforms, out_rows, draft_probs, draft_tokens, confidence, *d, st);
     else

@@ -1,5 +1,4 @@
-// Shared by the draft-sampling kernels that work on packed 16-bit logits (draft_fast.hip,
-// draft_split.hip): the probabilities of one 16-byte chunk.
+// The probabilities of one 16-byte chunk of 16-bit logits (draft_fast.hip).
 #pragma once
 #include <type_traits>
 

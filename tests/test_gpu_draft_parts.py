@@ -1,0 +1,47 @@
+"""Draft sampling in row parts (csrc/draft_parts.hip) over all pairs of storage types: vocabularies around a step of 256
+chunks, a wavefront's share, a part, and the largest one, on the path AUTO takes for them; rows with few finite logits, the
+ends of the uniforms' range, scattered rows. Bar of the other draft tests (one ulp per stored probability, tokens equal or
+a counted near-tie)."""
+import numpy as np
+import pytest
+
+import workloads as W
+from tests.test_gpu_draft import _check, pkg  # noqa: F401  (fixture)
+
+pytestmark = pytest.mark.gpu
+
+T = np.array([1.0, 0.0, 0.5, 1.3], np.float32)
+U = np.array([0.0, 0.5, 1.0 - 2.0 ** -24, 0.37], np.float32)
+
+
+def _logits(R, V, ldt, seed=3, masked=0.0):
+    rng = np.random.default_rng(seed + V)
+    x = (2.5 * rng.standard_normal((R, V))).astype(np.float32)
+    if masked:
+        gone = rng.random((R, V)) < masked
+        gone[np.arange(R), rng.integers(0, V, R)] = False
+        x[gone] = -np.inf
+    return x if ldt == "f32" else W.f32_to_bf16_bits(x) if ldt == "bf16" else x.astype(np.float16)
+
+
+@pytest.mark.parametrize("V", [32768, 33800, 36872])
+@pytest.mark.parametrize("ldt,pdt", [(a, b) for a in ("f32", "f16", "bf16") for b in ("f32", "f16", "bf16")])
+def test_draft_parts_types(ldt, pdt, V, oracle_mod, pkg):  # noqa: F811
+    _check(_logits(4, V, ldt), ldt, pdt, T, U, oracle_mod, pkg)
+
+
+@pytest.mark.parametrize("V,ldt,pdt", [(128256, "f32", "bf16"), (131080, "bf16", "bf16"), (262144, "f16", "f32"),
+                                       (524288, "f32", "f32"), (524280, "bf16", "bf16")])
+def test_draft_parts_large_vocabularies(V, ldt, pdt, oracle_mod, pkg):  # noqa: F811
+    _check(_logits(3, V, ldt), ldt, pdt, T[:3], U[:3], oracle_mod, pkg)
+
+
+@pytest.mark.parametrize("V", [8, 8192, 8200, 16384 + 8, 40000])
+def test_draft_parts_forced_on_small_rows(V, oracle_mod, pkg):  # noqa: F811
+    _check(_logits(4, V, "bf16"), "bf16", "bf16", T, U, oracle_mod, pkg, path="split")
+
+
+def test_draft_parts_masked_rows_and_scattered_output(oracle_mod, pkg):  # noqa: F811
+    rows = np.array([5, 0, 6, 2], np.int32)
+    for ldt in ("f32", "bf16"):
+        _check(_logits(4, 40000, ldt, masked=0.999), ldt, ldt, T, U, oracle_mod, pkg, out_rows=rows, n_prob_rows=7)
