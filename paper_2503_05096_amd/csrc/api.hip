@@ -98,6 +98,7 @@ static int validate_attn_dims(const adaspec_attn_dims *d)
 // 8 kv heads: 79.5 us per layer with it, 82.9 us direct).
 constexpr int kDirectMaxBatch = 256;
 constexpr int kDirectMaxUnits = 256;
+constexpr int kDirectShortCtx = 512, kDirectShortBatch = 1024;
 constexpr int kWavesPerUnit = 4;
 
 AttnKind attn_kind(const adaspec_attn_dims &d)
@@ -142,6 +143,19 @@ AttnPlan make_attn_plan(const adaspec_attn_dims &d, AttnKind kind)
                 p.direct = true;
                 p.split_tokens = s;
             }
+    }
+    if (scheduled && !p.direct && max_ctx <= 2 * kDirectShortCtx && d.batch <= kDirectShortBatch) {
+        // Short contexts: every request is one unit per kv head (no combine), all of them about equally short.  Measured
+        // with and without (MI355X, 32/8 heads of 128, bf16): 256 requests of 100-500 tokens 62.6 / 65.5 us, 126 of 119-185
+        // 14.0 / 18.5, 64 of 512-1000 39.5 / 42.3, 128 of 256-1000 64.6 / 63.4 (left to the schedule).  The row-split and
+        // the fp32 kernel lose more by not loading across unit boundaries (200 requests of 100-400 tokens, 72 rows per
+        // kv head: 104 / 87; 88 of 9-30 tokens, 40 rows: 12.4 / 19.2): up to 1024 possible tokens per compute unit.
+        const int64_t units = d.batch * (int64_t)d.n_kv_heads * attn_row_groups((d.max_spec_len + 1) * G);
+        const bool deep = kind == AttnKind::kMfmaF32 || (kind == AttnKind::kMfma128 && attn_row_tiles((d.max_spec_len + 1) * G) > 2);
+        if (deep ? units * max_ctx <= 262144 : units <= (max_ctx <= kDirectShortCtx ? 8192 : 512)) {
+            p.direct = true;
+            p.split_tokens = 2 * kDirectShortCtx;
+        }
     }
     const int64_t per_req = (max_ctx + p.split_tokens - 1) / p.split_tokens;
     p.per_req = (int)per_req;

@@ -34,6 +34,21 @@ def test_attention_direct_and_scheduled(shape, crowd, d, dtype, oracle_mod, pkg)
     check_attention(st, oracle_mod, pkg)
 
 
+@pytest.mark.parametrize("B,top,hq,hkv,d,dtype", [(300, 40, 32, 8, 128, "bf16"),     # 2400 units, no combine
+                                                  (70, 512, 8, 8, 64, "f16"), (70, 528, 8, 8, 64, "f16"),
+                                                  (60, 1008, 32, 8, 128, "bf16"), (60, 1040, 32, 8, 128, "bf16"),
+                                                  (90, 30, 64, 8, 128, "bf16"), (90, 300, 64, 8, 128, "bf16"),
+                                                  (40, 300, 32, 8, 128, "f32"), (100, 512, 16, 8, 64, "f32")])
+def test_attention_short_contexts_around_the_rule(B, top, hq, hkv, d, dtype, oracle_mod, pkg):  # noqa: F811
+    rng = np.random.default_rng(B + top)
+    spec = rng.integers(0, 6 if hq == 64 else 4, B)
+    ctx = np.maximum(rng.integers(1, top + 1, B), spec + 1)
+    ctx[B // 2] = top
+    st = W.make_custom_step(B + top, ctx_lens=ctx, spec_lens=spec, n_q_heads=hq, n_kv_heads=hkv, head_dim=d, dtype=dtype,
+                            acceptance=False, name=f"short-{B}-{top}")
+    check_attention(st, oracle_mod, pkg)
+
+
 def test_attention_direct_with_a_wide_block_table(oracle_mod, pkg):  # noqa: F811
     """A block table far wider than the contexts: most possible splits do not exist, and the entries behind a request's
     pages are not page ids."""
