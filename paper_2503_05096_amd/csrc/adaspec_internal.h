@@ -131,8 +131,9 @@ struct AcceptPlan {
     size_t off_half_stat;   // HalfStat[B][parts]: per part of the deciding row
     size_t off_part;        // WaveMass[B][parts][4]: masses of the deciding rows, per wavefront of a part
     bool parts;             // the workspace holds what the form in parts needs
-    size_t off_tree_stat;   // tree acceptance: per-node statistics (tree_node_stat_bytes() each)
+    size_t off_tree_stat;   // tree acceptance, last: per-node statistics (tree_node_stat_bytes() each)
     size_t total_bytes;
+    size_t noalloc_bytes;   // what adaspec_accept_noalloc's limit is compared with
 };
 // p_v = 2^((l_v - m) c) / Z of a row (first pass of the two-pass form -> second pass)
 struct RowStat { float m; float pad; double Z; };
@@ -178,9 +179,10 @@ hipError_t launch_accept_parts(const AcceptArgs &a);
 hipError_t launch_accept_tree_nodes(const AcceptArgs &a, const int32_t *parents);
 // 16-bit rows (shapes of the register-resident chain kernel): node statistics, then one workgroup per request
 // walks its tree and writes the outputs (no separate walk kernel)
-size_t tree_node_stat_bytes();
+size_t tree_node_stat_bytes(int vocab);
+constexpr size_t kTreeNodeStatMin = 528;
 bool tree_fast_needs_plan(const adaspec_accept_dims &d);   // large batches: row offsets from launch_accept_plan
-hipError_t launch_accept_tree_fast(const AcceptArgs &a, const int32_t *parents, int32_t *out_path);
+hipError_t launch_accept_tree_fast(const AcceptArgs &a, const int32_t *parents, int compute_units, int32_t *out_path);
 hipError_t launch_accept_tree_walk(const AcceptArgs &a, int32_t *out_path);
 hipError_t launch_kv_compact_path(void *k_pages, void *v_pages, const int32_t *block_table,
                                   const int32_t *ctx_lens, const int32_t *spec_lens,

@@ -209,10 +209,10 @@ AcceptPlan make_accept_plan(const adaspec_accept_dims &d)
     const size_t nb = (size_t)(d.batch > 0 ? d.batch : 1);
     p.off_row_stat = off;   off = align_up(off + tq * sizeof(RowStat), 256);
     p.off_req_ticket = off; off = align_up(off + nb * 4, 256);
-    p.off_tree_stat = off; off = align_up(off + tq * tree_node_stat_bytes(), 256);
-    // What the form in parts needs comes last.  16-bit rows of one type up to V = 131072 always have it; for the others
+    // What the form in parts needs.  16-bit rows of one type up to V = 131072 always have it; for the others
     // it is laid out only where the whole workspace still fits adaspec_accept_noalloc's built-in scratch, so that no
     // call outgrows that array because of it.
+    const size_t tree_min = align_up(tq * kTreeNodeStatMin, 256);
     p.parts = accept_parts_dims_fit(d);
     p.off_slot_rec = p.off_part_stat = p.off_half_stat = p.off_part = off;
     if (p.parts) {
@@ -222,9 +222,12 @@ AcceptPlan make_accept_plan(const adaspec_accept_dims &d)
         p.off_half_stat = end;  end = align_up(end + accept_parts_sum_stat_bytes(d), 256);
         p.off_part = end;       end = align_up(end + accept_parts_sum_bytes(d), 256);
         const bool narrow = d.logits_dtype != ADASPEC_F32 && d.logits_dtype == d.probs_dtype && d.vocab <= 131072;
-        p.parts = narrow || end <= kNoallocScratchBytes;
+        p.parts = narrow || end + tree_min <= kNoallocScratchBytes;
         if (p.parts) off = end;
     }
+    p.noalloc_bytes = off + tree_min;
+    // tree calls only, and therefore last: the chain call without a workspace does not need all of it
+    p.off_tree_stat = off; off = align_up(off + tq * tree_node_stat_bytes(d.vocab), 256);
     p.total_bytes = off;
     return p;
 }
@@ -357,7 +360,7 @@ static int accept_impl(const void *target_logits, const void *draft_probs,
 {
     int rc = validate_accept_dims(dims);
     if (rc != ADASPEC_OK) return rc;
-    if (use_static_scratch && make_accept_plan(*dims).total_bytes > kNoallocScratchBytes)
+    if (use_static_scratch && make_accept_plan(*dims).noalloc_bytes > kNoallocScratchBytes)
         return ADASPEC_ERR_WORKSPACE;           // larger than the built-in scratch: use adaspec_accept
     if (dims->batch == 0) return ADASPEC_OK;
     if (!target_logits || !uniforms || !spec_lens || !temperature || !out_tokens || !out_accept_len ||
@@ -376,7 +379,7 @@ static int accept_impl(const void *target_logits, const void *draft_probs,
                streaming = path == ADASPEC_PATH_STREAM;
     AcceptArgs a;
     a.plan = make_accept_plan(*dims);
-    if (workspace_bytes < a.plan.total_bytes) return ADASPEC_ERR_WORKSPACE;
+    if (!use_static_scratch && workspace_bytes < a.plan.total_bytes) return ADASPEC_ERR_WORKSPACE;
     a.logits = target_logits; a.probs = draft_probs; a.draft_tokens = draft_tokens;
     a.uniforms = uniforms; a.spec_lens = spec_lens; a.temperature = temperature;
     a.out_tokens = out_tokens; a.out_accept_len = out_accept_len;
@@ -469,7 +472,7 @@ int adaspec_accept_tree(const void *target_logits, const void *draft_probs,
     if ((!fast || tree_fast_needs_plan(*dims)) && launch_accept_plan(a) != hipSuccess) return ADASPEC_ERR_HIP;
     if (!record_event(dims->timing_start, dims->timing_stop, true, a.stream)) return ADASPEC_ERR_HIP;
     if (fast) {
-        if (launch_accept_tree_fast(a, parents, out_path) != hipSuccess) return ADASPEC_ERR_HIP;
+        if (launch_accept_tree_fast(a, parents, compute_units(), out_path) != hipSuccess) return ADASPEC_ERR_HIP;
     } else {
         if (launch_accept_tree_nodes(a, parents) != hipSuccess) return ADASPEC_ERR_HIP;
         if (launch_accept_tree_walk(a, out_path) != hipSuccess) return ADASPEC_ERR_HIP;

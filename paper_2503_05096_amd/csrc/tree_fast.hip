@@ -1,8 +1,10 @@
 // Tree acceptance for 16-bit logits and draft probabilities of one type, V % 8 == 0,
 // V <= 524288 (the shapes of the streaming chain kernel), in two kernels:
 //
-//   1. node statistics, one workgroup per node (= logits row), one read of the row: the maximum
-//      and its index, and for a sampled request the normaliser Z with its per-step parts S0[];
+//   1. node statistics: every node's logits row read once, in steps of 8192 elements shared out to small
+//      workgroups: per step the maximum and, for a sampled request, the normaliser relative to it (greedy:
+//      the arg-max); and per draft node what its accept test needs (its token, the token's logit and draft
+//      probability at the parent, the uniform) beside its parent;
 //   2. the walk, one workgroup per request: from the root, at every node it reaches it tests
 //      the children in turn and, after each rejection, sweeps the node's logits and
 //      draft-probability rows once for the next residual mass; where the walk stops it draws
@@ -18,157 +20,184 @@
 // elements of 16 neighbouring lanes, fp64 above that); R = sum of the S[s].  The draw needs no
 // sweep of its own: the step where the prefix crosses comes from S[]; the threads then load
 // their 8 elements of that one step again, a scan over the threads finds the one where the
-// prefix crosses, and it picks the element.  What a child's test needs (its token, the token's
-// logit and draft probability, its uniform) is fetched when the walk arrives at the parent, so a
-// test is arithmetic on values already on chip.
+// prefix crosses, and it picks the element.  A test is arithmetic on values already on chip.
+//
+// Bound: HBM for the statistics; vector arithmetic of one compute unit per sweep in the walk (about 11 us at
+// V = 128256), whose longest chain of sweeps sets its time.  MI355X, 64 requests, 288 nodes, trees of width 3:
+// statistics 16.0 us (one 1024-thread workgroup per node: 23.7), walk 42.9 us (with three dependent loads more at every
+// node and the test values fetched there: 47.2).
 #include "adaspec_internal.h"
 #include "device_utils.h"
-#include "row_registers.h"
+#include "row_parts.h"
 #include "row_stream.h"
 
 namespace adaspec {
 
 __device__ __forceinline__ int sane_parent_f(int p, int j) { return j == 0 ? -1 : min(max(p, 0), j - 1); }
 
-// what kernel 1 leaves per node
-struct TreeNodeStat {
-    float  m;               // maximum logit
-    int    arg;             // its lowest index (greedy requests; 0 for sampled ones, which never emit it)
-    double Z;               // sum_v 2^((l_v - m) c) = sum of S0[]      (sampled requests only)
-    double S0[kNSteps];     // the same sum step by step
-};
-size_t tree_node_stat_bytes() { return sizeof(TreeNodeStat); }
+// What kernel 1 leaves per node: a record for the accept test (nodes j >= 1), then per step of 8192 elements the
+// (maximum, arg-max, normaliser) of its elements.
+struct TreeNodeRec { int parent, x; float l, q, u0; int pad[3]; };
+constexpr int kStatsWgsPerCu = 6;                   // statistics: workgroups per compute unit the launch aims for (all resident)
+constexpr int kStepChunks = kNT;                    // 16-byte chunks per step
+static_assert(kStepChunks == kSumSteps * kQT, "a step is four chunks per thread of the statistics kernel");
+// (528 bytes is what a node took when the workspace rules were laid down: smaller ones keep that size)
+size_t tree_node_stat_bytes(int vocab)
+{
+    const size_t need = sizeof(TreeNodeRec) + (size_t)ceil_div(vocab / 8, kStepChunks) * sizeof(HalfStat);
+    return need > kTreeNodeStatMin ? need : kTreeNodeStatMin;
+}
 
 // ---- kernel 1: statistics of every node ---------------------------------------------------------
-// ONE read of the row.  The sums of a step are taken relative to the maximum of the 128 elements of
-// each 16-lane group (known as soon as the group's loads are there) and put on the row's maximum at
-// the end: S0[s] = sum_g part[s][g] * 2^((gmax[s][g] - m) c).  A sampled row costs one exponential
-// per element, as a second sweep would, but the row is not fetched a second time.
+// workgroup = (node, group of steps); the loads of the next step are under way while one is summed.
 template <class DT>
-__global__ __launch_bounds__(kNT, 8) void tree_node_stats_kernel(
-    const char *__restrict__ logits, const int32_t *__restrict__ spec_lens,
-    const float *__restrict__ temperature, int B, int V, int max_spec_len, int64_t lstride,
-    TreeNodeStat *__restrict__ stats)
+__global__ __launch_bounds__(kQT, 6) void tree_node_stats_kernel(
+    const char *__restrict__ logits, const char *__restrict__ probs, const int32_t *__restrict__ draft_tokens,
+    const int32_t *__restrict__ parents, const float *__restrict__ uniforms, const int32_t *__restrict__ spec_lens,
+    const float *__restrict__ temperature, int B, int V, int total_draft, int max_spec_len, int n_groups, int group_steps,
+    int64_t lstride, int64_t pstride, char *__restrict__ stats, int stat_bytes)
 {
-    __shared__ float wmax[kNW];
-    __shared__ int warg[kNW];
-    __shared__ float part[kNSteps][kWave], gmax[kNSteps][kWave];
-    __shared__ double S[kNSteps];
-    __shared__ int wtot[kNW], owner;
-    __shared__ float owner_T;
+    constexpr int kN = 8;
+    __shared__ float s_m[kNSteps][kQW];
+    __shared__ double s_z[kNSteps][kQW];
+    __shared__ int s_i[kQW], s_tot[kQW], s_own[3];
+    __shared__ float s_T;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int r = blockIdx.x;
-    const char *lrow = logits + (int64_t)r * lstride * 2;
-    const int nsteps = ceil_div(V / 8, kNT);
-
-    // The first 1024 draft lengths and temperatures, then the first steps of the row: all requested before
-    // anything is waited for.  Which request owns row r (only its temperature is needed) is found by a block
-    // scan of n_i = k_i + 1, 1024 requests at a time, while the row's data travels.
-    int n_first = 0;
-    float t_first = 0.f;
-    if (tid < B) {
-        n_first = min(max(spec_lens[tid], 0), max_spec_len) + 1;
-        t_first = temperature[tid];
-    }
-    RowPipe<false> pipe;
-    pipe.start(lrow, lrow, nsteps, V, tid);
-    if (tid == 0) owner = -1;
-    {
-        int carry = 0;
-        for (int base = 0; base < B; base += kNT) {
-            const int i = base + tid;
-            int n = n_first;
-            float tt = t_first;
-            if (base > 0) {
-                n = i < B ? min(max(spec_lens[i], 0), max_spec_len) + 1 : 0;
-                tt = i < B ? temperature[i] : 0.f;
-            }
-            const int inc = wave_scan_incl_dpp(n);
-            lds_barrier();                                      // (later trips: wtot of the trip before has been read)
-            if (lane == 63) wtot[wv] = inc;
-            lds_barrier();                                      // LDS only: the row's loads stay in flight
-            int pre = carry, tot = carry;
+    const int r = blockIdx.x / n_groups, h = blockIdx.x % n_groups;
+    const int row_chunks = V / kN, nsteps = ceil_div(row_chunks, kStepChunks);
+    const int first = h * group_steps, last = min(nsteps, first + group_steps);
+    const __amdgpu_buffer_rsrc_t rl =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(logits) + (int64_t)r * lstride * 2, 0, row_chunks * 16, 0x00020000);
+    auto load_step = [&](int s, uint4 (&lg)[kSumSteps]) {            // (past the row: zeros)
 #pragma unroll
-            for (int w = 0; w < kNW; ++w) {
-                if (w < wv) pre += wtot[w];
-                tot += wtot[w];
-            }
-            const int start = pre + inc - n;
-            if (i < B && r >= start && r < start + n) { owner = i; owner_T = tt; }
-            carry = tot;
-            if (r < carry) break;                               // uniform: found
+        for (int it = 0; it < kSumSteps; ++it)
+            lg[it] = part_load16<kAuxDefault>(rl, (uint32_t)tid * 16u, (s * kStepChunks + it * kQT) * 16);
+    };
+    // Which request owns row r is found by a block scan of n_i = k_i + 1, 1024 requests at a time; the lengths of
+    // the first ones are requested in front of the row's first step, which travels meanwhile.
+    int nn[4];
+    float tt[4];
+    auto lengths = [&](int base) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int i = base + tid * 4 + u;
+            nn[u] = i < B ? min(max(spec_lens[i], 0), max_spec_len) + 1 : 0;
+            tt[u] = i < B ? temperature[i] : 0.f;
         }
+    };
+    lengths(0);
+    uint4 lg[kSumSteps];
+    load_step(first, lg);
+    if (tid == 0) s_own[0] = -1;
+    int carry = 0;
+    for (int base = 0; base < B; base += 4 * kQT) {
+        if (base > 0) lengths(base);
+        const int n = (nn[0] + nn[1]) + (nn[2] + nn[3]);
+        const int inc = wave_scan_incl_dpp(n);
+        lds_barrier();                                      // (later trips: s_tot of the trip before has been read)
+        if (lane == 63) s_tot[wv] = inc;
+        lds_barrier();                                      // LDS only: the row's loads stay in flight
+        int pre = carry, tot = carry;
+#pragma unroll
+        for (int w = 0; w < kQW; ++w) {
+            if (w < wv) pre += s_tot[w];
+            tot += s_tot[w];
+        }
+        int start = pre + inc - n;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (r >= start && r < start + nn[u]) { s_own[0] = base + tid * 4 + u; s_own[1] = start; s_T = tt[u]; }
+            start += nn[u];
+        }
+        carry = tot;
+        if (r < carry) break;                               // uniform: found
     }
     lds_barrier();
-    if (owner < 0) {                                            // no request owns this row (inconsistent metadata)
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        return;
+    const int i = s_own[0];
+    if (i < 0) return;                                      // no request owns this row (inconsistent metadata)
+    const int r0 = s_own[1], j = r - r0;
+    const float T = s_T;
+    char *node = stats + (int64_t)r * stat_bytes;
+    HalfStat *entry = reinterpret_cast<HalfStat *>(node + sizeof(TreeNodeRec));
+    if (h == 0 && tid == 0 && j >= 1) {
+        TreeNodeRec rec = {};
+        rec.parent = sane_parent_f(parents[r], j);
+        const int d0 = r0 - i;                              // first draft row of the request
+        if (d0 + j - 1 < total_draft) {
+            rec.x = draft_tokens[d0 + j - 1];
+            const int xa = min(max(rec.x, 0), V - 1);
+            rec.l = load_as_float<DT>(logits, (int64_t)(r0 + rec.parent) * lstride + xa);
+            rec.q = load_as_float<DT>(probs, (int64_t)(d0 + rec.parent) * pstride + xa);
+            rec.u0 = uniforms[2 * (int64_t)(r - 1)];
+        }
+        *reinterpret_cast<TreeNodeRec *>(node) = rec;
     }
-    const float T = owner_T;
-    const bool sampled = T != 0.0f;
-    const float cexp = sampled ? 1.4426950408889634f / T : 0.f;
-    constexpr float kLowest = -3.0e38f;                          // stands in for -inf: differences stay defined
-
-    TreeNodeStat *st = stats + r;
-    if (!sampled) {
-        // greedy: the arg-max (lowest index on ties) is all the walk needs
+    if (T == 0.0f) {
+        // greedy: the arg-max of the group's steps (lowest index on ties), left in its first step
         ArgMax best{-INFINITY, V};
-        pipe.run([&](int s, bool in_range, const uint4 &lw, const uint4 &) {
-            if (!in_range) return;
-            const int v0 = (s * kNT + tid) * 8;
-            float x[8];
-            unpack8<DT>(lw, x);
+        for (int s = first; s < last; ++s) {
+            uint4 nx[kSumSteps];
+            load_step(s + 1 < last ? s + 1 : nsteps, nx);            // (another group's step: nothing)
 #pragma unroll
-            for (int e = 0; e < 8; ++e)
-                if (x[e] > best.v) best = ArgMax{x[e], v0 + e};
-        });
-        best = wave_argmax(best);
-        if (lane == 0) { wmax[wv] = best.v; warg[wv] = best.i; }
-        __syncthreads();
-        best = ArgMax{wmax[0], warg[0]};
+            for (int it = 0; it < kSumSteps; ++it) {
+                const int chunk = s * kStepChunks + it * kQT + tid;
+                Chunk<DT>::blank(lg[it], chunk >= row_chunks);
+                float x[kN];
+                Chunk<DT>::unpack(lg[it], x);
 #pragma unroll
-        for (int w = 1; w < kNW; ++w) best = argmax_merge(best, ArgMax{wmax[w], warg[w]});
-        if (best.i >= V) best.i = 0;
-        if (tid == 0) { st->m = best.v; st->arg = best.i; st->Z = 1.0; }
+                for (int e = 0; e < kN; ++e)
+                    if (x[e] > best.v) best = ArgMax{x[e], chunk * kN + e};
+                lg[it] = nx[it];
+            }
+        }
+        best = reduce_argmax(best, s_m[0], s_i, lane, wv);
+        if (tid < last - first) {
+            HalfStat st;
+            st.m = tid == 0 ? best.v : -INFINITY;
+            st.arg = tid == 0 && best.i < V ? best.i : -1;
+            st.Z = 0.0;
+            entry[first + tid] = st;
+        }
         return;
     }
-    // sampled: maximum and normaliser; the index of the maximum is not needed (a sampled walk never emits it)
-    float tmax = kLowest;
-    pipe.run([&](int s, bool in_range, const uint4 &lw, const uint4 &) {
-        float x[8];
-        float mx = kLowest;
-        if (in_range) {
-            unpack8<DT>(lw, x);
+    const float c = 1.4426950408889634f / T;
+    for (int s = first; s < last; ++s) {
+        uint4 nx[kSumSteps];
+        load_step(s + 1 < last ? s + 1 : nsteps, nx);            // (another group's step: nothing)
 #pragma unroll
-            for (int e = 0; e < 8; ++e) mx = fmaxf(mx, x[e]);
+        for (int it = 0; it < kSumSteps; ++it) Chunk<DT>::blank(lg[it], s * kStepChunks + it * kQT + tid >= row_chunks);
+        // every thread sums against its own maximum; the pairs are merged over the wavefront here, over the
+        // wavefronts at the end
+        const float mt = thread_max<DT, kSumSteps>(lg);
+        float zt = 0.f;
+        if (mt > -INFINITY) {
+            const float mtc = mt * c;
+#pragma unroll
+            for (int it = 0; it < kSumSteps; ++it) {
+                keep_packed(lg[it]);
+                float x[kN];
+                Chunk<DT>::unpack(lg[it], x);
+#pragma unroll
+                for (int e = 0; e < kN; ++e) zt += exp_weight<DT>(x[e], mt, c, mtc);
+            }
         }
-        const float gm = row16_max(mx);
-        tmax = fmaxf(tmax, gm);
-        float acc = 0.f;
-        if (in_range) {
-            const float off = fminf(-gm * cexp, 3.0e38f);        // stays finite when the whole group is -inf
+        const float mw = wave_max(mt);
+        const double zw = wave_sum(mt > -INFINITY ? (double)(zt * __builtin_amdgcn_exp2f((mt - mw) * c)) : 0.0);
+        if (lane == 0) { s_m[s - first][wv] = mw; s_z[s - first][wv] = zw; }
 #pragma unroll
-            for (int e = 0; e < 8; ++e) acc += __builtin_amdgcn_exp2f(fmaf(x[e], cexp, off));
-        }
-        acc = row16_sum(acc);
-        if ((lane & 15) == 0) { part[s][wv * 4 + (lane >> 4)] = acc; gmax[s][wv * 4 + (lane >> 4)] = gm; }
-    });
-    tmax = wave_max(tmax);
-    if (lane == 0) wmax[wv] = tmax;
-    __syncthreads();
-    float m = wmax[0];
-#pragma unroll
-    for (int w = 1; w < kNW; ++w) m = fmaxf(m, wmax[w]);
-    // wavefront w puts the 64 group sums of steps w, w + 16, ... on the row's maximum and adds them up
-    for (int s = wv; s < nsteps; s += kNW) {
-        const double t = wave_sum((double)(part[s][lane] * __builtin_amdgcn_exp2f((gmax[s][lane] - m) * cexp)));
-        if (lane == 0) S[s] = t;
+        for (int it = 0; it < kSumSteps; ++it) lg[it] = nx[it];
     }
-    __syncthreads();
-    double Z = 0.0;
-    for (int s = 0; s < nsteps; ++s) Z += S[s];
-    if (tid == 0) { st->m = m; st->arg = 0; st->Z = Z; }
-    if (tid < kNSteps) st->S0[tid] = tid < nsteps ? S[tid] : 0.0;
+    lds_barrier();
+    if (tid < last - first) {
+        HalfStat st;
+        st.m = s_m[tid][0]; st.arg = -1; st.Z = 0.0;
+#pragma unroll
+        for (int w = 1; w < kQW; ++w) st.m = fmaxf(st.m, s_m[tid][w]);
+#pragma unroll
+        for (int w = 0; w < kQW; ++w)
+            st.Z += s_m[tid][w] > -INFINITY ? s_z[tid][w] * (double)__builtin_amdgcn_exp2f((s_m[tid][w] - st.m) * c) : 0.0;
+        entry[first + tid] = st;
+    }
 }
 
 // ---- kernel 2: the walk of every request ---------------------------------------------------------
@@ -182,9 +211,12 @@ struct WalkScratch {
     float  part[kNSteps][kWave];        // per step: fp32 sums of the 64 groups of 16 lanes (wave * 4 + lane / 16)
     double S[kNSteps];
     double wsum[kNW];
-    float  ch_l[64], ch_q[64], ch_u[64];   // per child node: logit and draft probability of its token, its uniform
+    float  ch_l[64], ch_q[64], ch_u[64];   // per draft node: logit and draft probability (at its parent) of its token, its uniform
     int    ch_x[64];                    // its token
-    unsigned long long kids;
+    unsigned long long kids;            // of the node the walk stands on: its children, maximum, arg-max, total of S[]
+    float  m;
+    int    arg;
+    double R;
     int fallback, hit, last_thread;
     int fallback_tot[kNW];              // (start-up only) per-wavefront row counts of the requests before this one
 };
@@ -192,10 +224,9 @@ struct WalkScratch {
 template <class DT>
 __global__ __launch_bounds__(kNT, 4) void accept_tree_walk_fast_kernel(
     const char *__restrict__ logits, const char *__restrict__ probs,
-    const int32_t *__restrict__ draft_tokens, const int32_t *__restrict__ parents,
     const float *__restrict__ uniforms, const int32_t *__restrict__ spec_lens,
     const float *__restrict__ temperature, const int32_t *__restrict__ cu_q,
-    const TreeNodeStat *__restrict__ stats, int V, int total_q, int max_spec_len, int64_t lstride,
+    const char *__restrict__ stats, int stat_bytes, int V, int total_q, int max_spec_len, int64_t lstride,
     int64_t pstride, int out_stride, int32_t *__restrict__ out_tokens,
     int32_t *__restrict__ out_accept_len, int32_t *__restrict__ out_path)
 {
@@ -225,13 +256,21 @@ __global__ __launch_bounds__(kNT, 4) void accept_tree_walk_fast_kernel(
     int32_t *o = out_tokens + (int64_t)i * out_stride;
     int32_t *pth = out_path + (int64_t)i * out_stride;
 
+    // lane c of the first wavefront keeps node c's parent and leaves the rest of its record in LDS
+    int my_parent = -1;
+    if (tid >= 1 && tid <= k) {
+        const TreeNodeRec rec = *reinterpret_cast<const TreeNodeRec *>(stats + (int64_t)(r0 + tid) * stat_bytes);
+        my_parent = rec.parent;
+        sm.ch_x[tid] = rec.x; sm.ch_l[tid] = rec.l; sm.ch_q[tid] = rec.q; sm.ch_u[tid] = rec.u0;
+    }
+
     // state of the node the walk stands on
     const char *lrow = logits, *prow = probs;
-    float m = 0.f, invZ = 1.f;
+    float m = 0.f, mc = 0.f, invZ = 1.f;
 
     // max(0, p - c q) at one entry from its logit and draft probability (c = 0: p itself)
     auto residual = [&](float l, float q, float c) -> float {
-        return fmaxf(0.f, fmaf(-c, q, __builtin_amdgcn_exp2f((l - m) * cexp) * invZ));
+        return fmaxf(0.f, fmaf(-c, q, __builtin_amdgcn_exp2f(fmaf(l, cexp, -mc)) * invZ));
     };
     // this thread's 8 masses of one step: before any sweep the unnormalised 2^((l - m) cexp) the node's
     // statistics were summed from, afterwards max(0, p - c q)
@@ -244,7 +283,7 @@ __global__ __launch_bounds__(kNT, 4) void accept_tree_walk_fast_kernel(
             unpack8<DT>(lw, x);
             if (!swept) {
 #pragma unroll
-                for (int e = 0; e < 8; ++e) rv[e] = __builtin_amdgcn_exp2f((x[e] - m) * cexp);
+                for (int e = 0; e < 8; ++e) rv[e] = __builtin_amdgcn_exp2f(fmaf(x[e], cexp, -mc));
             } else {
                 float q[8];
                 unpack8<DT>(qw, q);
@@ -278,28 +317,29 @@ __global__ __launch_bounds__(kNT, 4) void accept_tree_walk_fast_kernel(
         const int r = r0 + u;
         lrow = logits + (int64_t)r * lstride * 2;
         prow = probs + (int64_t)(r - i) * pstride * 2;          // read only if the node has children
-        const TreeNodeStat *st = stats + r;
         __syncthreads();                                        // everything of the previous node has been read
-        // children of u (lane c of the first wavefront looks at node c) and what their tests need
+        // the first wavefront: the children of u (lane c looks at node c), and the node's statistics on one scale
         if (tid < kWave) {
-            const bool is_child = lane > u && lane <= k && sane_parent_f(parents[r0 + lane], lane) == u;
-            const unsigned long long kmask = __builtin_amdgcn_ballot_w64(is_child);
-            if (lane == 0) { sm.kids = kmask; sm.hit = -1; sm.last_thread = -1; sm.fallback = -1; }
-            if (is_child) {
-                const int x = draft_tokens[r0 - i + lane - 1];
-                sm.ch_x[lane] = x;
-                sm.ch_l[lane] = elem16<DT>(lrow, x);
-                sm.ch_q[lane] = elem16<DT>(prow, x);
-                sm.ch_u[lane] = uniforms[2 * (int64_t)(r0 + lane - 1)];
+            HalfStat st;
+            st.m = -INFINITY; st.arg = -1; st.Z = 0.0;
+            if (lane < nsteps) st = reinterpret_cast<const HalfStat *>(stats + (int64_t)r * stat_bytes + sizeof(TreeNodeRec))[lane];
+            const unsigned long long kmask = __builtin_amdgcn_ballot_w64(lane > u && lane <= k && my_parent == u);
+            const float mx = fmaxf(wave_max(st.m), -3.0e38f);   // (stays finite when no logit is: differences stay defined)
+            const double part = st.m > -INFINITY ? st.Z * (double)__builtin_amdgcn_exp2f((st.m - mx) * cexp) : 0.0;
+            const double total = wave_sum(part);
+            const ArgMax best = wave_argmax(st.arg >= 0 ? ArgMax{st.m, st.arg} : ArgMax{-INFINITY, 0x7fffffff});
+            if (lane < kNSteps) sm.S[lane] = part;
+            if (lane == 0) {
+                sm.kids = kmask; sm.hit = -1; sm.last_thread = -1; sm.fallback = -1;
+                sm.m = mx; sm.arg = best.i == 0x7fffffff ? 0 : best.i; sm.R = total;
             }
-        } else if (tid < kWave + kNSteps) {
-            sm.S[tid - kWave] = st->S0[tid - kWave];
         }
-        m = st->m;
-        const int arg = st->arg;
-        double R = st->Z;                                       // total of S[]
-        invZ = (float)(1.0 / R);
         __syncthreads();
+        m = sm.m;
+        mc = m * cexp;
+        const int arg = sm.arg;
+        double R = sm.R;                                        // total of S[]
+        invZ = (float)(1.0 / R);
         unsigned long long kids = sm.kids;
 
         int next = -1, cand = arg;
@@ -411,21 +451,26 @@ __global__ __launch_bounds__(kNT, 4) void accept_tree_walk_fast_kernel(
 // quadratic beyond; larger batches take the row offsets from the metadata kernel.
 bool tree_fast_needs_plan(const adaspec_accept_dims &d) { return d.batch > 2048; }
 
-hipError_t launch_accept_tree_fast(const AcceptArgs &a, const int32_t *parents, int32_t *out_path)
+hipError_t launch_accept_tree_fast(const AcceptArgs &a, const int32_t *parents, int compute_units, int32_t *out_path)
 {
     const adaspec_accept_dims &d = a.dims;
     if (d.total_q == 0) return hipSuccess;
-    TreeNodeStat *stats = (TreeNodeStat *)(a.ws + a.plan.off_tree_stat);
+    char *stats = a.ws + a.plan.off_tree_stat;
+    const int stat_bytes = (int)tree_node_stat_bytes(d.vocab), nsteps = ceil_div(d.vocab / 8, kStepChunks);
+    // steps per workgroup: the fewest with which the launch has about kStatsWgsPerCu workgroups per compute unit
+    int group = 1;
+    while (group < nsteps && (int64_t)d.total_q * ceil_div(nsteps, group) > (int64_t)kStatsWgsPerCu * compute_units) group *= 2;
+    const int n_groups = ceil_div(nsteps, group);
     auto launch = [&](auto tag) {
         using DT = decltype(tag);
-        hipLaunchKernelGGL((tree_node_stats_kernel<DT>), dim3(d.total_q), dim3(kNT), 0, a.stream,
-                           (const char *)a.logits, a.spec_lens, a.temperature, d.batch, d.vocab, d.max_spec_len,
-                           d.logits_row_stride, stats);
+        hipLaunchKernelGGL((tree_node_stats_kernel<DT>), dim3(d.total_q * n_groups), dim3(kQT), 0, a.stream,
+                           (const char *)a.logits, (const char *)a.probs, a.draft_tokens, parents, a.uniforms, a.spec_lens,
+                           a.temperature, d.batch, d.vocab, d.total_draft, d.max_spec_len, n_groups, group,
+                           d.logits_row_stride, d.probs_row_stride, stats, stat_bytes);
         hipLaunchKernelGGL((accept_tree_walk_fast_kernel<DT>), dim3(d.batch), dim3(kNT), 0, a.stream,
-                           (const char *)a.logits, (const char *)a.probs, a.draft_tokens, parents, a.uniforms,
-                           a.spec_lens, a.temperature,
-                           tree_fast_needs_plan(d) ? (const int32_t *)(a.ws + a.plan.off_cu_q) : nullptr, stats, d.vocab,
-                           d.total_q, d.max_spec_len, d.logits_row_stride, d.probs_row_stride, d.out_stride,
+                           (const char *)a.logits, (const char *)a.probs, a.uniforms, a.spec_lens, a.temperature,
+                           tree_fast_needs_plan(d) ? (const int32_t *)(a.ws + a.plan.off_cu_q) : nullptr, stats, stat_bytes,
+                           d.vocab, d.total_q, d.max_spec_len, d.logits_row_stride, d.probs_row_stride, d.out_stride,
                            a.out_tokens, a.out_accept_len, out_path);
     };
     if (d.logits_dtype == ADASPEC_F16) launch(F16{});
