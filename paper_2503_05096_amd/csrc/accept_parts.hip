@@ -532,7 +532,7 @@ __global__ __launch_bounds__(kQT, sizeof(typename PT::storage) > sizeof(typename
         at1 = pair_totals(s_pair, pm[0] + pm[1], tid, lane, wv, R);
     }
     const double tau = (double)u_draw * R;
-    const int pair = pick_pair(s_pair, use_p ? pm[0] : res[0], use_p ? pm[1] : res[1], at1, tau, tid);
+    const int pair = pick_pair(s_pair, use_p ? pm[0] : res[0], use_p ? pm[1] : res[1], at1, tau, tid, lane, wv);
     ADASPEC_STAMP(1, 6);
 
     // ---- inside the pair: the step (one wavefront each), then the lane, then the element ------------------

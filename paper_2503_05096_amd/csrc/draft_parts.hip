@@ -184,7 +184,7 @@ __global__ __launch_bounds__(kQT) void draft_pick_kernel(
     double Q;
     const double at1 = pair_totals(s_pair, w0 + w1, tid, lane, wv, Q);
     const double tau = (double)u * Q;
-    const int pair = pick_pair(s_pair, w0, w1, at1, tau, tid);
+    const int pair = pick_pair(s_pair, w0, w1, at1, tau, tid, lane, wv);
     if (pair < 0) {                           // no mass (non-finite input): stay defined
         if (tid == 0) { tokens[r] = 0; confidence[r] = 0.f; }
         return;

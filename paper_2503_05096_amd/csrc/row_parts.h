@@ -264,14 +264,13 @@ __device__ __forceinline__ ArgMax reduce_argmax(ArgMax best, float *s_m, int *s_
 // ---- the (part, wavefront) pair of a row that holds a point of its cumulative mass ------------------------------------
 // Thread t of a 256-thread workgroup brings the masses of the pairs 2t and 2t + 1 (0 past the end).  The first barrier of
 // pair_totals also makes room in the scratch.
-struct PairScratch { double wave[kQW]; double before; int pick, last, chosen; };
+struct PairScratch { double wave[kQW]; double before; int pick[kQW], last[kQW]; };
 // running total after this thread's two pairs; R = total of all
 __device__ __forceinline__ double pair_totals(PairScratch &s, double both, int tid, int lane, int wv, double &R)
 {
     const double incl = wave_scan_incl(both, lane);
     __syncthreads();
     if (lane == 63) s.wave[wv] = incl;
-    if (tid == 0) { s.pick = 0x7fffffff; s.last = -1; }
     __syncthreads();
     double before = 0.0;
     R = 0.0;
@@ -283,17 +282,27 @@ __device__ __forceinline__ double pair_totals(PairScratch &s, double both, int t
     return before + incl;
 }
 // the first pair with mass whose running total exceeds tau (rounding may leave none: then the last one with mass), or -1;
-// s.before = running total in front of it
-__device__ __forceinline__ int pick_pair(PairScratch &s, double w0, double w1, double at1, double tau, int tid)
+// s.before = running total in front of it.  (Ballots and one LDS word per wavefront: LDS atomics on one word, which half
+// of the threads would hit, took 2 us of a 10 us kernel.)
+__device__ __forceinline__ int pick_pair(PairScratch &s, double w0, double w1, double at1, double tau, int tid, int lane, int wv)
 {
     const double at0 = at1 - w1;
-    int claim = 0x7fffffff, pos = -1;
-    if (w1 > 0.0) { pos = 2 * tid + 1; if (at1 > tau) claim = 2 * tid + 1; }
-    if (w0 > 0.0) { pos = max(pos, 2 * tid); if (at0 > tau) claim = 2 * tid; }
-    if (claim != 0x7fffffff) atomicMin(&s.pick, claim);
-    if (pos >= 0) atomicMax(&s.last, pos);
+    const bool hit0 = w0 > 0.0 && at0 > tau, hit1 = w1 > 0.0 && at1 > tau;
+    const unsigned long long claims = __ballot(hit0 || hit1), first_of_two = __ballot(hit0);
+    const unsigned long long any = __ballot(w0 > 0.0 || w1 > 0.0), second_of_two = __ballot(w1 > 0.0);
+    if (lane == 0) {
+        const int c = claims ? (int)__builtin_ctzll(claims) : 0, l = any ? 63 - (int)__builtin_clzll(any) : 0;
+        s.pick[wv] = claims ? 2 * (kWave * wv + c) + ((first_of_two >> c) & 1 ? 0 : 1) : -1;
+        s.last[wv] = any ? 2 * (kWave * wv + l) + ((second_of_two >> l) & 1 ? 1 : 0) : -1;
+    }
     __syncthreads();
-    const int pick = s.pick != 0x7fffffff ? s.pick : s.last;
+    int pick = -1, last = -1;
+#pragma unroll
+    for (int w = 0; w < kQW; ++w) {
+        if (pick < 0) pick = s.pick[w];
+        last = max(last, s.last[w]);
+    }
+    if (pick < 0) pick = last;
     if (pick >= 0 && (pick >> 1) == tid) s.before = (pick & 1) ? at0 : at0 - w0;
     __syncthreads();
     return pick;
