@@ -459,9 +459,11 @@ typedef struct {
                                    (same shapes as FAST, needs the workspace):
                                    every row cut into parts over three small
                                    kernels; AUTO = the split form, of any storage
-                                   types, when a workspace is given and V >= 8192;
-                                   else FAST when it fits and V >= 32768, else
-                                   VECTOR */
+                                   types, when a workspace is given and V > 32768
+                                   (fp32 logits: 49152; not for 16-bit rows of at
+                                   most 65536 when they fill half of the chip one
+                                   per compute unit); else FAST when it fits and
+                                   V > 24576, else VECTOR */
     int32_t reserved;
     void   *timing_start;       /* optional pair of hipEvent_t (both or neither, NULL = none), recorded */
     void   *timing_stop;        /* on `stream` around the call's kernels                                */

@@ -446,8 +446,8 @@ __global__ __launch_bounds__(kFT) void accept_fast_kernel(
     double we = __shfl_up(wi, 1, kWave);
     if (lane == 0) we = 0.0;
     const double incl = base + wi, excl = base + we;
-    if (incl > tau && sstar > 0.f) atomicMin(&sm.first_hit, tid);
-    if (sstar > 0.f) atomicMax(&sm.last_pos, tid);
+    note_first(&sm.first_hit, incl > tau && sstar > 0.f, tid);
+    note_last(&sm.last_pos, sstar > 0.f, tid);
     __syncthreads();
     const int owner = sm.first_hit < kFT ? sm.first_hit : sm.last_pos;
     if (tid == owner) {

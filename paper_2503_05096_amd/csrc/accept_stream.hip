@@ -355,8 +355,8 @@ __global__ __launch_bounds__(kST, 8) void accept_stream_kernel(
     double we = __shfl_up(wi, 1, kWave);
     if (lane == 0) we = 0.0;
     const double incl = base + wi, excl = base + we;
-    if (incl > tau && sstar_sum > 0.f) atomicMin(&sm.first_hit, tid);
-    if (sstar_sum > 0.f) atomicMax(&sm.last_pos, tid);
+    note_first(&sm.first_hit, incl > tau && sstar_sum > 0.f, tid);
+    note_last(&sm.last_pos, sstar_sum > 0.f, tid);
     __syncthreads();
     const int owner = sm.first_hit < kST ? sm.first_hit : sm.last_pos;
     if (tid == owner) {

@@ -597,11 +597,27 @@ static int validate_draft_dims(const adaspec_draft_dims *d)
     return ADASPEC_OK;
 }
 
-// AUTO of draft sampling (MI355X, us per call, 128 rows): the form in parts from V = 8192 on (three launches: 12.1 whatever
-// the type; the three-sweep kernel 12-13 at V = 8192, 15 at 16384), the three-sweep kernel below (V = 4096: 10.0, in parts
-// 12.1, register-resident 14.0).  Without a workspace the register-resident kernel is ahead of the three sweeps from
-// V = 32768 on (V = 24576: 17.2 against 17.4; V = 128256: 36 against 46).
-constexpr int kDraftPartsFrom = 8192, kDraftFastFrom = 32768;
+// AUTO of draft sampling, measured on MI355X (us per call; three sweeps / register-resident / in parts):
+//   V = 16384 bf16   1 row  8.7 / 10.5 / 11.1   128 rows  9.6 / 11.2 / 11.9   256 rows 10.3 / 11.9 / 14.1
+//   V = 32768 bf16   1 row 11.9 / 10.4 / 11.9   128 rows 13.7 / 11.9 / 14.5   256 rows 14.9 / 13.1 / 18.3
+//   V = 32768 fp32   1 row 10.7 /   -  / 12.0   128 rows 14.3 /   -  / 16.9   256 rows 20.1 /   -  / 22.0
+//   V = 40000 fp32                           144 rows 17.1 /   -  / 19.3   256 rows 26.5 /   -  / 26.5
+//   V = 50272 fp32                           144 rows 21.1 /   -  / 22.0   256 rows 33.2 /   -  / 31.1
+//   V = 50272 bf16   1 row 16.0 / 15.6 / 11.9   128 rows 18.4 / 17.9 / 17.4   192 rows 19.6 / 18.7 / 21.1
+//   V = 65536 bf16                           128 rows 22.2 / 17.9 / 18.6   192 rows 23.3 / 19.1 / 22.2
+//   V = 81920 bf16                           144 rows 26.6 / 29.5 / 21.9   256 rows 29.4 / 31.2 / 28.8
+//   V = 131072 bf16  1 row 32.1 / 25.8 / 12.1   192 rows 40.6 / 32.7 / 32.6   256 rows 43.5 / 35.9 / 38.8   300 rows 64 / 62 / 47
+// In parts above V = 32768 (fp32 logits, which the single-workgroup kernels need not convert: above 49152), unless 16-bit
+// rows of at most 65536 occupy half of the compute units and no more than all of them; else the register-resident kernel
+// above V = 24576 where it fits, else three sweeps.
+constexpr int kDraftFastAbove = 24576, kDraftMediumRow = 65536;
+static bool draft_wants_parts(const adaspec_draft_dims &d)
+{
+    if (d.logits_dtype == ADASPEC_F32) return d.vocab > 49152;
+    const int cus = compute_units();
+    const bool one_wave = d.vocab <= kDraftMediumRow && d.rows > cus / 2 && d.rows <= cus;
+    return d.vocab > 32768 && !one_wave;
+}
 
 // Whether dims may take the form in parts: forced (ADASPEC_PATH_TWO_PASS) for 16-bit logits up to V = 131072; AUTO also
 // for fp32 logits and larger vocabularies.
@@ -609,7 +625,7 @@ static bool draft_parts_fit(const adaspec_draft_dims &d)
 {
     if (!draft_parts_supported(d)) return false;
     const bool small16 = d.logits_dtype != ADASPEC_F32 && d.vocab <= 131072;
-    return small16 || (d.path == ADASPEC_PATH_AUTO && d.vocab >= kDraftPartsFrom);
+    return small16 || (d.path == ADASPEC_PATH_AUTO && draft_wants_parts(d));
 }
 
 size_t adaspec_draft_sample_workspace_bytes(const adaspec_draft_dims *d)
@@ -643,11 +659,11 @@ int adaspec_draft_sample(const void *draft_logits, const float *temperature, con
         if (workspace_bytes < draft_parts_workspace_bytes(*d)) return ADASPEC_ERR_WORKSPACE;
         split = true;
     } else if (d->path == ADASPEC_PATH_AUTO) {
-        split = split_ok && d->vocab >= kDraftPartsFrom && workspace && !(reinterpret_cast<uintptr_t>(workspace) & 255u) &&
-                workspace_bytes >= draft_parts_workspace_bytes(*d);
+        split = split_ok && draft_wants_parts(*d) && workspace &&
+                !(reinterpret_cast<uintptr_t>(workspace) & 255u) && workspace_bytes >= draft_parts_workspace_bytes(*d);
     }
     const bool fast = !split && fast_ok &&
-                      (d->path == ADASPEC_PATH_FAST || (d->path == ADASPEC_PATH_AUTO && d->vocab >= kDraftFastFrom));
+                      (d->path == ADASPEC_PATH_FAST || (d->path == ADASPEC_PATH_AUTO && d->vocab > kDraftFastAbove));
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (!record_event(d->timing_start, d->timing_stop, true, st)) return ADASPEC_ERR_HIP;
     hipError_t e;

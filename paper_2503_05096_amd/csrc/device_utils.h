@@ -143,6 +143,19 @@ __device__ __forceinline__ ArgMax wave_argmax(ArgMax a)
     return last_lane(a);
 }
 
+// Lowest / highest thread number with a flag, over the workgroup (*word preset by the caller, read behind a barrier): one
+// LDS atomic per wavefront.  An atomic by every flagged thread is a loop over the lanes (about 1 us per wavefront).
+__device__ __forceinline__ void note_first(int *word, bool flag, int tid)
+{
+    const unsigned long long b = __ballot(flag);
+    if (b && (tid & 63) == 0) atomicMin(word, (tid & ~63) + (int)__builtin_ctzll(b));
+}
+__device__ __forceinline__ void note_last(int *word, bool flag, int tid)
+{
+    const unsigned long long b = __ballot(flag);
+    if (b && (tid & 63) == 0) atomicMax(word, (tid & ~63) + 63 - (int)__builtin_clzll(b));
+}
+
 // Workgroup barrier for data exchanged through LDS only.  __syncthreads() also drains the
 // vector-memory counter (its fences cover global memory), which would stall on every global load
 // that was deliberately left in flight across the barrier; this one waits for LDS traffic alone.

@@ -267,8 +267,8 @@ __global__ __launch_bounds__(kGT) void draft_fast_kernel(
     double we = __shfl_up(wi, 1, kWave);
     if (lane == 0) we = 0.0;
     const double incl = base + wi, excl = base + we;
-    if (incl > tau && mine > 0.f) atomicMin(&sm.first_hit, tid);
-    if (mine > 0.f) atomicMax(&sm.last_pos, tid);
+    note_first(&sm.first_hit, incl > tau && mine > 0.f, tid);
+    note_last(&sm.last_pos, mine > 0.f, tid);
     __syncthreads();
     const int owner = sm.first_hit < kGT ? sm.first_hit : sm.last_pos;
     if (tid == owner) {

@@ -9,6 +9,7 @@ namespace adaspec {
 constexpr int kNT = 1024;
 constexpr int kNW = kNT / kWave;
 constexpr int kNSteps = 64;             // V <= kNT * 8 * kNSteps = 524288
+static_assert(kNSteps == kWave, "one lane per step");
 
 
 template <class DT>
@@ -36,9 +37,7 @@ __device__ __forceinline__ double finish_sweep(const float (&part)[kNSteps][kWav
         if (lane == 0) S[s] = t;
     }
     __syncthreads();
-    double R = 0.0;
-    for (int s = 0; s < nsteps; ++s) R += S[s];
-    return R;
+    return wave_sum(lane < nsteps ? S[lane] : 0.0);       // (kNSteps lanes)
 }
 
 // Walks the steps of a row with the loads of the next kDepth steps in flight: f(step, in_range, logits

@@ -379,15 +379,12 @@ __global__ __launch_bounds__(kNT, 4) void accept_tree_walk_fast_kernel(
             if (next < 0) {
                 // ---- the draw from (S, R): of the last sweep, or of the node's statistics ----------------
                 const double tau = (double)uniforms[2 * (int64_t)r + 1] * R;
-                int sstar = -1, last_pos_step = 0;
-                double before = 0.0, run = 0.0, before_last = 0.0;
-                for (int s = 0; s < nsteps; ++s) {
-                    const double Ss = sm.S[s];
-                    if (Ss > 0.0) { last_pos_step = s; before_last = run; }
-                    if (sstar < 0 && run + Ss > tau) { sstar = s; before = run; }
-                    run += Ss;
-                }
-                if (sstar < 0) { sstar = last_pos_step; before = before_last; }   // rounding left no crossing
+                // lane s of every wavefront looks at step s: the first whose running total exceeds tau, else
+                // (rounding left no crossing) the last with mass
+                const double Ss = lane < nsteps ? sm.S[lane] : 0.0, upto = wave_scan_incl(Ss, lane);
+                const unsigned long long cross = __ballot(Ss > 0.0 && upto > tau), filled = __ballot(Ss > 0.0);
+                const int sstar = cross ? (int)__builtin_ctzll(cross) : (filled ? 63 - (int)__builtin_clzll(filled) : 0);
+                const double before = __shfl(upto - Ss, sstar, kWave);
                 float rv[8];
                 float mine;
                 {
@@ -404,7 +401,7 @@ __global__ __launch_bounds__(kNT, 4) void accept_tree_walk_fast_kernel(
                 double we = __shfl_up(wi, 1, kWave);
                 if (lane == 0) we = 0.0;
                 if (lane == 63) sm.wsum[wv] = wi;
-                if (mine > 0.f) atomicMax(&sm.last_thread, tid);
+                note_last(&sm.last_thread, mine > 0.f, tid);
                 __syncthreads();
                 double wp = 0.0;
 #pragma unroll
