@@ -16,6 +16,7 @@ namespace adaspec {
 // context lengths live there.
 struct AttnPlan {
     int   split_tokens;     // S: maximum tokens per split
+    int   long_units;       // > 0: the plan kernel doubles S when the batch has this many units of 2 S tokens
     int   block_tokens;     // split lengths are rounded up to a multiple of this
     int   max_items;        // host-side bound on the number of work items
     int   max_rows;         // (max_spec_len + 1) * G

@@ -114,6 +114,13 @@ AttnKind attn_kind(const adaspec_attn_dims &d)
     return AttnKind::kVector;
 }
 
+// Splits of 4096 tokens instead of 2048 for the row-split kernel (every wavefront of it writes the partial state of its
+// rows over the whole split) when the batch has this many units of the longer kind.  MI355X, 64/8 heads of 128, bf16, 2048
+// / 4096: 128 requests of 512-4096 tokens (1024 units) 246 / 222 us, 64 of 2048-8192 (850) 258 / 248, 100 of 1000-3000
+// with 36 rows (800) 173 / 159; too few to even out on 256 compute units: 64 of up to 4096 (512) 132 / 146, 32 of up to
+// 8192 (380) 144 / 148.  The token-split kernels, whose wavefronts share a split, lose: 128 of 128-4096, 32/8 heads, 121 / 130.
+constexpr int kLongSplitUnits = 768;
+
 AttnPlan make_attn_plan(const adaspec_attn_dims &d, AttnKind kind)
 {
     AttnPlan p;
@@ -126,12 +133,13 @@ AttnPlan make_attn_plan(const adaspec_attn_dims &d, AttnKind kind)
     const int64_t pairs = (int64_t)d.batch * d.n_kv_heads;
     if (scheduled) {
         p.block_tokens = kind == AttnKind::kMfma64 ? kAttnD64Block : (kind == AttnKind::kMfmaF32 ? 16 : 32);
-        p.split_tokens = pairs >= 512 ? 2048 : (pairs >= 256 ? 2048 : (pairs >= 128 ? 1024 : (pairs >= 32 ? 512 : 256)));
+        p.split_tokens = pairs >= 256 ? 2048 : (pairs >= 128 ? 1024 : (pairs >= 32 ? 512 : 256));
     } else {
         p.block_tokens = 64;
         p.split_tokens = 256;
     }
     const int64_t max_ctx = (int64_t)d.max_pages_per_req * d.page_size;
+    p.max_rows = (d.max_spec_len + 1) * G;
     p.direct = false;
     if (scheduled && d.batch <= kDirectMaxBatch) {
         // Small batches: the shortest split (two blocks per wavefront or more: with one, the workspace and the work of the
@@ -157,10 +165,13 @@ AttnPlan make_attn_plan(const adaspec_attn_dims &d, AttnKind kind)
             p.split_tokens = 2 * kDirectShortCtx;
         }
     }
+    p.long_units = 0;
+    if (kind == AttnKind::kMfma128 && !p.direct && p.split_tokens == 2048 && attn_row_tiles(p.max_rows) > 2 &&
+        pairs * attn_row_groups(p.max_rows) * ((max_ctx + 4095) / 4096) >= kLongSplitUnits)
+        p.long_units = kLongSplitUnits;       // the plan kernel counts them
     const int64_t per_req = (max_ctx + p.split_tokens - 1) / p.split_tokens;
     p.per_req = (int)per_req;
     p.max_items = (int)((int64_t)d.batch * per_req);
-    p.max_rows = (d.max_spec_len + 1) * G;
     size_t off = 0;
     p.off_header = off;     off = align_up(off + 16 * sizeof(int32_t), 256);
     p.off_cu_q = off;       off = align_up(off + (size_t)(d.batch + 1) * 4, 256);

@@ -19,6 +19,9 @@ __host__ __device__ inline int log2_exact(int v)          // v is a power of two
     return l;
 }
 
+// a context length no split count of which overflows
+__device__ __forceinline__ int plan_ctx(int ctx_len) { return min(max(ctx_len, 1), 1 << 30); }
+
 // One workgroup.  cu_q = exclusive scan of n_i = spec_lens[i] + 1; split_base = exclusive scan of
 // the per-request split counts ceil(L_i / S); a work item is one (request, split).  Values are
 // clamped to the host-declared bounds so that inconsistent device data cannot make the library
@@ -35,7 +38,7 @@ __host__ __device__ inline int log2_exact(int v)          // v is a power of two
 // requests, more than kSchedItems items) read their own global stores back, behind a full barrier.
 __global__ __launch_bounds__(kPlanThreads) void attn_plan_kernel(
     const int32_t *__restrict__ ctx_lens, const int32_t *__restrict__ spec_lens, int B, int total_q,
-    int max_spec_len, int split_log2, int block_log2, int max_items, int G, int32_t *__restrict__ header,
+    int max_spec_len, int split_log2, int long_units, int block_log2, int max_items, int G, int32_t *__restrict__ header,
     int32_t *__restrict__ cu_q, int32_t *__restrict__ split_base, int32_t *__restrict__ item_req,
     int32_t *__restrict__ item_order, int32_t *__restrict__ unit_meta, int32_t *__restrict__ row_rec,
     int W, int Hkv, int n_row_groups, int rows_per_group, int32_t *__restrict__ sched, int cus,
@@ -63,18 +66,31 @@ __global__ __launch_bounds__(kPlanThreads) void attn_plan_kernel(
     __shared__ uint8_t item_blocks[kSchedItems], item_groups[kSchedItems];   // per SORTED item: token blocks, row groups
     __shared__ int bins[kPlanThreads], wg_work[kPlanThreads], wave_tot[kPlanThreads / kWave];
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int split_tokens = 1 << split_log2, block_tokens = 1 << block_log2;
     const bool fast = W > 0;
     const bool items_on_chip = max_items <= kSchedItems && B <= 65535;  // host-side bounds: uniform
     const bool reqs_on_chip = B <= kPlanThreads;
+    const int L_first = tid < B ? plan_ctx(ctx_lens[tid]) : 0;
     if (tid == 0) { carry[0] = 0; carry[1] = 0; }
+    if (long_units > 0) {                      // splits twice as long, if the batch has enough of them
+        int longer = (L_first + (2 << split_log2) - 1) >> (split_log2 + 1);
+        for (int i = tid + kPlanThreads; i < B; i += kPlanThreads)
+            longer += (plan_ctx(ctx_lens[i]) + (2 << split_log2) - 1) >> (split_log2 + 1);
+        longer = wave_sum(longer);
+        if (lane == 0) wave_tot[wv] = longer;
+        lds_barrier();
+        int all = 0;
+#pragma unroll
+        for (int w = 0; w < kPlanThreads / kWave; ++w) all += wave_tot[w];
+        if ((int64_t)all * Hkv * n_row_groups >= long_units) ++split_log2;
+    }
+    const int split_tokens = 1 << split_log2, block_tokens = 1 << block_log2;
     lds_barrier();
     for (int base = 0; base < B; base += kPlanThreads) {
         const int i = base + tid;
         int n = 0, ns = 0, L = 1;
         if (i < B) {
             n = min(max(spec_lens[i], 0), max_spec_len) + 1;
-            L = max(ctx_lens[i], 1);
+            L = base == 0 ? L_first : plan_ctx(ctx_lens[i]);
             ns = (L + split_tokens - 1) >> split_log2;
         }
         const int inc_n = wave_scan_incl_dpp(n), inc_s = wave_scan_incl_dpp(ns);
@@ -125,7 +141,7 @@ __global__ __launch_bounds__(kPlanThreads) void attn_plan_kernel(
         it.i = items_on_chip ? (int)item_req_l[item] : item_req[item];
         if (it.i < kPlanThreads) it.rq = req[it.i];
         else
-            it.rq = make_int4(max(ctx_lens[it.i], 1), min(max(spec_lens[it.i], 0), max_spec_len) + 1, cu_q[it.i],
+            it.rq = make_int4(plan_ctx(ctx_lens[it.i]), min(max(spec_lens[it.i], 0), max_spec_len) + 1, cu_q[it.i],
                               split_base[it.i]);
         const int L = it.rq.x, ns = (L + split_tokens - 1) >> split_log2;
         it.s = item - it.rq.w;
@@ -246,7 +262,7 @@ hipError_t launch_attn_plan(const AttnArgs &a)
     const int mask_wgs = fused_masks ? ceil_div(a.dims.batch, kPlanThreads / kWave) : 0;
     hipLaunchKernelGGL(attn_plan_kernel, dim3(1 + mask_wgs), dim3(kPlanThreads), 0, a.stream, a.ctx_lens,
                        a.spec_lens, a.dims.batch, a.dims.total_q, a.dims.max_spec_len,
-                       log2_exact(p.split_tokens), log2_exact(p.block_tokens), p.max_items,
+                       log2_exact(p.split_tokens), p.long_units, log2_exact(p.block_tokens), p.max_items,
                        a.dims.n_q_heads / a.dims.n_kv_heads, (int32_t *)(a.ws + p.off_header),
                        (int32_t *)(a.ws + p.off_cu_q), (int32_t *)(a.ws + p.off_split_base),
                        (int32_t *)(a.ws + p.off_item_req), (int32_t *)(a.ws + p.off_item_order),
