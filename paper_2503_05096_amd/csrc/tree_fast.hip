@@ -207,6 +207,9 @@ __global__ __launch_bounds__(kQT, 6) void tree_node_stats_kernel(
 // So the walk keeps two numbers per node, (c, G), and every sweep costs the same few operations per
 // element whatever the stage.  A stage whose residual has no mass leaves (c, G) as they are, and so does
 // every later stage at that node.
+// A sweep is bound by these operations (one workgroup has a row of 128 K elements to itself, 9 us and more), so p stays
+// unnormalised in it: c and G carry the factor Z, p_v is w_v = 2^((l_v - m) / T * log2(e) - 1).  The -1 keeps w_v, and with
+// it w_v - c q_v, below 1 whatever the rounding of the exponent, so that the cut at 0 is the clamp bit of the multiply-add.
 struct WalkScratch {
     float  part[kNSteps][kWave];        // per step: fp32 sums of the 64 groups of 16 lanes (wave * 4 + lane / 16)
     double S[kNSteps];
@@ -266,14 +269,13 @@ __global__ __launch_bounds__(kNT, 4) void accept_tree_walk_fast_kernel(
 
     // state of the node the walk stands on
     const char *lrow = logits, *prow = probs;
-    float m = 0.f, mc = 0.f, invZ = 1.f;
+    float m = 0.f, mc = 0.f;
 
-    // max(0, p - c q) at one entry from its logit and draft probability (c = 0: p itself)
+    // max(0, w - c q) at one entry from its logit and draft probability (c = 0: w itself)
     auto residual = [&](float l, float q, float c) -> float {
-        return fmaxf(0.f, fmaf(-c, q, __builtin_amdgcn_exp2f(fmaf(l, cexp, -mc)) * invZ));
+        return __builtin_amdgcn_fmed3f(fmaf(-c, q, __builtin_amdgcn_exp2f(fmaf(l, cexp, -mc))), 0.f, 1.f);
     };
-    // this thread's 8 masses of one step: before any sweep the unnormalised 2^((l - m) cexp) the node's
-    // statistics were summed from, afterwards max(0, p - c q)
+    // this thread's 8 masses of one step: before any sweep w (S[] and the node's statistics halved), afterwards max(0, w - c q)
     auto mass8 = [&](bool in_range, const uint4 &lw, const uint4 &qw, bool swept, float c, float (&rv)[8]) -> float {
         float acc = 0.f;
 #pragma unroll
@@ -325,7 +327,7 @@ __global__ __launch_bounds__(kNT, 4) void accept_tree_walk_fast_kernel(
             if (lane < nsteps) st = reinterpret_cast<const HalfStat *>(stats + (int64_t)r * stat_bytes + sizeof(TreeNodeRec))[lane];
             const unsigned long long kmask = __builtin_amdgcn_ballot_w64(lane > u && lane <= k && my_parent == u);
             const float mx = fmaxf(wave_max(st.m), -3.0e38f);   // (stays finite when no logit is: differences stay defined)
-            const double part = st.m > -INFINITY ? st.Z * (double)__builtin_amdgcn_exp2f((st.m - mx) * cexp) : 0.0;
+            const double part = st.m > -INFINITY ? st.Z * (double)__builtin_amdgcn_exp2f(fmaf(st.m - mx, cexp, -1.f)) : 0.0;
             const double total = wave_sum(part);
             const ArgMax best = wave_argmax(st.arg >= 0 ? ArgMax{st.m, st.arg} : ArgMax{-INFINITY, 0x7fffffff});
             if (lane < kNSteps) sm.S[lane] = part;
@@ -336,10 +338,9 @@ __global__ __launch_bounds__(kNT, 4) void accept_tree_walk_fast_kernel(
         }
         __syncthreads();
         m = sm.m;
-        mc = m * cexp;
+        mc = fmaf(m, cexp, 1.f);
         const int arg = sm.arg;
         double R = sm.R;                                        // total of S[]
-        invZ = (float)(1.0 / R);
         unsigned long long kids = sm.kids;
 
         int next = -1, cand = arg;
@@ -351,8 +352,8 @@ __global__ __launch_bounds__(kNT, 4) void accept_tree_walk_fast_kernel(
                 if (sm.ch_x[c] == arg) next = c;
             }
         } else {
-            double cd = 0.0, Gd = 1.0;                          // (c, G) of the current distribution
-            float cf = 0.f, invG = 1.f;
+            double cd = 0.0, Gd = R;                            // (c, G) of the current distribution
+            float cf = 0.f, invG = (float)(1.0 / R);
             bool swept = false, frozen = false;
             while (kids != 0ull) {
                 const int c = __builtin_ctzll(kids);
