@@ -114,13 +114,6 @@ AttnKind attn_kind(const adaspec_attn_dims &d)
     return AttnKind::kVector;
 }
 
-// Splits of 4096 tokens instead of 2048 for the row-split kernel (every wavefront of it writes the partial state of its
-// rows over the whole split) when the batch has this many units of the longer kind.  MI355X, 64/8 heads of 128, bf16, 2048
-// / 4096: 128 requests of 512-4096 tokens (1024 units) 246 / 222 us, 64 of 2048-8192 (850) 258 / 248, 100 of 1000-3000
-// with 36 rows (800) 173 / 159; too few to even out on 256 compute units: 64 of up to 4096 (512) 132 / 146, 32 of up to
-// 8192 (380) 144 / 148.  The token-split kernels, whose wavefronts share a split, lose: 128 of 128-4096, 32/8 heads, 121 / 130.
-constexpr int kLongSplitUnits = 768;
-
 AttnPlan make_attn_plan(const adaspec_attn_dims &d, AttnKind kind)
 {
     AttnPlan p;
@@ -165,10 +158,9 @@ AttnPlan make_attn_plan(const adaspec_attn_dims &d, AttnKind kind)
             p.split_tokens = 2 * kDirectShortCtx;
         }
     }
-    p.long_units = 0;
-    if (kind == AttnKind::kMfma128 && !p.direct && p.split_tokens == 2048 && attn_row_tiles(p.max_rows) > 2 &&
-        pairs * attn_row_groups(p.max_rows) * ((max_ctx + 4095) / 4096) >= kLongSplitUnits)
-        p.long_units = kLongSplitUnits;       // the plan kernel counts them
+    // the row-split kernel may take splits of 4096 tokens: the plan kernel decides from the lengths (attn_plan_kernel)
+    p.may_double = kind == AttnKind::kMfma128 && !p.direct && p.split_tokens == 2048 && max_ctx > 2048 && attn_row_tiles(p.max_rows) > 2 &&
+                   d.batch <= kAttnPlanThreads;
     const int64_t per_req = (max_ctx + p.split_tokens - 1) / p.split_tokens;
     p.per_req = (int)per_req;
     p.max_items = (int)((int64_t)d.batch * per_req);

@@ -22,10 +22,10 @@
 // their 8 elements of that one step again, a scan over the threads finds the one where the
 // prefix crosses, and it picks the element.  A test is arithmetic on values already on chip.
 //
-// Bound: HBM for the statistics; vector arithmetic of one compute unit per sweep in the walk (about 11 us at
+// Bound: HBM for the statistics; vector arithmetic of one compute unit per sweep in the walk (about 9.6 us at
 // V = 128256), whose longest chain of sweeps sets its time.  MI355X, 64 requests, 288 nodes, trees of width 3:
-// statistics 16.0 us (one 1024-thread workgroup per node: 23.7), walk 42.9 us (with three dependent loads more at every
-// node and the test values fetched there: 47.2).
+// statistics 16.0 us (one 1024-thread workgroup per node: 23.7), walk 47.2 us with three dependent loads more at every
+// node and the test values fetched there, 42.9 without, 39.5 with searches by ballots, 35.4 with unnormalised sweeps.
 #include "adaspec_internal.h"
 #include "device_utils.h"
 #include "row_parts.h"

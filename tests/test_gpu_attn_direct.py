@@ -68,15 +68,16 @@ def test_attention_direct_with_a_wide_block_table(oracle_mod, pkg):  # noqa: F81
         assert compare_attention(out, ref, None, "bf16")["max_abs_vs_f64"] <= 2e-5
 
 
-@pytest.mark.parametrize("B,hq,hkv,k", [(92, 64, 8, 4), (94, 64, 8, 4), (94, 64, 8, 8), (1100, 16, 1, 2), (262, 28, 4, 7)])
-def test_attention_long_splits_around_the_rule(B, hq, hkv, k, oracle_mod, pkg):  # noqa: F811
-    """Row-split kernel: with enough units the plan doubles the splits of 2048 tokens. Contexts at the edges of both
-    splits among short ones; counts of units below and above the line, more requests than threads of the plan kernel."""
+@pytest.mark.parametrize("B,lo,hi,hq,hkv,k", [(62, 2500, 2600, 64, 8, 4), (70, 2500, 2600, 64, 8, 4), (40, 3000, 3600, 64, 8, 8),
+                                              (76, 1, 8193, 64, 8, 4), (1100, 1, 50, 16, 1, 2), (140, 1, 4600, 28, 4, 7)])
+def test_attention_long_splits_around_the_rule(B, lo, hi, hq, hkv, k, oracle_mod, pkg):  # noqa: F811
+    """Row-split kernel: with enough work per workgroup the plan doubles the splits of 2048 tokens. Batches below and above
+    the line, one and two row groups, contexts at the edges of both splits, more requests than threads of the plan kernel."""
     rng = np.random.default_rng(B + k)
     spec = rng.integers(0, k + 1, B)
     spec[0] = k
-    ctx = np.maximum(rng.integers(1, 50, B), spec + 1)
-    ctx[np.arange(7) * (B // 8) + 1] = [2047, 2048, 2049, 4096, 4097, 6100, 8193]
+    ctx = np.maximum(rng.integers(lo, hi + 1, B), spec + 1)
+    ctx[np.arange(6) * (B // 8) + 1] = [2047, 2048, 2049, min(hi, 4096), min(hi, 4097), max(hi, 2050)]
     st = W.make_custom_step(B + k, ctx_lens=ctx, spec_lens=spec, n_q_heads=hq, n_kv_heads=hkv, head_dim=128, dtype="bf16",
                             acceptance=False, name=f"long-{B}-{k}")
     check_attention(st, oracle_mod, pkg)
