@@ -75,7 +75,7 @@ __global__ __launch_bounds__(kPlanThreads) void attn_plan_kernel(
     // work of a workgroup.  MI355X, 64/8 heads of 128, bf16, splits of 2048 / 4096: 64 requests of 2048-8192 tokens (share
     // 5100 tokens) 258 / 248 us, 128 of 512-4096 (4600) 245 / 225, 100 of 1000-3000 with 36 rows (3100) 173 / 163; the
     // other side: 64 of up to 4096 (2000) 132 / 146, 32 of up to 8192 (2000) 144 / 148, 128 log-normal ones of up to 4096
-    // with 36 rows (2560) 136 / 163.  The token-split kernels, whose wavefronts share a split, lose on both sides.
+    // with 36 rows (2560) main kernel 134 / 161.  The token-split kernels, whose wavefronts share a split, lose on both sides.
     if (tid == 0) { carry[0] = 0; carry[1] = 0; }
     int split_tokens = 1 << split_log2;
     const int block_tokens = 1 << block_log2;
