@@ -16,7 +16,6 @@ namespace adaspec {
 // context lengths live there.
 struct AttnPlan {
     int   split_tokens;     // S: maximum tokens per split
-    bool  may_double;       // the plan kernel may take splits of 2 S
     int   block_tokens;     // split lengths are rounded up to a multiple of this
     int   max_items;        // host-side bound on the number of work items
     int   max_rows;         // (max_spec_len + 1) * G
@@ -94,7 +93,6 @@ inline DirectArgs direct_args(const AttnArgs &a)
 }
 
 // Upper bound on W for which the workspace holds a schedule table.
-constexpr int kAttnPlanThreads = 1024;   // of the one workgroup that plans an attention call
 constexpr int kMaxSchedW = 1024;
 constexpr int64_t kMaxAttnItems = (int64_t)1 << 24;   // (request, split) work items of one attention call
 

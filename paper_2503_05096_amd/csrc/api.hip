@@ -158,9 +158,6 @@ AttnPlan make_attn_plan(const adaspec_attn_dims &d, AttnKind kind)
             p.split_tokens = 2 * kDirectShortCtx;
         }
     }
-    // the row-split kernel may take splits of 4096 tokens: the plan kernel decides from the lengths (attn_plan_kernel)
-    p.may_double = kind == AttnKind::kMfma128 && !p.direct && p.split_tokens == 2048 && max_ctx > 2048 && attn_row_tiles(p.max_rows) > 2 &&
-                   d.batch <= kAttnPlanThreads;
     const int64_t per_req = (max_ctx + p.split_tokens - 1) / p.split_tokens;
     p.per_req = (int)per_req;
     p.max_items = (int)((int64_t)d.batch * per_req);

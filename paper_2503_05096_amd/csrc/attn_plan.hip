@@ -6,7 +6,7 @@
 
 namespace adaspec {
 
-constexpr int kPlanThreads = kAttnPlanThreads;
+constexpr int kPlanThreads = 1024;
 constexpr int kSchedItems = 8192;        // work items whose request and length the kernel keeps on chip
 constexpr int kUnitFixedBlocks = 2;      // fixed cost of a unit (Q load, merge, output), in token blocks
 constexpr int kBalancedRounds = 1;       // last rounds of the schedule that are assigned by accumulated work
@@ -38,7 +38,7 @@ __device__ __forceinline__ int plan_ctx(int ctx_len) { return min(max(ctx_len, 1
 // requests, more than kSchedItems items) read their own global stores back, behind a full barrier.
 __global__ __launch_bounds__(kPlanThreads) void attn_plan_kernel(
     const int32_t *__restrict__ ctx_lens, const int32_t *__restrict__ spec_lens, int B, int total_q,
-    int max_spec_len, int split_log2, int may_double, int block_log2, int max_items, int G, int32_t *__restrict__ header,
+    int max_spec_len, int split_log2, int block_log2, int max_items, int G, int32_t *__restrict__ header,
     int32_t *__restrict__ cu_q, int32_t *__restrict__ split_base, int32_t *__restrict__ item_req,
     int32_t *__restrict__ item_order, int32_t *__restrict__ unit_meta, int32_t *__restrict__ row_rec,
     int W, int Hkv, int n_row_groups, int rows_per_group, int32_t *__restrict__ sched, int cus,
@@ -58,27 +58,19 @@ __global__ __launch_bounds__(kPlanThreads) void attn_plan_kernel(
         tree_masks_of_request(parents, r0, n, lane, anc);
         return;
     }
-    __shared__ int tot_n[kPlanThreads / kWave], tot_s[2][kPlanThreads / kWave];   // (tot_s: S and 2 S)
+    __shared__ int tot_n[kPlanThreads / kWave], tot_s[kPlanThreads / kWave];
     __shared__ int carry[2];
     __shared__ int hist[64];
     __shared__ int4 req[kPlanThreads];         // (L, n, cu_q, split_base) of the first kPlanThreads requests
     __shared__ uint16_t item_req_l[kSchedItems];                        // request of each item
     __shared__ uint8_t item_blocks[kSchedItems], item_groups[kSchedItems];   // per SORTED item: token blocks, row groups
-    __shared__ float2 tot_ctx[kPlanThreads / kWave];
     __shared__ int bins[kPlanThreads], wg_work[kPlanThreads], wave_tot[kPlanThreads / kWave];
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int split_tokens = 1 << split_log2, block_tokens = 1 << block_log2;
     const bool fast = W > 0;
     const bool items_on_chip = max_items <= kSchedItems && B <= 65535;  // host-side bounds: uniform
     const bool reqs_on_chip = B <= kPlanThreads;
-    // Row-split kernel, many long requests: splits twice as long.  Every wavefront of it leaves the state of its rows per
-    // split, to be merged again, so fewer splits are cheaper as long as one of them is no more than an even share of the
-    // work of a workgroup.  MI355X, 64/8 heads of 128, bf16, splits of 2048 / 4096: 64 requests of 2048-8192 tokens (share
-    // 5100 tokens) 258 / 248 us, 128 of 512-4096 (4600) 245 / 225, 100 of 1000-3000 with 36 rows (3100) 173 / 163; the
-    // other side: 64 of up to 4096 (2000) 132 / 146, 32 of up to 8192 (2000) 144 / 148, 128 log-normal ones of up to 4096
-    // with 36 rows (2560) main kernel 134 / 161.  The token-split kernels, whose wavefronts share a split, lose on both sides.
     if (tid == 0) { carry[0] = 0; carry[1] = 0; }
-    int split_tokens = 1 << split_log2;
-    const int block_tokens = 1 << block_log2;
     lds_barrier();
     for (int base = 0; base < B; base += kPlanThreads) {
         const int i = base + tid;
@@ -88,37 +80,14 @@ __global__ __launch_bounds__(kPlanThreads) void attn_plan_kernel(
             L = plan_ctx(ctx_lens[i]);
             ns = (L + split_tokens - 1) >> split_log2;
         }
-        const int inc_n = wave_scan_incl_dpp(n);
-        int inc_s = wave_scan_incl_dpp(ns), ns_long = 0, inc_long = 0;
-        if (lane == 63) { tot_n[wv] = inc_n; tot_s[0][wv] = inc_s; }
-        if (may_double) {                      // (host: one pass, B <= kPlanThreads)
-            ns_long = i < B ? (L + 2 * split_tokens - 1) >> (split_log2 + 1) : 0;
-            inc_long = wave_scan_incl_dpp(ns_long);
-            const float tokens = wave_sum(i < B ? (float)L : 0.f), longest = wave_max((float)L);
-            if (lane == 63) { tot_s[1][wv] = inc_long; tot_ctx[wv] = make_float2(tokens, longest); }
-        }
+        const int inc_n = wave_scan_incl_dpp(n), inc_s = wave_scan_incl_dpp(ns);
+        if (lane == 63) { tot_n[wv] = inc_n; tot_s[wv] = inc_s; }
         lds_barrier();
-        int longer = 0;
-        if (may_double) {
-            float tokens = 0.f, longest = 0.f;
-#pragma unroll
-            for (int w = 0; w < kPlanThreads / kWave; ++w) {
-                tokens += tot_ctx[w].x;
-                longest = fmaxf(longest, tot_ctx[w].y);
-            }
-            if (tokens * (float)(Hkv * n_row_groups) >= (float)W * fminf(longest, (float)(2 * split_tokens))) {
-                ++split_log2;
-                split_tokens *= 2;
-                ns = ns_long;
-                inc_s = inc_long;
-                longer = 1;
-            }
-        }
         int pre_n = carry[0], pre_s = carry[1];
 #pragma unroll
         for (int w = 0; w < kPlanThreads / kWave; ++w) {   // fixed trip count: the reads go out together
             pre_n += w < wv ? tot_n[w] : 0;
-            pre_s += w < wv ? tot_s[longer][w] : 0;
+            pre_s += w < wv ? tot_s[w] : 0;
         }
         const int my_q = pre_n + inc_n - n, my_s = pre_s + inc_s - ns;
         if (i < B) {
@@ -280,7 +249,7 @@ hipError_t launch_attn_plan(const AttnArgs &a)
     const int mask_wgs = fused_masks ? ceil_div(a.dims.batch, kPlanThreads / kWave) : 0;
     hipLaunchKernelGGL(attn_plan_kernel, dim3(1 + mask_wgs), dim3(kPlanThreads), 0, a.stream, a.ctx_lens,
                        a.spec_lens, a.dims.batch, a.dims.total_q, a.dims.max_spec_len,
-                       log2_exact(p.split_tokens), p.may_double ? 1 : 0, log2_exact(p.block_tokens), p.max_items,
+                       log2_exact(p.split_tokens), log2_exact(p.block_tokens), p.max_items,
                        a.dims.n_q_heads / a.dims.n_kv_heads, (int32_t *)(a.ws + p.off_header),
                        (int32_t *)(a.ws + p.off_cu_q), (int32_t *)(a.ws + p.off_split_base),
                        (int32_t *)(a.ws + p.off_item_req), (int32_t *)(a.ws + p.off_item_order),

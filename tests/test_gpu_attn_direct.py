@@ -81,3 +81,24 @@ def test_attention_long_splits_around_the_rule(B, lo, hi, hq, hkv, k, oracle_mod
     st = W.make_custom_step(B + k, ctx_lens=ctx, spec_lens=spec, n_q_heads=hq, n_kv_heads=hkv, head_dim=128, dtype="bf16",
                             acceptance=False, name=f"long-{B}-{k}")
     check_attention(st, oracle_mod, pkg)
+
+
+@pytest.mark.parametrize("hq,k", [(64, 4), (64, 8), (32, 4)])
+def test_attention_of_a_request_does_not_depend_on_the_lengths_of_the_others(hq, k, pkg):  # noqa: F811
+    """How a request is cut into splits follows from its own length and the dims of the call, so the same request among
+    long and among short ones gives the same bits (all requests read one sequence's pages)."""
+    import torch
+    B, L, hkv, d = 64, 8192, 8, 128
+    gen = torch.Generator(device="cuda").manual_seed(k)
+    kv = [torch.randn((L // 16, hkv, 16, d), generator=gen, device="cuda").bfloat16() for _ in range(2)]
+    q = torch.randn((B * (k + 1), hq, d), generator=gen, device="cuda").bfloat16()
+    table = torch.arange(L // 16, dtype=torch.int32, device="cuda").repeat(B, 1)
+    spec = torch.full((B,), k, dtype=torch.int32, device="cuda")
+    outs = []
+    for others in (L, 300):
+        ctx = torch.full((B,), others, dtype=torch.int32, device="cuda")
+        ctx[B // 2] = L
+        out = pkg.verify_attn(q, *kv, table, ctx, spec, max_spec_len=k, out_dtype=0)
+        torch.cuda.synchronize()
+        outs.append(out[B // 2 * (k + 1):(B // 2 + 1) * (k + 1)].clone())
+    assert torch.equal(*outs)
