@@ -24,7 +24,7 @@ FLAGS = [
 ]
 
 
-def build_fastcall(verbose: bool = False) -> str:
+def build_fastcall(verbose: bool = False, out: str = FASTCALL_PATH, defines=()) -> str:
     """The extension module uses torch's and Python's headers only (no HIP), so the host compiler builds it."""
     import sysconfig
 
@@ -33,14 +33,14 @@ def build_fastcall(verbose: bool = False) -> str:
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared",
            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
            "-I", os.path.join(root, "include"), "-I", os.path.join(root, "include", "torch", "csrc", "api", "include"),
-           "-I", sysconfig.get_paths()["include"], FASTCALL_SOURCE, "-o", FASTCALL_PATH,
+           "-I", sysconfig.get_paths()["include"], *(f"-D{d}" for d in defines), FASTCALL_SOURCE, "-o", out,
            "-L", os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
     if verbose:
         print(" ".join(cmd), flush=True)
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"g++ failed on {FASTCALL_SOURCE}:\n{r.stderr}")
-    return FASTCALL_PATH
+    return out
 
 
 def build_library(verbose: bool = False, jobs: int = 8) -> str:

@@ -24,6 +24,16 @@ namespace {
 
 struct Bail {};                                        // not a plain call: leave it to Python
 
+// (a build for the tests of this file: tensors without memory stand in for device memory, stubs for the library)
+#ifdef ADASPEC_FASTCALL_ON_META
+constexpr at::DeviceType kDevice = at::kMeta;
+int meta_index = 0;                                    // they have no device index of their own
+int device_index(const at::Tensor &) { return meta_index; }
+#else
+constexpr at::DeviceType kDevice = at::kCUDA;
+int device_index(const at::Tensor &t) { return t.get_device(); }
+#endif
+
 struct Api {
     decltype(&adaspec_verify_attn_workspace_bytes) attn_ws;
     decltype(&adaspec_verify_attn) attn;
@@ -57,7 +67,7 @@ const at::Tensor &tensor(PyObject *o)
 {
     if (!THPVariable_CheckExact(o)) throw Bail{};
     const at::Tensor &t = THPVariable_Unpack(o);
-    if (!t.defined() || !t.is_cuda() || t.layout() != at::kStrided) throw Bail{};
+    if (!t.defined() || t.device().type() != kDevice || t.layout() != at::kStrided) throw Bail{};
     return t;
 }
 const at::Tensor &dense(PyObject *o, at::ScalarType dt)
@@ -134,7 +144,7 @@ at::Tensor workspace(PyObject *given, size_t nbytes, Family family, const at::Te
 {
     if (given != Py_None) return tensor(given);
     auto &all = workspaces[family];
-    const size_t dev = (size_t)like.get_device();
+    const size_t dev = (size_t)device_index(like);
     if (all.size() <= dev) all.resize(dev + 1);
     at::Tensor &ws = all[dev];
     if (!ws.defined() || (size_t)ws.numel() < nbytes) {
@@ -168,14 +178,19 @@ struct Output {
     }
 };
 
-// The C call runs without the interpreter lock, as it does through ctypes.
-template <class F>
-void call(F &&f)
+struct Unlocked {                                      // the interpreter lock is given up for the life of this object
+    PyThreadState *state = PyEval_SaveThread();
+    ~Unlocked() { PyEval_RestoreThread(state); }
+};
+// The C call runs without the interpreter lock, as it does through ctypes.  Its arguments are values: whatever looks at
+// Python objects has been done, and may have thrown, before the lock is given up.
+template <class F, class... A>
+void call(F entry, A... args)
 {
-    int rc;
-    Py_BEGIN_ALLOW_THREADS
-    rc = f();
-    Py_END_ALLOW_THREADS
+    const int rc = [&] {
+        const Unlocked unlocked;
+        return entry(args...);
+    }();
     if (rc != ADASPEC_OK) throw Bail{};
 }
 
@@ -231,24 +246,20 @@ PyObject *verify_attn(PyObject *, PyObject *const *a, Py_ssize_t nargs)
             need(p.dim() == 1 && p.size(0) == q.size(0));
             parents = ptr<int32_t>(p);
         }
+        const auto run = [&](void *out) {
+            if (a[13] != Py_None)
+                call(api.attn_tree, ptr(q), ptr(k), ptr(v), ptr<int32_t>(bt), ptr<int32_t>(ctx), ptr<int32_t>(spec), parents, out, &d,
+                     ptr(ws), (size_t)ws.numel(), s);
+            else
+                call(api.attn, ptr(q), ptr(k), ptr(v), ptr<int32_t>(bt), ptr<int32_t>(ctx), ptr<int32_t>(spec), out, &d, ptr(ws),
+                     (size_t)ws.numel(), s);
+        };
         if (build && a[6] == Py_None) {
-            call([&] {
-                return a[13] != Py_None
-                           ? api.attn_tree(ptr(q), ptr(k), ptr(v), ptr<int32_t>(bt), ptr<int32_t>(ctx), ptr<int32_t>(spec), parents,
-                                           nullptr, &d, ptr(ws), (size_t)ws.numel(), s)
-                           : api.attn(ptr(q), ptr(k), ptr(v), ptr<int32_t>(bt), ptr<int32_t>(ctx), ptr<int32_t>(spec), nullptr, &d,
-                                      ptr(ws), (size_t)ws.numel(), s);
-            });
+            run(nullptr);
             Py_RETURN_NONE;
         }
         const Output out(a[6], q.sizes(), scalar_type(d.out_dtype), q);
-        call([&] {
-            return a[13] != Py_None
-                       ? api.attn_tree(ptr(q), ptr(k), ptr(v), ptr<int32_t>(bt), ptr<int32_t>(ctx), ptr<int32_t>(spec), parents,
-                                       ptr(out.t), &d, ptr(ws), (size_t)ws.numel(), s)
-                       : api.attn(ptr(q), ptr(k), ptr(v), ptr<int32_t>(bt), ptr<int32_t>(ctx), ptr<int32_t>(spec), ptr(out.t), &d,
-                                  ptr(ws), (size_t)ws.numel(), s);
-        });
+        run(ptr(out.t));
         return out.result();
     });
 }
@@ -296,10 +307,8 @@ PyObject *accept(PyObject *, PyObject *const *a, Py_ssize_t nargs)
         const Output toks(a[7], {r.d.batch, r.d.out_stride}, at::kInt, logits), lens(a[8], {r.d.batch}, at::kInt, logits);
         const at::Tensor ws = workspace(a[10], std::max<size_t>(api.accept_ws(&r.d), 256), kAccept, logits);
         void *s = stream_of(a[11]);
-        call([&] {
-            return api.accept(ptr(logits), r.probs, r.tokens, ptr<float>(uni), ptr<int32_t>(spec), ptr<float>(temp),
-                              ptr<int32_t>(toks.t), ptr<int32_t>(lens.t), &r.d, ptr(ws), (size_t)ws.numel(), s);
-        });
+        call(api.accept, ptr(logits), r.probs, r.tokens, ptr<float>(uni), ptr<int32_t>(spec), ptr<float>(temp), ptr<int32_t>(toks.t),
+             ptr<int32_t>(lens.t), &r.d, ptr(ws), (size_t)ws.numel(), s);
         return Py_BuildValue("(NN)", toks.result(), lens.result());
     });
 }
@@ -317,11 +326,8 @@ PyObject *accept_tree(PyObject *, PyObject *const *a, Py_ssize_t nargs)
         const Output path(a[10], {r.d.batch, r.d.out_stride}, at::kInt, logits);
         const at::Tensor ws = workspace(a[12], std::max<size_t>(api.accept_ws(&r.d), 256), kAccept, logits);
         void *s = stream_of(a[13]);
-        call([&] {
-            return api.accept_tree(ptr(logits), r.probs, r.tokens, ptr<int32_t>(parents), ptr<float>(uni), ptr<int32_t>(spec),
-                                   ptr<float>(temp), ptr<int32_t>(toks.t), ptr<int32_t>(lens.t), ptr<int32_t>(path.t), &r.d, ptr(ws),
-                                   (size_t)ws.numel(), s);
-        });
+        call(api.accept_tree, ptr(logits), r.probs, r.tokens, ptr<int32_t>(parents), ptr<float>(uni), ptr<int32_t>(spec),
+             ptr<float>(temp), ptr<int32_t>(toks.t), ptr<int32_t>(lens.t), ptr<int32_t>(path.t), &r.d, ptr(ws), (size_t)ws.numel(), s);
         return Py_BuildValue("(NNN)", toks.result(), lens.result(), path.result());
     });
 }
@@ -353,9 +359,7 @@ PyObject *kv_append(PyObject *, PyObject *const *a, Py_ssize_t nargs)
         for (const at::Tensor *t : {&kn, &vn, &k, &v}) need(t->is_contiguous() && t->scalar_type() == kn.scalar_type());
         const adaspec_attn_dims d = cache_dims(k, bt, size32(kn.size(0)), a[7]);
         void *s = stream_of(a[8]);
-        call([&] {
-            return api.kv_append(ptr(kn), ptr(vn), ptr(k), ptr(v), ptr<int32_t>(bt), ptr<int32_t>(ctx), ptr<int32_t>(spec), &d, s);
-        });
+        call(api.kv_append, ptr(kn), ptr(vn), ptr(k), ptr(v), ptr<int32_t>(bt), ptr<int32_t>(ctx), ptr<int32_t>(spec), &d, s);
         Py_RETURN_NONE;
     });
 }
@@ -371,10 +375,8 @@ PyObject *kv_compact_path(PyObject *, PyObject *const *a, Py_ssize_t nargs)
         need(k.is_contiguous() && v.is_contiguous() && v.scalar_type() == k.scalar_type());
         const adaspec_attn_dims d = cache_dims(k, bt, size32(bt.size(0)), a[7]);
         void *s = stream_of(a[8]);
-        call([&] {
-            return api.kv_compact(ptr(k), ptr(v), ptr<int32_t>(bt), ptr<int32_t>(ctx), ptr<int32_t>(spec), ptr<int32_t>(path),
-                                  ptr<int32_t>(lens), &d, size32(path.size(1)), s);
-        });
+        call(api.kv_compact, ptr(k), ptr(v), ptr<int32_t>(bt), ptr<int32_t>(ctx), ptr<int32_t>(spec), ptr<int32_t>(path),
+             ptr<int32_t>(lens), &d, size32(path.size(1)), s);
         Py_RETURN_NONE;
     });
 }
@@ -402,11 +404,9 @@ PyObject *commit(PyObject *, PyObject *const *a, Py_ssize_t nargs)
             d.seq_stride = size32(seq.size(1));
         }
         void *s = stream_of(a[11]);
-        call([&] {
-            return api.commit(ptr<int32_t>(toks), ptr<int32_t>(lens), ptr<int32_t>(spec), ptr<int32_t>(ctx), ptr_or_null<int32_t>(a[5]),
-                              ptr<int32_t>(kept.t), next ? ptr<int32_t>(next_ctx) : nullptr, ptr<int32_t>(last.t),
-                              ptr_or_null<int32_t>(a[9]), ptr_or_null<int32_t>(a[10]), &d, s);
-        });
+        call(api.commit, ptr<int32_t>(toks), ptr<int32_t>(lens), ptr<int32_t>(spec), ptr<int32_t>(ctx), ptr_or_null<int32_t>(a[5]),
+             ptr<int32_t>(kept.t), next ? ptr<int32_t>(next_ctx) : nullptr, ptr<int32_t>(last.t), ptr_or_null<int32_t>(a[9]),
+             ptr_or_null<int32_t>(a[10]), &d, s);
         PyObject *n = Py_None;
         if (a[7] != Py_None) { n = a[7]; Py_INCREF(n); }
         else if (next) n = THPVariable_Wrap(next_ctx);
@@ -442,10 +442,8 @@ PyObject *draft_sample(PyObject *, PyObject *const *a, Py_ssize_t nargs)
         at::Tensor ws;
         if (nbytes) ws = workspace(a[8], nbytes, kDraft, logits);
         void *s = stream_of(a[9]);
-        call([&] {
-            return api.draft(ptr(logits), ptr<float>(temp), ptr<float>(uni), ptr_or_null<int32_t>(a[5]), ptr(probs.t),
-                             ptr<int32_t>(toks.t), ptr<float>(conf.t), &d, nbytes ? ptr(ws) : nullptr, nbytes ? (size_t)ws.numel() : 0, s);
-        });
+        call(api.draft, ptr(logits), ptr<float>(temp), ptr<float>(uni), ptr_or_null<int32_t>(a[5]), ptr(probs.t), ptr<int32_t>(toks.t),
+             ptr<float>(conf.t), &d, nbytes ? ptr(ws) : nullptr, nbytes ? (size_t)ws.numel() : (size_t)0, s);
         return Py_BuildValue("(NNN)", probs.result(), toks.result(), conf.result());
     });
 }
@@ -472,9 +470,20 @@ PyObject *setup(PyObject *, PyObject *args)
     Py_RETURN_NONE;
 }
 
+#ifdef ADASPEC_FASTCALL_ON_META
+PyObject *set_meta_index(PyObject *, PyObject *i)
+{
+    meta_index = (int)PyLong_AsLong(i);
+    Py_RETURN_NONE;
+}
+#endif
+
 #define FASTCALL(name) {#name, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(name)), METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {FASTCALL(verify_attn), FASTCALL(accept), FASTCALL(accept_tree), FASTCALL(kv_append),
                          FASTCALL(kv_compact_path), FASTCALL(commit), FASTCALL(draft_sample),
+#ifdef ADASPEC_FASTCALL_ON_META
+                         {"set_meta_index", set_meta_index, METH_O, nullptr},
+#endif
                          {"setup", setup, METH_VARARGS, nullptr}, {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_fastcall", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 

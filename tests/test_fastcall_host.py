@@ -1,0 +1,85 @@
+"""The native call path (csrc_python/fastcall.cpp) where no GPU is needed: a build of it that takes meta tensors, with
+functions of this file in the place of the library's entry points."""
+import ctypes as C
+import importlib.util
+
+import pytest
+import torch
+
+from paper_2503_05096_amd import binding, build
+
+OK, ERR_DIM, ERR_HIP = 0, -2, -7
+# (name, result type, number of pointer-sized arguments); kv_compact has an int32 among them, which fits
+ENTRIES = [("attn_ws", C.c_size_t, 1), ("attn", C.c_int, 11), ("attn_tree", C.c_int, 12), ("accept_ws", C.c_size_t, 1),
+           ("accept", C.c_int, 12), ("accept_tree", C.c_int, 14), ("kv_append", C.c_int, 9), ("kv_compact", C.c_int, 10),
+           ("commit", C.c_int, 12), ("draft_ws", C.c_size_t, 1), ("draft", C.c_int, 11)]
+
+
+@pytest.fixture(scope="module")
+def module(tmp_path_factory):
+    path = build.build_fastcall(out=str(tmp_path_factory.mktemp("fastcall") / "_fastcall.so"), defines=["ADASPEC_FASTCALL_ON_META"])
+    spec = importlib.util.spec_from_file_location("_fastcall", path)
+    m = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(m)
+    return m
+
+
+class Stubs:
+    """calls: entry points called so far; status: what they answer; workspace: stands in for binding._workspace"""
+
+    def __init__(self, module):
+        self.calls, self.status, self.keep = [], OK, []
+        for name, res, n in ENTRIES:
+            self.keep.append(C.CFUNCTYPE(res, *[C.c_void_p] * n)(
+                (lambda *a: 512) if res is C.c_size_t else (lambda *a, name=name: self.calls.append(name) or self.status)))
+        self.workspace = lambda nbytes, device, given, family: torch.empty(nbytes, dtype=torch.uint8, device=device)
+        module.setup(tuple(C.cast(f, C.c_void_p).value for f in self.keep), lambda *a: self.workspace(*a), lambda dev: 0, lambda: 0)
+
+
+@pytest.fixture
+def stubs(module):
+    return Stubs(module)
+
+
+def ints(*shape, dev="meta"):
+    return torch.zeros(shape, dtype=torch.int32, device=dev)
+
+
+def commit_args(next_spec=None, seq=None, seq_lens=None):
+    return (ints(3, 4), ints(3), ints(3), ints(3), 3, next_spec, None, None, None, seq, seq_lens, None)
+
+
+def draft_args(out_rows=None, dev="meta", **kw):
+    x = torch.zeros((2, 64), device=dev)
+    probs = None if out_rows is None else torch.zeros((5, 64), device=dev)
+    return (x, torch.ones(2, device=dev), torch.zeros(2, device=dev), None, probs, out_rows, None, None, None, None)
+
+
+class Sub(torch.Tensor):
+    pass
+
+
+NOT_PLAIN = {"list": [0, 1, 2], "another device": torch.zeros(3, dtype=torch.int32), "subclass": ints(3).as_subclass(Sub)}
+
+
+@pytest.mark.parametrize("what", NOT_PLAIN)
+def test_optional_arguments_that_are_not_plain_are_left_to_python(module, stubs, what):
+    x = NOT_PLAIN[what]
+    assert module.commit(*commit_args()) is not NotImplemented and module.draft_sample(*draft_args()) is not NotImplemented
+    stubs.calls.clear()
+    assert module.commit(*commit_args(next_spec=x)) is NotImplemented
+    assert module.commit(*commit_args(seq_lens=x)) is NotImplemented
+    assert module.draft_sample(*draft_args(out_rows=x)) is NotImplemented
+    assert stubs.calls == []
+
+
+def test_tensors_without_a_data_pointer_are_left_to_python(module, stubs):
+    """Under vmap a tensor has the plain type, but asking for its address throws."""
+    seen = []
+
+    def f(x):
+        seen.append(module.draft_sample(x, torch.ones(2, device="meta"), torch.zeros(2, device="meta"), None, None, None, None, None,
+                                        None, None))
+        return x
+    torch.vmap(f)(torch.zeros((3, 2, 64), device="meta"))
+    assert seen == [NotImplemented] and stubs.calls == []
