@@ -90,7 +90,7 @@ def _native():
             raise ImportError(f"{os.path.join(_HERE, '_fastcall.so')} is missing or does not fit this torch: build it "
                               "together with the library (python paper_2503_05096_amd/build.py)") from e
         _fastcall.setup(tuple(C.cast(getattr(L, n), C.c_void_p).value for n in _FAST_ENTRIES), _workspace,
-                        torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice)
+                        torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice, AdaspecError)
         _fast = _fastcall
     return _fast
 

@@ -5,7 +5,8 @@
 // Every function here either makes the call and returns its result, or returns NotImplemented and has done nothing that
 // counts: the wrapper in binding.py then goes on in Python, which raises the right error or handles the unusual form.
 // NotImplemented is the answer to anything that is not plain: tensor subclasses, active torch modes, a forced path, timing
-// events, a failed check, an error status of the library (on which nothing has been enqueued), any C++ exception.
+// events, a failed check, a status that the library's checks answer with (nothing has been enqueued then), any C++ exception.
+// ADASPEC_ERR_HIP may come after a launch: it is raised here, and the call is not made a second time.
 //
 // The entry points of libadaspec.so arrive as addresses from binding.py, which owns the library's handle; the default
 // workspaces are binding.py's as well (one owner for both ways into the library), held here by reference.
@@ -23,6 +24,7 @@
 namespace {
 
 struct Bail {};                                        // not a plain call: leave it to Python
+struct Raised {};                                      // a Python exception is set: the caller's
 
 // (a build for the tests of this file: tensors without memory stand in for device memory, stubs for the library)
 #ifdef ADASPEC_FASTCALL_ON_META
@@ -48,6 +50,7 @@ struct Api {
     decltype(&adaspec_draft_sample) draft;
 } api;
 PyObject *get_workspace, *raw_stream, *current_device;   // binding._workspace, torch._C._cuda_getCurrentRawStream / _getDevice
+PyObject *error_class;                                   // binding.AdaspecError
 bool ready = false;
 
 // the default workspaces in use: [family][device], the tensors of binding._ws_cache
@@ -185,12 +188,19 @@ struct Unlocked {                                      // the interpreter lock i
 // The C call runs without the interpreter lock, as it does through ctypes.  Its arguments are values: whatever looks at
 // Python objects has been done, and may have thrown, before the lock is given up.
 template <class F, class... A>
-void call(F entry, A... args)
+void call(const char *name, F entry, A... args)
 {
     const int rc = [&] {
         const Unlocked unlocked;
         return entry(args...);
     }();
+    if (rc == ADASPEC_ERR_HIP) {
+        if (PyObject *e = PyObject_CallFunction(error_class, "is", rc, name)) {
+            PyErr_SetObject(error_class, e);
+            Py_DECREF(e);
+        }
+        throw Raised{};
+    }
     if (rc != ADASPEC_OK) throw Bail{};
 }
 
@@ -203,6 +213,8 @@ PyObject *guarded(Py_ssize_t nargs, Py_ssize_t want, F &&f)
             PyObject *r = f();
             if (r) return r;
             PyErr_Clear();
+        } catch (const Raised &) {
+            return nullptr;
         } catch (...) {
             if (PyErr_Occurred()) PyErr_Clear();
         }
@@ -248,10 +260,10 @@ PyObject *verify_attn(PyObject *, PyObject *const *a, Py_ssize_t nargs)
         }
         const auto run = [&](void *out) {
             if (a[13] != Py_None)
-                call(api.attn_tree, ptr(q), ptr(k), ptr(v), ptr<int32_t>(bt), ptr<int32_t>(ctx), ptr<int32_t>(spec), parents, out, &d,
+                call("adaspec_verify_attn_tree", api.attn_tree, ptr(q), ptr(k), ptr(v), ptr<int32_t>(bt), ptr<int32_t>(ctx), ptr<int32_t>(spec), parents, out, &d,
                      ptr(ws), (size_t)ws.numel(), s);
             else
-                call(api.attn, ptr(q), ptr(k), ptr(v), ptr<int32_t>(bt), ptr<int32_t>(ctx), ptr<int32_t>(spec), out, &d, ptr(ws),
+                call("adaspec_verify_attn", api.attn, ptr(q), ptr(k), ptr(v), ptr<int32_t>(bt), ptr<int32_t>(ctx), ptr<int32_t>(spec), out, &d, ptr(ws),
                      (size_t)ws.numel(), s);
         };
         if (build && a[6] == Py_None) {
@@ -307,7 +319,7 @@ PyObject *accept(PyObject *, PyObject *const *a, Py_ssize_t nargs)
         const Output toks(a[7], {r.d.batch, r.d.out_stride}, at::kInt, logits), lens(a[8], {r.d.batch}, at::kInt, logits);
         const at::Tensor ws = workspace(a[10], std::max<size_t>(api.accept_ws(&r.d), 256), kAccept, logits);
         void *s = stream_of(a[11]);
-        call(api.accept, ptr(logits), r.probs, r.tokens, ptr<float>(uni), ptr<int32_t>(spec), ptr<float>(temp), ptr<int32_t>(toks.t),
+        call("adaspec_accept", api.accept, ptr(logits), r.probs, r.tokens, ptr<float>(uni), ptr<int32_t>(spec), ptr<float>(temp), ptr<int32_t>(toks.t),
              ptr<int32_t>(lens.t), &r.d, ptr(ws), (size_t)ws.numel(), s);
         return Py_BuildValue("(NN)", toks.result(), lens.result());
     });
@@ -326,7 +338,7 @@ PyObject *accept_tree(PyObject *, PyObject *const *a, Py_ssize_t nargs)
         const Output path(a[10], {r.d.batch, r.d.out_stride}, at::kInt, logits);
         const at::Tensor ws = workspace(a[12], std::max<size_t>(api.accept_ws(&r.d), 256), kAccept, logits);
         void *s = stream_of(a[13]);
-        call(api.accept_tree, ptr(logits), r.probs, r.tokens, ptr<int32_t>(parents), ptr<float>(uni), ptr<int32_t>(spec),
+        call("adaspec_accept_tree", api.accept_tree, ptr(logits), r.probs, r.tokens, ptr<int32_t>(parents), ptr<float>(uni), ptr<int32_t>(spec),
              ptr<float>(temp), ptr<int32_t>(toks.t), ptr<int32_t>(lens.t), ptr<int32_t>(path.t), &r.d, ptr(ws), (size_t)ws.numel(), s);
         return Py_BuildValue("(NNN)", toks.result(), lens.result(), path.result());
     });
@@ -359,7 +371,7 @@ PyObject *kv_append(PyObject *, PyObject *const *a, Py_ssize_t nargs)
         for (const at::Tensor *t : {&kn, &vn, &k, &v}) need(t->is_contiguous() && t->scalar_type() == kn.scalar_type());
         const adaspec_attn_dims d = cache_dims(k, bt, size32(kn.size(0)), a[7]);
         void *s = stream_of(a[8]);
-        call(api.kv_append, ptr(kn), ptr(vn), ptr(k), ptr(v), ptr<int32_t>(bt), ptr<int32_t>(ctx), ptr<int32_t>(spec), &d, s);
+        call("adaspec_kv_append", api.kv_append, ptr(kn), ptr(vn), ptr(k), ptr(v), ptr<int32_t>(bt), ptr<int32_t>(ctx), ptr<int32_t>(spec), &d, s);
         Py_RETURN_NONE;
     });
 }
@@ -375,7 +387,7 @@ PyObject *kv_compact_path(PyObject *, PyObject *const *a, Py_ssize_t nargs)
         need(k.is_contiguous() && v.is_contiguous() && v.scalar_type() == k.scalar_type());
         const adaspec_attn_dims d = cache_dims(k, bt, size32(bt.size(0)), a[7]);
         void *s = stream_of(a[8]);
-        call(api.kv_compact, ptr(k), ptr(v), ptr<int32_t>(bt), ptr<int32_t>(ctx), ptr<int32_t>(spec), ptr<int32_t>(path),
+        call("adaspec_kv_compact_path", api.kv_compact, ptr(k), ptr(v), ptr<int32_t>(bt), ptr<int32_t>(ctx), ptr<int32_t>(spec), ptr<int32_t>(path),
              ptr<int32_t>(lens), &d, size32(path.size(1)), s);
         Py_RETURN_NONE;
     });
@@ -404,7 +416,7 @@ PyObject *commit(PyObject *, PyObject *const *a, Py_ssize_t nargs)
             d.seq_stride = size32(seq.size(1));
         }
         void *s = stream_of(a[11]);
-        call(api.commit, ptr<int32_t>(toks), ptr<int32_t>(lens), ptr<int32_t>(spec), ptr<int32_t>(ctx), ptr_or_null<int32_t>(a[5]),
+        call("adaspec_commit", api.commit, ptr<int32_t>(toks), ptr<int32_t>(lens), ptr<int32_t>(spec), ptr<int32_t>(ctx), ptr_or_null<int32_t>(a[5]),
              ptr<int32_t>(kept.t), next ? ptr<int32_t>(next_ctx) : nullptr, ptr<int32_t>(last.t), ptr_or_null<int32_t>(a[9]),
              ptr_or_null<int32_t>(a[10]), &d, s);
         PyObject *n = Py_None;
@@ -442,17 +454,18 @@ PyObject *draft_sample(PyObject *, PyObject *const *a, Py_ssize_t nargs)
         at::Tensor ws;
         if (nbytes) ws = workspace(a[8], nbytes, kDraft, logits);
         void *s = stream_of(a[9]);
-        call(api.draft, ptr(logits), ptr<float>(temp), ptr<float>(uni), ptr_or_null<int32_t>(a[5]), ptr(probs.t), ptr<int32_t>(toks.t),
+        call("adaspec_draft_sample", api.draft, ptr(logits), ptr<float>(temp), ptr<float>(uni), ptr_or_null<int32_t>(a[5]), ptr(probs.t), ptr<int32_t>(toks.t),
              ptr<float>(conf.t), &d, nbytes ? ptr(ws) : nullptr, nbytes ? (size_t)ws.numel() : (size_t)0, s);
         return Py_BuildValue("(NNN)", probs.result(), toks.result(), conf.result());
     });
 }
 
-// (tuple of the entry points' addresses in Api's order, binding._workspace, raw stream getter, current device getter)
+// (tuple of the entry points' addresses in Api's order, binding._workspace, raw stream getter, current device getter,
+//  binding.AdaspecError)
 PyObject *setup(PyObject *, PyObject *args)
 {
-    PyObject *table, *ws, *stream, *device;
-    if (!PyArg_ParseTuple(args, "O!OOO", &PyTuple_Type, &table, &ws, &stream, &device)) return nullptr;
+    PyObject *table, *ws, *stream, *device, *error;
+    if (!PyArg_ParseTuple(args, "O!OOOO", &PyTuple_Type, &table, &ws, &stream, &device, &error)) return nullptr;
     void **slot = reinterpret_cast<void **>(&api);
     constexpr Py_ssize_t n = sizeof(Api) / sizeof(void *);
     if (PyTuple_GET_SIZE(table) != n) {
@@ -466,6 +479,7 @@ PyObject *setup(PyObject *, PyObject *args)
     get_workspace = Py_NewRef(ws);
     raw_stream = Py_NewRef(stream);
     current_device = Py_NewRef(device);
+    error_class = Py_NewRef(error);
     ready = true;
     Py_RETURN_NONE;
 }

@@ -33,7 +33,8 @@ class Stubs:
             self.keep.append(C.CFUNCTYPE(res, *[C.c_void_p] * n)(
                 (lambda *a: 512) if res is C.c_size_t else (lambda *a, name=name: self.calls.append(name) or self.status)))
         self.workspace = lambda nbytes, device, given, family: torch.empty(nbytes, dtype=torch.uint8, device=device)
-        module.setup(tuple(C.cast(f, C.c_void_p).value for f in self.keep), lambda *a: self.workspace(*a), lambda dev: 0, lambda: 0)
+        module.setup(tuple(C.cast(f, C.c_void_p).value for f in self.keep), lambda *a: self.workspace(*a), lambda dev: 0, lambda: 0,
+                     binding.AdaspecError)
 
 
 @pytest.fixture
@@ -83,3 +84,31 @@ def test_tensors_without_a_data_pointer_are_left_to_python(module, stubs):
         return x
     torch.vmap(f)(torch.zeros((3, 2, 64), device="meta"))
     assert seen == [NotImplemented] and stubs.calls == []
+
+
+def every_call(module):
+    q, kv, bt = torch.zeros((4, 2, 64), device="meta"), torch.zeros((2, 2, 16, 64), device="meta"), ints(1, 2)
+    rows, probs, uni, t = (torch.zeros(n, device="meta") for n in ((4, 64), (3, 64), (4, 2), (1,)))
+    attn = (q, kv, kv, bt, ints(1), ints(1), None, 3, 0.0, None, "run", None, None)
+    return {"verify_attn": lambda: module.verify_attn(*attn, None),
+            "verify_attn_tree": lambda: module.verify_attn(*attn, ints(4)),
+            "accept": lambda: module.accept(rows, probs, ints(3), uni, ints(1), t, 3, None, None, None, None, None),
+            "accept_tree": lambda: module.accept_tree(rows, probs, ints(3), ints(4), uni, ints(1), t, 3, *[None] * 6),
+            "kv_append": lambda: module.kv_append(q, q, kv, kv, bt, ints(1), ints(1), 3, None),
+            "kv_compact_path": lambda: module.kv_compact_path(kv, kv, bt, ints(1), ints(1), ints(1, 4), ints(1), 3, None),
+            "commit": lambda: module.commit(*commit_args()), "draft_sample": lambda: module.draft_sample(*draft_args())}
+
+
+def test_statuses_of_the_library(module, stubs):
+    """What its checks refuse goes to the Python path; a call that failed in HIP may have enqueued work (commit() would
+    append its tokens again): it is made once, and raises."""
+    for name, f in every_call(module).items():
+        stubs.status = OK
+        assert f() is not NotImplemented, name
+        stubs.status = ERR_DIM
+        assert f() is NotImplemented, name
+        stubs.status = ERR_HIP
+        stubs.calls.clear()
+        with pytest.raises(binding.AdaspecError, match=f"^adaspec_{name}: ") as e:
+            f()
+        assert e.value.status == ERR_HIP and len(stubs.calls) == 1, name
