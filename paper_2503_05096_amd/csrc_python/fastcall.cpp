@@ -148,17 +148,18 @@ at::Tensor workspace(PyObject *given, size_t nbytes, Family family, const at::Te
     if (given != Py_None) return tensor(given);
     auto &all = workspaces[family];
     const size_t dev = (size_t)device_index(like);
+    if (dev < all.size() && all[dev].defined() && (size_t)all[dev].numel() >= nbytes) return all[dev];
+    // (the interpreter lock may change hands in this call, and another thread's device lengthen the table: nothing in it
+    // is referred to across the call)
+    PyObject *device = PyObject_GetAttrString(py::cast(like).ptr(), "device");
+    PyObject *t = device ? PyObject_CallFunction(get_workspace, "nOOs", (Py_ssize_t)nbytes, device, Py_None, kFamilyName[family]) : nullptr;
+    Py_XDECREF(device);
+    if (!t) { PyErr_Clear(); throw Bail{}; }
+    if (!THPVariable_CheckExact(t)) { Py_DECREF(t); throw Bail{}; }
+    const at::Tensor ws = THPVariable_Unpack(t);
+    Py_DECREF(t);
     if (all.size() <= dev) all.resize(dev + 1);
-    at::Tensor &ws = all[dev];
-    if (!ws.defined() || (size_t)ws.numel() < nbytes) {
-        PyObject *device = PyObject_GetAttrString(py::cast(like).ptr(), "device");
-        PyObject *t = device ? PyObject_CallFunction(get_workspace, "nOOs", (Py_ssize_t)nbytes, device, Py_None, kFamilyName[family]) : nullptr;
-        Py_XDECREF(device);
-        if (!t) { PyErr_Clear(); throw Bail{}; }
-        if (!THPVariable_CheckExact(t)) { Py_DECREF(t); throw Bail{}; }
-        ws = THPVariable_Unpack(t);
-        Py_DECREF(t);
-    }
+    all[dev] = ws;
     return ws;
 }
 

@@ -112,3 +112,31 @@ def test_statuses_of_the_library(module, stubs):
         with pytest.raises(binding.AdaspecError, match=f"^adaspec_{name}: ") as e:
             f()
         assert e.value.status == ERR_HIP and len(stubs.calls) == 1, name
+
+
+def test_default_workspaces_when_another_device_is_first_used_meanwhile(module):
+    """binding._workspace runs Python, so a thread of another device may make its first call inside it (here: the same
+    thread, inside the function that stands in for it)."""
+    s, asked = Stubs(module), []
+
+    def on(device, rows):
+        module.set_meta_index(device)
+        return module.draft_sample(torch.zeros((rows, 64), device="meta"), torch.ones(rows, device="meta"), torch.zeros(rows, device="meta"),
+                                   *[None] * 7)
+
+    def workspace(nbytes, device, given, family):
+        asked.append(len(asked))
+        if len(asked) == 1:
+            for other in range(20, 3000, 500):
+                assert on(other, 2) is not NotImplemented
+            module.set_meta_index(10)
+        return torch.empty(1 << 20, dtype=torch.uint8, device="meta")
+    s.workspace = workspace
+    try:
+        assert on(10, 2) is not NotImplemented
+        n = len(asked)
+        assert n == 7
+        assert on(10, 2) is not NotImplemented and on(20, 2) is not NotImplemented
+        assert len(asked) == n                            # every device has kept its own
+    finally:
+        module.set_meta_index(0)
