@@ -25,6 +25,14 @@ namespace {
 
 struct Bail {};                                        // not a plain call: leave it to Python
 struct Raised {};                                      // a Python exception is set: the caller's
+// After a Python call that failed: an ordinary error is left to the Python path, which runs into it as well; a
+// KeyboardInterrupt or the like is not an answer of what was called, and goes up from here.
+[[noreturn]] void failed_in_python()
+{
+    if (PyErr_Occurred() && !PyErr_ExceptionMatches(PyExc_Exception)) throw Raised{};
+    PyErr_Clear();
+    throw Bail{};
+}
 
 // (a build for the tests of this file: tensors without memory stand in for device memory, stubs for the library)
 #ifdef ADASPEC_FASTCALL_ON_META
@@ -129,16 +137,17 @@ void *stream_of(PyObject *stream)
     PyObject *v;
     if (stream == Py_None) {
         PyObject *dev = PyObject_CallNoArgs(current_device);
-        if (!dev) { PyErr_Clear(); throw Bail{}; }
+        if (!dev) failed_in_python();
         v = PyObject_CallOneArg(raw_stream, dev);
         Py_DECREF(dev);
     } else {
         v = PyObject_GetAttrString(stream, "cuda_stream");
     }
-    if (!v || !PyLong_Check(v)) { Py_XDECREF(v); PyErr_Clear(); throw Bail{}; }
+    if (!v) failed_in_python();
+    if (!PyLong_Check(v)) { Py_DECREF(v); throw Bail{}; }
     void *p = PyLong_AsVoidPtr(v);
     Py_DECREF(v);
-    if (PyErr_Occurred()) { PyErr_Clear(); throw Bail{}; }
+    if (PyErr_Occurred()) failed_in_python();
     return p;
 }
 
@@ -154,7 +163,7 @@ at::Tensor workspace(PyObject *given, size_t nbytes, Family family, const at::Te
     PyObject *device = PyObject_GetAttrString(py::cast(like).ptr(), "device");
     PyObject *t = device ? PyObject_CallFunction(get_workspace, "nOOs", (Py_ssize_t)nbytes, device, Py_None, kFamilyName[family]) : nullptr;
     Py_XDECREF(device);
-    if (!t) { PyErr_Clear(); throw Bail{}; }
+    if (!t) failed_in_python();
     if (!THPVariable_CheckExact(t)) { Py_DECREF(t); throw Bail{}; }
     const at::Tensor ws = THPVariable_Unpack(t);
     Py_DECREF(t);

@@ -140,3 +140,35 @@ def test_default_workspaces_when_another_device_is_first_used_meanwhile(module):
         assert len(asked) == n                            # every device has kept its own
     finally:
         module.set_meta_index(0)
+
+
+def test_interrupts_inside_a_call_are_not_swallowed(module):
+    """Ordinary errors of the Python functions behind the native path send the call to the Python path, which meets them
+    again; an interrupt that arrives in one of them ends the call."""
+    s = Stubs(module)
+
+    def workspace_raises(e):
+        def f(*a):
+            raise e
+        s.workspace = f
+        return module.draft_sample(torch.zeros((2, 64), device="meta"), torch.ones(2, device="meta"), torch.zeros(2, device="meta"),
+                                   *[None] * 7)
+
+    class Stream:
+        def __init__(self, e):
+            self.e = e
+
+        @property
+        def cuda_stream(self):
+            raise self.e
+    module.set_meta_index(4000)                           # a device without a workspace yet
+    try:
+        assert workspace_raises(RuntimeError("out of memory")) is NotImplemented
+        with pytest.raises(KeyboardInterrupt):
+            workspace_raises(KeyboardInterrupt())
+    finally:
+        module.set_meta_index(0)
+    assert module.commit(*commit_args()[:-1], Stream(ValueError())) is NotImplemented
+    with pytest.raises(SystemExit):
+        module.commit(*commit_args()[:-1], Stream(SystemExit()))
+    assert s.calls == []
