@@ -17,6 +17,7 @@
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <array>
+#include <optional>
 #include <vector>
 
 #include "../../include/adaspec.h"
@@ -176,19 +177,20 @@ at::Tensor empty(at::IntArrayRef shape, at::ScalarType dt, const at::Tensor &lik
 {
     return at::empty(shape, at::TensorOptions().dtype(dt).device(like.device()));
 }
-// an output argument: the caller's object (checked by nobody but the library, as in Python) or a new tensor
+// an output argument: the caller's object (checked by nobody but the library, as in Python) or a new tensor, whose Python
+// object exists before the call is made: after it nothing may fail that could send the call to Python again
 struct Output {
-    PyObject *given;
     at::Tensor t;
-    Output(PyObject *o, at::IntArrayRef shape, at::ScalarType dt, const at::Tensor &like) : given(o)
+    PyObject *object;
+    Output(PyObject *given, at::IntArrayRef shape, at::ScalarType dt, const at::Tensor &like)
     {
-        t = o != Py_None ? tensor(o) : empty(shape, dt, like);
+        t = given != Py_None ? tensor(given) : empty(shape, dt, like);
+        object = given != Py_None ? Py_NewRef(given) : THPVariable_Wrap(t);
+        if (!object) failed_in_python();
     }
-    PyObject *result() const
-    {
-        if (given != Py_None) { Py_INCREF(given); return given; }
-        return THPVariable_Wrap(t);
-    }
+    ~Output() { Py_DECREF(object); }
+    Output(const Output &) = delete;
+    PyObject *result() const { return Py_NewRef(object); }
 };
 
 struct Unlocked {                                      // the interpreter lock is given up for the life of this object
@@ -220,9 +222,7 @@ PyObject *guarded(Py_ssize_t nargs, Py_ssize_t want, F &&f)
     if (nargs == want) {
         try {
             no_modes();
-            PyObject *r = f();
-            if (r) return r;
-            PyErr_Clear();
+            return f();                                // (null: the result's tuple could not be made)
         } catch (const Raised &) {
             return nullptr;
         } catch (...) {
@@ -416,10 +416,8 @@ PyObject *commit(PyObject *, PyObject *const *a, Py_ssize_t nargs)
         d.max_spec_len = small_int(a[4]);
         d.out_stride = size32(toks.size(1));
         const Output kept(a[6], {d.batch}, at::kInt, toks), last(a[8], {d.batch}, at::kInt, toks);
-        const bool next = a[5] != Py_None || a[7] != Py_None;
-        at::Tensor next_ctx;
-        if (a[7] != Py_None) next_ctx = tensor(a[7]);
-        else if (a[5] != Py_None) next_ctx = empty({d.batch}, at::kInt, toks);
+        std::optional<Output> next;
+        if (a[5] != Py_None || a[7] != Py_None) next.emplace(a[7], at::IntArrayRef{d.batch}, at::kInt, toks);
         if (a[9] != Py_None) {
             const at::Tensor &seq = dense(a[9], at::kInt);
             need(seq.dim() == 2 && a[10] != Py_None && tensor(a[10]).scalar_type() == at::kInt);
@@ -427,13 +425,9 @@ PyObject *commit(PyObject *, PyObject *const *a, Py_ssize_t nargs)
         }
         void *s = stream_of(a[11]);
         call("adaspec_commit", api.commit, ptr<int32_t>(toks), ptr<int32_t>(lens), ptr<int32_t>(spec), ptr<int32_t>(ctx), ptr_or_null<int32_t>(a[5]),
-             ptr<int32_t>(kept.t), next ? ptr<int32_t>(next_ctx) : nullptr, ptr<int32_t>(last.t), ptr_or_null<int32_t>(a[9]),
+             ptr<int32_t>(kept.t), next ? ptr<int32_t>(next->t) : nullptr, ptr<int32_t>(last.t), ptr_or_null<int32_t>(a[9]),
              ptr_or_null<int32_t>(a[10]), &d, s);
-        PyObject *n = Py_None;
-        if (a[7] != Py_None) { n = a[7]; Py_INCREF(n); }
-        else if (next) n = THPVariable_Wrap(next_ctx);
-        else Py_INCREF(n);
-        return Py_BuildValue("(NNN)", kept.result(), n, last.result());
+        return Py_BuildValue("(NNN)", kept.result(), next ? next->result() : Py_NewRef(Py_None), last.result());
     });
 }
 
