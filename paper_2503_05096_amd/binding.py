@@ -79,20 +79,32 @@ _FAST_ENTRIES = ("adaspec_verify_attn_workspace_bytes", "adaspec_verify_attn", "
 
 def _native():
     """The native call path (csrc_python/fastcall.cpp): its functions make an ordinary call in full, or return
-    NotImplemented without having done anything, and the wrapper goes on in Python."""
+    NotImplemented without having done anything, and the wrapper goes on in Python.  Where the module is missing or was
+    built for another torch, every call goes on in Python: the same kernels, some microseconds later."""
     global _fast
     if _fast is None:
         L = lib()
         import torch
         try:
             from . import _fastcall
-        except ImportError as e:
-            raise ImportError(f"{os.path.join(_HERE, '_fastcall.so')} is missing or does not fit this torch: build it "
-                              "together with the library (python paper_2503_05096_amd/build.py)") from e
-        _fastcall.setup(tuple(C.cast(getattr(L, n), C.c_void_p).value for n in _FAST_ENTRIES), _workspace,
-                        torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice, AdaspecError)
-        _fast = _fastcall
+            if _fastcall.torch_version != torch.__version__:
+                raise ImportError(f"it was built for torch {_fastcall.torch_version}")
+            _fastcall.setup(tuple(C.cast(getattr(L, n), C.c_void_p).value for n in _FAST_ENTRIES), _workspace,
+                            torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice, AdaspecError)
+            _fast = _fastcall
+        except (ImportError, AttributeError) as e:
+            import warnings
+            warnings.warn(f"no native call path, calls go through Python ({e}); build it together with the library: "
+                          "python paper_2503_05096_amd/build.py", RuntimeWarning, stacklevel=3)
+            _fast = _PythonOnly()
     return _fast
+
+
+class _PythonOnly:
+    """Stands in for the native call path where there is none."""
+    def _decline(*args):
+        return NotImplemented
+    verify_attn = accept = accept_tree = kv_append = kv_compact_path = commit = draft_sample = _decline
 
 
 def lib() -> C.CDLL:

@@ -33,7 +33,8 @@ def build_fastcall(verbose: bool = False, out: str = FASTCALL_PATH, defines=()) 
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared",
            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
            "-I", os.path.join(root, "include"), "-I", os.path.join(root, "include", "torch", "csrc", "api", "include"),
-           "-I", sysconfig.get_paths()["include"], *(f"-D{d}" for d in defines), FASTCALL_SOURCE, "-o", out,
+           "-I", sysconfig.get_paths()["include"], f'-DADASPEC_TORCH_VERSION="{torch.__version__}"',
+           *(f"-D{d}" for d in defines), FASTCALL_SOURCE, "-o", out,
            "-L", os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
     if verbose:
         print(" ".join(cmd), flush=True)
@@ -61,7 +62,12 @@ def build_library(verbose: bool = False, jobs: int = 8) -> str:
     with ThreadPoolExecutor(jobs) as ex:
         fastcall = ex.submit(build_fastcall, verbose)
         logs = list(ex.map(compile_one, zip(sources, objects)))
+    try:
         fastcall.result()
+    except Exception as e:      # no host compiler, no Python headers: the binding makes its calls in Python then
+        if os.path.exists(FASTCALL_PATH):
+            os.remove(FASTCALL_PATH)                # never one that is older than the library
+        print(f"_fastcall.so was not built, calls from Python take some microseconds longer: {e}", file=sys.stderr)
     if verbose:
         for log in logs:
             # hipcc's host pass does not know the device-only feature flag: harmless

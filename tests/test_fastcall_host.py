@@ -172,3 +172,37 @@ def test_interrupts_inside_a_call_are_not_swallowed(module):
     with pytest.raises(SystemExit):
         module.commit(*commit_args()[:-1], Stream(SystemExit()))
     assert s.calls == []
+
+
+@pytest.mark.parametrize("what", ["missing", "another torch"])
+def test_the_binding_without_its_native_path(what, monkeypatch):
+    """The Python route is complete: without the module (or with one built for another torch) the binding warns once and
+    takes it."""
+    import paper_2503_05096_amd as pkg
+    import sys
+    import types
+    name = "paper_2503_05096_amd._fastcall"
+    monkeypatch.setattr(binding, "_fast", None)
+    monkeypatch.delattr(pkg, "_fastcall", raising=False)
+    monkeypatch.setitem(sys.modules, name, None if what == "missing" else types.SimpleNamespace(torch_version="0.0"))
+    t = torch.zeros(2, 2)
+    with pytest.warns(RuntimeWarning, match="no native call path"):
+        with pytest.raises(AssertionError):               # the Python route's own check: not on a GPU
+            pkg.commit(ints(1, 1, dev="cpu"), ints(1, dev="cpu"), ints(1, dev="cpu"), ints(1, dev="cpu"), max_spec_len=0)
+    fast = binding._fast
+    for f, n in (("verify_attn", 14), ("accept", 12), ("accept_tree", 14), ("kv_append", 9), ("kv_compact_path", 9), ("commit", 12),
+                 ("draft_sample", 10)):
+        assert getattr(fast, f)(*[t] * n) is NotImplemented
+
+
+def test_a_library_without_the_native_path_can_be_built(tmp_path, monkeypatch, capsys):
+    """A machine without a host C++ compiler still gets the library; no older module stays beside it."""
+    stale = tmp_path / "_fastcall.so"
+    stale.write_bytes(b"")
+    monkeypatch.setenv("CXX", str(tmp_path / "no-compiler"))
+    monkeypatch.setattr(build, "FASTCALL_PATH", str(stale))
+    monkeypatch.setattr(build, "LIB_PATH", str(tmp_path / "lib.so"))
+    monkeypatch.setattr(build, "BUILD_DIR", str(tmp_path / "objects"))
+    monkeypatch.setattr(build, "HIPCC", "true")
+    build.build_library()
+    assert not stale.exists() and "_fastcall.so was not built" in capsys.readouterr().err
