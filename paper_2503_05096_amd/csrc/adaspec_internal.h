@@ -66,7 +66,7 @@ inline int attn_row_groups(int max_rows)
 enum class AttnKind { kVector, kMfma128, kMfma64, kMfmaF32 };
 constexpr int kAttnD64Block = 64;   // tokens per block of the head_dim 64 form (attn_d64.hip)
 AttnKind attn_kind(const adaspec_attn_dims &d);
-AttnPlan make_attn_plan(const adaspec_attn_dims &d, AttnKind kind);
+AttnPlan make_attn_plan(const adaspec_attn_dims &d, AttnKind kind, bool tree);
 bool attn_fast_path_supported(const adaspec_attn_dims &d);
 
 struct AttnArgs {
@@ -84,7 +84,7 @@ struct AttnArgs {
     int sched_cus = 1;        // compute units of the device
     int n_row_groups = 1;     // units per (item, kv head)
     int rows_per_group = 16;  // query rows (times G) one unit covers
-    bool direct = false;      // plan.direct and a chain call
+    bool direct = false;      // plan.direct
 };
 
 inline DirectArgs direct_args(const AttnArgs &a)

@@ -93,12 +93,12 @@ static int validate_attn_dims(const adaspec_attn_dims *d)
 }
 
 // Direct calls (no metadata kernel): at most this many requests (the combine kernel finds a row's request with one scan
-// of four per lane) and possible units.  Up to one unit per compute unit there is nothing to balance; with 512 units the
-// schedule, which pairs long and short units on a compute unit, is worth its kernel (64 requests of 1024-2048 tokens,
-// 8 kv heads: 79.5 us per layer with it, 82.9 us direct).
+// of four per lane) and possible units.  Up to one unit per compute unit there is nothing to balance; with 512 units of
+// many requests the schedule, which pairs long and short units on a compute unit, is worth its kernel (64 requests of
+// 1024-2048 tokens, 8 kv heads: 79.5 us per layer with it, 82.9 us direct), with 512 of a few requests it is not.
 constexpr int kDirectMaxBatch = 256;
-constexpr int kDirectMaxUnits = 256;
-constexpr int kDirectShortCtx = 512, kDirectShortBatch = 1024;
+constexpr int kDirectMaxUnits = 256, kDirectFewPairs = 128, kDirectMaxUnitsFew = 512;
+constexpr int kDirectShortCtx = 512, kDirectLongestShort = 1024, kDirectShortBatch = 1024;
 constexpr int kWavesPerUnit = 4;
 
 AttnKind attn_kind(const adaspec_attn_dims &d)
@@ -114,7 +114,7 @@ AttnKind attn_kind(const adaspec_attn_dims &d)
     return AttnKind::kVector;
 }
 
-AttnPlan make_attn_plan(const adaspec_attn_dims &d, AttnKind kind)
+AttnPlan make_attn_plan(const adaspec_attn_dims &d, AttnKind kind, bool tree)
 {
     AttnPlan p;
     const int G = d.n_q_heads / d.n_kv_heads;
@@ -134,29 +134,36 @@ AttnPlan make_attn_plan(const adaspec_attn_dims &d, AttnKind kind)
     const int64_t max_ctx = (int64_t)d.max_pages_per_req * d.page_size;
     p.max_rows = (d.max_spec_len + 1) * G;
     p.direct = false;
-    if (scheduled && d.batch <= kDirectMaxBatch) {
+    const int n_groups = attn_row_groups(p.max_rows);
+    if (scheduled && !tree && d.batch <= kDirectMaxBatch) {
         // Small batches: the shortest split (two blocks per wavefront or more: with one, the workspace and the work of the
-        // combine double and the call gets no faster) with which every possible unit has a compute unit of its own.
-        // Such a call needs no metadata kernel.  MI355X, 4 layers of one request of 1500 tokens: 91 -> 84 us.
-        const int64_t per_item = (int64_t)d.n_kv_heads * attn_row_groups((d.max_spec_len + 1) * G);
-        for (int s = 2 * kWavesPerUnit * p.block_tokens; s <= 2048 && !p.direct; s *= 2)
-            if (d.batch * ((max_ctx + s - 1) / s) * per_item <= kDirectMaxUnits) {
+        // combine double and the call gets no faster) with which every possible unit has a compute unit of its own, or half
+        // of one where there are few (request, kv head) pairs.  Such a call needs no metadata kernel.  What is possible
+        // follows from the width of the block table, which a server makes as wide as its longest request: it must not
+        // decide how coarsely contexts are cut, so the split is never longer than the one above (or those two blocks); longer
+        // ones also sum longer in fp32 (one request of 64000 tokens in f16: error of the output 1.79e-4, 2.05e-4 in splits of
+        // 2048).
+        // MI355X, one request of 1500 tokens, 6 rows, 32/8 heads of 128, tables of 1.5K / 16K / 32K / 64K tokens: 11.2 /
+        // 11.1 / 15.4 / 15.4 us (metadata first: 17.2; splits of up to 2048 to stay direct: 11.2 / 13.2 / 15.1 / 20.5);
+        // 16000 tokens under 16K: 22.6 (35.1 with metadata).  With 1024 possible units for few pairs full tables lose
+        // (4 requests of 8000 under 8K: 30.2 -> 39.3).
+        const int shortest = 2 * kWavesPerUnit * p.block_tokens, longest = p.split_tokens > shortest ? p.split_tokens : shortest;
+        const int most = pairs < kDirectFewPairs ? kDirectMaxUnitsFew : kDirectMaxUnits;
+        for (int s = shortest; s <= longest && !p.direct; s *= 2)
+            if (d.batch * ((max_ctx + s - 1) / s) * d.n_kv_heads * n_groups <= most) {
                 p.direct = true;
                 p.split_tokens = s;
             }
     }
-    if (scheduled && !p.direct && max_ctx <= 2 * kDirectShortCtx && d.batch <= kDirectShortBatch) {
+    if (scheduled && !tree && !p.direct && max_ctx <= p.split_tokens && max_ctx <= kDirectLongestShort && d.batch <= kDirectShortBatch) {
         // Short contexts: every request is one unit per kv head (no combine), all of them about equally short.  Measured
         // with and without (MI355X, 32/8 heads of 128, bf16): 256 requests of 100-500 tokens 62.6 / 65.5 us, 126 of 119-185
         // 14.0 / 18.5, 64 of 512-1000 39.5 / 42.3, 128 of 256-1000 64.6 / 63.4 (left to the schedule).  The row-split and
         // the fp32 kernel lose more by not loading across unit boundaries (200 requests of 100-400 tokens, 72 rows per
         // kv head: 104 / 87; 88 of 9-30 tokens, 40 rows: 12.4 / 19.2): up to 1024 possible tokens per compute unit.
-        const int64_t units = d.batch * (int64_t)d.n_kv_heads * attn_row_groups((d.max_spec_len + 1) * G);
-        const bool deep = kind == AttnKind::kMfmaF32 || (kind == AttnKind::kMfma128 && attn_row_tiles((d.max_spec_len + 1) * G) > 2);
-        if (deep ? units * max_ctx <= 262144 : units <= (max_ctx <= kDirectShortCtx ? 8192 : 512)) {
-            p.direct = true;
-            p.split_tokens = 2 * kDirectShortCtx;
-        }
+        const int64_t units = pairs * n_groups;
+        const bool deep = kind == AttnKind::kMfmaF32 || (kind == AttnKind::kMfma128 && attn_row_tiles(p.max_rows) > 2);
+        p.direct = deep ? units * max_ctx <= 262144 : units <= (max_ctx <= kDirectShortCtx ? 8192 : 512);
     }
     const int64_t per_req = (max_ctx + p.split_tokens - 1) / p.split_tokens;
     p.per_req = (int)per_req;
@@ -180,6 +187,13 @@ AttnPlan make_attn_plan(const adaspec_attn_dims &d, AttnKind kind)
     off = align_up(off + (size_t)p.max_items * d.n_kv_heads * p.max_rows * d.head_dim * sizeof(float), 256);
     p.total_bytes = off;
     return p;
+}
+
+// chain and tree calls of the same dims ask for the same workspace
+static size_t attn_workspace_bytes(const adaspec_attn_dims &d, AttnKind kind)
+{
+    const size_t chain = make_attn_plan(d, kind, false).total_bytes, tree = make_attn_plan(d, kind, true).total_bytes;
+    return chain > tree ? chain : tree;
 }
 
 static int validate_accept_dims(const adaspec_accept_dims *d)
@@ -241,7 +255,7 @@ extern "C" {
 size_t adaspec_verify_attn_workspace_bytes(const adaspec_attn_dims *dims)
 {
     if (validate_attn_dims(dims) != ADASPEC_OK) return 0;
-    return make_attn_plan(*dims, attn_kind(*dims)).total_bytes;
+    return attn_workspace_bytes(*dims, attn_kind(*dims));
 }
 
 // chain (parents == NULL, tree == false) and tree verification share everything but the mask
@@ -264,8 +278,8 @@ static int verify_attn_impl(const void *q, const void *k_pages, const void *v_pa
         return ADASPEC_ERR_ALIGN;
     AttnArgs a;
     const AttnKind kind = attn_kind(*dims);
-    a.plan = make_attn_plan(*dims, kind);
-    if (workspace_bytes < a.plan.total_bytes) return ADASPEC_ERR_WORKSPACE;
+    a.plan = make_attn_plan(*dims, kind, tree);
+    if (workspace_bytes < attn_workspace_bytes(*dims, kind)) return ADASPEC_ERR_WORKSPACE;
     a.q = q; a.k_pages = k_pages; a.v_pages = v_pages;
     a.block_table = block_table; a.ctx_lens = ctx_lens; a.spec_lens = spec_lens;
     a.parents = tree ? parents : nullptr;
@@ -274,7 +288,7 @@ static int verify_attn_impl(const void *q, const void *k_pages, const void *v_pa
     const float scale = dims->scale > 0.0f ? dims->scale : 1.0f / sqrtf((float)dims->head_dim);
     a.scale_log2 = scale * 1.4426950408889634f;
 
-    a.direct = a.plan.direct && !tree;
+    a.direct = a.plan.direct;
     if (kind != AttnKind::kVector) attn_mfma_shape(a, kind);
     if (dims->plan_mode != ADASPEC_PLAN_REUSE && !a.direct) {
         if (launch_attn_plan(a) != hipSuccess) return ADASPEC_ERR_HIP;

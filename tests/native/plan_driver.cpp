@@ -1,0 +1,22 @@
+// Prints the attention plan of every line of "batch max_pages_per_req n_q_heads n_kv_heads head_dim max_spec_len dtype"
+// read from standard input: split and direct flag of a chain call, of a tree call, bytes of both and of the query.
+#include <cstdio>
+
+#include "../../paper_2503_05096_amd/csrc/adaspec_internal.h"
+
+int main()
+{
+    adaspec_attn_dims d = {};
+    d.page_size = 16;
+    d.num_pages = 1;
+    while (scanf("%d %d %d %d %d %d %d", &d.batch, &d.max_pages_per_req, &d.n_q_heads, &d.n_kv_heads, &d.head_dim, &d.max_spec_len,
+                 &d.dtype) == 7) {
+        d.out_dtype = d.dtype;
+        d.total_q = d.batch * (d.max_spec_len + 1);
+        const adaspec::AttnKind kind = adaspec::attn_kind(d);
+        const adaspec::AttnPlan chain = adaspec::make_attn_plan(d, kind, false), tree = adaspec::make_attn_plan(d, kind, true);
+        printf("%d %d %d %d %d %zu %zu %zu\n", chain.split_tokens, (int)chain.direct, tree.split_tokens, (int)tree.direct,
+               chain.block_tokens, chain.total_bytes, tree.total_bytes, adaspec_verify_attn_workspace_bytes(&d));
+    }
+    return 0;
+}

@@ -1,0 +1,48 @@
+"""How the host cuts an attention call into splits (make_attn_plan), through a small program linked with the library: no
+GPU needed."""
+import itertools
+import os
+import subprocess
+
+import pytest
+
+from paper_2503_05096_amd import build
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.fixture(scope="module")
+def plans(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("plan") / "plan_driver")
+    lib = os.path.dirname(build.LIB_PATH)
+    subprocess.check_call(["g++", "-O1", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I", "/opt/rocm/include", "-I", build.INCLUDE,
+                           os.path.join(ROOT, "tests", "native", "plan_driver.cpp"),
+                           "-o", exe, build.LIB_PATH, f"-Wl,-rpath,{lib}"])
+
+    def run(cases):
+        text = "\n".join(" ".join(map(str, c)) for c in cases)
+        lines = subprocess.run([exe], input=text, capture_output=True, text=True, check=True).stdout.splitlines()
+        assert len(lines) == len(cases)
+        return [tuple(map(int, l.split())) for l in lines]
+    return run
+
+
+F32, BF16 = 0, 2
+
+
+def test_the_width_of_the_block_table_does_not_lengthen_splits(plans):
+    """The length of a split follows from the number of (request, kv head) pairs; calls without a metadata kernel may take
+    a shorter one, down to two blocks per wavefront, but never a longer one, however wide the table; trees always take it."""
+    heads = [(32, 8, 128, BF16), (64, 8, 128, BF16), (16, 2, 128, BF16), (32, 32, 128, BF16), (32, 8, 64, BF16), (8, 8, 64, F32)]
+    cases = [(B, pages, hq, hkv, d, k, dt) for B, pages, k, (hq, hkv, d, dt) in
+             itertools.product((1, 2, 3, 4, 8, 20, 33, 70, 200, 256, 257, 1024), (1, 8, 32, 33, 64, 65, 94, 512, 1024, 2048, 4096), (0, 5, 11), heads)]
+    direct_calls = 0
+    for c, (split, direct, tree_split, tree_direct, block, chain_bytes, tree_bytes, asked) in zip(cases, plans(cases)):
+        pairs = c[0] * c[3]
+        by_pairs = 2048 if pairs >= 256 else 1024 if pairs >= 128 else 512 if pairs >= 32 else 256
+        two_blocks = 2 * 4 * block
+        assert (tree_split, tree_direct) == (by_pairs, 0), c
+        assert split <= max(by_pairs, two_blocks) if direct else split == by_pairs, (c, split)
+        assert asked == max(chain_bytes, tree_bytes), c          # one query serves chains and trees
+        direct_calls += direct
+    assert direct_calls > len(cases) // 8
