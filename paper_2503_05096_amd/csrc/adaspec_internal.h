@@ -114,6 +114,7 @@ int attn_d64_grid_slots(const AttnArgs &a, int cus);
 hipError_t launch_attn_f32(const AttnArgs &a);
 int attn_f32_grid_slots(const AttnArgs &a, int cus);
 hipError_t launch_attn_combine(const AttnArgs &a);
+int attn_combine_waves(const AttnPlan &p, const adaspec_attn_dims &d);   // wavefronts per (row, head) of the combine kernel
 
 // ---- accept workspace ------------------------------------------------------
 struct AcceptPlan {

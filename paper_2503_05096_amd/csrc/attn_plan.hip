@@ -267,9 +267,8 @@ hipError_t launch_attn_plan(const AttnArgs &a)
 //
 // kDirect: no metadata kernel has run; the wavefront finds its row's request from the lengths (up to 256 requests, four
 // per lane), and the splits of request i are the items i * per_req, i * per_req + 1, ...
-// kW: wavefronts per (row, head): 1, or 4 where a request can have more than 8 splits (a wavefront takes every fourth
-// split and the four states are merged through LDS), so that the number of dependent memory round trips stays at one or
-// two (12 splits of one request, 192 (row, head) pairs: 3.9 us, what the kernel takes for 6 splits with one wavefront).
+// kW: wavefronts per (row, head), 1 or 4 (a wavefront takes every fourth split and the four states are merged through LDS,
+// so that the number of dependent memory round trips stays at one or two; see attn_combine_waves).
 template <bool kDirect, int kW>
 __global__ __launch_bounds__(256) void attn_combine_kernel(
     const int32_t *__restrict__ row_rec, const float *__restrict__ part_ml,
@@ -380,6 +379,17 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(
     }
 }
 
+// Four wavefronts per (row, head) where a request can have more than 8 splits and there are at most three pairs per
+// compute unit: 12 splits of one request, 192 pairs: 3.9 us, what the kernel takes for 6 splits with one wavefront.  How
+// many splits are possible follows from the width of the block table; with more pairs than that the additional wavefronts,
+// most of which find no split, cost more than they save.  MI355X, whole calls, bf16, a table of 32K tokens, one wavefront /
+// four: 32/8 heads, 1 request of 6000 tokens (192 pairs) 20.5 / 18.4 us, 4 (768) 31.1 / 31.7, 8 (1536) 46.3 / 48.9, 64
+// (12288) 287 / 296; 64/8 heads, 2 of 6000 (768) 32.0 / 29.4, 4 of 1500 (1536) 29.3 / 30.1, 128 of 1500 (49152) 151 / 158.
+int attn_combine_waves(const AttnPlan &p, const adaspec_attn_dims &d)
+{
+    return p.per_req > 8 && (int64_t)d.total_q * d.n_q_heads <= 768 ? 4 : 1;
+}
+
 hipError_t launch_attn_combine(const AttnArgs &a)
 {
     const AttnPlan &p = a.plan;
@@ -395,7 +405,7 @@ hipError_t launch_attn_combine(const AttnArgs &a)
                            a.dims.n_kv_heads, a.dims.head_dim, p.max_rows, a.dims.out_dtype, direct_args(a));
     };
     auto with_waves = [&](auto direct) {
-        if (p.per_req > 8) launch(direct, std::integral_constant<int, 4>{});
+        if (attn_combine_waves(p, a.dims) == 4) launch(direct, std::integral_constant<int, 4>{});
         else launch(direct, std::integral_constant<int, 1>{});
     };
     if (a.direct) with_waves(std::true_type{});

@@ -1,5 +1,6 @@
 // Prints the attention plan of every line of "batch max_pages_per_req n_q_heads n_kv_heads head_dim max_spec_len dtype"
-// read from standard input: split and direct flag of a chain call, of a tree call, bytes of both and of the query.
+// read from standard input: split and direct flag of a chain call, of a tree call, tokens per block, bytes of
+// both and of the query, wavefronts per row of the chain's combine kernel.
 #include <cstdio>
 
 #include "../../paper_2503_05096_amd/csrc/adaspec_internal.h"
@@ -15,8 +16,8 @@ int main()
         d.total_q = d.batch * (d.max_spec_len + 1);
         const adaspec::AttnKind kind = adaspec::attn_kind(d);
         const adaspec::AttnPlan chain = adaspec::make_attn_plan(d, kind, false), tree = adaspec::make_attn_plan(d, kind, true);
-        printf("%d %d %d %d %d %zu %zu %zu\n", chain.split_tokens, (int)chain.direct, tree.split_tokens, (int)tree.direct,
-               chain.block_tokens, chain.total_bytes, tree.total_bytes, adaspec_verify_attn_workspace_bytes(&d));
+        printf("%d %d %d %d %d %zu %zu %zu %d\n", chain.split_tokens, (int)chain.direct, tree.split_tokens, (int)tree.direct,
+               chain.block_tokens, chain.total_bytes, tree.total_bytes, adaspec_verify_attn_workspace_bytes(&d), adaspec::attn_combine_waves(chain, d));
     }
     return 0;
 }

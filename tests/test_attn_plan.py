@@ -37,7 +37,7 @@ def test_the_width_of_the_block_table_does_not_lengthen_splits(plans):
     cases = [(B, pages, hq, hkv, d, k, dt) for B, pages, k, (hq, hkv, d, dt) in
              itertools.product((1, 2, 3, 4, 8, 20, 33, 70, 200, 256, 257, 1024), (1, 8, 32, 33, 64, 65, 94, 512, 1024, 2048, 4096), (0, 5, 11), heads)]
     direct_calls = 0
-    for c, (split, direct, tree_split, tree_direct, block, chain_bytes, tree_bytes, asked) in zip(cases, plans(cases)):
+    for c, (split, direct, tree_split, tree_direct, block, chain_bytes, tree_bytes, asked, _) in zip(cases, plans(cases)):
         pairs = c[0] * c[3]
         by_pairs = 2048 if pairs >= 256 else 1024 if pairs >= 128 else 512 if pairs >= 32 else 256
         two_blocks = 2 * 4 * block
@@ -46,3 +46,11 @@ def test_the_width_of_the_block_table_does_not_lengthen_splits(plans):
         assert asked == max(chain_bytes, tree_bytes), c          # one query serves chains and trees
         direct_calls += direct
     assert direct_calls > len(cases) // 8
+
+
+def test_the_width_of_the_block_table_does_not_multiply_the_combine(plans):
+    """Several wavefronts per (row, head) only while they fit the device beside each other."""
+    cases = [(B, pages, 32, 8, 128, k, BF16) for B in (1, 4, 5, 64, 256) for pages in (32, 128, 129, 2048) for k in (0, 5)]
+    for c, p in zip(cases, plans(cases)):
+        possible, pairs = -(-c[1] * 16 // p[0]), c[0] * (c[5] + 1) * c[2]
+        assert p[8] == (4 if possible > 8 and pairs <= 768 else 1), (c, p)
