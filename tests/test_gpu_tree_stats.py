@@ -32,3 +32,32 @@ def test_tree_accept_many_nodes(B, V, oracle_mod, pkg):  # noqa: F811
 
 def test_tree_accept_masked_rows(oracle_mod, pkg):  # noqa: F811
     _check_tree_accept(_tree([4, 2, 6], 16392, "bf16", [0.9, 1.0, 0.0], masked_frac=0.95), oracle_mod, pkg)
+
+
+@pytest.mark.parametrize("dtype", ["bfloat16", "float16"])
+@pytest.mark.parametrize("T,offset", [(0.8, 60.0), (0.8, -60.0), (1.0, -40.0), (1.0, 0.0)])
+def test_tree_accept_turns_where_the_ratio_is(dtype, T, offset, pkg):  # noqa: F811
+    """One child per root, uniforms a hair below and above p / q: logits far from zero must not move p.
+
+    Bound: the argument of the exponential, (l - m) / T * log2(e) of magnitude at most 8, is rounded twice (2.4e-7 each, times
+    ln 2); exponential, reciprocal of the normaliser, product and quotient 1.2e-7 at most each, of which two are half that;
+    fp32 sums of 32 terms in the normaliser 1e-7; the uniform 6e-8: 1e-6 in all. Tested 1.3e-6 away from the ratio."""
+    import torch
+    B, V = 256, 8192
+    dt = getattr(torch, dtype)
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    logits = (3.0 * torch.randn((2 * B, V), generator=gen, device="cuda") + offset).to(dt)
+    p = torch.softmax(logits[0::2].double() / T, dim=1)
+    i = torch.arange(B, device="cuda")
+    x = p.topk(8, dim=1).indices[i, i % 8]
+    q = torch.zeros((B, V), dtype=dt, device="cuda")
+    q[i, x] = (p[i, x] / 0.7).to(dt)
+    ratio = p[i, x] / q[i, x].double()
+    parents = torch.tensor([-1, 0] * B, dtype=torch.int32, device="cuda")
+    spec, temp = torch.ones(B, dtype=torch.int32, device="cuda"), torch.full((B,), T, device="cuda")
+    for side in (-1.3e-6, 1.3e-6):
+        uni = torch.zeros((2 * B, 2), device="cuda")
+        uni[0::2, 0] = (ratio * (1.0 + side)).float()
+        accepted = pkg.accept_tree(logits, q, x.int(), parents, uni, spec, temp, max_spec_len=1)[1]
+        torch.cuda.synchronize()
+        assert int((accepted == 1).sum()) == (B if side < 0 else 0), side
