@@ -203,7 +203,7 @@ __global__ __launch_bounds__(256, (RT <= 2 ? 2 : 1)) void attn_d64_kernel(
         f32x4 o[RT][4];
 #pragma unroll
         for (int nt = 0; nt < RT; ++nt) {
-            m[nt] = kNegBig; lsum[nt] = 0.f;
+            m[nt] = kLowestRef; lsum[nt] = 0.f;
 #pragma unroll
             for (int dt = 0; dt < 4; ++dt) o[nt][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
         }
@@ -272,13 +272,10 @@ __global__ __launch_bounds__(256, (RT <= 2 ? 2 : 1)) void attn_d64_kernel(
 #pragma unroll
                     for (int dt = 0; dt < 4; ++dt) o[nt][dt] *= alpha;
                 }
-                const float m_ref = m[nt] - WeightSplit<T>::kShiftLog2;
+                softmax_weights<16>(p[nt], scale_log2, m[nt], WeightSplit<T>::kShiftLog2);
                 float psum = 0.f;
 #pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    p[nt][e] = __builtin_amdgcn_exp2f(fmaf(p[nt][e], scale_log2, -m_ref));
-                    psum += p[nt][e];
-                }
+                for (int e = 0; e < 16; ++e) psum += p[nt][e];
                 lsum[nt] += psum;
             }
 

@@ -153,7 +153,7 @@ __global__ __launch_bounds__(256, (RT <= 2 ? 2 : 1)) void attn_f32_kernel(
         f32x4 o[RT][kH][4];
 #pragma unroll
         for (int nt = 0; nt < RT; ++nt) {
-            m[nt] = kNegBig; lsum[nt] = 0.f;
+            m[nt] = kLowestRef; lsum[nt] = 0.f;
 #pragma unroll
             for (int h = 0; h < kH; ++h)
 #pragma unroll
@@ -219,8 +219,7 @@ __global__ __launch_bounds__(256, (RT <= 2 ? 2 : 1)) void attn_f32_kernel(
 #pragma unroll
                         for (int e = 0; e < 4; ++e) o[nt][h][e] *= alpha;
                 }
-#pragma unroll
-                for (int e = 0; e < 4; ++e) p[nt][e] = __builtin_amdgcn_exp2f(fmaf(p[nt][e], scale_log2, -m[nt]));
+                softmax_weights<4>(p[nt], scale_log2, m[nt], 0.f);
                 lsum[nt] += (p[nt][0] + p[nt][1]) + (p[nt][2] + p[nt][3]);
             }
 

@@ -21,6 +21,30 @@ constexpr int kORowStride = 132;        // floats per row of the merge buffer (p
 constexpr float kNegBig = -1.0e30f;     // "no token seen yet": finite, so differences never give NaN
 constexpr float kLazyLog2 = 8.0f;       // a row's softmax reference trails its running maximum by at most this (log2 units)
 
+// ---- scores of any size (attn_d64.hip, attn_f32.hip) ------------------------------------------------------------------
+// 2^(p scale - m + shift) of N scores, in place.  One multiply-add per score as long as that is no further
+// off than the difference of the rounded products; where the reference m is so large that its own rounding would be a
+// visible factor (and from 2^31 on one that overflows), the products are rounded as m was and subtracted.
+constexpr float kLowestRef = -3.4028235e38f;    // "no token seen yet": below every finite score, and finite itself
+constexpr float kLargeRef = 1048576.f;
+template <int N, class P>
+__device__ __forceinline__ void softmax_weights(P &p, float scale_log2, float m, float shift)
+{
+    const bool large = fabsf(m) > kLargeRef && m > kLowestRef;
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(large) != 0, 0)) {
+#pragma clang fp contract(off)
+#pragma unroll
+        for (int e = 0; e < N; ++e) {
+            const float t = p[e] * scale_log2;
+            p[e] = __builtin_amdgcn_exp2f((t - m) + shift);
+        }
+    } else {
+        const float m_ref = m - shift;
+#pragma unroll
+        for (int e = 0; e < N; ++e) p[e] = __builtin_amdgcn_exp2f(fmaf(p[e], scale_log2, -m_ref));
+    }
+}
+
 template <class T> struct Mma;
 template <> struct Mma<BF16> {
     // bf16 keeps 8 significant bits: a softmax weight rounded to it is off by up to 2^-9 relative,

@@ -40,3 +40,28 @@ def test_tree_attention_f32_edges(hq, hkv, d, oracle_mod, pkg):  # noqa: F811
                             acceptance=False, name=f"f32-tree-d{d}")
     W.attach_tree(st, max_width=4)
     _check_tree_attention(st, oracle_mod, pkg)
+
+
+@pytest.mark.parametrize("d,dtype", [(64, "f32"), (128, "f32"), (64, "bf16"), (64, "f16")])
+@pytest.mark.parametrize("kind", ["equal and negative", "equal and positive", "far apart"])
+@pytest.mark.parametrize("tree", [False, True])
+def test_attention_of_very_large_scores(kind, d, dtype, tree, oracle_mod, pkg):  # noqa: F811
+    """Scores at the far ends of the storage type (f16: 4e10 in the exponent's units): equal ones average the values, others
+    pick the largest, as in the vector kernel and in 64 bits; both these kernels and the head_dim 64 ones."""
+    import numpy as np
+    from workloads.verify_step import _store, to_f64
+    st = W.make_custom_step(77, ctx_lens=[1, 17, 130, 700, 300], spec_lens=[0, 2, 5, 3, 1], n_q_heads=8, n_kv_heads=2, head_dim=d,
+                            dtype=dtype, acceptance=False, name=f"large-{dtype}-d{d}")
+    big_q, big_k = {"f32": (1e16, 1e16), "bf16": (1e16, 1e16), "f16": (6e4, 6e4)}[dtype]
+    if kind == "far apart":
+        q, k = to_f64(st.q, dtype), to_f64(st.k_pages, dtype)
+        f = {"f32": 1e7, "bf16": 1e7, "f16": 3e3}[dtype]
+        q, k = np.clip(q * f, -big_q, big_q), np.clip(k * f, -big_k, big_k)
+    else:
+        q, k = np.full(st.q.shape, big_q), np.full(st.k_pages.shape, big_k if kind == "equal and positive" else -big_k)
+    st.q, st.k_pages = _store(q.astype(np.float32), dtype), _store(k.astype(np.float32), dtype)
+    if tree:
+        W.attach_tree(st, max_width=2)
+        _check_tree_attention(st, oracle_mod, pkg)
+    else:
+        check_attention(st, oracle_mod, pkg)
