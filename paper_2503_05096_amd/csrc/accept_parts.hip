@@ -129,7 +129,7 @@ __device__ __forceinline__ bool part_max_and_norm(uint4 (&lg)[STEPS], float c, f
     const float mt = thread_max<LT, STEPS>(lg);
     float zt = 0.f;
     if (mt > -INFINITY) {
-        const float mtc = mt * c;
+        const float mtc = scaled_ref(mt, c);
 #pragma unroll
         for (int it = 0; it < STEPS; ++it) {
             keep_packed(lg[it]);
@@ -140,7 +140,7 @@ __device__ __forceinline__ bool part_max_and_norm(uint4 (&lg)[STEPS], float c, f
         }
     }
     const float mw = wave_max(mt);
-    const double zw = wave_sum(mt > -INFINITY ? (double)(zt * __builtin_amdgcn_exp2f((mt - mw) * c)) : 0.0);
+    const double zw = wave_sum(mt > -INFINITY ? (double)(zt * __builtin_amdgcn_exp2f(ref_gap<LT>(mt, mw, c))) : 0.0);
     if (lane == 0) { s_m[wv] = mw; s_z[wv] = zw; }
     lds_barrier();
     float m = s_m[0];
@@ -149,7 +149,7 @@ __device__ __forceinline__ bool part_max_and_norm(uint4 (&lg)[STEPS], float c, f
     double z = 0.0;
 #pragma unroll
     for (int w = 0; w < kQW; ++w)
-        z += s_m[w] > -INFINITY ? s_z[w] * (double)__builtin_amdgcn_exp2f((s_m[w] - m) * c) : 0.0;
+        z += s_m[w] > -INFINITY ? s_z[w] * (double)__builtin_amdgcn_exp2f(ref_gap<LT>(s_m[w], m, c)) : 0.0;
     m_out = m; z_out = z;
     return m > -INFINITY;
 }
@@ -277,7 +277,7 @@ __global__ __launch_bounds__(kQT, kStatWgsPerCu) void accept_rowparts_kernel(
     }
     const float c = 1.4426950408889634f / T;
     const PartStream st = stream_part<LT, true, false, kAuxStream>(rl, row_chunks, n_parts, h, V, c, tid, leave_slot);
-    const HalfStat out = reduce_norm(st, c, s_m, s_z, lane, wv);
+    const HalfStat out = reduce_norm<LT>(st, c, s_m, s_z, lane, wv);
     if (tid == 0) *my_stat = out;
     ADASPEC_STAMP(0, 3);
 }
@@ -292,6 +292,7 @@ __device__ __forceinline__ void load_row_parts(const HalfStat *__restrict__ st, 
         if (p < n_parts) s[p] = st[p];
     }
 }
+template <class LT>
 __device__ __forceinline__ RowMerge merge_row_parts(const HalfStat (&s)[kStatParts], float c, bool greedy)
 {
     RowMerge out;
@@ -310,7 +311,7 @@ __device__ __forceinline__ RowMerge merge_row_parts(const HalfStat (&s)[kStatPar
     for (int p = 1; p < kStatParts; ++p) m = fmaxf(m, s[p].m);
 #pragma unroll
     for (int p = 0; p < kStatParts; ++p)
-        out.Z += s[p].m > -INFINITY ? s[p].Z * (double)__builtin_amdgcn_exp2f((s[p].m - m) * c) : 0.0;
+        out.Z += s[p].m > -INFINITY ? s[p].Z * (double)__builtin_amdgcn_exp2f(ref_gap<LT>(s[p].m, m, c)) : 0.0;
     out.m = m;
     return out;
 }
@@ -373,10 +374,10 @@ __global__ __launch_bounds__(kQT, sizeof(typename PT::storage) > sizeof(typename
                     rec = slot_rec[slot];
                     load_row_parts(part_stat + slot * kStatParts, n_stat_parts, parts);
                 }
-                mine = merge_row_parts(parts, c, !sampled);
+                mine = merge_row_parts<LT>(parts, c, !sampled);
                 if (sampled) {
                     const float lx = __uint_as_float(rec.lx_bits), qx = __uint_as_float(rec.qx_bits);
-                    const float px = exp_weight<LT>(lx, mine.m, c, mine.m * c) * (float)(1.0 / mine.Z);
+                    const float px = exp_weight<LT>(lx, mine.m, c, scaled_ref(mine.m, c)) * (float)(1.0 / mine.Z);
                     flag = (qx > 0.f) ? (__uint_as_float(rec.u0_bits) < px / qx) : 1;
                 } else {
                     flag = rec.x == mine.arg;
@@ -455,7 +456,7 @@ __global__ __launch_bounds__(kQT, sizeof(typename PT::storage) > sizeof(typename
         if (bonus) any = part_max_and_norm<LT, kSumSteps>(lg, c, s_m, s_z, lane, wv, m, Zd);
         double res = 0.0, prob = 0.0;
         if (any) {
-            const float mc = m * c, invZ = (float)(1.0 / Zd);
+            const float mc = scaled_ref(m, c), invZ = (float)(1.0 / Zd);
 #pragma unroll
             for (int it = 0; it < kSumSteps; ++it) {
                 float rv[kN], pv[kN], acc_r = 0.f, acc_p = 0.f;
@@ -522,7 +523,7 @@ __global__ __launch_bounds__(kQT, sizeof(typename PT::storage) > sizeof(typename
     for (int w = 1; w < kQW; ++w) M = fmaxf(M, (float)s_pair.wave[w]);
     // p_v of part h was computed as 2^((l_v - m_h) c) / Z_h: times Z_h 2^((m_h - M) c) it is relative to M in
     // every part (a rejected draft row has the same (m, Z) in all parts: a common factor, which tau absorbs)
-    const double my_sc = st.m > -INFINITY ? st.Z * (double)__builtin_amdgcn_exp2f((st.m - M) * c) : 0.0;
+    const double my_sc = st.m > -INFINITY ? st.Z * (double)__builtin_amdgcn_exp2f(ref_gap<LT>(st.m, M, c)) : 0.0;
 #pragma unroll
     for (int u = 0; u < 2; ++u) { res[u] *= my_sc; pm[u] *= my_sc; }
     bool use_p = bonus;                                       // (for a bonus row the two sums are the same numbers)
@@ -543,7 +544,7 @@ __global__ __launch_bounds__(kQT, sizeof(typename PT::storage) > sizeof(typename
     const int hh = pair / kQW;
     HalfStat sth;
     sth.m = s_m[hh]; sth.Z = s_z[hh];
-    const double sch = sth.m > -INFINITY ? sth.Z * (double)__builtin_amdgcn_exp2f((sth.m - M) * c) : 0.0;
+    const double sch = sth.m > -INFINITY ? sth.Z * (double)__builtin_amdgcn_exp2f(ref_gap<LT>(sth.m, M, c)) : 0.0;
     const int chunk = hh * kSumChunks + ((pair % kQW) * kSumSteps + wv) * kWave + lane;   // this lane's chunk of the row
     const bool with_q = has_q && !use_p;
     uint4 lv = make_uint4(0, 0, 0, 0);
@@ -555,7 +556,7 @@ __global__ __launch_bounds__(kQT, sizeof(typename PT::storage) > sizeof(typename
     }
     Chunk<LT>::blank(lv, chunk >= row_chunks);
     float rv[kN], pv[kN], mine32 = 0.f;
-    part_chunk_masses<LT, PT>(lv, qv, sth.m, c, sth.m * c, (float)(1.0 / sth.Z), rv, pv);   // same expressions as the sums
+    part_chunk_masses<LT, PT>(lv, qv, sth.m, c, scaled_ref(sth.m, c), (float)(1.0 / sth.Z), rv, pv);   // same expressions as the sums
 #pragma unroll
     for (int e = 0; e < kN; ++e) {
         if (use_p) rv[e] = pv[e];

@@ -83,7 +83,7 @@ __global__ __launch_bounds__(kGT) void draft_fast_kernel(
     // maximum 0) is redone with the exact float maximum.
     const float c2 = greedy ? 1.4426950408889634f : 1.4426950408889634f / T;
     short2v pm = {0, 0};
-    float m_run = 0.f, zt = 0.f;
+    float m_run = 0.f, ref = 0.f, zt = 0.f;           // zt is relative to ref = scaled_ref(m_run, c2)
 #pragma unroll
     for (int it = 0; it < ITER; ++it) {
         if (it + kLPre < ITER) lg[it + kLPre] = load_chunk(it + kLPre);
@@ -93,9 +93,10 @@ __global__ __launch_bounds__(kGT) void draft_fast_kernel(
 #pragma unroll
         for (int e = 0; e < 4; ++e) pm = __builtin_elementwise_max(pm, __builtin_bit_cast(short2v, w[e]));
         const float mn = P::lo((uint32_t)(uint16_t)max(pm.x, pm.y));
-        zt *= __builtin_amdgcn_exp2f((m_run - mn) * c2);
+        const float mnc = scaled_ref(mn, c2);
+        zt *= __builtin_amdgcn_exp2f(ref - mnc);
         m_run = mn;
-        const float mnc = mn * c2;
+        ref = mnc;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             zt += __builtin_amdgcn_exp2f(fmaf(P::lo(w[e]), c2, -mnc));
@@ -106,7 +107,7 @@ __global__ __launch_bounds__(kGT) void draft_fast_kernel(
     }
     {
         const float mw = wave_max(m_run);
-        const float zw = wave_sum(zt * __builtin_amdgcn_exp2f((m_run - mw) * c2));
+        const float zw = wave_sum(zt * __builtin_amdgcn_exp2f(ref - scaled_ref(mw, c2)));
         if (lane == 0) { sm.wm[wv] = mw; sm.wz[wv] = zw; }
     }
     __syncthreads();
@@ -115,7 +116,7 @@ __global__ __launch_bounds__(kGT) void draft_fast_kernel(
     for (int w = 1; w < kGW; ++w) m = fmaxf(m, sm.wm[w]);
     double Zd = 0.0;
 #pragma unroll
-    for (int w = 0; w < kGW; ++w) Zd += (double)(sm.wz[w] * __builtin_amdgcn_exp2f((sm.wm[w] - m) * c2));
+    for (int w = 0; w < kGW; ++w) Zd += (double)(sm.wz[w] * __builtin_amdgcn_exp2f(scaled_ref(sm.wm[w], c2) - scaled_ref(m, c2)));
     if (m == 0.f) {                           // rare: no positive logit in the row -> exact two-sweep form
         float mt = -INFINITY;
 #pragma unroll
@@ -133,7 +134,7 @@ __global__ __launch_bounds__(kGT) void draft_fast_kernel(
         m = sm.wm[0];
 #pragma unroll
         for (int w = 1; w < kGW; ++w) m = fmaxf(m, sm.wm[w]);
-        const float mc0 = m * c2;
+        const float mc0 = scaled_ref(m, c2);
         float z2 = 0.f;
 #pragma unroll
         for (int it = 0; it < ITER; ++it) {
@@ -153,7 +154,7 @@ __global__ __launch_bounds__(kGT) void draft_fast_kernel(
 #pragma unroll
         for (int w = 0; w < kGW; ++w) Zd += (double)sm.wz[w];
     }
-    const float mc = m * c2;
+    const float mc = scaled_ref(m, c2);
     const float invZ = (float)(1.0 / Zd);
 
     // ---- 2. the probability row: rounded once, stored once; its mass per (step, wavefront) ------

@@ -44,6 +44,7 @@ __device__ __forceinline__ float draft_exponent_scale(float T)     // log2(e) / 
 }
 
 // (m, Z, arg-max or -1) of a row from its parts
+template <class LT>
 __device__ __forceinline__ HalfStat merge_stats(const HalfStat *__restrict__ st, int n_parts, float c)
 {
     HalfStat s[kStatParts], out;
@@ -60,7 +61,7 @@ __device__ __forceinline__ HalfStat merge_stats(const HalfStat *__restrict__ st,
 #pragma unroll
     for (int p = 0; p < kStatParts; ++p) {
         if (s[p].m == out.m && s[p].arg >= 0 && (out.arg < 0 || s[p].arg < out.arg)) out.arg = s[p].arg;
-        out.Z += s[p].m > -INFINITY ? s[p].Z * (double)__builtin_amdgcn_exp2f((s[p].m - out.m) * c) : 0.0;
+        out.Z += s[p].m > -INFINITY ? s[p].Z * (double)__builtin_amdgcn_exp2f(ref_gap<LT>(s[p].m, out.m, c)) : 0.0;
     }
     return out;
 }
@@ -82,13 +83,13 @@ __global__ __launch_bounds__(kQT, kStatWgsPerCu) void draft_stats_kernel(
     HalfStat out;
     if (T == 0.0f) {
         const PartStream st = stream_part<LT, true, true, kAuxDefault>(rl, row_chunks, n_parts, h, V, c, tid, [] {});
-        out = reduce_norm(st, c, s_m, s_z, lane, wv);
+        out = reduce_norm<LT>(st, c, s_m, s_z, lane, wv);
         lds_barrier();                                       // s_m is used again
         const ArgMax b = reduce_argmax(st.best, s_m, s_i, lane, wv);
         out.arg = b.i < V ? b.i : -1;
     } else {
         const PartStream st = stream_part<LT, true, false, kAuxDefault>(rl, row_chunks, n_parts, h, V, c, tid, [] {});
-        out = reduce_norm(st, c, s_m, s_z, lane, wv);
+        out = reduce_norm<LT>(st, c, s_m, s_z, lane, wv);
     }
     if (tid == 0) stats[(int64_t)r * kStatParts + h] = out;
 }
@@ -111,8 +112,8 @@ __global__ __launch_bounds__(kQT, 8) void draft_probs_kernel(
 #pragma unroll
     for (int it = 0; it < kSumSteps; ++it) lg[it] = part_load16<kAuxDefault>(rl, (uint32_t)my_chunk * 16u, it * (kWave * 16));
     const float T = temperature[r], c = draft_exponent_scale(T);
-    const HalfStat row = merge_stats(stats + (int64_t)r * kStatParts, n_stat_parts, c);
-    const float mc = row.m * c, invZ = (float)(1.0 / row.Z);   // (a row without any finite logit: q = NaN, as in the other kernels)
+    const HalfStat row = merge_stats<LT>(stats + (int64_t)r * kStatParts, n_stat_parts, c);
+    const float mc = scaled_ref(row.m, c), invZ = (float)(1.0 / row.Z);   // (a row without any finite logit: q = NaN, as in the other kernels)
     char *prow = probs + (int64_t)(out_rows ? out_rows[r] : r) * pstride_bytes + (int64_t)chunk0 * kBytes;
     const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc(prow, 0, nchunks * kBytes, 0x00020000);
     double total = 0.0;
@@ -175,7 +176,7 @@ __global__ __launch_bounds__(kQT) void draft_pick_kernel(
     }
     if (T == 0.0f) {
         if (tid == 0) {
-            const int arg = merge_stats(stats + (int64_t)r * kStatParts, n_stat_parts, 1.4426950408889634f).arg;
+            const int arg = merge_stats<PT>(stats + (int64_t)r * kStatParts, n_stat_parts, 1.4426950408889634f).arg;
             tokens[r] = arg >= 0 ? arg : 0;
             confidence[r] = arg >= 0 ? load_as_float<PT>(prow, arg) : 0.f;
         }

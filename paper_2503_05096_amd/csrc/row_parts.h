@@ -102,14 +102,21 @@ template <int N, class PT> struct ProbChunk {
     }
 };
 
-// 2^((l - m) c).  16-bit logits: one fused operation with mc = m * c (the rounding of mc is far below that of
-// the logits' storage type).  fp32 logits: the difference first, as the portable kernel does it: for large
-// logits the rounding of mc would be visible in how the parts of a row are put together.
+// 2^((l - m) c).  16-bit logits: one fused operation, relative to mc = scaled_ref(m, c).  fp32
+// logits: the difference first, as the portable kernel does it.
 template <class LT>
 __device__ __forceinline__ float exp_weight(float l, float m, float c, float mc)
 {
     if constexpr (sizeof(typename LT::storage) == 4) return __builtin_amdgcn_exp2f((l - m) * c);
     else return __builtin_amdgcn_exp2f(fmaf(l, c, -mc));
+}
+
+// exponent that moves a sum of such weights from the reference a to the reference b
+template <class LT>
+__device__ __forceinline__ float ref_gap(float a, float b, float c)
+{
+    if constexpr (sizeof(typename LT::storage) == 4) return (a - b) * c;
+    else return scaled_ref(a, c) - scaled_ref(b, c);
 }
 
 // exact maximum of the values of a chunk
@@ -215,11 +222,11 @@ __device__ __forceinline__ PartStream stream_part(__amdgpu_buffer_rsrc_t rl, int
                     mn = top >= 0 ? Pair16<LT>::lo((uint32_t)top & 0xffffu) : chunk_max<LT>(v, out.m_run);
                 }
                 if (mn > out.m_run) {
-                    out.zt *= __builtin_amdgcn_exp2f((out.m_run - mn) * c);      // (-inf - finite) -> 0
+                    out.zt *= __builtin_amdgcn_exp2f(ref_gap<LT>(out.m_run, mn, c));      // (-inf - finite) -> 0
                     out.m_run = mn;
                 }
                 if (out.m_run > -INFINITY) {
-                    const float mnc = out.m_run * c;
+                    const float mnc = scaled_ref(out.m_run, c);
                     Chunk<LT>::unpack(v, x);
 #pragma unroll
                     for (int e = 0; e < kN; ++e) out.zt += exp_weight<LT>(x[e], out.m_run, c, mnc);
@@ -234,10 +241,11 @@ __device__ __forceinline__ PartStream stream_part(__amdgpu_buffer_rsrc_t rl, int
 }
 
 // over the workgroup: (maximum, normaliser) of the threads' streams; the result is thread 0's
+template <class LT>
 __device__ __forceinline__ HalfStat reduce_norm(const PartStream &st, float c, float *s_m, double *s_z, int lane, int wv)
 {
     const float mw = wave_max(st.m_run);
-    const double zw = wave_sum(st.m_run > -INFINITY ? (double)(st.zt * __builtin_amdgcn_exp2f((st.m_run - mw) * c)) : 0.0);
+    const double zw = wave_sum(st.m_run > -INFINITY ? (double)(st.zt * __builtin_amdgcn_exp2f(ref_gap<LT>(st.m_run, mw, c))) : 0.0);
     if (lane == 0) { s_m[wv] = mw; s_z[wv] = zw; }
     lds_barrier();
     HalfStat out;
@@ -246,7 +254,7 @@ __device__ __forceinline__ HalfStat reduce_norm(const PartStream &st, float c, f
     for (int w = 1; w < kQW; ++w) out.m = fmaxf(out.m, s_m[w]);
 #pragma unroll
     for (int w = 0; w < kQW; ++w)
-        out.Z += s_m[w] > -INFINITY ? s_z[w] * (double)__builtin_amdgcn_exp2f((s_m[w] - out.m) * c) : 0.0;
+        out.Z += s_m[w] > -INFINITY ? s_z[w] * (double)__builtin_amdgcn_exp2f(ref_gap<LT>(s_m[w], out.m, c)) : 0.0;
     return out;
 }
 // over the workgroup: arg-max (index >= V if nothing is above -inf)

@@ -37,6 +37,12 @@ __device__ __forceinline__ float row16_sum(float v)
     return v;
 }
 
+// Weights of 16-bit logits are 2^fma(l, c, -r), relative to r and not to the maximum m.  r is a whole number near m c: what
+// moves a sum from one reference to another (the maxima seen so far, those of threads and parts) is then an exact power of
+// two.  With r = m c rounded and factors of 2^((a - b) c) the roundings of the products stayed in the sum, 1e-6 to 1e-5 of it
+// where m c is 20 to 100, and nothing took them out of p = weight / sum.
+__device__ __forceinline__ float scaled_ref(float m, float c) { return ceilf(m * c); }
+
 // maximum over the 16 lanes of a DPP row (every lane of the row ends up with it)
 __device__ __forceinline__ float row16_max(float v)
 {

@@ -51,3 +51,31 @@ def test_accept_beyond_the_parts_layout(oracle_mod, pkg):  # noqa: F811
     """Rows whose stride is not a multiple of 8 elements, and an odd vocabulary, stay on the portable kernel."""
     for V in (1001, 4100):
         check_accept(_step(V, "f32", "f32"), oracle_mod, pkg)
+
+
+@pytest.mark.parametrize("ldt,pdt", [("bf16", "f32"), ("f16", "bf16"), ("bf16", "bf16"), ("f16", "f16"), ("f32", "f32"), ("f32", "bf16")])
+@pytest.mark.parametrize("T,offset,V", [(0.8, 60.0, 32000), (0.8, -60.0, 32000), (1.0, -40.0, 8192), (1.0, 0.0, 128256)])
+def test_accept_parts_turn_where_the_ratio_is(ldt, pdt, T, offset, V, pkg):  # noqa: F811
+    """One draft per request, uniforms a hair below and above p / q: logits far from zero must not move p.
+
+    Bound: exponential, reciprocal of the normaliser, product and quotient 1.2e-7 at most each, of which two are half that;
+    fp32 sums of up to 512 terms per thread in the normaliser 3e-7; log2(e) / T rounded in fp32 1.2e-7 of the exponent, which
+    is 5 away from its mean at most: 4e-7; the uniform 6e-8: 1.2e-6 in all. Tested 1.3e-6 away from the ratio."""
+    import torch
+    dts = {"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16}
+    B, dt = 192, dts[ldt]
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    logits = (3.0 * torch.randn((2 * B, V), generator=gen, device="cuda") + offset).to(dt)
+    p = torch.softmax(logits[0::2].double() / T, dim=1)
+    i = torch.arange(B, device="cuda")
+    x = p.topk(8, dim=1).indices[i, i % 8]
+    q = torch.zeros((B, V), dtype=dts[pdt], device="cuda")
+    q[i, x] = (p[i, x] / 0.7).to(q.dtype)
+    ratio = p[i, x] / q[i, x].double()
+    spec, temp = torch.ones(B, dtype=torch.int32, device="cuda"), torch.full((B,), T, device="cuda")
+    for side in (-1.3e-6, 1.3e-6):
+        uni = torch.zeros((2 * B, 2), device="cuda")
+        uni[0::2, 0] = (ratio * (1.0 + side)).float()
+        accepted = pkg.accept(logits, q, x.int(), uni, spec, temp, max_spec_len=1)[1]
+        torch.cuda.synchronize()
+        assert int((accepted == 1).sum()) == (B if side < 0 else 0), side

@@ -45,3 +45,18 @@ def test_draft_parts_masked_rows_and_scattered_output(oracle_mod, pkg):  # noqa:
     rows = np.array([5, 0, 6, 2], np.int32)
     for ldt in ("f32", "bf16"):
         _check(_logits(4, 50000, ldt, masked=0.999), ldt, ldt, T, U, oracle_mod, pkg, out_rows=rows, n_prob_rows=7)
+
+
+@pytest.mark.parametrize("V", [32768, 50272, 128256, 262144])
+@pytest.mark.parametrize("ldt", ["bf16", "f16", "f32"])
+@pytest.mark.parametrize("T", [1.0, 0.3, 0.02])
+def test_draft_rows_in_fp32_sum_to_one(V, ldt, T, pkg):  # noqa: F811
+    """What every probability of a row is off by in common: reciprocal of the normaliser 6e-8, fp32 sums of up to 512 terms per
+    thread in it 1.5e-7, the exponential's rounding, which the few largest weights share, 1.2e-7: 3.3e-7."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(V)
+    x = (3.0 * torch.randn((64, V), generator=gen, device="cuda")).to({"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16}[ldt])
+    probs, _, _ = pkg.draft_sample(x, torch.full((64,), T, device="cuda"), torch.rand(64, generator=gen, device="cuda"),
+                                   probs_dtype=torch.float32)
+    torch.cuda.synchronize()
+    assert float((probs.double().sum(1) - 1.0).abs().max()) <= 3.3e-7
