@@ -275,7 +275,7 @@ __global__ __launch_bounds__(kQT, kStatWgsPerCu) void accept_rowparts_kernel(
         }
         return;
     }
-    const float c = 1.4426950408889634f / T;
+    const float c = exponent_scale<LT>(T);
     const PartStream st = stream_part<LT, true, false, kAuxStream>(rl, row_chunks, n_parts, h, V, c, tid, leave_slot);
     const HalfStat out = reduce_norm<LT>(st, c, s_m, s_z, lane, wv);
     if (tid == 0) *my_stat = out;
@@ -358,7 +358,7 @@ __global__ __launch_bounds__(kQT, sizeof(typename PT::storage) > sizeof(typename
     const int k = min(max(spec_lens[i], 0), max_spec_len);          // uniform: scalar loads
     const float T = temperature[i];
     const bool sampled = T != 0.0f;
-    const float c = sampled ? 1.4426950408889634f / T : 0.f;
+    const float c = sampled ? exponent_scale<LT>(T) : 0.f;
     if (wv == 0) {
         int a0 = k;
         RowMerge row0;                                               // statistics of the deciding row, if a draft

@@ -38,9 +38,10 @@ __device__ __forceinline__ uint32_t round_pair(float a, float b)
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(x, typename Round16<PT>::v2));
 }
 
-__device__ __forceinline__ float draft_exponent_scale(float T)     // log2(e) / T; T == 0 stands for T = 1
+template <class LT>
+__device__ __forceinline__ float draft_exponent_scale(float T)     // T == 0 stands for T = 1
 {
-    return T == 0.0f ? 1.4426950408889634f : 1.4426950408889634f / T;
+    return T == 0.0f ? 1.4426950408889634f : exponent_scale<LT>(T);
 }
 
 // (m, Z, arg-max or -1) of a row from its parts
@@ -76,7 +77,7 @@ __global__ __launch_bounds__(kQT, kStatWgsPerCu) void draft_stats_kernel(
     __shared__ int s_i[kQW];
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int r = blockIdx.x / n_parts, h = blockIdx.x % n_parts;
-    const float T = temperature[r], c = draft_exponent_scale(T);
+    const float T = temperature[r], c = draft_exponent_scale<LT>(T);
     const int row_chunks = V / Chunk<LT>::kN;
     const __amdgpu_buffer_rsrc_t rl =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(logits) + (int64_t)r * lstride_bytes, 0, row_chunks * 16, 0x00020000);
@@ -111,7 +112,7 @@ __global__ __launch_bounds__(kQT, 8) void draft_probs_kernel(
     uint4 lg[kSumSteps];
 #pragma unroll
     for (int it = 0; it < kSumSteps; ++it) lg[it] = part_load16<kAuxDefault>(rl, (uint32_t)my_chunk * 16u, it * (kWave * 16));
-    const float T = temperature[r], c = draft_exponent_scale(T);
+    const float T = temperature[r], c = draft_exponent_scale<LT>(T);
     const HalfStat row = merge_stats<LT>(stats + (int64_t)r * kStatParts, n_stat_parts, c);
     const float mc = scaled_ref(row.m, c), invZ = (float)(1.0 / row.Z);   // (a row without any finite logit: q = NaN, as in the other kernels)
     char *prow = probs + (int64_t)(out_rows ? out_rows[r] : r) * pstride_bytes + (int64_t)chunk0 * kBytes;

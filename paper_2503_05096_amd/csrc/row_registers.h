@@ -43,6 +43,16 @@ __device__ __forceinline__ float row16_sum(float v)
 // where m c is 20 to 100, and nothing took them out of p = weight / sum.
 __device__ __forceinline__ float scaled_ref(float m, float c) { return ceilf(m * c); }
 
+// log2(e) / T.  For 16-bit rows no more than 2^22: a reference (or a product m c) from 2^31 on is so coarse that what it
+// leaves of the largest logit's exponent overflows.  Below T = 3.4e-7, where that sets in, 16-bit logits that differ at all
+// differ by a weight of 0, unless all of them are below 1e-2.
+template <class LT>
+__device__ __forceinline__ float exponent_scale(float T)
+{
+    const float c = 1.4426950408889634f / T;
+    return sizeof(typename LT::storage) == 2 ? fminf(c, 4194304.f) : c;
+}
+
 // maximum over the 16 lanes of a DPP row (every lane of the row ends up with it)
 __device__ __forceinline__ float row16_max(float v)
 {

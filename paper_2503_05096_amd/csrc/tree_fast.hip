@@ -160,7 +160,7 @@ __global__ __launch_bounds__(kQT, 6) void tree_node_stats_kernel(
         }
         return;
     }
-    const float c = 1.4426950408889634f / T;
+    const float c = exponent_scale<DT>(T);
     for (int s = first; s < last; ++s) {
         uint4 nx[kSumSteps];
         load_step(s + 1 < last ? s + 1 : nsteps, nx);            // (another group's step: nothing)
@@ -259,7 +259,7 @@ __global__ __launch_bounds__(kNT, 4) void accept_tree_walk_fast_kernel(
         for (int w = 0; w < kNW; ++w) r0 += sm.fallback_tot[w];
     }
     if (r0 < 0 || r0 + k + 1 > total_q) return;                 // inconsistent metadata: leave the request alone
-    const float cexp = T == 0.0f ? 0.f : 1.4426950408889634f / T;
+    const float cexp = T == 0.0f ? 0.f : exponent_scale<DT>(T);
     const int nsteps = ceil_div(V / 8, kNT);
     int32_t *o = out_tokens + (int64_t)i * out_stride;
     int32_t *pth = out_path + (int64_t)i * out_stride;

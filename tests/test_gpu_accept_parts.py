@@ -79,3 +79,12 @@ def test_accept_parts_turn_where_the_ratio_is(ldt, pdt, T, offset, V, pkg):  # n
         accepted = pkg.accept(logits, q, x.int(), uni, spec, temp, max_spec_len=1)[1]
         torch.cuda.synchronize()
         assert int((accepted == 1).sum()) == (B if side < 0 else 0), side
+
+
+@pytest.mark.parametrize("ldt,pdt", [("bf16", "f32"), ("f16", "f32"), ("f16", "bf16"), ("f32", "f32"), ("bf16", "bf16")])
+@pytest.mark.parametrize("offset", [0.0, 40.0])
+def test_accept_parts_at_temperatures_next_to_zero(ldt, pdt, offset, oracle_mod, pkg):  # noqa: F811
+    """Temperatures that stand for 'greedy' without being 0: scaled logits up to 1e12."""
+    st = _step(4096, ldt, pdt, spec=[3, 0, 2, 6, 1, 4], temp=[1e-8, 1e-10, 1e-7, 1e-9, 1e-6, 1e-10])
+    st.target_logits = _store((to_f64(st.target_logits, ldt) + offset).astype(np.float32), ldt)
+    check_accept(st, oracle_mod, pkg)

@@ -60,3 +60,9 @@ def test_draft_rows_in_fp32_sum_to_one(V, ldt, T, pkg):  # noqa: F811
                                    probs_dtype=torch.float32)
     torch.cuda.synchronize()
     assert float((probs.double().sum(1) - 1.0).abs().max()) <= 3.3e-7
+
+
+@pytest.mark.parametrize("V", [50184, 262144])
+@pytest.mark.parametrize("ldt", ["bf16", "f16", "f32"])
+def test_draft_parts_at_temperatures_next_to_zero(V, ldt, oracle_mod, pkg):  # noqa: F811
+    _check(_logits(4, V, ldt), ldt, ldt, np.array([1e-8, 1e-10, 1e-7, 1e-9], np.float32), U, oracle_mod, pkg)

@@ -61,3 +61,7 @@ def test_tree_accept_turns_where_the_ratio_is(dtype, T, offset, pkg):  # noqa: F
         accepted = pkg.accept_tree(logits, q, x.int(), parents, uni, spec, temp, max_spec_len=1)[1]
         torch.cuda.synchronize()
         assert int((accepted == 1).sum()) == (B if side < 0 else 0), side
+
+
+def test_tree_accept_at_temperatures_next_to_zero(oracle_mod, pkg):  # noqa: F811
+    _check_tree_accept(_tree([3, 5, 2, 6, 1], 8200, "bf16", [1e-8, 1e-10, 1e-7, 1e-9, 1e-6]), oracle_mod, pkg)
