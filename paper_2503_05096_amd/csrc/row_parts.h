@@ -202,16 +202,19 @@ __device__ __forceinline__ PartStream stream_part(__amdgpu_buffer_rsrc_t rl, int
             uint4 v = lg[u];
             Chunk<LT>::blank(v, chunk >= row_chunks);
             float x[kN];
+            float mn;                                        // maximum so far
             if constexpr (kArgMax) {
-                Chunk<LT>::unpack(v, x);
+                mn = chunk_max<LT>(v, out.best.v);
+                if (mn > out.best.v) {                       // (rarely: the search stays off the common path)
+                    Chunk<LT>::unpack(v, x);
+                    int at = 0;
 #pragma unroll
-                for (int e = 0; e < kN; ++e)
-                    if (x[e] > out.best.v) out.best = ArgMax{x[e], chunk * kN + e};
+                    for (int e = kN - 1; e >= 0; --e) at = x[e] == mn ? e : at;
+                    out.best = ArgMax{mn, chunk * kN + at};
+                }
             }
             if constexpr (kNorm) {
-                float mn;
                 if constexpr (kArgMax) {
-                    mn = out.best.v;
                 } else if constexpr (kN == 4) {
                     mn = chunk_max<LT>(v, out.m_run);
                 } else {

@@ -66,3 +66,22 @@ def test_draft_rows_in_fp32_sum_to_one(V, ldt, T, pkg):  # noqa: F811
 @pytest.mark.parametrize("ldt", ["bf16", "f16", "f32"])
 def test_draft_parts_at_temperatures_next_to_zero(V, ldt, oracle_mod, pkg):  # noqa: F811
     _check(_logits(4, V, ldt), ldt, ldt, np.array([1e-8, 1e-10, 1e-7, 1e-9], np.float32), U, oracle_mod, pkg)
+
+
+def test_draft_parts_greedy_rows_with_rising_and_equal_maxima(oracle_mod, pkg):  # noqa: F811
+    """The arg-max is searched for only where a chunk raises the running maximum: rows that rise to the last element, fall
+    from the first, repeat their maximum in later elements, chunks, steps and parts, or hold one finite logit."""
+    V = 50184
+    x = np.zeros((5, V), np.float32)
+    # (63 steps: the smallest probability, e^-63 / 800 = 6e-31, is a normal number of fp32 and bf16; the exponential of what
+    # is not comes out as 0, which the oracle's comparison of fp32 rows does not allow)
+    x[0] = np.floor(np.arange(V) / 800.0)                            # ends on a run of equal maxima
+    x[1] = -np.floor(np.arange(V) / 800.0)
+    x[2, [3, 5, 11, 2048, 4096 * 8, V - 1]] = 7.0                    # the lowest of them
+    x[3] = -np.inf
+    x[3, V - 1] = -30.0
+    x[4, :] = -2.0
+    T5, U5 = np.zeros(5, np.float32), np.full(5, 0.5, np.float32)
+    for ldt in ("bf16", "f16", "f32"):
+        y = x if ldt == "f32" else W.f32_to_bf16_bits(x) if ldt == "bf16" else x.astype(np.float16)
+        _check(y, ldt, ldt, T5, U5, oracle_mod, pkg)
