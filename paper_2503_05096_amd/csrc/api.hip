@@ -148,7 +148,10 @@ AttnPlan make_attn_plan(const adaspec_attn_dims &d, AttnKind kind, bool tree)
         // 16000 tokens under 16K: 22.6 (35.1 with metadata).  With 1024 possible units for few pairs full tables lose
         // (4 requests of 8000 under 8K: 30.2 -> 39.3).
         const int shortest = 2 * kWavesPerUnit * p.block_tokens, longest = p.split_tokens > shortest ? p.split_tokens : shortest;
-        const int most = pairs < kDirectFewPairs ? kDirectMaxUnitsFew : kDirectMaxUnits;
+        // (two units side by side on a compute unit: not with four row tiles in one wavefront's registers; 48 requests of 850
+        // tokens, 49 rows, 14/2 heads of 64, under 1800: 29.9 us with 384 possible units, 21.8 with the schedule)
+        const bool one_per_cu = kind != AttnKind::kMfma128 && attn_row_tiles(p.max_rows) > 2;
+        const int most = pairs < kDirectFewPairs && !one_per_cu ? kDirectMaxUnitsFew : kDirectMaxUnits;
         for (int s = shortest; s <= longest && !p.direct; s *= 2)
             if (d.batch * ((max_ctx + s - 1) / s) * d.n_kv_heads * n_groups <= most) {
                 p.direct = true;
