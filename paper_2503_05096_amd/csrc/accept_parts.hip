@@ -71,10 +71,6 @@ struct SlotRec { int x; uint32_t lx_bits, qx_bits, u0_bits; };
 // stores and loads (write-through / read-through to the level all XCDs share); the writer waits until its
 // stores have been acknowledged before it takes its ticket, and the reader's loads depend on the ticket's
 // return value.  No cache-wide write-back or invalidate is needed, and nobody waits for anybody.
-__device__ __forceinline__ void publish_f32(float *p, float v)
-{
-    __hip_atomic_store(reinterpret_cast<uint32_t *>(p), __float_as_uint(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
 __device__ __forceinline__ void publish_u64(void *p, unsigned long long v)
 {
     __hip_atomic_store(reinterpret_cast<unsigned long long *>(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -571,17 +567,6 @@ __global__ __launch_bounds__(kQT, sizeof(typename PT::storage) > sizeof(typename
     ADASPEC_STAMP(1, 7);
 }
 
-static int parts_compute_units()
-{
-    static int cus = 0;
-    if (cus == 0) {
-        int dev = 0, n = 0;
-        cus = (hipGetDevice(&dev) == hipSuccess &&
-               hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0) ? n : 256;
-    }
-    return cus;
-}
-
 static int sum_parts(const adaspec_accept_dims &d) { return parts_sum_parts(d.vocab, d.logits_dtype); }
 
 bool accept_parts_dims_fit(const adaspec_accept_dims &d)
@@ -607,11 +592,11 @@ size_t accept_parts_sum_stat_bytes(const adaspec_accept_dims &d)
     return (size_t)(d.batch > 0 ? d.batch : 1) * sum_parts(d) * sizeof(HalfStat);
 }
 
-hipError_t launch_accept_parts(const AcceptArgs &a)
+hipError_t launch_accept_parts(const AcceptArgs &a, int compute_units)
 {
     const adaspec_accept_dims &d = a.dims;
     if (d.batch == 0) return hipSuccess;
-    const int n_stat_parts = parts_stat_parts(d.total_draft, d.vocab, d.logits_dtype, parts_compute_units());
+    const int n_stat_parts = parts_stat_parts(d.total_draft, d.vocab, d.logits_dtype, compute_units);
     const int n_sum_parts = sum_parts(d);
     int32_t *cu_q = (int32_t *)(a.ws + a.plan.off_cu_q);
     int32_t *ticket = (int32_t *)(a.ws + a.plan.off_req_ticket);

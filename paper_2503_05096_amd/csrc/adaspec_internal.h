@@ -172,7 +172,7 @@ size_t accept_parts_slot_bytes(const adaspec_accept_dims &d);
 size_t accept_parts_stat_bytes(const adaspec_accept_dims &d);
 size_t accept_parts_sum_bytes(const adaspec_accept_dims &d);
 size_t accept_parts_sum_stat_bytes(const adaspec_accept_dims &d);
-hipError_t launch_accept_parts(const AcceptArgs &a);
+hipError_t launch_accept_parts(const AcceptArgs &a, int compute_units);
 
 // tree verification (tree.hip, tree_fast.hip): every node's acceptance, then the walk; needs the accept plan's cu_q / row_req
 // portable form (any types and sizes): a per-node kernel writes (next node or -1, token if the walk stops here)

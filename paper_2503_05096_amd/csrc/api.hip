@@ -415,7 +415,7 @@ static int accept_impl(const void *target_logits, const void *draft_probs,
         // 1024 requests, larger batches with one workgroup per row and then per request
         if (!record_event(dims->timing_start, dims->timing_stop, true, a.stream)) return ADASPEC_ERR_HIP;
         if (in_parts) {
-            if (launch_accept_parts(a) != hipSuccess) return ADASPEC_ERR_HIP;
+            if (launch_accept_parts(a, compute_units()) != hipSuccess) return ADASPEC_ERR_HIP;
         } else {
             if (launch_accept_test(a) != hipSuccess) return ADASPEC_ERR_HIP;
             if (launch_accept_resolve(a) != hipSuccess) return ADASPEC_ERR_HIP;

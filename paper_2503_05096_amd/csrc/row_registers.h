@@ -53,14 +53,4 @@ __device__ __forceinline__ float exponent_scale(float T)
     return sizeof(typename LT::storage) == 2 ? fminf(c, 4194304.f) : c;
 }
 
-// maximum over the 16 lanes of a DPP row (every lane of the row ends up with it)
-__device__ __forceinline__ float row16_max(float v)
-{
-    v = fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0xB1, 0xF, 0xF, true)));
-    v = fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x4E, 0xF, 0xF, true)));
-    v = fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x124, 0xF, 0xF, true)));
-    v = fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x128, 0xF, 0xF, true)));
-    return v;
-}
-
 }  // namespace adaspec

@@ -20,11 +20,6 @@ __device__ __forceinline__ void unpack8(const uint4 &w, float (&x)[8])
     x[4] = Pair16<DT>::lo(w.z); x[5] = Pair16<DT>::hi(w.z);
     x[6] = Pair16<DT>::lo(w.w); x[7] = Pair16<DT>::hi(w.w);
 }
-template <class DT>
-__device__ __forceinline__ float elem16(const char *row, int v)
-{
-    return Pair16<DT>::lo((uint32_t) reinterpret_cast<const uint16_t *>(row)[v]);
-}
 
 // Per-step totals from the 64 partial sums each step left in `part`: wavefront w adds up steps w, w + 16, ...
 // Every thread returns R = sum of S[0 .. nsteps); ends on a barrier.
