@@ -208,8 +208,9 @@ size_t adaspec_accept_workspace_bytes(const adaspec_accept_dims *dims);
  * only with more logits rows than compute units or V >= 65536), register-resident when it fits,
  * streaming for larger vocabularies, else vector.  Where AUTO names the streaming or the vector path
  * (larger vocabularies up to 524288, fp32 rows, rows of two types) and V, strides and base pointers are
- * aligned as above, up to 1024 requests run with the two-pass form's kernels instead (as long as the
- * workspace stays within ADASPEC_NOALLOC_SCRATCH_BYTES).
+ * aligned as above, up to 1024 requests (of at most 32768 drafts in all, counted at max_spec_len) run
+ * with the two-pass form's kernels instead, as long as the workspace stays within
+ * ADASPEC_NOALLOC_SCRATCH_BYTES.
  */
 int adaspec_accept(const void *target_logits, const void *draft_probs,
                    const int32_t *draft_tokens, const float *uniforms,
@@ -225,8 +226,10 @@ int adaspec_accept(const void *target_logits, const void *draft_probs,
  * bit.  What the workspace would hold lives in a device array of ADASPEC_NOALLOC_SCRATCH_BYTES that is
  * part of the library's code object: every GPU the library runs on holds it from the first use until
  * the process ends.  The call allocates and frees nothing and synchronises nothing.
- *   - dims whose adaspec_accept_workspace_bytes exceeds ADASPEC_NOALLOC_SCRATCH_BYTES are rejected
- *     with ADASPEC_ERR_WORKSPACE before anything is enqueued (use adaspec_accept for those).
+ *   - dims that need more than ADASPEC_NOALLOC_SCRATCH_BYTES are rejected with ADASPEC_ERR_WORKSPACE
+ *     before anything is enqueued (use adaspec_accept for those).  What they need is
+ *     adaspec_accept_workspace_bytes; above V = 253952, where that query counts more than 528 bytes
+ *     per row for tree calls, it is less by those.
  *   - All calls on one GPU share that GPU's array: calls that can overlap in time on one GPU (other
  *     streams, other threads) race on it; order them on one stream.  The array keeps the previous
  *     call's contents; the kernels initialise whatever they rely on.
@@ -245,7 +248,10 @@ int adaspec_accept_noalloc(const void *target_logits, const void *draft_probs,
  * itself unless it is ADASPEC_PATH_AUTO; a negative adaspec_status if dims are invalid or a
  * forced path does not fit.  Host-only, launches nothing.  For callers that account for the bytes
  * a call reads: the two-pass path skips rows (see above).  ADASPEC_PATH_STREAM and _VECTOR as the
- * answer to AUTO are upper bounds: such a call may run with the two-pass form's kernels. */
+ * answer to AUTO name the per-row path of the shape.  The call itself runs with the two-pass form's
+ * kernels, and reads what they read, if V % 8 == 0, V <= 524288, both strides % 8 == 0, the base
+ * pointers are 16-byte aligned, batch <= 1024, batch * max_spec_len <= 32768 and its workspace stays
+ * within ADASPEC_NOALLOC_SCRATCH_BYTES: see adaspec_accept. */
 int adaspec_accept_resolved_path(const void *target_logits, const void *draft_probs,
                                  const adaspec_accept_dims *dims);
 
@@ -461,8 +467,8 @@ typedef struct {
                                    kernels; AUTO = the split form, of any storage
                                    types, when a workspace is given and V > 32768
                                    (fp32 logits: 49152; not for 16-bit rows of at
-                                   most 65536 when they fill half of the chip one
-                                   per compute unit); else FAST when it fits and
+                                   most 65536 when they fill more than half of the
+                                   chip one per compute unit); else FAST when it fits and
                                    V > 24576, else VECTOR */
     int32_t reserved;
     void   *timing_start;       /* optional pair of hipEvent_t (both or neither, NULL = none), recorded */

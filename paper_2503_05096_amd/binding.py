@@ -320,7 +320,8 @@ def accept_dims(target_logits, draft_probs, draft_tokens, spec_lens, max_spec_le
 
 def accept_resolved_path(target_logits, draft_probs, draft_tokens, spec_lens, *, max_spec_len: int,
                          out_stride: Optional[int] = None, path: str = "auto") -> str:
-    """adaspec_accept_resolved_path: the kernel path adaspec_accept takes for these tensors."""
+    """adaspec_accept_resolved_path: the kernel path adaspec_accept takes for these tensors ("stream" and "vector" as the
+    answer to "auto": the per-row path of the shape; the header says which of those calls run in row parts)."""
     dims, pp, _ = accept_dims(target_logits, draft_probs, draft_tokens, spec_lens, max_spec_len, out_stride, path)
     rc = lib().adaspec_accept_resolved_path(target_logits.data_ptr(), pp, C.byref(dims))
     if rc < 0:
@@ -385,7 +386,7 @@ def accept_tree(target_logits, draft_probs, draft_tokens, parents, uniforms, spe
                 max_spec_len: int, out_tokens=None, out_accept_len=None, out_path=None,
                 out_stride: Optional[int] = None, path: str = "auto", workspace=None, stream=None, timing=None):
     """adaspec_accept_tree; returns (out_tokens [B][out_stride], out_accept_len [B], out_path [B][out_stride]).
-    path: "auto", "vector" (portable per-node kernel) or "fast" (1024-thread per-node kernel)."""
+    path: "auto", "vector" (portable per-node kernel) or "fast" (node statistics, then one workgroup per request)."""
     if path == "auto" and timing is None:
         r = (_fast or _native()).accept_tree(target_logits, draft_probs, draft_tokens, parents, uniforms, spec_lens,
                                              temperature, max_spec_len, out_tokens, out_accept_len, out_path, out_stride,
@@ -546,7 +547,7 @@ def commit(out_tokens, out_accept_len, spec_lens, ctx_lens, *, max_spec_len: int
 def draft_sample(draft_logits, temperature, uniforms, *, probs_dtype=None, draft_probs=None, out_rows=None,
                  draft_tokens=None, confidence=None, path: str = "auto", workspace=None, stream=None, timing=None):
     """adaspec_draft_sample; returns (draft_probs, draft_tokens [R] int32, confidence [R] float32).
-    path "split" (ADASPEC_PATH_TWO_PASS for this call) cuts every row into four parts."""
+    path "split" (ADASPEC_PATH_TWO_PASS for this call) cuts every row into parts."""
     if path == "auto" and timing is None:
         r = (_fast or _native()).draft_sample(draft_logits, temperature, uniforms, probs_dtype, draft_probs, out_rows,
                                               draft_tokens, confidence, workspace, stream)

@@ -35,8 +35,8 @@
 // What the time goes to (MI355X, 510 rows of V = 128256, time stamps): a dependent memory access costs
 // 1.2-1.7 us and the chain has six of them (first pass: lengths -> row; second pass: slot records -> row,
 // then stores acknowledged -> ticket -> partial sums -> the chunks of the draw), the two launches add
-// 1.7 us each, and the rows themselves stream at 5.0-5.5 TB/s.  Whole calls: 510 rows of V = 128256 bf16 38.5 us, 256
-// rows of it in fp32 39.8 us, 192 rows of V = 262144 bf16 32.5 us.  Masses are published per wavefront (16 bytes per 256 chunks) and
+// 1.7 us each, and the rows themselves stream at 5.0-5.5 TB/s.  Whole calls: 510 rows of V = 128256 bf16 38.9 us, 256
+// rows of it in fp32 39.7 us, 192 rows of V = 262144 bf16 32.3 us.  Masses are published per wavefront (16 bytes per 256 chunks) and
 // not per step and 16-lane row, so that a row of any length fits the final search of one workgroup with two pairs per
 // thread; the four steps of the winning pair are recomputed by one wavefront each.
 #include "adaspec_internal.h"

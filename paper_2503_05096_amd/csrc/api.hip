@@ -108,8 +108,8 @@ AttnKind attn_kind(const adaspec_attn_dims &d)
     // head_dim 64 in 16 bits: the vector kernel is never ahead (MI355X, whole call, bf16, 32/8 heads: 64 requests of
     // 256-4096 tokens 1024 us against 65 us) and its fp32 accumulator is further from 64 bits (3.4e-7 against 2.4e-7)
     if (d.dtype != ADASPEC_F32 && d.head_dim == 64) return AttnKind::kMfma64;
-    // fp32 at these head dims: likewise (4 requests of 128-512 tokens, 8 heads of 64: 109 us against 19 us, of which
-    // the GPU works 10; error against 64 bits 3.7e-7 against 2.1e-7)
+    // fp32 at these head dims: likewise (4 requests of 128-512 tokens, 8 heads of 64: 109 us against 10 us;
+    // error against 64 bits 3.7e-7 against 2.1e-7)
     if (d.dtype == ADASPEC_F32 && (d.head_dim == 64 || d.head_dim == 128)) return AttnKind::kMfmaF32;
     return AttnKind::kVector;
 }
@@ -348,7 +348,7 @@ static int resolve_accept_path(const adaspec_accept_dims &d, const void *logits,
     // sampling step runs on one row per request) and spreads every row over many small workgroups; measured
     // on MI355X it is ahead of the per-row kernels (+ emit kernel) on every benchmark shape: V = 32000, 150
     // rows 16.5 against 21.4 us; V = 128256: 227 rows 28 against 38 us, 380 rows 39 against 63 us, 510 rows
-    // 42 against 70 us; all greedy 17.1 against 16.9 us.  Batches it does not take (more than 1024 requests)
+    // 39 against 70 us; all greedy 17.1 against 16.9 us.  Batches it does not take (more than 1024 requests)
     // use the older two-pass pair when there are more rows than compute units or the vocabulary is large; a
     // row that does not fit the registers of one workgroup (V > 131072) goes to the streaming kernel, anything
     // else to the vector kernel.
@@ -405,8 +405,8 @@ static int accept_impl(const void *target_logits, const void *draft_probs,
 
     // AUTO: rows that the two-pass form in parts can read (any storage types, V up to 524288, aligned) take it in place of
     // the streaming and vector kernels too, which evaluate every row in one workgroup (MI355X, whole call: V = 128256
-    // in fp32, 256 rows: vector kernel 746 us, in parts 43 us; V = 262144 in bf16, 192 rows: streaming kernel 65 us, in
-    // parts 36 us).  Forced paths keep their kernels, and so do AUTO calls with other rows or too many requests.
+    // in fp32, 256 rows: vector kernel 746 us, in parts 39.7 us; V = 262144 in bf16, 192 rows: streaming kernel 65 us, in
+    // parts 32.3 us).  Forced paths keep their kernels, and so do AUTO calls with other rows or too many requests.
     const bool aligned = aligned16(target_logits) && (dims->total_draft == 0 || aligned16(draft_probs));
     const bool in_parts = a.plan.parts && aligned && (two_pass || (dims->path == ADASPEC_PATH_AUTO && !fast));
     if (two_pass || in_parts) {
@@ -615,18 +615,19 @@ static int validate_draft_dims(const adaspec_draft_dims *d)
 }
 
 // AUTO of draft sampling, measured on MI355X (us per call; three sweeps / register-resident / in parts):
-//   V = 16384 bf16   1 row  8.7 / 10.5 / 11.1   128 rows  9.6 / 11.2 / 11.9   256 rows 10.3 / 11.9 / 14.1
-//   V = 32768 bf16   1 row 11.9 / 10.4 / 11.9   128 rows 13.7 / 11.9 / 14.5   256 rows 14.9 / 13.1 / 18.3
-//   V = 32768 fp32   1 row 10.7 /   -  / 12.0   128 rows 14.3 /   -  / 16.9   256 rows 20.1 /   -  / 22.0
-//   V = 40000 fp32                           144 rows 17.1 /   -  / 19.3   256 rows 26.5 /   -  / 26.5
-//   V = 50272 fp32                           144 rows 21.1 /   -  / 22.0   256 rows 33.2 /   -  / 31.1
-//   V = 50272 bf16   1 row 16.0 / 15.6 / 11.9   128 rows 18.4 / 17.9 / 17.4   192 rows 19.6 / 18.7 / 21.1
-//   V = 65536 bf16                           128 rows 22.2 / 17.9 / 18.6   192 rows 23.3 / 19.1 / 22.2
-//   V = 81920 bf16                           144 rows 26.6 / 29.5 / 21.9   256 rows 29.4 / 31.2 / 28.8
-//   V = 131072 bf16  1 row 32.1 / 25.8 / 12.1   192 rows 40.6 / 32.7 / 32.6   256 rows 43.5 / 35.9 / 38.8   300 rows 64 / 62 / 47
+//   V = 16384 bf16   1 row  9.1 / 10.8 /  9.7   128 rows 10.0 / 11.6 / 10.9   256 rows 10.8 / 12.3 / 12.2
+//   V = 32768 bf16   1 row 12.2 / 10.6 /  9.9   128 rows 13.7 / 12.1 / 12.8   256 rows 15.8 / 13.8 / 18.1
+//   V = 32768 fp32   1 row 11.0 /   -  /   -   128 rows 13.8 /   -  /   -   256 rows 20.9 /   -  /   -
+//   V = 50272 fp32   1 row 14.1 /   -  /  9.1   144 rows 21.2 /   -  / 22.1   256 rows 33.9 /   -  / 31.5   300 rows 43 / - / 37
+//   V = 50272 bf16   1 row 16.4 / 16.1 / 10.2   128 rows 18.3 / 18.1 / 16.6   192 rows 19.8 / 19.0 / 20.8   300 rows 29 / 34 / 26
+//   V = 65536 bf16   1 row 19.1 / 16.1 / 10.1   128 rows 21.5 / 18.3 / 17.8   144 rows 23.6 / 18.6 / 19.9   192 rows 25 / 19 / 22
+//   V = 81920 bf16   1 row 22.5 / 26.3 /  9.9   144 rows 26.3 / 29.9 / 22.0   256 rows 29.9 / 31.7 / 29.2   300 rows 41 / 55 / 34
+//   V = 131072 bf16  1 row 32.4 / 26.4 / 10.3   192 rows 41.3 / 32.7 / 32.1   256 rows 43.7 / 33.5 / 39.3   300 rows 62 / 57 / 47
+// fp32 rows in parts are measured as AUTO takes them, so not below its line; an earlier version of that form, slower than
+// today's, took 12.0, 16.9 and 22.0 us at V = 32768 and 19.3 (144 rows) and 26.5 (256) at V = 40000 against 17.1 and 26.5.
 // In parts above V = 32768 (fp32 logits, which the single-workgroup kernels need not convert: above 49152), unless 16-bit
-// rows of at most 65536 occupy half of the compute units and no more than all of them; else the register-resident kernel
-// above V = 24576 where it fits, else three sweeps.
+// rows of at most 65536 occupy more than half of the compute units and no more than all of them; else the
+// register-resident kernel above V = 24576 where it fits, else three sweeps.
 constexpr int kDraftFastAbove = 24576, kDraftMediumRow = 65536;
 static bool draft_wants_parts(const adaspec_draft_dims &d)
 {

@@ -12,8 +12,8 @@
 //                        and element from the stored row; greedy rows: the arg-max of the parts
 // The second kernel re-reads the logits (16-bit rows of a step fit the memory-side cache).  Bound: HBM for large steps, the
 // three launches and their dependent accesses for small ones.  MI355X, whole call, one
-// workgroup per row before: 64 rows of V = 128256 in fp32 43.6 -> 22 us, of V = 262144 in bf16 71 -> 28 us; 128 rows of
-// V = 128256 in bf16 23.3 us (26.1 in four parts of 1024 threads).
+// workgroup per row before: 64 rows of V = 128256 in fp32 43.6 -> 22.4 us, of V = 262144 in bf16 71 -> 25.3 us; 128 rows of
+// V = 128256 in bf16 23.4-24.1 us (26.1 in four parts of 1024 threads).
 #include <type_traits>
 
 #include "adaspec_internal.h"

@@ -25,7 +25,9 @@
 // Bound: HBM for the statistics; vector arithmetic of one compute unit per sweep in the walk (about 9.6 us at
 // V = 128256), whose longest chain of sweeps sets its time.  MI355X, 64 requests, 288 nodes, trees of width 3:
 // statistics 16.0 us (one 1024-thread workgroup per node: 23.7), walk 47.2 us with three dependent loads more at every
-// node and the test values fetched there, 42.9 without, 39.5 with searches by ballots, 35.4 with unnormalised sweeps.
+// node and the test values fetched there, 42.9 without, 39.5 with searches by ballots, 33.5 with unnormalised sweeps,
+// 35.2 since every exponent is a difference again (one more operation per element; the accept test's p is off by 7e-8 on
+// average instead of 3.2e-7, and a drawn token differed from the walk in 64 bits in 7 of 38400 requests instead of 13).
 #include "adaspec_internal.h"
 #include "device_utils.h"
 #include "row_parts.h"

@@ -1,6 +1,6 @@
 // The binding's calls with their ordinary arguments, without the interpreter: checks, dims struct, output tensors, stream
 // and the C-ABI call in one native function each.  A Python wrapper spends 6-12 us per call on attribute lookups, asserts
-// and ctypes conversions (MI355X machine; a kernel launch is 3 us), which is what a small call consists of.
+// and ctypes conversions (MI355X host; a kernel launch is 3 us), which is what a small call consists of.
 //
 // Every function here either makes the call and returns its result, or returns NotImplemented and has done nothing that
 // counts: the wrapper in binding.py then goes on in Python, which raises the right error or handles the unusual form.

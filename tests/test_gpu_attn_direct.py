@@ -71,8 +71,8 @@ def test_attention_direct_with_a_wide_block_table(oracle_mod, pkg):  # noqa: F81
 @pytest.mark.parametrize("B,lo,hi,hq,hkv,k", [(62, 2500, 2600, 64, 8, 4), (70, 2500, 2600, 64, 8, 4), (40, 3000, 3600, 64, 8, 8),
                                               (76, 1, 8193, 64, 8, 4), (1100, 1, 50, 16, 1, 2), (140, 1, 4600, 28, 4, 7)])
 def test_attention_long_splits_around_the_rule(B, lo, hi, hq, hkv, k, oracle_mod, pkg):  # noqa: F811
-    """Row-split kernel: with enough work per workgroup the plan doubles the splits of 2048 tokens. Batches below and above
-    the line, one and two row groups, contexts at the edges of both splits, more requests than threads of the plan kernel."""
+    """Row-split kernel: many long requests, one and two row groups, contexts at the edges of one and two splits of 2048 tokens,
+    more requests than threads of the plan kernel."""
     rng = np.random.default_rng(B + k)
     spec = rng.integers(0, k + 1, B)
     spec[0] = k

@@ -141,7 +141,7 @@ def test_tree_attention_metadata_reuse(oracle_mod, pkg):
 @pytest.mark.parametrize("cfg,greedy,width", [(1, False, 2), (2, False, 3), (3, False, 3), (4, False, 2),
                                               (4, True, 3), (5, False, 2)])
 def test_config_tree_accept(cfg, greedy, width, oracle_mod, pkg):
-    """AUTO: the 1024-thread node kernel for the 16-bit configs, the portable one for config 1."""
+    """AUTO: node statistics and walk for the 16-bit configs, the portable kernels for config 1."""
     st = W.attach_tree(W.make_verify_step(cfg, greedy=greedy, attention=False), max_width=width)
     rep, _ = _check_tree_accept(st, oracle_mod, pkg)
     assert 0 < rep["oracle_mean_accept_len"]
@@ -156,7 +156,7 @@ def test_config_tree_accept_portable_kernel(cfg, width, oracle_mod, pkg):
 @pytest.mark.parametrize("dtype,V,sigma", [("bf16", 4096, 0.3), ("f16", 32000, 0.5), ("bf16", 131072, 0.6),
                                            ("bf16", 8, 0.3), ("bf16", 200008, 0.6), ("f16", 524288, 0.8)])
 def test_tree_accept_fast_kernel_shapes(dtype, V, sigma, oracle_mod, pkg):
-    """The 1024-thread kernels on vocabularies from one partial step to the sixty-four steps they hold, with
+    """Node statistics and walk on vocabularies from one partial step to the sixty-four steps they hold, with
     a draft close enough to the target that later children get tested and long paths occur."""
     rng = np.random.default_rng(8)
     spec = np.array([0, 1, 8, 8, 20, 63, 3, 5, 12, 2, 7, 7, 30, 4], np.int32)

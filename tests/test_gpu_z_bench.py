@@ -1,4 +1,4 @@
-"""The benchmark's contract on a GPU machine: one JSON line with the agreed fields (short runs)."""
+"""The benchmark's contract on a GPU: one JSON line with the agreed fields (short runs)."""
 import json
 import os
 import subprocess
