@@ -162,13 +162,6 @@ class StepRunner:
         return self.pkg.accept_resolved_path(d.target_logits, d.draft_probs, d.draft_tokens, d.spec_lens,
                                              max_spec_len=self.kmax, path=self.path)
 
-    def in_row_parts(self, accept_path: str) -> bool:
-        """Whether a call that AUTO names a per-row path for runs with the two-pass form's kernels all the same
-        (the rule of adaspec_accept_resolved_path in include/adaspec.h; the workspace limit is far away here)."""
-        st = self.st
-        return (self.path == "auto" and accept_path in ("stream", "vector") and st.vocab % 8 == 0 and st.vocab <= 524288
-                and st.batch <= 1024 and st.batch * self.kmax <= 32768)
-
     def algorithmic_bytes(self) -> dict:
         """What counts as algorithmic bytes of the acceptance depends on the form that ran: the per-row
         forms read every logits row and every sampled draft-probability row; the two-pass form and the tree
@@ -182,7 +175,7 @@ class StepRunner:
         if self.tree and "walk" in ap:
             walk = W.tree_accept_bytes_walk_form(st, self.tpath.cpu().numpy(), self.alen.cpu().numpy())
             nb.update(accept=walk["accept"], total=nb["attn"] + walk["accept"])
-        elif ap == "two_pass" or self.in_row_parts(ap):
+        elif ap == "two_pass":
             skip = W.accept_bytes_skipping_form(st, self.alen.cpu().numpy())
             nb.update(accept=skip["accept"], total=nb["attn"] + skip["accept"])
         return nb
@@ -424,7 +417,7 @@ def main() -> int:
                                      "two-pass form: algorithmic bytes = every draft row's logits row once (accept "
                                      "test) + per request the deciding row (with its draft-probability row if it is a "
                                      "rejected sampled draft); rows the form skips are NOT counted"
-                                     if accept_path == "two_pass" or run.in_row_parts(accept_path) else
+                                     if accept_path == "two_pass" else
                                      "per-row form: every logits row and every sampled draft-probability row once"),
                             "per_row_form_bytes": nbytes["per_row_form_accept"],
                             "achieved": gbs(nbytes["accept"], acc_ms), "peak": HBM_PEAK_GBS, "unit": "GB/s",
