@@ -36,7 +36,7 @@ __global__ __launch_bounds__(256, (RT <= 2 ? 2 : 1)) void attn_mfma_kernel(
     const int32_t *__restrict__ unit_meta, const int32_t *__restrict__ sched,
     const unsigned long long *__restrict__ anc, float *__restrict__ part_ml, float *__restrict__ part_o,
     int Hq, int Hkv, int max_pages_per_req, int max_rows, int n_row_groups, float scale_log2,
-    int out_dtype, DirectArgs direct)
+    int out_dtype, int cus, DirectArgs direct)
 {
     constexpr int kRows = 16 * RT;
     // per wavefront: its V^T tile, later its [rows][d] fp32 state for the merge
@@ -71,7 +71,7 @@ __global__ __launch_bounds__(256, (RT <= 2 ? 2 : 1)) void attn_mfma_kernel(
     const int W = gridDim.x, wg = blockIdx.x;
     const int n_rounds = kDirect ? 0 : header[2];
     int round = 0;
-    int idx_ahead = wg;                                             // round 0 is the identity
+    int idx_ahead = sched_position(0, wg, W, cus);                  // round 0 needs no table
     auto next_unit = [&](Unit &u) -> bool {
         for (; round < n_rounds; ++round) {
             const int idx = idx_ahead;
@@ -486,7 +486,7 @@ hipError_t launch_attn_mfma(const AttnArgs &a)
                            (const int32_t *)(a.ws + p.off_unit_meta), (const int32_t *)(a.ws + p.off_sched),
                            (const unsigned long long *)(a.ws + p.off_anc), (float *)(a.ws + p.off_part_ml),
                            (float *)(a.ws + p.off_part_o), d.n_q_heads, d.n_kv_heads, d.max_pages_per_req, p.max_rows,
-                           a.n_row_groups, a.scale_log2, d.out_dtype, direct_args(a));
+                           a.n_row_groups, a.scale_log2, d.out_dtype, a.sched_cus, direct_args(a));
     });
     return hipGetLastError();
 }

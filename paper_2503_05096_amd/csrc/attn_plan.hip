@@ -171,18 +171,12 @@ __global__ __launch_bounds__(kPlanThreads) void attn_plan_kernel(
     if (!fast) return;
 
     // ---- static schedule of the matrix-core kernel ---------------------------------------------
-    // Units (item, kv head, row group) in the sorted item order are handed out in rounds of W, one
-    // per workgroup and round; thread w plays workgroup w.  Rounds alternate direction (round 0 is
-    // the identity, round 1 the reverse, ...), which evens out the work when every workgroup takes
-    // the same number of units.  The last kBalancedRounds rounds are assigned by accumulated work
-    // instead.  What has to be even there is the work per COMPUTE UNIT, not per workgroup: the
-    // workgroups resident on one compute unit share its load pipeline (the older one is served
-    // first), and a compute unit finishes when its total is done.  Workgroups w, w + cus,
-    // w + 2 cus, ... land on the same compute unit (the dispatcher fills the compute units in
-    // order, one workgroup each, then starts over), so such a round is cut into sub-rounds of
-    // `cus` units: in each the j-th longest unit goes to the compute unit with the j-th least
-    // work, found by a counting sort.  The table only decides who computes what; results do not
-    // depend on it, nor on the assumed placement.
+    // Units (item, kv head, row group) in the sorted item order are handed out in rounds of W, one per workgroup and
+    // round; thread w plays workgroup w.  Rounds follow sched_position, which evens out the work per compute unit when all
+    // of them take the same number of units.  The last kBalancedRounds rounds (never the first) are assigned by accumulated
+    // work instead: such a round is cut into sub-rounds of `cus` units, and in each the j-th longest unit goes to the
+    // compute unit with the j-th least work, found by a counting sort.  The table only decides who computes what; results
+    // do not depend on it, nor on the assumed placement.
     const int units_per_item = Hkv * n_row_groups;
     const int upi_log2 = (units_per_item & (units_per_item - 1)) == 0 ? log2_exact(units_per_item) : -1;
     const int total_units = n_items * units_per_item;
@@ -209,7 +203,7 @@ __global__ __launch_bounds__(kPlanThreads) void attn_plan_kernel(
     };
     for (int r = 0; r < rounds; ++r) {
         if (!(r >= 1 && items_on_chip && rounds - r <= kBalancedRounds)) {
-            if (tid < W) take(r, r * W + ((r & 1) ? (W - 1 - tid) : tid));
+            if (tid < W) take(r, sched_position(r, tid, W, cus));
             continue;
         }
         for (int base = 0; base < W; base += cus) {
