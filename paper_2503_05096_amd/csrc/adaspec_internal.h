@@ -50,11 +50,11 @@ __host__ __device__ inline int split_len_of(int L, int ns, int block_tokens)
 }
 
 // Matrix-core kernels: 16-row query tiles one unit holds and units per (item, kv head).  Up to 32 rows per
-// kv head: 1 or 2 tiles, the wavefronts of a workgroup split the unit's tokens (attn_mfma.hip); more: groups
-// of 4 tiles (64 rows), the wavefronts split the rows (attn_rows.hip).
+// kv head: 1 or 2 tiles (head_dim 128: attn_mfma.hip); up to 48: 3; more: groups of 4 tiles (attn_ring.hip).  The head_dim 64
+// and fp32 kernels use 4 tiles for 3.
 inline int attn_row_tiles(int max_rows)
 {
-    return max_rows <= 16 ? 1 : (max_rows <= 32 ? 2 : 4);
+    return max_rows <= 16 ? 1 : max_rows <= 32 ? 2 : max_rows <= 48 ? 3 : 4;
 }
 inline int attn_row_groups(int max_rows)
 {
@@ -121,9 +121,9 @@ hipError_t launch_attn_plan(const AttnArgs &a);
 hipError_t launch_tree_masks(const AttnArgs &a);
 hipError_t launch_attn_vector(const AttnArgs &a);
 hipError_t launch_attn_mfma(const AttnArgs &a);
-// row-split form for units of more than 32 rows (attn_rows.hip); launch_attn_mfma forwards to it
-hipError_t launch_attn_rows(const AttnArgs &a);
-int attn_rows_grid_slots(const AttnArgs &a, int cus);   // resident workgroups = columns of the schedule table
+// units of more than 32 rows (attn_ring.hip); launch_attn_mfma forwards to it
+hipError_t launch_attn_ring(const AttnArgs &a);
+int attn_ring_grid_slots(const AttnArgs &a, int cus);   // resident workgroups = columns of the schedule table
 // head_dim 64 (attn_d64.hip)
 hipError_t launch_attn_d64(const AttnArgs &a);
 int attn_d64_grid_slots(const AttnArgs &a, int cus);

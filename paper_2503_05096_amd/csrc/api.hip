@@ -124,6 +124,8 @@ AttnPlan make_attn_plan(const adaspec_attn_dims &d, AttnKind kind, bool tree)
     // item.  With few (request, kv head) pairs the splits are shortened so that
     // the chip still sees enough independent items.
     const int64_t pairs = (int64_t)d.batch * d.n_kv_heads;
+    p.max_rows = (d.max_spec_len + 1) * G;
+    const bool ring = kind == AttnKind::kMfma128 && attn_row_tiles(p.max_rows) > 2;
     if (scheduled) {
         p.block_tokens = kind == AttnKind::kMfma64 ? kAttnD64Block : (kind == AttnKind::kMfmaF32 ? 16 : 32);
         p.split_tokens = pairs >= 256 ? 2048 : (pairs >= 128 ? 1024 : (pairs >= 32 ? 512 : 256));
@@ -132,7 +134,6 @@ AttnPlan make_attn_plan(const adaspec_attn_dims &d, AttnKind kind, bool tree)
         p.split_tokens = 256;
     }
     const int64_t max_ctx = (int64_t)d.max_pages_per_req * d.page_size;
-    p.max_rows = (d.max_spec_len + 1) * G;
     p.direct = false;
     const int n_groups = attn_row_groups(p.max_rows);
     if (scheduled && !tree && d.batch <= kDirectMaxBatch) {
@@ -161,12 +162,13 @@ AttnPlan make_attn_plan(const adaspec_attn_dims &d, AttnKind kind, bool tree)
     if (scheduled && !tree && !p.direct && max_ctx <= p.split_tokens && max_ctx <= kDirectLongestShort && d.batch <= kDirectShortBatch) {
         // Short contexts: every request is one unit per kv head (no combine), all of them about equally short.  Measured
         // with and without (MI355X, 32/8 heads of 128, bf16): 256 requests of 100-500 tokens 62.6 / 65.5 us, 126 of 119-185
-        // 14.0 / 18.5, 64 of 512-1000 39.5 / 42.3, 128 of 256-1000 64.6 / 63.4 (left to the schedule).  The row-split and
-        // the fp32 kernel lose more by not loading across unit boundaries (200 requests of 100-400 tokens, 72 rows per
-        // kv head: 104 / 87; 88 of 9-30 tokens, 40 rows: 12.4 / 19.2): up to 1024 possible tokens per compute unit.
+        // 14.0 / 18.5, 64 of 512-1000 39.5 / 42.3, 128 of 256-1000 64.6 / 63.4 (left to the schedule).  The ring
+        // and the fp32 kernel lose more by not loading across unit boundaries, and gain as much where units are few: up to 4096
+        // and 1024 possible tokens per compute unit (ring, 64/8 heads, direct / scheduled: 100 of 50-300 tokens, 48 rows
+        // 25.5 / 30.8, 64 of 300-1000 37.4 / 39.6, of 400-1000, 40 rows 38.2 / 41.5, 200 of 20-120 30.6 / 37.2).
         const int64_t units = pairs * n_groups;
-        const bool deep = kind == AttnKind::kMfmaF32 || (kind == AttnKind::kMfma128 && attn_row_tiles(p.max_rows) > 2);
-        p.direct = deep ? units * max_ctx <= 262144 : units <= (max_ctx <= kDirectShortCtx ? 8192 : 512);
+        const int64_t deep = kind == AttnKind::kMfmaF32 ? 262144 : ring ? 1048576 : 0;
+        p.direct = deep ? units * max_ctx <= deep : units <= (max_ctx <= kDirectShortCtx ? 8192 : 512);
     }
     const int64_t per_req = (max_ctx + p.split_tokens - 1) / p.split_tokens;
     p.per_req = (int)per_req;

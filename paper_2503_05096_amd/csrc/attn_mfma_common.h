@@ -1,6 +1,5 @@
-// Pieces shared by the two matrix-core attention kernels (attn_mfma.hip: the wavefronts of a workgroup
-// split a unit's TOKENS; attn_rows.hip: they split its query ROWS): MFMA wrappers, the V^T tile layout,
-// the work-unit record.
+// Pieces shared by the matrix-core attention kernels (attn_mfma.hip, attn_ring.hip, attn_d64.hip, attn_f32.hip): MFMA
+// wrappers, loads into LDS, the V^T tile layout, the work-unit record.
 #pragma once
 #include "adaspec_internal.h"
 #include "device_utils.h"
@@ -85,6 +84,69 @@ __device__ __forceinline__ uint4 ld16_stream(const char *p)
 {
     const u32x4 t = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
     return make_uint4(t.x, t.y, t.z, t.w);
+}
+
+// ---- memory straight into LDS ------------------------------------------------------------------------------------------
+// Buffer loads with an LDS destination: lane i lands at lds + 16 i (M0 carries the LDS address; the data never passes through
+// registers).  Written in assembly on purpose: the compiler, not knowing which LDS bytes such a load will write, would make
+// every later LDS read wait until ALL loads in flight have landed.  The kernels wait for the one they need themselves
+// (wait_loads with the number of younger loads): the vector-memory counter retires in order, and whatever the compiler
+// puts in front or between only makes such a wait longer.
+typedef int v4i32 __attribute__((ext_vector_type(4)));
+
+// raw buffer: offsets in bytes, reads past the end give 0
+__device__ __forceinline__ v4i32 buffer_rsrc(const char *p, uint32_t bytes)
+{
+    const unsigned long long a = reinterpret_cast<unsigned long long>(p);
+    v4i32 r;
+    r.x = (int)(uint32_t)a;
+    r.y = (int)(uint32_t)(a >> 32);
+    r.z = (int)bytes;
+    r.w = 0x00020000;
+    return r;
+}
+// one (page, kv head) block of 4 KB
+__device__ __forceinline__ v4i32 page_rsrc(const char *p) { return buffer_rsrc(p, 16 * kD * 2); }
+
+__device__ __forceinline__ uint32_t lds_address(const void *p)
+{
+    return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const char *)p;
+}
+// a page: instruction j moves 1024 bytes; the offset field moves the memory AND the LDS address by 1024 j
+__device__ __forceinline__ void load_page_to_lds(const v4i32 &rsrc, uint32_t off0, uint32_t off1, uint32_t off2, uint32_t off3, uint32_t lds)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %5, 0 offen nt lds\n\t"
+                 "buffer_load_dwordx4 %2, %5, 0 offen offset:1024 nt lds\n\t"
+                 "buffer_load_dwordx4 %3, %5, 0 offen offset:2048 nt lds\n\t"
+                 "buffer_load_dwordx4 %4, %5, 0 offen offset:3072 nt lds"
+                 :: "s"(lds), "v"(off0), "v"(off1), "v"(off2), "v"(off3), "s"(rsrc) : "memory", "m0");
+}
+__device__ __forceinline__ void load16_to_lds(const v4i32 &rsrc, uint32_t off, uint32_t lds)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" :: "s"(lds), "v"(off), "s"(rsrc) : "memory", "m0");
+}
+// 4 bytes per lane, lane i at lds + 4 i
+__device__ __forceinline__ void load4_to_lds(const v4i32 &rsrc, uint32_t off, uint32_t lds)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds" :: "s"(lds), "v"(off), "s"(rsrc) : "memory", "m0");
+}
+// until at most N of this wavefront's vector-memory operations are outstanding / until its LDS reads have returned
+template <int N> __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
+__device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+
+// 16 bytes of a split's state, written through to the level that all compute units share
+__device__ __forceinline__ void store_state(float *p, f32x4 v)
+{
+    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" :: "v"(p), "v"(v) : "memory");
+}
+
+// 64-bit transposing LDS read: inside each group of 16 lanes, lane i gives the address of four 16-bit elements, row i / 4 and
+// columns 4 (i % 4) .. + 3 of a 4 x 16 tile, and gets column i (rows 0 .. 3).
+__device__ __forceinline__ uint2 read_transposed(uint32_t lds)
+{
+    typedef short v4i16 __attribute__((ext_vector_type(4)));
+    typedef __attribute__((address_space(3))) v4i16 lds_v4i16;
+    return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16 *)lds));
 }
 
 // Maximum over the four lanes n, n + 16, n + 32, n + 48 (the lanes that hold the same query row in the
