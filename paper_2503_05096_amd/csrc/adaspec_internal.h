@@ -72,11 +72,16 @@ inline int attn_row_groups(int max_rows)
 // long units land beside the shortest ones of the first.  Fullest compute unit over the mean, before (rounds of W
 // workgroups in turn, the first one straight) / now: 64 requests of 1024-2048 tokens, 8 kv heads (512 units for 512
 // workgroups) 1.15 / 1.00, main kernel 69.6 / 65.4 us; 64 log-normal ones of 128-4096 1.23 / 1.13, 64.3 / 60.8 us.
+// (in workgroup c of sub-round `sub`; n_sub = sub-rounds per round)
+__host__ __device__ inline int sched_position_in(int round, int sub, int c, int n_sub, int W, int cus)
+{
+    const int base = sub * cus, width = W - base < cus ? W - base : cus;
+    return round * W + base + ((__builtin_popcount(round * n_sub + sub) & 1) ? c : width - 1 - c);
+}
 __host__ __device__ inline int sched_position(int round, int w, int W, int cus)
 {
-    const int sub = w / cus, base = sub * cus, width = W - base < cus ? W - base : cus, c = w - base;
-    const int turn = round * ((W + cus - 1) / cus) + sub;
-    return round * W + base + ((__builtin_popcount(turn) & 1) ? c : width - 1 - c);
+    const int sub = w / cus;
+    return sched_position_in(round, sub, w - sub * cus, (W + cus - 1) / cus, W, cus);
 }
 
 // Which kernel family a call takes.  ADASPEC_PATH_FAST names the head_dim 128 form; AUTO also reaches the others.

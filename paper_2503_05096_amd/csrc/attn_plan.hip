@@ -22,6 +22,23 @@ __host__ __device__ inline int log2_exact(int v)          // v is a power of two
 // a context length no split count of which overflows
 __device__ __forceinline__ int plan_ctx(int ctx_len) { return min(max(ctx_len, 1), 1 << 30); }
 
+// Tree calls (batches up to kFusedMaskMaxBatch): the plan kernels' workgroups 1.. build the ancestor masks beside the
+// plan, one wavefront per request.  They share nothing with workgroup 0: each wavefront adds up the rows of the requests
+// before its own.
+template <int kThreads>
+__device__ __forceinline__ void mask_workgroup(const int32_t *__restrict__ spec_lens, int B, int total_q, int max_spec_len,
+                                               const int32_t *__restrict__ parents, unsigned long long *__restrict__ anc)
+{
+    const int i = (blockIdx.x - 1) * (kThreads / kWave) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (i >= B) return;
+    int part = 0;
+    for (int j = lane; j < i; j += kWave) part += min(max(spec_lens[j], 0), max_spec_len) + 1;
+    const int r0 = wave_sum(part);
+    const int n = min(max(spec_lens[i], 0), max_spec_len) + 1;
+    if (r0 + n > total_q) return;                       // inconsistent metadata: leave the rows alone
+    tree_masks_of_request(parents, r0, n, lane, anc);
+}
+
 // One workgroup.  cu_q = exclusive scan of n_i = spec_lens[i] + 1; split_base = exclusive scan of
 // the per-request split counts ceil(L_i / S); a work item is one (request, split).  Values are
 // clamped to the host-declared bounds so that inconsistent device data cannot make the library
@@ -45,17 +62,7 @@ __global__ __launch_bounds__(kPlanThreads) void attn_plan_kernel(
     int want_cu_q, const int32_t *__restrict__ parents, unsigned long long *__restrict__ anc)
 {
     if (blockIdx.x > 0) {
-        // Tree calls (batches up to kFusedMaskMaxBatch): workgroups 1.. build the ancestor masks beside the
-        // plan, one wavefront per request.  They share nothing with workgroup 0: each wavefront adds up the
-        // rows of the requests before its own.
-        const int i = (blockIdx.x - 1) * (kPlanThreads / kWave) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-        if (i >= B) return;
-        int part = 0;
-        for (int j = lane; j < i; j += kWave) part += min(max(spec_lens[j], 0), max_spec_len) + 1;
-        const int r0 = wave_sum(part);
-        const int n = min(max(spec_lens[i], 0), max_spec_len) + 1;
-        if (r0 + n > total_q) return;                   // inconsistent metadata: leave the rows alone
-        tree_masks_of_request(parents, r0, n, lane, anc);
+        mask_workgroup<kPlanThreads>(spec_lens, B, total_q, max_spec_len, parents, anc);
         return;
     }
     __shared__ int tot_n[kPlanThreads / kWave], tot_s[kPlanThreads / kWave];
@@ -235,13 +242,161 @@ __global__ __launch_bounds__(kPlanThreads) void attn_plan_kernel(
     }
 }
 
+// The same for the batches that serve: up to kSmallThreads requests, their items and the device's compute units on chip.  One
+// wavefront per SIMD, so that a barrier costs a tenth of a microsecond less, and fewer of them: a request puts all its
+// items in place itself (two lengths at most: full splits and the last one), and thread c keeps the work of compute unit c,
+// whose workgroups c, c + cus, ... it plays, in a register.
+//
+// Bound: latency (launch, one memory round trip for the lengths, LDS round trips and barriers).  Kernel time on MI355X,
+// the general kernel / this one: 64 requests of 1024-2048 tokens, 8 kv heads (one round) 4.2 / 3.0 us, 64 of
+// 256-4096 (two) 7.1 / 5.3, 32 of 256-2048, 32 kv heads 7.2 / 5.5, 64 of 2048-8192 (three) 7.4 / 5.9.
+constexpr int kSmallThreads = 256;
+constexpr int kWorkBins = 1024;          // of the counting sort by accumulated work
+
+__global__ __launch_bounds__(kSmallThreads) void attn_plan_small_kernel(
+    const int32_t *__restrict__ ctx_lens, const int32_t *__restrict__ spec_lens, int B, int total_q,
+    int max_spec_len, int split_log2, int block_log2, int max_items, int G, int32_t *__restrict__ header,
+    int32_t *__restrict__ unit_meta, int32_t *__restrict__ row_rec, int W, int Hkv, int n_row_groups, int rows_per_group,
+    int32_t *__restrict__ sched, int cus, const int32_t *__restrict__ parents, unsigned long long *__restrict__ anc)
+{
+    if (blockIdx.x > 0) {
+        mask_workgroup<kSmallThreads>(spec_lens, B, total_q, max_spec_len, parents, anc);
+        return;
+    }
+    constexpr int kPlanWaves = kSmallThreads / kWave, kBinsPerThread = kWorkBins / kSmallThreads;
+    static_assert(kBinsPerThread == 4, "a thread's bins are one 16-byte access");
+    __shared__ int2 tot[kPlanWaves];
+    __shared__ int hist[kWave], taken[kWave], wave_tot[kPlanWaves];
+    __shared__ __attribute__((aligned(16))) int bins[kWorkBins], place[kWorkBins];
+    __shared__ uint16_t item_size[kSchedItems];                 // per SORTED item: token blocks, row groups << 8
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, i = tid;
+    const int split_tokens = 1 << split_log2, block_tokens = 1 << block_log2;
+    int n = 0, ns = 0, L = 1;
+    if (i < B) {
+        n = min(max(spec_lens[i], 0), max_spec_len) + 1;
+        L = plan_ctx(ctx_lens[i]);
+        ns = (L + split_tokens - 1) >> split_log2;
+    }
+    if (tid < kWave) { hist[tid] = 0; taken[tid] = 0; }
+    *reinterpret_cast<int4 *>(bins + 4 * tid) = make_int4(0, 0, 0, 0);
+
+    // ---- first row and first item of every request ----------------------------------------------
+    const int inc_n = wave_scan_incl_dpp(n), inc_s = wave_scan_incl_dpp(ns);
+    if (lane == 63) tot[wv] = make_int2(inc_n, inc_s);
+    lds_barrier();
+    int my_q = inc_n - n, my_s = inc_s - ns, all_s = 0;
+#pragma unroll
+    for (int w = 0; w < kPlanWaves; ++w) {
+        const int2 t = tot[w];
+        my_q += w < wv ? t.x : 0;
+        my_s += w < wv ? t.y : 0;
+        all_s += t.y;
+    }
+    const int n_items = min(all_s, max_items);
+
+    // ---- items by length, longest first (counting sort on the length in token blocks) -----------
+    const int per_split = split_tokens >> block_log2;
+    const int nbins = min(kWave, max(1, per_split));
+    const int slen = split_len_of(L, max(ns, 1), block_tokens);
+    const int last_len = ns > 0 ? L - (ns - 1) * slen : 1;
+    auto blocks_of = [&](int len) { return (len + block_tokens - 1) >> block_log2; };
+    auto bin_of = [&](int len) {              // bin 0 = longest; more than 64 blocks per split are scaled down to 64 bins
+        const int scaled = per_split <= kWave ? blocks_of(len) : (int)(((int64_t)len * nbins + split_tokens - 1) >> split_log2);
+        return nbins - min(max(scaled, 1), nbins);
+    };
+    const int here = min(ns, max(max_items - my_s, 0));        // (all of them unless the lengths contradict the host's bounds)
+    const int n_full = min(here, max(ns - 1, 0)), n_last = here - n_full;
+    const int bin_full = bin_of(slen), bin_last = bin_of(last_len);
+    if (n_full > 0) atomicAdd(&hist[bin_full], n_full);
+    if (n_last > 0) atomicAdd(&hist[bin_last], 1);
+    // (under way meanwhile) record for the combine kernel: (request, number of splits, first split, first row index of
+    // this query row inside its (item, kv head) partial block)
+    for (int j = 0; j < n; ++j)
+        if (my_q + j < total_q) *reinterpret_cast<int4 *>(row_rec + 4 * (int64_t)(my_q + j)) = make_int4(i, ns, my_s, j * G);
+    lds_barrier();
+    const int in_bin = hist[lane], before = wave_scan_incl_dpp(in_bin) - in_bin;    // every wavefront for itself
+    const int groups = min(ceil_div(n * G, rows_per_group), 255);
+    auto put = [&](int pos, int s, int len) {
+        int32_t *m = unit_meta + 8 * (int64_t)pos;
+        *reinterpret_cast<int4 *>(m) = make_int4(i, s, ns, L);
+        *reinterpret_cast<int4 *>(m + 4) = make_int4(n, my_q, my_s + s, 0);
+        item_size[pos] = (uint16_t)(min(blocks_of(len), 255) | groups << 8);
+    };
+    const int at_full = __shfl(before, bin_full, kWave), at_last = __shfl(before, bin_last, kWave);
+    if (n_full > 0) {
+        const int pos = at_full + atomicAdd(&taken[bin_full], n_full);
+        for (int s = 0; s < n_full; ++s) put(pos + s, s, slen);
+    }
+    if (n_last > 0) put(at_last + atomicAdd(&taken[bin_last], 1), n_full, last_len);
+
+    // ---- static schedule (see the general kernel) -------------------------------------------------
+    const int units_per_item = Hkv * n_row_groups;
+    const int upi_log2 = (units_per_item & (units_per_item - 1)) == 0 ? log2_exact(units_per_item) : -1;
+    const int total_units = n_items * units_per_item;
+    const int rounds = ceil_div(total_units, W), n_sub = ceil_div(W, cus);
+    if (tid == 0) { header[0] = n_items; header[1] = 0; header[2] = rounds; }
+    int shift = 0;                              // compute-unit work >> shift fits the bins
+    {
+        const int64_t most = (int64_t)rounds * n_sub * (255 + kUnitFixedBlocks);
+        while ((most >> shift) >= kWorkBins) ++shift;
+    }
+    lds_barrier();                             // item_size is complete
+    int work = 0;                              // of compute unit tid, so far
+    auto take = [&](int r, int w, int idx) {   // workgroup w takes unit idx (if it exists) in round r
+        int v = -1;
+        if (idx < total_units) {
+            v = idx;
+            const int pos = upi_log2 >= 0 ? idx >> upi_log2 : idx / units_per_item;
+            const int rg = n_row_groups == 1 ? 0 : idx % n_row_groups;
+            const int size = item_size[pos];
+            if (rg < size >> 8) work += (size & 255) + kUnitFixedBlocks;
+        }
+        if (r > 0) sched[(int64_t)r * W + w] = v;                // (round 0 is not looked up)
+    };
+    for (int r = 0; r < rounds; ++r) {
+        const bool balanced = r >= 1 && rounds - r <= kBalancedRounds;
+        for (int sub = 0; sub < n_sub; ++sub) {
+            const int base = sub * cus;
+            const bool active = tid < min(cus, W - base);
+            if (!balanced || r * W + base >= total_units) {
+                if (active) take(r, base + tid, balanced ? total_units : sched_position_in(r, sub, tid, n_sub, W, cus));
+                continue;
+            }
+            const int key = min(work >> shift, kWorkBins - 1);
+            if (active) atomicAdd(&bins[key], 1);
+            lds_barrier();
+            int4 b = *reinterpret_cast<const int4 *>(bins + 4 * tid);
+            *reinterpret_cast<int4 *>(bins + 4 * tid) = make_int4(0, 0, 0, 0);       // for the next sub-round
+            const int mine = (b.x + b.y) + (b.z + b.w), inc = wave_scan_incl_dpp(mine);
+            if (lane == 63) wave_tot[wv] = inc;
+            lds_barrier();
+            int pre = inc - mine;
+#pragma unroll
+            for (int w = 0; w < kPlanWaves; ++w) pre += w < wv ? wave_tot[w] : 0;
+            *reinterpret_cast<int4 *>(place + 4 * tid) = make_int4(pre, pre + b.x, pre + b.x + b.y, pre + b.x + b.y + b.z);
+            lds_barrier();
+            if (active) take(r, base + tid, r * W + base + atomicAdd(&place[key], 1));
+        }
+    }
+}
+
 hipError_t launch_attn_plan(const AttnArgs &a)
 {
     const AttnPlan &p = a.plan;
-    // tree calls: one more workgroup per 16 requests for the ancestor masks (see the kernel)
+    // tree calls: more workgroups for the ancestor masks, a wavefront per request (see the kernels)
     const bool fused_masks = a.parents != nullptr && a.dims.batch <= kFusedMaskMaxBatch;
-    const int mask_wgs = fused_masks ? ceil_div(a.dims.batch, kPlanThreads / kWave) : 0;
-    hipLaunchKernelGGL(attn_plan_kernel, dim3(1 + mask_wgs), dim3(kPlanThreads), 0, a.stream, a.ctx_lens,
+    auto workgroups = [&](int threads) { return dim3(1 + (fused_masks ? ceil_div(a.dims.batch, threads / kWave) : 0)); };
+    if (a.sched_w > 0 && a.dims.batch <= kSmallThreads && p.max_items <= kSchedItems && a.sched_cus <= kSmallThreads) {
+        hipLaunchKernelGGL(attn_plan_small_kernel, workgroups(kSmallThreads), dim3(kSmallThreads), 0, a.stream, a.ctx_lens,
+                           a.spec_lens, a.dims.batch, a.dims.total_q, a.dims.max_spec_len,
+                           log2_exact(p.split_tokens), log2_exact(p.block_tokens), p.max_items,
+                           a.dims.n_q_heads / a.dims.n_kv_heads, (int32_t *)(a.ws + p.off_header),
+                           (int32_t *)(a.ws + p.off_unit_meta), (int32_t *)(a.ws + p.off_row_rec), a.sched_w,
+                           a.dims.n_kv_heads, a.n_row_groups, a.rows_per_group, (int32_t *)(a.ws + p.off_sched),
+                           a.sched_cus, a.parents, (unsigned long long *)(a.ws + p.off_anc));
+        return hipGetLastError();
+    }
+    hipLaunchKernelGGL(attn_plan_kernel, workgroups(kPlanThreads), dim3(kPlanThreads), 0, a.stream, a.ctx_lens,
                        a.spec_lens, a.dims.batch, a.dims.total_q, a.dims.max_spec_len,
                        log2_exact(p.split_tokens), log2_exact(p.block_tokens), p.max_items,
                        a.dims.n_q_heads / a.dims.n_kv_heads, (int32_t *)(a.ws + p.off_header),
