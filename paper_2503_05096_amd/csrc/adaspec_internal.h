@@ -31,15 +31,21 @@ struct AttnPlan {
     size_t off_anc;         // uint64[TQ]: tree verification only, ancestor-or-self mask of each query row's node
     size_t off_part_ml;     // float[max_items][Hkv][max_rows][2]  (m in log2 units, l)
     size_t off_part_o;      // float[max_items][Hkv][max_rows][d]
+    size_t off_flags;       // uint64[units][4]: direct calls that merge their splits in the kernel (attn_mfma_common.h)
     size_t total_bytes;
     bool direct;            // small chain calls: one workgroup per possible unit, no metadata kernel (attn_mfma_common.h)
     int per_req;            // possible splits per request: ceil(max_pages_per_req * page_size / split_tokens)
+    bool merged;            // direct, and whoever finishes a request's last split merges them: no combine kernel
 };
+
+// Direct calls whose requests can have up to so many splits merge them in the kernel (attn_mfma_common.h).
+constexpr int kMergeMaxSplits = 4;
 
 // What a kernel of a direct call needs to find its unit by itself.
 struct DirectArgs {
     const int32_t *ctx_lens, *spec_lens;
     int batch, max_spec_len, total_q, per_req, split_tokens;
+    unsigned long long *flags, mark;    // splits merged in the kernel, else null: a word per unit and wavefront; what this launch leaves there
 };
 
 // Length of every split of a request with L cached tokens cut into ns splits.
@@ -109,10 +115,7 @@ struct AttnArgs {
     bool direct = false;      // plan.direct
 };
 
-inline DirectArgs direct_args(const AttnArgs &a)
-{
-    return DirectArgs{a.ctx_lens, a.spec_lens, a.dims.batch, a.dims.max_spec_len, a.dims.total_q, a.plan.per_req, a.plan.split_tokens};
-}
+DirectArgs direct_args(const AttnArgs &a);      // (api.hip; every call gives another mark)
 
 // Upper bound on W for which the workspace holds a schedule table.
 constexpr int kMaxSchedW = 1024;

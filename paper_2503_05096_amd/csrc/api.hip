@@ -6,7 +6,9 @@
 #include <math.h>
 #include <string.h>
 
+#include <atomic>
 #include <mutex>
+#include <random>
 
 #include "adaspec_internal.h"
 #include "device_utils.h"
@@ -172,6 +174,13 @@ AttnPlan make_attn_plan(const adaspec_attn_dims &d, AttnKind kind, bool tree)
     }
     const int64_t per_req = (max_ctx + p.split_tokens - 1) / p.split_tokens;
     p.per_req = (int)per_req;
+    // Splits merged in the kernel, not by a second one: up to 4 possible splits, up to two row tiles (beyond that the last
+    // workgroup of a request has more to read than the other launch costs).  MI355X, whole calls back to back, with the
+    // combine kernel / without: fp32, 4 requests of 128-512 tokens 10.8 / 7.8 us, 8 of 100-500 10.0 / 9.0; 16 bits, 8 of
+    // 300-1000, 32/8 heads of 128 11.9 / 11.5, 1 of 600 11.4 / 11.4, 16 of 100-900, 16/2 heads 13.3 / 12.7, 32 of 100-900, 8/1
+    // 13.4 / 12.6, 8 of 500-2000, 14/2 heads of 64 13.2 / 11.7.  With 8 splits 1 of 2000 11.0-11.5 / 10.8-11.4 (10.6 / 11.2 in a
+    // captured graph, where a launch costs less), with 6 and two tiles 1 of 1500 12.0 / 12.7.
+    p.merged = p.direct && per_req > 1 && per_req <= kMergeMaxSplits && attn_row_tiles(p.max_rows) <= 2;
     p.max_items = (int)((int64_t)d.batch * per_req);
     size_t off = 0;
     p.off_header = off;     off = align_up(off + 16 * sizeof(int32_t), 256);
@@ -190,8 +199,32 @@ AttnPlan make_attn_plan(const adaspec_attn_dims &d, AttnKind kind, bool tree)
     off = align_up(off + (size_t)p.max_items * d.n_kv_heads * p.max_rows * 2 * sizeof(float), 256);
     p.off_part_o = off;
     off = align_up(off + (size_t)p.max_items * d.n_kv_heads * p.max_rows * d.head_dim * sizeof(float), 256);
+    p.off_flags = off;
+    if (p.merged) off = align_up(off + (size_t)p.max_items * d.n_kv_heads * n_groups * kWavesPerUnit * sizeof(uint64_t), 256);
     p.total_bytes = off;
     return p;
+}
+
+// Marks are never given twice, and start at an arbitrary place: leftovers in a workspace, of whatever kind, do not look
+// like one.
+static uint64_t next_mark()
+{
+    static std::atomic<uint64_t> mark{[] {
+        std::random_device rd;
+        return (uint64_t)rd() << 32 | rd();
+    }()};
+    uint64_t m = mark.fetch_add(1, std::memory_order_relaxed);
+    return m != 0 ? m : mark.fetch_add(1, std::memory_order_relaxed);      // (0 is what a merge leaves)
+}
+
+DirectArgs direct_args(const AttnArgs &a)
+{
+    DirectArgs d{a.ctx_lens, a.spec_lens, a.dims.batch, a.dims.max_spec_len, a.dims.total_q, a.plan.per_req, a.plan.split_tokens, nullptr, 0};
+    if (a.plan.merged) {
+        d.flags = reinterpret_cast<unsigned long long *>(a.ws + a.plan.off_flags);
+        d.mark = next_mark();
+    }
+    return d;
 }
 
 // chain and tree calls of the same dims ask for the same workspace
@@ -306,7 +339,7 @@ static int verify_attn_impl(const void *q, const void *k_pages, const void *v_pa
                    : kind == AttnKind::kMfmaF32 ? launch_attn_f32(a) : launch_attn_mfma(a);
     if (e != hipSuccess) return ADASPEC_ERR_HIP;
     if (!record_event(dims->timing_start, dims->timing_stop, false, a.stream)) return ADASPEC_ERR_HIP;
-    if (launch_attn_combine(a) != hipSuccess) return ADASPEC_ERR_HIP;
+    if (!a.plan.merged && launch_attn_combine(a) != hipSuccess) return ADASPEC_ERR_HIP;
     return ADASPEC_OK;
 }
 

@@ -375,14 +375,25 @@ __global__ __launch_bounds__(256, (RT <= 2 ? 2 : 1)) void attn_d64_kernel(
                 }
             } else {
                 const int64_t idx_row = ((int64_t)u.item * Hkv + u.gkv) * max_rows + row;
-                *reinterpret_cast<f32x4 *>(part_o + idx_row * kD64 + 4 * c4) = acc;
-                if (c4 == 0) {
-                    part_ml[idx_row * 2] = ms;
-                    part_ml[idx_row * 2 + 1] = ltot;
+                if (kDirect && direct.flags) {
+                    store_state(part_o + idx_row * kD64 + 4 * c4, acc);
+                    if (c4 == 0) store_ml(part_ml + idx_row * 2, ms, ltot);
+                } else {
+                    *reinterpret_cast<f32x4 *>(part_o + idx_row * kD64 + 4 * c4) = acc;
+                    if (c4 == 0) {
+                        part_ml[idx_row * 2] = ms;
+                        part_ml[idx_row * 2 + 1] = ltot;
+                    }
                 }
             }
         }
-        if constexpr (kDirect) break;
+        if constexpr (kDirect) {
+            if constexpr (RT <= 2) {
+                if (u.ns > 1 && direct.flags)
+                    merge_splits<T, kD64, kRows>(direct, u, part_ml, part_o, out, out_dtype, Hq, Hkv, G, max_rows, n_row_groups, tid);
+            }
+            break;
+        }
         // the next loop iteration overwrites q_lds, the V^T tiles and s_m: everyone must be done reading the states
         lds_barrier();
         cur = nxt;
