@@ -103,7 +103,7 @@ typedef struct {
     int32_t plan_mode;          /* adaspec_plan_mode (below); 0 for a self-contained call */
     void   *timing_start;       /* optional pair of hipEvent_t (both or neither, NULL = none):      */
     void   *timing_stop;        /* recorded on `stream` right before / right after the call's main
-                                   kernel (not the metadata kernel, not the split-KV combine), for
+                                   kernel (not the metadata kernel, not a split-KV combine of its own), for
                                    callers that want the kernel's own duration.  Events belong to
                                    the caller, who must keep them alive until they have completed. */
 } adaspec_attn_dims;

@@ -7,6 +7,7 @@
 #include <string.h>
 
 #include <atomic>
+#include <chrono>
 #include <mutex>
 #include <random>
 
@@ -209,9 +210,13 @@ AttnPlan make_attn_plan(const adaspec_attn_dims &d, AttnKind kind, bool tree)
 // like one.
 static uint64_t next_mark()
 {
-    static std::atomic<uint64_t> mark{[] {
-        std::random_device rd;
-        return (uint64_t)rd() << 32 | rd();
+    static std::atomic<uint64_t> mark{[]() -> uint64_t {
+        try {
+            std::random_device rd;
+            return (uint64_t)rd() << 32 | rd();
+        } catch (...) {                         // (no source of entropy: the clock, spread over the word)
+            return (uint64_t)std::chrono::system_clock::now().time_since_epoch().count() * 0x9e3779b97f4a7c15ull;
+        }
     }()};
     uint64_t m = mark.fetch_add(1, std::memory_order_relaxed);
     return m != 0 ? m : mark.fetch_add(1, std::memory_order_relaxed);      // (0 is what a merge leaves)
