@@ -35,6 +35,7 @@ struct AttnPlan {
     size_t total_bytes;
     bool direct;            // small chain calls: one workgroup per possible unit, no metadata kernel (attn_mfma_common.h)
     int per_req;            // possible splits per request: ceil(max_pages_per_req * page_size / split_tokens)
+    bool row_split;         // more than 32 rows per kv head: attn_rows.hip instead of attn_ring.hip (api.hip)
     bool merged;            // direct, and whoever finishes a request's last split merges them: no combine kernel
 };
 
@@ -56,7 +57,7 @@ __host__ __device__ inline int split_len_of(int L, int ns, int block_tokens)
 }
 
 // Matrix-core kernels: 16-row query tiles one unit holds and units per (item, kv head).  Up to 32 rows per
-// kv head: 1 or 2 tiles (head_dim 128: attn_mfma.hip); up to 48: 3; more: groups of 4 tiles (attn_ring.hip).  The head_dim 64
+// kv head: 1 or 2 tiles (head_dim 128: attn_mfma.hip); up to 48: 3; more: groups of 4 tiles (attn_ring.hip, attn_rows.hip).  The head_dim 64
 // and fp32 kernels use 4 tiles for 3.
 inline int attn_row_tiles(int max_rows)
 {
@@ -129,9 +130,11 @@ hipError_t launch_attn_plan(const AttnArgs &a);
 hipError_t launch_tree_masks(const AttnArgs &a);
 hipError_t launch_attn_vector(const AttnArgs &a);
 hipError_t launch_attn_mfma(const AttnArgs &a);
-// units of more than 32 rows (attn_ring.hip); launch_attn_mfma forwards to it
+// units of more than 32 rows (attn_ring.hip, or attn_rows.hip where plan.row_split); launch_attn_mfma forwards to them
 hipError_t launch_attn_ring(const AttnArgs &a);
 int attn_ring_grid_slots(const AttnArgs &a, int cus);   // resident workgroups = columns of the schedule table
+hipError_t launch_attn_rows(const AttnArgs &a);
+int attn_rows_grid_slots(const AttnArgs &a, int cus);
 // head_dim 64 (attn_d64.hip)
 hipError_t launch_attn_d64(const AttnArgs &a);
 int attn_d64_grid_slots(const AttnArgs &a, int cus);

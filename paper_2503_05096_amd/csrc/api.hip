@@ -102,6 +102,7 @@ static int validate_attn_dims(const adaspec_attn_dims *d)
 constexpr int kDirectMaxBatch = 256;
 constexpr int kDirectMaxUnits = 256, kDirectFewPairs = 128, kDirectMaxUnitsFew = 512;
 constexpr int kDirectShortCtx = 512, kDirectLongestShort = 1024, kDirectShortBatch = 1024;
+constexpr int kDirectF32Tokens = 262144, kDirectRowsTokens = 262144, kDirectRingTokens = 1048576;   // possible tokens of all units
 constexpr int kWavesPerUnit = 4;
 
 AttnKind attn_kind(const adaspec_attn_dims &d)
@@ -117,6 +118,35 @@ AttnKind attn_kind(const adaspec_attn_dims &d)
     return AttnKind::kVector;
 }
 
+// More than 32 rows per kv head (16 bits, head_dim 128): the kernel whose wavefronts split the rows (attn_rows.hip) or the
+// one whose wavefronts split the tokens (attn_ring.hip).  A unit of a few blocks gives the ring's wavefronts a block each, or
+// none, all row tiles of it one after the other, and a merge behind; a unit of many blocks gives the row split a barrier per
+// block.  `tokens`: a split of the longest possible request.  The line moves with the number of row tiles and groups (four
+// tiles: a longer chain in the ring), with units > 256, where two workgroups share a compute unit, and for trees, whose masks the
+// ring with four tiles reads from memory.  MI355X, captured calls, bf16, row split / ring:
+//   3 tiles, 64/8 heads, 8 requests of 16-32 tokens 5.9 / 7.1 us, 33-64 6.9 / 8.0, 48-96 7.8 / 8.1, 64-128 8.7 / 8.4, 128-256
+//   12.1 / 10.1; 64 of 96-192 14.1 / 15.1, 128-256 16.4 / 16.4; trees, 64 of 128-256 20.3 / 21.3, 256-512 28.2 / 27.2
+//   4 tiles, 64/8 heads, 8 requests of 16-32 6.2 / 8.3, 64-128 9.0 / 9.3, 96-192 10.3 / 11.3, 128-256 12.2 / 11.7; 64 of 128-256
+//   17.2 / 19.1, 256-512 26.6 / 27.4, 300-600 33.4 / 30.4; trees, 64 of 300-600 32.5 / 34.4, 500-1000 45.9 / 45.5, 128 of 500-1000
+//   80 / 82, 1000-2000 143 / 143
+//   two groups of 4 (72 rows), 64/8 heads, 32 of 128-256 16.3 / 18.3, 256-512 24.8 / 24.3; 250 of 128-256 84.3 / 99.1
+// Requests of several splits have units of any length up to the whole split, so only one or two of them are safe to judge by
+// the longest: 1 of 288 tokens, 56 rows 12.8 / 14.6, 2 of 375 and 525 13.9 / 15.0, 4 of 200-400 15.6 / 15.0.
+static bool rows_split_wins(int tiles, int groups, bool tree, int batch, int64_t units, int64_t per_req, int64_t tokens)
+{
+    const bool four = tiles > 3, single = groups == 1;
+    if (per_req > 1) {
+        if (!single && !tree && units > 256 && units <= 512) return tokens <= 256;      // (8 of 300-600, 72 rows: 18.7 / 20.0)
+        return four ? batch <= 2 && tokens <= 224 : batch == 1 && tokens <= 160;
+    }
+    // beyond this many tokens chains in one group are direct calls with the ring only (below), which is ahead of the row split
+    // with its schedule (250 of 96-192, 8 kv heads, 3 tiles 51.6 / 46.5; in two groups, whose second is mostly empty, 73.9 / 92.1)
+    if (!tree && single && units * tokens > kDirectRowsTokens) return false;
+    if (units <= 256) return tokens <= (four ? (tree ? 320 : 192) : (tree ? 128 : 96));
+    if (units <= 512) return tokens <= (!four ? (tree ? 416 : 192) : single ? (tree ? 768 : 512) : (tree ? 512 : 384));
+    return tokens <= (!four ? (tree ? 128 : 96) : single ? (tree ? 1024 : 192) : (tree ? 512 : 320));
+}
+
 AttnPlan make_attn_plan(const adaspec_attn_dims &d, AttnKind kind, bool tree)
 {
     AttnPlan p;
@@ -128,7 +158,7 @@ AttnPlan make_attn_plan(const adaspec_attn_dims &d, AttnKind kind, bool tree)
     // the chip still sees enough independent items.
     const int64_t pairs = (int64_t)d.batch * d.n_kv_heads;
     p.max_rows = (d.max_spec_len + 1) * G;
-    const bool ring = kind == AttnKind::kMfma128 && attn_row_tiles(p.max_rows) > 2;
+    const bool many_rows = kind == AttnKind::kMfma128 && attn_row_tiles(p.max_rows) > 2;
     if (scheduled) {
         p.block_tokens = kind == AttnKind::kMfma64 ? kAttnD64Block : (kind == AttnKind::kMfmaF32 ? 16 : 32);
         p.split_tokens = pairs >= 256 ? 2048 : (pairs >= 128 ? 1024 : (pairs >= 32 ? 512 : 256));
@@ -139,6 +169,11 @@ AttnPlan make_attn_plan(const adaspec_attn_dims &d, AttnKind kind, bool tree)
     const int64_t max_ctx = (int64_t)d.max_pages_per_req * d.page_size;
     p.direct = false;
     const int n_groups = attn_row_groups(p.max_rows);
+    auto row_split = [&]() -> bool {                        // (with the splits of now)
+        const int64_t per_req = (max_ctx + p.split_tokens - 1) / p.split_tokens, even = (max_ctx + per_req - 1) / per_req;
+        return many_rows && rows_split_wins(attn_row_tiles(p.max_rows), n_groups, tree, d.batch, pairs * n_groups * per_req, per_req,
+                                            (even + p.block_tokens - 1) / p.block_tokens * p.block_tokens);
+    };
     if (scheduled && !tree && d.batch <= kDirectMaxBatch) {
         // Small batches: the shortest split (two blocks per wavefront or more: with one, the workspace and the work of the
         // combine double and the call gets no faster) with which every possible unit has a compute unit of its own, or half
@@ -165,16 +200,18 @@ AttnPlan make_attn_plan(const adaspec_attn_dims &d, AttnKind kind, bool tree)
     if (scheduled && !tree && !p.direct && max_ctx <= p.split_tokens && max_ctx <= kDirectLongestShort && d.batch <= kDirectShortBatch) {
         // Short contexts: every request is one unit per kv head (no combine), all of them about equally short.  Measured
         // with and without (MI355X, 32/8 heads of 128, bf16): 256 requests of 100-500 tokens 62.6 / 65.5 us, 126 of 119-185
-        // 14.0 / 18.5, 64 of 512-1000 39.5 / 42.3, 128 of 256-1000 64.6 / 63.4 (left to the schedule).  The ring
-        // and the fp32 kernel lose more by not loading across unit boundaries, and gain as much where units are few: up to 4096
-        // and 1024 possible tokens per compute unit (ring, 64/8 heads, direct / scheduled: 100 of 50-300 tokens, 48 rows
+        // 14.0 / 18.5, 64 of 512-1000 39.5 / 42.3, 128 of 256-1000 64.6 / 63.4 (left to the schedule).  The
+        // kernels of more than 32 rows and the fp32 kernel lose more by not loading across unit boundaries, and gain as much where
+        // units are few: up to 4096 possible tokens per compute unit (ring), 1024 (the others; row split, 72 rows, 200 of 100-400
+        // 104 / 87; ring, 64/8 heads, direct / scheduled: 100 of 50-300 tokens, 48 rows
         // 25.5 / 30.8, 64 of 300-1000 37.4 / 39.6, of 400-1000, 40 rows 38.2 / 41.5, 200 of 20-120 30.6 / 37.2).
         const int64_t units = pairs * n_groups;
-        const int64_t deep = kind == AttnKind::kMfmaF32 ? 262144 : ring ? 1048576 : 0;
+        const int64_t deep = kind == AttnKind::kMfmaF32 ? kDirectF32Tokens : !many_rows ? 0 : row_split() ? kDirectRowsTokens : kDirectRingTokens;
         p.direct = deep ? units * max_ctx <= deep : units <= (max_ctx <= kDirectShortCtx ? 8192 : 512);
     }
     const int64_t per_req = (max_ctx + p.split_tokens - 1) / p.split_tokens;
     p.per_req = (int)per_req;
+    p.row_split = row_split();
     // Splits merged in the kernel, not by a second one: up to 4 possible splits, up to two row tiles (beyond that the last
     // workgroup of a request has more to read than the other launch costs).  MI355X, whole calls back to back, with the
     // combine kernel / without: fp32, 4 requests of 128-512 tokens 10.8 / 7.8 us, 8 of 100-500 10.0 / 9.0; 16 bits, 8 of

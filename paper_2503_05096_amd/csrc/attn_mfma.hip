@@ -471,7 +471,7 @@ void attn_mfma_shape(AttnArgs &a, AttnKind kind)
     } else if (kind == AttnKind::kMfma64) {
         slots = attn_d64_grid_slots(a, device_cus());
     } else if (rt > 2) {
-        slots = attn_ring_grid_slots(a, device_cus());               // more than 32 rows
+        slots = p.row_split ? attn_rows_grid_slots(a, device_cus()) : attn_ring_grid_slots(a, device_cus());
     } else {
         with_instance(a, [&](auto tag, auto rt_tag, auto tree, auto direct) {
             slots = attn_mfma_slots<decltype(tag), decltype(rt_tag)::value, decltype(tree)::value, decltype(direct)::value>();
@@ -485,7 +485,7 @@ hipError_t launch_attn_mfma(const AttnArgs &a)
     const AttnPlan &p = a.plan;
     const adaspec_attn_dims &d = a.dims;
     if (a.sched_w <= 0) return hipSuccess;                          // no work item can exist
-    if (attn_row_tiles(p.max_rows) > 2) return launch_attn_ring(a);
+    if (attn_row_tiles(p.max_rows) > 2) return p.row_split ? launch_attn_rows(a) : launch_attn_ring(a);
     with_instance(a, [&](auto tag, auto rt, auto tree, auto direct) {
         hipLaunchKernelGGL((attn_mfma_kernel<decltype(tag), decltype(rt)::value, decltype(tree)::value, decltype(direct)::value>),
                            dim3(a.sched_w), dim3(256), 0, a.stream, (const char *)a.q, (const char *)a.k_pages,

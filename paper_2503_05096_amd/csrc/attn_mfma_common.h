@@ -1,4 +1,4 @@
-// Pieces shared by the matrix-core attention kernels (attn_mfma.hip, attn_ring.hip, attn_d64.hip, attn_f32.hip): MFMA
+// Pieces shared by the matrix-core attention kernels (attn_mfma.hip, attn_ring.hip, attn_rows.hip, attn_d64.hip, attn_f32.hip): MFMA
 // wrappers, loads into LDS, the V^T tile layout, the work-unit record.
 #pragma once
 #include "adaspec_internal.h"

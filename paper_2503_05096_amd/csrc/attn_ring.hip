@@ -10,9 +10,9 @@
 // as soon as its operands are out of it, K's ahead of the arithmetic, V's behind it.  K operands are ordinary 16-byte reads;
 // V^T operands come out of the row-major slot through gfx950's transposing reads.
 //
-// Bound: HBM.  The row-split form that stood here before shared every block among the four wavefronts, one row tile each,
-// behind a barrier per block: a unit of 8 rows kept one wavefront busy and three waiting, and the operands of a block were
-// read four times.  Whole calls on MI355X (bf16, 64/8 heads, up to 48 rows), before / now: 64 requests of 2048-8192 tokens
+// Bound: HBM.  The row split (attn_rows.hip, which keeps the short contexts) shares every block among the four wavefronts, one
+// row tile each, behind a barrier per block: a unit of 8 rows keeps one wavefront busy and three waiting, and the operands of a
+// block are read four times.  Whole calls on MI355X (bf16, 64/8 heads, up to 48 rows), row split / ring: 64 requests of 2048-8192 tokens
 // 259 / 250 us, 48 of 1024-4096 119 / 105, 40 of 4000 160 / 138, 60 of 500 and 4 of 16000 103 / 85, 64 of 300-1000 44.3 / 39.8;
 // 28/4 heads, 80 of 1000-6000 137 / 126.  A probe that only loads reaches 6.3 TB/s on this pattern through registers or one
 // shared ring and 6.8 TB/s with a ring per wavefront; without the states of the splits the kernel runs at 6.5 TB/s, but
@@ -363,8 +363,8 @@ __global__ __launch_bounds__(256, 2) void attn_ring_kernel(
             }
         }
 
-        // ---- a context of one block has one state: straight out of the registers (88 requests of 9-30 tokens, 40 rows, 64/8
-        // heads: 13.3 us, 14.9 through the merge).  Lane (g, n16) holds O^T[16 dt + 4 g .. + 3][row n16 of the tile].
+        // ---- a context of one block (beside longer ones: calls of short contexts only take attn_rows.hip) has one state: straight
+        // out of the registers (88 requests of 9-30 tokens, 40 rows, 64/8 heads: 13.3 us, 14.9 through the merge).  Lane (g, n16) holds O^T[16 dt + 4 g .. + 3][row n16 of the tile].
         if (kDirect && u.ns == 1 && u.nblk == 1) {
             if (wv > 0) break;
 #pragma unroll

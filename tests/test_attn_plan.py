@@ -19,9 +19,9 @@ def plans(tmp_path_factory):
                            os.path.join(ROOT, "tests", "native", "plan_driver.cpp"),
                            "-o", exe, build.LIB_PATH, f"-Wl,-rpath,{lib}"])
 
-    def run(cases):
+    def run(cases, *args):
         text = "\n".join(" ".join(map(str, c)) for c in cases)
-        lines = subprocess.run([exe], input=text, capture_output=True, text=True, check=True).stdout.splitlines()
+        lines = subprocess.run([exe, *args], input=text, capture_output=True, text=True, check=True).stdout.splitlines()
         assert len(lines) == len(cases)
         return [tuple(map(int, l.split())) for l in lines]
     return run
@@ -54,3 +54,18 @@ def test_the_width_of_the_block_table_does_not_multiply_the_combine(plans):
     for c, p in zip(cases, plans(cases)):
         possible, pairs = -(-c[1] * 16 // p[0]), c[0] * (c[5] + 1) * c[2]
         assert p[8] == (4 if possible > 8 and pairs <= 768 else 1), (c, p)
+
+
+def test_short_contexts_of_many_rows_split_the_rows(plans):
+    """More than 32 rows per kv head: a context of a few blocks leaves a ring per wavefront without work for most of them,
+    so those calls take the kernel whose wavefronts split the rows; up to 32 rows and other types know no such choice."""
+    def kernels(*c):
+        return plans([c], "kernels")[0][2:]
+    for B in (1, 16, 88, 250):
+        for hq, hkv, k in ((64, 8, 4), (64, 8, 5), (28, 4, 7), (64, 8, 8), (16, 1, 7)):       # 40, 48, 56, 72, 128 rows
+            assert kernels(B, 2, hq, hkv, 128, k, BF16) == (1, 1), (B, hq, hkv, k)
+            assert kernels(B, 128, hq, hkv, 128, k, BF16) == (0, 0), (B, hq, hkv, k)
+    assert kernels(88, 12, 64, 8, 128, 7, BF16) == (1, 1)       # 192 tokens: four tiles
+    assert kernels(88, 12, 64, 8, 128, 5, BF16) == (0, 0)       # three
+    assert kernels(48, 12, 64, 8, 128, 5, BF16) == (1, 1)       # three, two units side by side on a compute unit
+    assert kernels(88, 2, 32, 8, 128, 7, BF16) == kernels(88, 2, 64, 8, 64, 7, BF16) == kernels(88, 2, 64, 8, 128, 7, F32) == (0, 0)
