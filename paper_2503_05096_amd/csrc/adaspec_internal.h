@@ -20,7 +20,7 @@ struct AttnPlan {
     int   max_items;        // host-side bound on the number of work items
     int   max_rows;         // (max_spec_len + 1) * G
     // byte offsets into the workspace
-    size_t off_header;      // int32[16]: [0] n_items, [1] unused, [2] rounds of the static schedule
+    size_t off_header;      // int32[16]: [0] n_items, [1] order of the static schedule, [2] its rounds
     size_t off_cu_q;        // int32[B + 1]
     size_t off_split_base;  // int32[B + 1]: first item of each request
     size_t off_item_req;    // int32[max_items]
@@ -72,23 +72,64 @@ inline int attn_row_groups(int max_rows)
 // Schedule of the matrix-core kernels: which unit (in the order of decreasing length) workgroup w of W takes in a round that
 // is not balanced by accumulated work.  What has to be even is the work per COMPUTE UNIT: workgroups w, w + cus, w + 2 cus,
 // ... land on the same one (the dispatcher fills the compute units in order, one workgroup each, then starts over), share
-// its load pipeline, and are done when their total is done.  So a round is cut into sub-rounds of `cus` workgroups, each of
-// which runs through its units forwards or backwards.  Directions by the parity of the bits of the sub-round's number
-// (backwards, forwards, forwards, backwards, ...): four sub-rounds then even out a convex distribution of lengths as well
-// as a linear one, which strict alternation does not; the first runs backwards, so that where the second is not full its
-// long units land beside the shortest ones of the first.  Fullest compute unit over the mean, before (rounds of W
-// workgroups in turn, the first one straight) / now: 64 requests of 1024-2048 tokens, 8 kv heads (512 units for 512
-// workgroups) 1.15 / 1.00, main kernel 69.6 / 65.4 us; 64 log-normal ones of 128-4096 1.23 / 1.13, 64.3 / 60.8 us.
+// its load pipeline, and are done when their total is done.  Orders (sched_order chooses, the header carries):
+//
+// kSchedEven, up to four rounds: a round is cut into sub-rounds of `cus` workgroups, each of which runs through its units
+// forwards or backwards.  Directions by the parity of the bits of the sub-round's number (backwards, forwards, forwards,
+// backwards, ...): four sub-rounds then even out a convex distribution of lengths as well as a linear one, which strict
+// alternation does not; the first runs backwards, so that where the second is not full its long units land beside the shortest
+// ones of the first.  Fullest compute unit over the mean, whole rounds in turn / this way: 64 requests of 1024-2048 tokens, 8
+// kv heads (512 units for 512 workgroups) 1.15 / 1.00, main kernel 69.6 / 65.4 us; 64 log-normal ones of 128-4096 1.23 / 1.13,
+// 64.3 / 60.8 us.
+//
+// n > 0: two sub-rounds, and n compute units take a third unit in a second round.  On top of even totals that would be streamed
+// by those few alone at the end: they take the shortest units for their first two, the others pairs of the longest.  Captured
+// calls, whole rounds in turn / even / this way: 270 requests of 500-1500 tokens, 2 kv heads (540 units) 57.6 / 60.5 / 55.4 us, 300
+// (600) 60.8 / 64.4 / 60.5, 67 of 1000-1900, 8 kv heads (536) 81.3 / 84.4 / 75.1.  Skewed lengths stay even: pairs of the longest
+// would be the longest by far (175 log-normal ones of 128-2000, 4 kv heads 64.3 / 59.0 / 70.9).
+//
+// kSchedRounds, more rounds: whole rounds in turn, forwards and backwards (300 requests of 100-500, 8 kv heads of 64, five
+// rounds: main kernel 41.1 us, even 41.8; three and four rounds gain 3 % from even ones where lengths are skewed).
+constexpr int kSchedEven = 0, kSchedRounds = -1;
 // (in workgroup c of sub-round `sub`; n_sub = sub-rounds per round)
-__host__ __device__ inline int sched_position_in(int round, int sub, int c, int n_sub, int W, int cus)
+__host__ __device__ inline int sched_position_in(int round, int sub, int c, int n_sub, int W, int cus, int order)
 {
-    const int base = sub * cus, width = W - base < cus ? W - base : cus;
+    const int base = sub * cus, w = base + c;
+    if (order == kSchedRounds) return round * W + ((round & 1) ? W - 1 - w : w);
+    if (order > 0 && round == 0) {
+        const int two = cus - order;                                // compute units with two units
+        if (c < order) return sub == 0 ? W - 1 - c : 2 * two + c;   // (the third goes to workgroup c: behind the shorter one)
+        return sub == 0 ? c - order : 2 * two - 1 - (c - order);
+    }
+    const int width = W - base < cus ? W - base : cus;
     return round * W + base + ((__builtin_popcount(round * n_sub + sub) & 1) ? c : width - 1 - c);
 }
-__host__ __device__ inline int sched_position(int round, int w, int W, int cus)
+__host__ __device__ inline int sched_position(int round, int w, int W, int cus, int order)
 {
     const int sub = w / cus;
-    return sched_position_in(round, sub, w - sub * cus, (W + cus - 1) / cus, W, cus);
+    return sched_position_in(round, sub, w - sub * cus, (W + cus - 1) / cus, W, cus, order);
+}
+// Order of a schedule of `total` units.  Whether some third units go on even pairs or on the shortest units follows from which
+// leaves the fullest compute unit less: size[k] is the work of unit sched_sample(k) in the order of decreasing length (even
+// pairs (k, W - 1 - k) looked at in both ends and in the middle, as most distributions make their sums monotonic between).
+__host__ __device__ inline bool sched_asks_sizes(int total, int W, int cus) { return W == 2 * cus && total > W && total <= W + cus; }
+constexpr int kSchedSamples = 9;
+__host__ __device__ inline int sched_sample(int k, int total, int W, int cus)
+{
+    const int two = cus - (total - W);
+    const int at = k == 0 ? 0 : k == 1 ? W - 1 : k == 2 ? cus / 2 : k == 3 ? W - 1 - cus / 2 : k == 4 ? cus - 1 : k == 5 ? cus
+                   : k == 6 ? W : k == 7 ? 2 * two - 1 : 2 * two;
+    return at < 0 ? 0 : at;
+}
+__host__ __device__ inline int sched_order(int total, int W, int cus, const int (&size)[kSchedSamples])
+{
+    if (!sched_asks_sizes(total, W, cus)) return total > 4 * W ? kSchedRounds : kSchedEven;
+    const int ends = size[0] + size[1], quarter = size[2] + size[3], middle = size[4] + size[5];
+    const int most = ends > quarter ? (ends > middle ? ends : middle) : (quarter > middle ? quarter : middle);
+    const int least = ends < quarter ? (ends < middle ? ends : middle) : (quarter < middle ? quarter : middle);
+    const int even = most > least + size[6] ? most : least + size[6];
+    const int pair = total < W + cus ? size[0] + size[7] : 0, three = size[8] + size[1] + size[6];
+    return even > (pair > three ? pair : three) ? total - W : kSchedEven;
 }
 
 // Which kernel family a call takes.  ADASPEC_PATH_FAST names the head_dim 128 form; AUTO also reaches the others.

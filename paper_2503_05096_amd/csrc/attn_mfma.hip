@@ -71,7 +71,7 @@ __global__ __launch_bounds__(256, (RT <= 2 ? 2 : 1)) void attn_mfma_kernel(
     const int W = gridDim.x, wg = blockIdx.x;
     const int n_rounds = kDirect ? 0 : header[2];
     int round = 0;
-    int idx_ahead = sched_position(0, wg, W, cus);                  // round 0 needs no table
+    int idx_ahead = kDirect ? 0 : sched_position(0, wg, W, cus, header[1]);     // round 0 needs no table
     auto next_unit = [&](Unit &u) -> bool {
         for (; round < n_rounds; ++round) {
             const int idx = idx_ahead;

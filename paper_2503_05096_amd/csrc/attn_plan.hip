@@ -39,6 +39,19 @@ __device__ __forceinline__ void mask_workgroup(const int32_t *__restrict__ spec_
     tree_masks_of_request(parents, r0, n, lane, anc);
 }
 
+// sched_order with the sizes it asks for looked up by a lane each
+template <class F>
+__device__ __forceinline__ int order_of(int total, int W, int cus, int lane, F &&size_of)
+{
+    int size[kSchedSamples] = {};
+    if (sched_asks_sizes(total, W, cus)) {
+        const int mine = size_of(sched_sample(min(lane, kSchedSamples - 1), total, W, cus));
+#pragma unroll
+        for (int k = 0; k < kSchedSamples; ++k) size[k] = __builtin_amdgcn_readlane(mine, k);
+    }
+    return sched_order(total, W, cus, size);
+}
+
 // One workgroup.  cu_q = exclusive scan of n_i = spec_lens[i] + 1; split_base = exclusive scan of
 // the per-request split counts ceil(L_i / S); a work item is one (request, split).  Values are
 // clamped to the host-declared bounds so that inconsistent device data cannot make the library
@@ -119,7 +132,6 @@ __global__ __launch_bounds__(kPlanThreads) void attn_plan_kernel(
     if (tid == 0) {
         if (!fast) { cu_q[B] = carry[0]; split_base[B] = carry[1]; }
         header[0] = min(carry[1], max_items);   // number of work items
-        header[1] = 0;                          // (unused)
     }
     // Schedule order: longest items first (counting sort on the length in token blocks), so that
     // the workgroups that take units last get the short items and the tail of the launch is short.
@@ -179,11 +191,10 @@ __global__ __launch_bounds__(kPlanThreads) void attn_plan_kernel(
 
     // ---- static schedule of the matrix-core kernel ---------------------------------------------
     // Units (item, kv head, row group) in the sorted item order are handed out in rounds of W, one per workgroup and
-    // round; thread w plays workgroup w.  Rounds follow sched_position, which evens out the work per compute unit when all
-    // of them take the same number of units.  The last kBalancedRounds rounds (never the first) are assigned by accumulated
-    // work instead: such a round is cut into sub-rounds of `cus` units, and in each the j-th longest unit goes to the
-    // compute unit with the j-th least work, found by a counting sort.  The table only decides who computes what; results
-    // do not depend on it, nor on the assumed placement.
+    // round; thread w plays workgroup w.  Rounds follow sched_position in the order sched_order chooses.  The last
+    // kBalancedRounds rounds (never the first) are assigned by accumulated work instead: such a round is cut into sub-rounds
+    // of `cus` units, and in each the j-th longest unit goes to the compute unit with the j-th least work, found by a counting
+    // sort.  The table only decides who computes what; results do not depend on it, nor on the assumed placement.
     const int units_per_item = Hkv * n_row_groups;
     const int upi_log2 = (units_per_item & (units_per_item - 1)) == 0 ? log2_exact(units_per_item) : -1;
     const int total_units = n_items * units_per_item;
@@ -196,21 +207,21 @@ __global__ __launch_bounds__(kPlanThreads) void attn_plan_kernel(
         while ((most >> shift) >= kPlanThreads) ++shift;
     }
     lds_barrier();                             // item_blocks / item_groups are complete
+    auto size_of = [&](int idx) -> int {
+        const int pos = upi_log2 >= 0 ? idx >> upi_log2 : idx / units_per_item;
+        const int rg = n_row_groups == 1 ? 0 : idx % n_row_groups;
+        const int blocks = item_blocks[pos], groups = item_groups[pos];
+        return rg < groups ? blocks + kUnitFixedBlocks : 0;
+    };
+    const int order = items_on_chip || !sched_asks_sizes(total_units, W, cus) ? order_of(total_units, W, cus, lane, size_of) : kSchedEven;
+    if (tid == 0) header[1] = order;
     auto take = [&](int r, int idx) {          // workgroup tid takes unit idx (if it exists) in round r
-        int v = -1;
-        if (idx < total_units) {
-            v = idx;
-            if (items_on_chip) {
-                const int pos = upi_log2 >= 0 ? idx >> upi_log2 : idx / units_per_item;
-                const int rg = n_row_groups == 1 ? 0 : idx % n_row_groups;
-                if (rg < item_groups[pos]) wg_work[tid] += item_blocks[pos] + kUnitFixedBlocks;
-            }
-        }
-        sched[(int64_t)r * W + tid] = v;
+        if (items_on_chip && idx < total_units) wg_work[tid] += size_of(idx);
+        sched[(int64_t)r * W + tid] = idx < total_units ? idx : -1;
     };
     for (int r = 0; r < rounds; ++r) {
         if (!(r >= 1 && items_on_chip && rounds - r <= kBalancedRounds)) {
-            if (tid < W) take(r, sched_position(r, tid, W, cus));
+            if (tid < W) take(r, sched_position(r, tid, W, cus, order));
             continue;
         }
         for (int base = 0; base < W; base += cus) {
@@ -334,7 +345,7 @@ __global__ __launch_bounds__(kSmallThreads) void attn_plan_small_kernel(
     const int upi_log2 = (units_per_item & (units_per_item - 1)) == 0 ? log2_exact(units_per_item) : -1;
     const int total_units = n_items * units_per_item;
     const int rounds = ceil_div(total_units, W), n_sub = ceil_div(W, cus);
-    if (tid == 0) { header[0] = n_items; header[1] = 0; header[2] = rounds; }
+    if (tid == 0) { header[0] = n_items; header[2] = rounds; }
     int shift = 0;                              // compute-unit work >> shift fits the bins
     {
         const int64_t most = (int64_t)rounds * n_sub * (255 + kUnitFixedBlocks);
@@ -342,16 +353,16 @@ __global__ __launch_bounds__(kSmallThreads) void attn_plan_small_kernel(
     }
     lds_barrier();                             // item_size is complete
     int work = 0;                              // of compute unit tid, so far
+    auto size_of = [&](int idx) -> int {
+        const int pos = upi_log2 >= 0 ? idx >> upi_log2 : idx / units_per_item;
+        const int rg = n_row_groups == 1 ? 0 : idx % n_row_groups, size = item_size[pos];
+        return rg < (size >> 8) ? (size & 255) + kUnitFixedBlocks : 0;
+    };
+    const int order = order_of(total_units, W, cus, lane, size_of);
+    if (tid == 0) header[1] = order;
     auto take = [&](int r, int w, int idx) {   // workgroup w takes unit idx (if it exists) in round r
-        int v = -1;
-        if (idx < total_units) {
-            v = idx;
-            const int pos = upi_log2 >= 0 ? idx >> upi_log2 : idx / units_per_item;
-            const int rg = n_row_groups == 1 ? 0 : idx % n_row_groups;
-            const int size = item_size[pos];
-            if (rg < size >> 8) work += (size & 255) + kUnitFixedBlocks;
-        }
-        if (r > 0) sched[(int64_t)r * W + w] = v;                // (round 0 is not looked up)
+        if (idx < total_units) work += size_of(idx);
+        if (r > 0) sched[(int64_t)r * W + w] = idx < total_units ? idx : -1;      // (round 0 is not looked up)
     };
     for (int r = 0; r < rounds; ++r) {
         const bool balanced = r >= 1 && rounds - r <= kBalancedRounds;
@@ -359,7 +370,7 @@ __global__ __launch_bounds__(kSmallThreads) void attn_plan_small_kernel(
             const int base = sub * cus;
             const bool active = tid < min(cus, W - base);
             if (!balanced || r * W + base >= total_units) {
-                if (active) take(r, base + tid, balanced ? total_units : sched_position_in(r, sub, tid, n_sub, W, cus));
+                if (active) take(r, base + tid, balanced ? total_units : sched_position_in(r, sub, tid, n_sub, W, cus, order));
                 continue;
             }
             const int key = min(work >> shift, kWorkBins - 1);

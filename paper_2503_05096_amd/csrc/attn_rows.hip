@@ -73,6 +73,7 @@ __global__ __launch_bounds__(256, 2) void attn_rows_kernel(
     const int total_units = kDirect ? 0 : header[0] * Hkv * n_row_groups;
     const int n_rounds = kDirect ? 0 : header[2];
     const int W = gridDim.x, wg = blockIdx.x;
+    const int first = kDirect ? 0 : sched_position(0, wg, W, cus, header[1]);
 
     // ---- work units of this workgroup, in schedule order; two cursors walk them: the loader runs kAhead
     // blocks ahead of the arithmetic, across unit boundaries
@@ -80,7 +81,7 @@ __global__ __launch_bounds__(256, 2) void attn_rows_kernel(
         if constexpr (kDirect)                                      // one unit per workgroup
             return round++ == 0 && direct_unit(u, direct, block_table, G, Hkv, n_row_groups, kRowsPerGroup, kBlk, max_pages_per_req, 0, lane);
         for (; round < n_rounds; ++round) {
-            const int idx = round == 0 ? sched_position(0, wg, W, cus) : sched[(int64_t)round * W + wg];
+            const int idx = round == 0 ? first : sched[(int64_t)round * W + wg];
             if (idx < 0 || idx >= total_units) continue;
             const int rg = idx % n_row_groups;
             u.gkv = (idx / n_row_groups) % Hkv;

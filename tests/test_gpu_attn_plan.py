@@ -5,7 +5,9 @@ import numpy as np
 import pytest
 import torch
 
+import workloads as W
 from tests.test_gpu_parity import pkg  # noqa: F401  (fixture)
+from tests.test_gpu_tree import _check_tree_attention
 
 pytestmark = pytest.mark.gpu
 
@@ -43,3 +45,15 @@ def test_both_metadata_kernels_give_the_same(B, hq, hkv, d, k, dtype, tree, pkg)
     outs = [pkg.verify_attn(q, kp, vp, dev(t), dev(ctx), dev(spec), max_spec_len=k, **kw) for t in (narrow, wide)]
     assert torch.isfinite(outs[0]).all()
     assert torch.equal(*outs)
+
+
+@pytest.mark.parametrize("hq,hkv,d,k,dtype", [(8, 8, 64, 2, "f32"), (16, 8, 64, 3, "bf16"), (8, 8, 128, 3, "f16"), (32, 8, 128, 6, "bf16"),
+                                              (64, 8, 128, 4, "bf16")], ids=lambda v: str(v))
+@pytest.mark.parametrize("B,longest", [(66, 900), (80, 300)])
+def test_some_compute_units_take_a_third_unit(B, longest, hq, hkv, d, k, dtype, pkg, oracle_mod):  # noqa: F811
+    """A few more units than a round of two per compute unit holds; kernels and metadata have to agree on who takes which."""
+    ctx = longest // 3 + (longest - longest // 3) * np.random.default_rng(B).permutation(B) // B
+    st = W.make_custom_step(B + k, ctx_lens=ctx, spec_lens=[k - i % 2 for i in range(B)], n_q_heads=hq, n_kv_heads=hkv, head_dim=d, dtype=dtype,
+                            vocab=64, name=f"thirds-{B}-{hq}-{d}-{dtype}")
+    W.attach_tree(st, 2)
+    _check_tree_attention(st, oracle_mod, pkg)
