@@ -90,6 +90,8 @@ __global__ __launch_bounds__(kPlanThreads) void attn_plan_kernel(
     const bool fast = W > 0;
     const bool items_on_chip = max_items <= kSchedItems && B <= 65535;  // host-side bounds: uniform
     const bool reqs_on_chip = B <= kPlanThreads;
+    int sub = tid / cus;                       // of workgroup tid in a round (a division: done while the lengths travel)
+    asm volatile("" : "+v"(sub));
     if (tid == 0) { carry[0] = 0; carry[1] = 0; }
     lds_barrier();
     for (int base = 0; base < B; base += kPlanThreads) {
@@ -200,7 +202,6 @@ __global__ __launch_bounds__(kPlanThreads) void attn_plan_kernel(
     const int total_units = n_items * units_per_item;
     const int rounds = ceil_div(total_units, W);
     if (tid == 0) header[2] = rounds;
-    wg_work[tid] = 0;
     int shift = 0;                              // compute-unit work >> shift fits the bins
     {
         const int64_t most = (int64_t)rounds * ceil_div(W, cus) * (255 + kUnitFixedBlocks);
@@ -215,15 +216,24 @@ __global__ __launch_bounds__(kPlanThreads) void attn_plan_kernel(
     };
     const int order = items_on_chip || !sched_asks_sizes(total_units, W, cus) ? order_of(total_units, W, cus, lane, size_of) : kSchedEven;
     if (tid == 0) header[1] = order;
-    auto take = [&](int r, int idx) {          // workgroup tid takes unit idx (if it exists) in round r
-        if (items_on_chip && idx < total_units) wg_work[tid] += size_of(idx);
-        sched[(int64_t)r * W + tid] = idx < total_units ? idx : -1;
-    };
-    for (int r = 0; r < rounds; ++r) {
-        if (!(r >= 1 && items_on_chip && rounds - r <= kBalancedRounds)) {
-            if (tid < W) take(r, sched_position(r, tid, W, cus, order));
-            continue;
+    int work = 0;                              // of workgroup tid, so far
+    // workgroup tid takes unit idx (if it exists) in round r; no branch around the look-up, so that those of several rounds are
+    // under way together
+    auto take = [&](int r, int idx) {
+        const bool exists = idx < total_units;
+        if (items_on_chip) {
+            const int size = size_of(exists ? idx : 0);
+            work += exists ? size : 0;
         }
+        sched[(int64_t)r * W + tid] = exists ? idx : -1;
+    };
+    const int plain = items_on_chip && rounds > 1 ? max(rounds - kBalancedRounds, 1) : rounds;      // rounds by position
+    if (tid < W) {
+        const int n_sub = ceil_div(W, cus);
+#pragma unroll 4
+        for (int r = 0; r < plain; ++r) take(r, sched_position_in(r, sub, tid - sub * cus, n_sub, W, cus, order));
+    }
+    for (int r = plain; r < rounds; ++r) {
         for (int base = 0; base < W; base += cus) {
             const int c = tid - base;
             const bool active = c >= 0 && c < min(cus, W - base);
@@ -231,6 +241,7 @@ __global__ __launch_bounds__(kPlanThreads) void attn_plan_kernel(
                 if (active) take(r, total_units);
                 continue;
             }
+            wg_work[tid] = work;
             lds_barrier();                      // wg_work of everything assigned so far
             bins[tid] = 0;
             int cu_work = 0;
@@ -258,9 +269,12 @@ __global__ __launch_bounds__(kPlanThreads) void attn_plan_kernel(
 // items in place itself (two lengths at most: full splits and the last one), and thread c keeps the work of compute unit c,
 // whose workgroups c, c + cus, ... it plays, in a register.
 //
-// Bound: latency (launch, one memory round trip for the lengths, LDS round trips and barriers).  Kernel time on MI355X,
-// the general kernel / this one: 64 requests of 1024-2048 tokens, 8 kv heads (one round) 4.2 / 3.0 us, 64 of
-// 256-4096 (two) 7.1 / 5.3, 32 of 256-2048, 32 kv heads 7.2 / 5.5, 64 of 2048-8192 (three) 7.4 / 5.9.
+// Bound: latency (launch, one memory round trip for the lengths, LDS round trips and barriers); with many rounds the look-ups and
+// stores of the table, a row of it per thread and sub-round: they run four at a time, which takes as long as in the general
+// kernel, whose threads have one per round (behind branches, one after the other, 16 rounds took 13.2 us).  Medians of kernel
+// traces of whole calls on MI355X, contexts of 600-1100 tokens, the general kernel / this one: 8 kv heads, 64 requests (one
+// round) 4.7 / 4.7 us, 80 (two) 5.7 / 4.8, 128 (two) 7.1 / 5.3, 250 (four) 7.5 / 6.4; 32 kv heads, 64 (four) 7.3 / 6.1, 128 (eight) 8.4 / 7.5, 200
+// 8.4 / 8.5, 250 (sixteen) 10.3 / 10.3.  Requests of many splits are no worse: one of 2097152 tokens (8192 items) 853 / 780 us the call.
 constexpr int kSmallThreads = 256;
 constexpr int kWorkBins = 1024;          // of the counting sort by accumulated work
 
@@ -360,17 +374,27 @@ __global__ __launch_bounds__(kSmallThreads) void attn_plan_small_kernel(
     };
     const int order = order_of(total_units, W, cus, lane, size_of);
     if (tid == 0) header[1] = order;
-    auto take = [&](int r, int w, int idx) {   // workgroup w takes unit idx (if it exists) in round r
-        if (idx < total_units) work += size_of(idx);
-        if (r > 0) sched[(int64_t)r * W + w] = idx < total_units ? idx : -1;      // (round 0 is not looked up)
+    // workgroup w takes unit idx (if it exists) in round r; no branch around the look-up (as above)
+    auto take = [&](int r, int w, int idx, bool active) {
+        const bool exists = active && idx < total_units;
+        const int size = size_of(exists ? idx : 0);
+        work += exists ? size : 0;
+        if (active && r > 0) sched[(int64_t)r * W + w] = exists ? idx : -1;       // (round 0 is not looked up)
     };
-    for (int r = 0; r < rounds; ++r) {
-        const bool balanced = r >= 1 && rounds - r <= kBalancedRounds;
-        for (int sub = 0; sub < n_sub; ++sub) {
+    const int plain = rounds > 1 ? max(rounds - kBalancedRounds, 1) : rounds;      // rounds by position
+    int r = 0, sub = 0;
+#pragma unroll 4
+    for (int k = 0; k < plain * n_sub; ++k) {
+        const int base = sub * cus;
+        take(r, base + tid, sched_position_in(r, sub, tid, n_sub, W, cus, order), tid < min(cus, W - base));
+        if (++sub == n_sub) { sub = 0; ++r; }
+    }
+    for (r = plain; r < rounds; ++r) {
+        for (sub = 0; sub < n_sub; ++sub) {
             const int base = sub * cus;
             const bool active = tid < min(cus, W - base);
-            if (!balanced || r * W + base >= total_units) {
-                if (active) take(r, base + tid, balanced ? total_units : sched_position_in(r, sub, tid, n_sub, W, cus, order));
+            if (r * W + base >= total_units) {                   // nothing left for this sub-round
+                take(r, base + tid, total_units, active);
                 continue;
             }
             const int key = min(work >> shift, kWorkBins - 1);
@@ -386,7 +410,7 @@ __global__ __launch_bounds__(kSmallThreads) void attn_plan_small_kernel(
             for (int w = 0; w < kPlanWaves; ++w) pre += w < wv ? wave_tot[w] : 0;
             *reinterpret_cast<int4 *>(place + 4 * tid) = make_int4(pre, pre + b.x, pre + b.x + b.y, pre + b.x + b.y + b.z);
             lds_barrier();
-            if (active) take(r, base + tid, r * W + base + atomicAdd(&place[key], 1));
+            take(r, base + tid, active ? r * W + base + atomicAdd(&place[key], 1) : 0, active);
         }
     }
 }
