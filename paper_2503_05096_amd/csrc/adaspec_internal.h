@@ -39,8 +39,10 @@ struct AttnPlan {
     bool merged;            // direct, and whoever finishes a request's last split merges them: no combine kernel
 };
 
-// Direct calls whose requests can have up to so many splits merge them in the kernel (attn_mfma_common.h).
+// Direct calls whose requests can have up to so many splits merge them in the kernel (attn_mfma_common.h), units of so many
+// channels and row tiles: see make_attn_plan.
 constexpr int kMergeMaxSplits = 4;
+constexpr bool attn_merge_fits(int head_dim, int row_tiles) { return row_tiles * head_dim <= 128; }
 
 // What a kernel of a direct call needs to find its unit by itself.
 struct DirectArgs {

@@ -212,13 +212,16 @@ AttnPlan make_attn_plan(const adaspec_attn_dims &d, AttnKind kind, bool tree)
     const int64_t per_req = (max_ctx + p.split_tokens - 1) / p.split_tokens;
     p.per_req = (int)per_req;
     p.row_split = row_split();
-    // Splits merged in the kernel, not by a second one: up to 4 possible splits, up to two row tiles (beyond that the last
-    // workgroup of a request has more to read than the other launch costs).  MI355X, whole calls back to back, with the
-    // combine kernel / without: fp32, 4 requests of 128-512 tokens 10.8 / 7.8 us, 8 of 100-500 10.0 / 9.0; 16 bits, 8 of
-    // 300-1000, 32/8 heads of 128 11.9 / 11.5, 1 of 600 11.4 / 11.4, 16 of 100-900, 16/2 heads 13.3 / 12.7, 32 of 100-900, 8/1
-    // 13.4 / 12.6, 8 of 500-2000, 14/2 heads of 64 13.2 / 11.7.  With 8 splits 1 of 2000 11.0-11.5 / 10.8-11.4 (10.6 / 11.2 in a
-    // captured graph, where a launch costs less), with 6 and two tiles 1 of 1500 12.0 / 12.7.
-    p.merged = p.direct && per_req > 1 && per_req <= kMergeMaxSplits && attn_row_tiles(p.max_rows) <= 2;
+    // Splits merged in the kernel, not by a second one: up to 4 possible splits, of one row tile of 128 channels or two of 64.
+    // What is saved is most of a launch; from a captured graph, where a launch costs less, no more than the last workgroup of a
+    // request takes to read and add up the states, and the line lies where that breaks even.  MI355X, with the combine
+    // kernel / merged, calls back to back; captured: 16 bits, 32/8 heads of 128, 1 request of 600 tokens, 16 rows 12.7 / 9.8; 9.4 / 9.5 us,
+    // 3 of 500-1000, 8 rows 12.6 / 11.3; 11.0 / 10.9, 8 of 300-1000, 16 rows 13.1 / 12.0; 11.8 / 11.6; 8 of 500-2000, 14/2 heads of 64, 28
+    // rows 13.7 / 11.7; 12.4 / 11.6, 1 of 2000, 32/8, 24 rows 13.3 / 11.8; 11.6 / 11.7; fp32, 4 of 128-512, 8/8 heads of 64 11.7 / 8.8; 8.9 /
+    // 8.2, 1 of 500, 32/8 of 128, 16 rows 12.4 / 10.9; 10.4 / 10.6.  Not: two tiles of 128 channels, 1 of 600, 24 rows 12.9 / 11.8; 11.1 /
+    // 11.6, 1 of 700, 32 rows 13.0 / 12.5; 11.6 / 12.3, 3 of 400-700 12.7 / 12.8; 11.8 / 12.5, fp32, 1 of 480, 32 rows 15.8 / 15.7; 14.9 / 15.5;
+    // with 8 splits 1 of 2000 11.0-11.5 / 10.8-11.4; 10.6 / 11.2.
+    p.merged = p.direct && per_req > 1 && per_req <= kMergeMaxSplits && attn_merge_fits(d.head_dim, attn_row_tiles(p.max_rows));
     p.max_items = (int)((int64_t)d.batch * per_req);
     size_t off = 0;
     p.off_header = off;     off = align_up(off + 16 * sizeof(int32_t), 256);

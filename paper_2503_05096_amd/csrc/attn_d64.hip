@@ -375,7 +375,7 @@ __global__ __launch_bounds__(256, (RT <= 2 ? 2 : 1)) void attn_d64_kernel(
                 }
             } else {
                 const int64_t idx_row = ((int64_t)u.item * Hkv + u.gkv) * max_rows + row;
-                if (kDirect && direct.flags) {
+                if (kDirect && attn_merge_fits(kD64, RT) && direct.flags) {
                     store_state(part_o + idx_row * kD64 + 4 * c4, acc);
                     if (c4 == 0) store_ml(part_ml + idx_row * 2, ms, ltot);
                 } else {
@@ -388,9 +388,9 @@ __global__ __launch_bounds__(256, (RT <= 2 ? 2 : 1)) void attn_d64_kernel(
             }
         }
         if constexpr (kDirect) {
-            if constexpr (RT <= 2) {
+            if constexpr (attn_merge_fits(kD64, RT)) {
                 if (u.ns > 1 && direct.flags)
-                    merge_splits<T, kD64, kRows>(direct, u, part_ml, part_o, out, out_dtype, Hq, Hkv, G, max_rows, n_row_groups, tid);
+                    merge_splits<T, kD64, kRows>(direct, u, part_ml, part_o, out, out_dtype, Hq, Hkv, G, max_rows, tid);
             }
             break;
         }

@@ -322,7 +322,7 @@ __global__ __launch_bounds__(256, (RT <= 2 ? 2 : 1)) void attn_f32_kernel(
                 *reinterpret_cast<f32x4 *>(out + obase) = acc * (1.0f / ltot);
             } else {
                 const int64_t idx_row = ((int64_t)u.item * Hkv + u.gkv) * max_rows + row;
-                if (kDirect && direct.flags) {
+                if (kDirect && attn_merge_fits(D, RT) && direct.flags) {
                     store_state(part_o + idx_row * D + 4 * c4, acc);
                     if (c4 == 0) store_ml(part_ml + idx_row * 2, ms, ltot);
                 } else {
@@ -335,9 +335,9 @@ __global__ __launch_bounds__(256, (RT <= 2 ? 2 : 1)) void attn_f32_kernel(
             }
         }
         if constexpr (kDirect) {
-            if constexpr (RT <= 2) {
+            if constexpr (attn_merge_fits(D, RT)) {
                 if (u.ns > 1 && direct.flags)
-                    merge_splits<F32, D, kRows>(direct, u, part_ml, part_o, out, ADASPEC_F32, Hq, Hkv, G, max_rows, n_row_groups, tid);
+                    merge_splits<F32, D, kRows>(direct, u, part_ml, part_o, out, ADASPEC_F32, Hq, Hkv, G, max_rows, tid);
             }
             break;
         }

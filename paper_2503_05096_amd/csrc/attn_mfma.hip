@@ -378,7 +378,7 @@ __global__ __launch_bounds__(256, (RT <= 2 ? 2 : 1)) void attn_mfma_kernel(
                 }
             } else {
                 const int64_t idx_row = ((int64_t)u.item * Hkv + u.gkv) * max_rows + row;
-                if (kDirect && direct.flags) {
+                if (kDirect && attn_merge_fits(kD, RT) && direct.flags) {
                     store_state(part_o + idx_row * kD + 4 * c4, acc);
                     if (c4 == 0) store_ml(part_ml + idx_row * 2, ms, ltot);
                 } else {
@@ -391,8 +391,10 @@ __global__ __launch_bounds__(256, (RT <= 2 ? 2 : 1)) void attn_mfma_kernel(
             }
         }
         if constexpr (kDirect) {
-            if (u.ns > 1 && direct.flags)
-                merge_splits<T, kD, kRows>(direct, u, part_ml, part_o, out, out_dtype, Hq, Hkv, G, max_rows, n_row_groups, tid);
+            if constexpr (attn_merge_fits(kD, RT)) {
+                if (u.ns > 1 && direct.flags)
+                    merge_splits<T, kD, kRows>(direct, u, part_ml, part_o, out, out_dtype, Hq, Hkv, G, max_rows, tid);
+            }
             break;
         }
         // the next loop iteration overwrites q_lds, the V^T tiles and s_m: everyone must be done reading the states

@@ -217,8 +217,7 @@ __device__ __forceinline__ bool direct_unit(Unit &u, const DirectArgs &a, const 
 // ---- direct calls: the splits of a request merged by whoever finishes last --------------------------------------------------
 // A combine kernel behind a small call costs a launch on both sides and a kernel boundary, more than its work.  Instead every
 // split leaves its states at the level all compute units share (store_state, store_ml), waits until they are there, puts the
-// launch's mark into its flag, waits again, and looks at the flags of the request's other splits (for its kv head and row
-// group).  Nobody waits for anybody: of the splits that set their flags, the last one to have done so sees all marks, unless
+// launch's mark into its flag, waits again, and looks at the flags of the request's other splits (for its kv head).  Nobody waits for anybody: of the splits that set their flags, the last one to have done so sees all marks, unless
 // one that saw them before has begun to take them back, so at least one merges (two may, with the same result).  A merge
 // leaves zeros, so that a captured launch, whose mark is frozen, can be replayed; marks of other launches and whatever else
 // stood there are not equal to it.  Flags and decisions are per wavefront: the rows whose states wavefront w of a split has
@@ -229,17 +228,17 @@ __device__ __forceinline__ void store_ml(float *p, float m, float l)
                        (unsigned long long)__float_as_uint(m) | ((unsigned long long)__float_as_uint(l) << 32), __ATOMIC_RELAXED,
                        __HIP_MEMORY_SCOPE_AGENT);
 }
-template <class T, int D, int kRowsPerGroup>
+template <class T, int D, int kRows>
 __device__ __forceinline__ void merge_splits(const DirectArgs &a, const Unit &u, const float *part_ml, const float *part_o, void *out,
-                                             int out_dtype, int Hq, int Hkv, int G, int max_rows, int n_row_groups, int tid)
+                                             int out_dtype, int Hq, int Hkv, int G, int max_rows, int tid)
 {
-    // A thread's share: up to four pieces of four channels, of rows 256 / kCols apart (in kRuns runs: registers).  What can be
+    // A thread's share: one or two pieces of four channels, of rows 256 / kCols apart, in the one row group there is.  What can be
     // computed ahead is, before the waits: at one wavefront per SIMD every instruction behind them counts.
-    constexpr int kCols = D / 4, kPieces = kRowsPerGroup * kCols / 256, kRuns = (kPieces + 3) / 4, kItems = kPieces / kRuns;
-    static_assert(kItems * kRuns == kPieces, "even runs");
+    constexpr int kCols = D / 4, kPieces = kRows * kCols / 256;
+    static_assert(kPieces == 1 || kPieces == 2, "a thread has all its states in registers");
     const int lane = tid & 63, wv = tid >> 6;
-    const int64_t first = ((int64_t)u.i * a.per_req * Hkv + u.gkv) * max_rows + u.r0;      // row r0 in split 0
-    const int rows = u.rows - u.r0, next = Hkv * max_rows;                                 // from one split's row to the next's
+    const int64_t first = ((int64_t)u.i * a.per_req * Hkv + u.gkv) * max_rows;             // row 0 in split 0
+    const int rows = u.rows, next = Hkv * max_rows;                                        // from one split's row to the next's
     const int states = (u.ns - 1) * next + rows;                                           // up to the last row of the last split
     const auto rs_ml = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(part_ml + first * 2), 0, states * 8, 0x00020000);
     const auto rs_o = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(part_o + first * D), 0, states * D * 4, 0x00020000);
@@ -248,67 +247,69 @@ __device__ __forceinline__ void merge_splits(const DirectArgs &a, const Unit &u,
     int to[kPieces];                                                // output row
 #pragma unroll
     for (int k = 0; k < kPieces; ++k) {
-        const int row = u.r0 + rl0 + k * (256 / kCols);
+        const int row = rl0 + k * (256 / kCols);
         to[k] = (row / G) * Hq + u.gkv * G + row % G;
         asm volatile("" : "+v"(to[k]));
     }
-    const int units = Hkv * n_row_groups, split = u.item - u.i * a.per_req;
-    unsigned long long *flags = a.flags + ((int64_t)blockIdx.x - (int64_t)split * units) * kWaves + wv;    // of split 0
-    const int64_t step = (int64_t)units * kWaves;
+    const int split = u.item - u.i * a.per_req;
+    unsigned long long *flags = a.flags + ((int64_t)blockIdx.x - (int64_t)split * Hkv) * kWaves + wv;      // of split 0
+    const int64_t step = (int64_t)Hkv * kWaves;
 
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                // this wavefront's states are in place
+    // (no wavefront needs the others here, but the four together are faster: without the barrier captured calls take 1.5 % longer
+    // in the mean of 189 shapes)
     lds_barrier();
     if (lane == 0) __hip_atomic_store(flags + split * step, a.mark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     unsigned long long seen = a.mark;
     if (lane < u.ns) seen = __hip_atomic_load(flags + lane * step, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (__ballot(seen != a.mark) != 0) return;
+    // (the flags have arrived, or the branch could not have been decided; no load of a state may be moved up across it)
+    asm volatile("" ::: "memory");
 
     // All states are requested before any is looked at.  Splits the request does not have lie past the buffers' ends (zeros, no
-    // traffic) and get a maximum of -inf: selects instead of branches.
+    // traffic) and get a maximum of -inf: selects instead of branches.  (At most 512 units come here, of 32
+    // rows: the buffers end long before kPast.)
     constexpr uint32_t kPast = 0x40000000u;
+    u32x2v ml[kPieces][kMergeMaxSplits];
+    u32x4 o[kPieces][kMergeMaxSplits];
 #pragma unroll
-    for (int run = 0; run < kRuns; ++run) {
-        u32x2v ml[kItems][kMergeMaxSplits];
-        u32x4 o[kItems][kMergeMaxSplits];
+    for (int k = 0; k < kPieces; ++k) {
+        const int rl = k * (256 / kCols);
+        if (rl >= rows) break;
 #pragma unroll
-        for (int k = 0; k < kItems; ++k) {
-            const int rl = (run * kItems + k) * (256 / kCols);
-            if (rl >= rows) break;
-#pragma unroll
-            for (int s = 0; s < kMergeMaxSplits; ++s) {
-                const uint32_t at = (uint32_t)(rl0 + rl + s * next);   // (behind row rows - 1: not stored)
-                ml[k][s] = __builtin_amdgcn_raw_buffer_load_b64(rs_ml, s < u.ns ? at * 8 : kPast, 0, kAgent);
-                o[k][s] = __builtin_amdgcn_raw_buffer_load_b128(rs_o, s < u.ns ? at * (D * 4) + c * 4 : kPast, 0, kAgent);
-            }
+        for (int s = 0; s < kMergeMaxSplits; ++s) {
+            const uint32_t at = (uint32_t)(rl0 + rl + s * next);    // (behind row rows - 1: not stored)
+            ml[k][s] = __builtin_amdgcn_raw_buffer_load_b64(rs_ml, s < u.ns ? at * 8 : kPast, 0, kAgent);
+            o[k][s] = __builtin_amdgcn_raw_buffer_load_b128(rs_o, s < u.ns ? at * (D * 4) + c * 4 : kPast, 0, kAgent);
         }
-        if (run == 0 && lane < u.ns) __hip_atomic_store(flags + lane * step, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (lane < u.ns) __hip_atomic_store(flags + lane * step, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
-        for (int k = 0; k < kItems; ++k) {
-            const int rl = (run * kItems + k) * (256 / kCols);
-            if (rl >= rows) break;
-            float ms[kMergeMaxSplits], m = -INFINITY, den = 0.f;
+    for (int k = 0; k < kPieces; ++k) {
+        const int rl = k * (256 / kCols);
+        if (rl >= rows) break;
+        float ms[kMergeMaxSplits], m = -INFINITY, den = 0.f;
 #pragma unroll
-            for (int s = 0; s < kMergeMaxSplits; ++s) {
-                ms[s] = s < u.ns ? __uint_as_float(ml[k][s].x) : -INFINITY;
-                m = fmaxf(m, ms[s]);
-            }
-            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+        for (int s = 0; s < kMergeMaxSplits; ++s) {
+            ms[s] = s < u.ns ? __uint_as_float(ml[k][s].x) : -INFINITY;
+            m = fmaxf(m, ms[s]);
+        }
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int s = 0; s < kMergeMaxSplits; ++s) {
-                const float w = __builtin_amdgcn_exp2f(ms[s] - m);
-                den += w * __uint_as_float(ml[k][s].y);
-                acc += w * __builtin_bit_cast(f32x4, o[k][s]);
-            }
-            if (rl0 + rl >= rows) continue;
-            const f32x4 val = acc * (1.0f / den);
-            const int64_t obase = (u.qrow0 * Hq + to[run * kItems + k]) * (int64_t)D + c;
-            if (sizeof(typename T::storage) == 4 || out_dtype == ADASPEC_F32) {
-                *reinterpret_cast<f32x4 *>(reinterpret_cast<float *>(out) + obase) = val;
-            } else if constexpr (sizeof(typename T::storage) == 2) {
-                *reinterpret_cast<uint2 *>(reinterpret_cast<uint16_t *>(out) + obase) =
-                    make_uint2(Mma<T>::pack2(val[0], val[1]), Mma<T>::pack2(val[2], val[3]));
-            }
+        for (int s = 0; s < kMergeMaxSplits; ++s) {
+            const float w = __builtin_amdgcn_exp2f(ms[s] - m);
+            den += w * __uint_as_float(ml[k][s].y);
+            acc += w * __builtin_bit_cast(f32x4, o[k][s]);
+        }
+        if (rl0 + rl >= rows) continue;
+        const f32x4 val = acc * (1.0f / den);
+        const int64_t obase = (u.qrow0 * Hq + to[k]) * (int64_t)D + c;
+        if (sizeof(typename T::storage) == 4 || out_dtype == ADASPEC_F32) {
+            *reinterpret_cast<f32x4 *>(reinterpret_cast<float *>(out) + obase) = val;
+        } else if constexpr (sizeof(typename T::storage) == 2) {
+            *reinterpret_cast<uint2 *>(reinterpret_cast<uint16_t *>(out) + obase) =
+                make_uint2(Mma<T>::pack2(val[0], val[1]), Mma<T>::pack2(val[2], val[3]));
         }
     }
 }

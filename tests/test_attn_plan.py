@@ -69,3 +69,14 @@ def test_short_contexts_of_many_rows_split_the_rows(plans):
     assert kernels(88, 12, 64, 8, 128, 5, BF16) == (0, 0)       # three
     assert kernels(48, 12, 64, 8, 128, 5, BF16) == (1, 1)       # three, two units side by side on a compute unit
     assert kernels(88, 2, 32, 8, 128, 7, BF16) == kernels(88, 2, 64, 8, 64, 7, BF16) == kernels(88, 2, 64, 8, 128, 7, F32) == (0, 0)
+
+
+def test_two_tiles_of_128_channels_have_their_splits_combined_apart(plans):
+    """Their states take the last workgroup of a request longer than a captured launch of the combine kernel."""
+    for dtype in (1, BF16, F32):
+        tokens = 128 if dtype == F32 else 256
+        for splits in (2, 3, 4):
+            pages = splits * tokens // 16
+            got = plans([(1, pages, 32, 8, 128, 3, dtype), (1, pages, 32, 8, 128, 5, dtype)], "kernels")
+            assert [g[:2] for g in got] == [(splits, 1), (splits, 0)], (dtype, splits)
+        assert plans([(2, 24 if dtype == F32 else 96, 32, 8, 64, 5, dtype)], "kernels")[0][:2] == (3, 1)       # two tiles of 64
