@@ -80,3 +80,14 @@ def test_two_tiles_of_128_channels_have_their_splits_combined_apart(plans):
             got = plans([(1, pages, 32, 8, 128, 3, dtype), (1, pages, 32, 8, 128, 5, dtype)], "kernels")
             assert [g[:2] for g in got] == [(splits, 1), (splits, 0)], (dtype, splits)
         assert plans([(2, 24 if dtype == F32 else 96, 32, 8, 64, 5, dtype)], "kernels")[0][:2] == (3, 1)       # two tiles of 64
+
+
+def test_which_splits_are_merged_in_the_main_kernel(plans):
+    """The shapes that the GPU tests of the merge are about are merged, and the flag words end the workspace."""
+    from tests.test_gpu_attn_merge import APART, MERGED
+    for shapes, merged in ((MERGED, 1), (APART, 0)):
+        cases = [(len(ctx), -(-max(ctx) // 16), hq, hkv, d, max(spec), {"f32": F32, "f16": 1, "bf16": BF16}[dtype])
+                 for ctx, spec, hq, hkv, d, dtype, _ in shapes]
+        for s, c, (per_req, is_merged, _, _), p in zip(shapes, cases, plans(cases, "kernels"), plans(cases)):
+            assert (p[1], per_req, is_merged) == (1, s[6], merged), c
+            assert not merged or p[7] == p[5] >= p[6], c
