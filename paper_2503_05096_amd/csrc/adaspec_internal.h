@@ -174,6 +174,7 @@ hipError_t launch_tree_masks(const AttnArgs &a);
 hipError_t launch_attn_vector(const AttnArgs &a);
 hipError_t launch_attn_mfma(const AttnArgs &a);
 // units of more than 32 rows (attn_ring.hip, or attn_rows.hip where plan.row_split); launch_attn_mfma forwards to them
+constexpr int kRingQRows = 65;          // query rows that the (query row, head) rows of one of its units span at most
 hipError_t launch_attn_ring(const AttnArgs &a);
 int attn_ring_grid_slots(const AttnArgs &a, int cus);   // resident workgroups = columns of the schedule table
 hipError_t launch_attn_rows(const AttnArgs &a);

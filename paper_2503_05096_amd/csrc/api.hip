@@ -171,6 +171,9 @@ AttnPlan make_attn_plan(const adaspec_attn_dims &d, AttnKind kind, bool tree)
     const int n_groups = attn_row_groups(p.max_rows);
     auto row_split = [&]() -> bool {                        // (with the splits of now)
         const int64_t per_req = (max_ctx + p.split_tokens - 1) / p.split_tokens, even = (max_ctx + per_req - 1) / per_req;
+        // the ring finds a unit's Q by 32-bit offsets from its first row, the row split by addresses
+        const int64_t q_rows = d.max_spec_len + 1 < kRingQRows ? d.max_spec_len + 1 : kRingQRows;
+        if (many_rows && q_rows * d.n_q_heads * d.head_dim * 2 > UINT32_MAX) return true;
         return many_rows && rows_split_wins(attn_row_tiles(p.max_rows), n_groups, tree, d.batch, pairs * n_groups * per_req, per_req,
                                             (even + p.block_tokens - 1) / p.block_tokens * p.block_tokens);
     };

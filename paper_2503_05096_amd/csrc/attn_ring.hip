@@ -52,6 +52,7 @@ __global__ __launch_bounds__(256, 2) void attn_ring_kernel(
 {
     using Lds = RingLds<RT, kTree>;
     constexpr int kRows = 16 * RT;
+    static_assert(kRows + 1 <= kRingQRows, "what the plan allows for");
     __shared__ __attribute__((aligned(1024))) char smem[Lds::kBytes];
     const uint32_t lds_base = lds_address(smem);
     float *s_m = reinterpret_cast<float *>(smem + Lds::kMl), *s_l = s_m + kWaves * kRows;    // [wavefront][row]

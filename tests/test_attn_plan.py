@@ -91,3 +91,9 @@ def test_which_splits_are_merged_in_the_main_kernel(plans):
         for s, c, (per_req, is_merged, _, _), p in zip(shapes, cases, plans(cases, "kernels"), plans(cases)):
             assert (p[1], per_req, is_merged) == (1, s[6], merged), c
             assert not merged or p[7] == p[5] >= p[6], c
+
+
+def test_query_rows_beyond_32_bits_of_offsets_split_the_rows(plans):
+    """A unit's rows of Q span (query rows x heads x 256 bytes): from 4 GB on only the row split reaches them all."""
+    for hkv, split in ((262143, 0), (262144, 1), (400000, 1)):
+        assert plans([(1, 80, hkv, hkv, 128, 63, BF16)], "kernels")[0][2:] == (split, split), hkv
