@@ -76,7 +76,7 @@ inline int attn_row_groups(int max_rows)
 // ... land on the same one (the dispatcher fills the compute units in order, one workgroup each, then starts over), share
 // its load pipeline, and are done when their total is done.  Orders (sched_order chooses, the header carries):
 //
-// kSchedEven, up to four rounds: a round is cut into sub-rounds of `cus` workgroups, each of which runs through its units
+// kSchedEven, up to four rounds (two for the row split): a round is cut into sub-rounds of `cus` workgroups, each of which runs through its units
 // forwards or backwards.  Directions by the parity of the bits of the sub-round's number (backwards, forwards, forwards,
 // backwards, ...): four sub-rounds then even out a convex distribution of lengths as well as a linear one, which strict
 // alternation does not; the first runs backwards, so that where the second is not full its long units land beside the shortest
@@ -91,8 +91,11 @@ inline int attn_row_groups(int max_rows)
 // would be the longest by far (175 log-normal ones of 128-2000, 4 kv heads 64.3 / 59.0 / 70.9).
 //
 // kSchedRounds, more rounds: whole rounds in turn, forwards and backwards (300 requests of 100-500, 8 kv heads of 64, five
-// rounds: main kernel 41.1 us, even 41.8; three and four rounds gain 3 % from even ones where lengths are skewed).
+// rounds: main kernel 41.1 us, even 41.8; three and four rounds gain 3 % from even ones where lengths are skewed, but not in the
+// row split, 300 trees of 512-1024, 56 rows: 106 us, even 109).  Also instead of
+// thirds where units have several row groups and are not listed by their work (300 trees of 48-96, 128 rows: 12.4 us, thirds 13.0).
 constexpr int kSchedEven = 0, kSchedRounds = -1;
+constexpr int kEvenRounds = 4, kEvenRoundsRowSplit = 2;
 // (in workgroup c of sub-round `sub`; n_sub = sub-rounds per round)
 __host__ __device__ inline int sched_position_in(int round, int sub, int c, int n_sub, int W, int cus, int order)
 {
@@ -123,9 +126,9 @@ __host__ __device__ inline int sched_sample(int k, int total, int W, int cus)
                    : k == 6 ? W : k == 7 ? 2 * two - 1 : 2 * two;
     return at < 0 ? 0 : at;
 }
-__host__ __device__ inline int sched_order(int total, int W, int cus, const int (&size)[kSchedSamples])
+__host__ __device__ inline int sched_order(int total, int W, int cus, int even_rounds, const int (&size)[kSchedSamples])
 {
-    if (!sched_asks_sizes(total, W, cus)) return total > 4 * W ? kSchedRounds : kSchedEven;
+    if (!sched_asks_sizes(total, W, cus)) return total > even_rounds * W ? kSchedRounds : kSchedEven;
     const int ends = size[0] + size[1], quarter = size[2] + size[3], middle = size[4] + size[5];
     const int most = ends > quarter ? (ends > middle ? ends : middle) : (quarter > middle ? quarter : middle);
     const int least = ends < quarter ? (ends < middle ? ends : middle) : (quarter < middle ? quarter : middle);

@@ -143,7 +143,7 @@ static bool rows_split_wins(int tiles, int groups, bool tree, int batch, int64_t
     // with its schedule (250 of 96-192, 8 kv heads, 3 tiles 51.6 / 46.5; in two groups, whose second is mostly empty, 73.9 / 92.1)
     if (!tree && single && units * tokens > kDirectRowsTokens) return false;
     if (units <= 256) return tokens <= (four ? (tree ? 320 : 192) : (tree ? 128 : 96));
-    if (units <= 512) return tokens <= (!four ? (tree ? 416 : 192) : single ? (tree ? 768 : 512) : (tree ? 512 : 384));
+    if (units <= 512) return tokens <= (!four ? (tree ? 416 : 192) : single ? (tree ? 768 : 512) : (tree ? 512 : 416));
     return tokens <= (!four ? (tree ? 128 : 96) : single ? (tree ? 1024 : 192) : (tree ? 512 : 320));
 }
 

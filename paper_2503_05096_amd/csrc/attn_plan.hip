@@ -39,17 +39,19 @@ __device__ __forceinline__ void mask_workgroup(const int32_t *__restrict__ spec_
     tree_masks_of_request(parents, r0, n, lane, anc);
 }
 
-// sched_order with the sizes it asks for looked up by a lane each
+// sched_order with the sizes it asks for looked up by a lane each.  With several row groups units are not listed by their work
+// (most requests leave the last group empty): whole rounds.
 template <class F>
-__device__ __forceinline__ int order_of(int total, int W, int cus, int lane, F &&size_of)
+__device__ __forceinline__ int order_of(int total, int W, int cus, int even_rounds, int n_row_groups, int lane, F &&size_of)
 {
     int size[kSchedSamples] = {};
     if (sched_asks_sizes(total, W, cus)) {
+        if (n_row_groups > 1) return kSchedRounds;
         const int mine = size_of(sched_sample(min(lane, kSchedSamples - 1), total, W, cus));
 #pragma unroll
         for (int k = 0; k < kSchedSamples; ++k) size[k] = __builtin_amdgcn_readlane(mine, k);
     }
-    return sched_order(total, W, cus, size);
+    return sched_order(total, W, cus, even_rounds, size);
 }
 
 // One workgroup.  cu_q = exclusive scan of n_i = spec_lens[i] + 1; split_base = exclusive scan of
@@ -71,7 +73,7 @@ __global__ __launch_bounds__(kPlanThreads) void attn_plan_kernel(
     int max_spec_len, int split_log2, int block_log2, int max_items, int G, int32_t *__restrict__ header,
     int32_t *__restrict__ cu_q, int32_t *__restrict__ split_base, int32_t *__restrict__ item_req,
     int32_t *__restrict__ item_order, int32_t *__restrict__ unit_meta, int32_t *__restrict__ row_rec,
-    int W, int Hkv, int n_row_groups, int rows_per_group, int32_t *__restrict__ sched, int cus,
+    int W, int Hkv, int n_row_groups, int rows_per_group, int32_t *__restrict__ sched, int cus, int even_rounds,
     int want_cu_q, const int32_t *__restrict__ parents, unsigned long long *__restrict__ anc)
 {
     if (blockIdx.x > 0) {
@@ -214,7 +216,7 @@ __global__ __launch_bounds__(kPlanThreads) void attn_plan_kernel(
         const int blocks = item_blocks[pos], groups = item_groups[pos];
         return rg < groups ? blocks + kUnitFixedBlocks : 0;
     };
-    const int order = items_on_chip || !sched_asks_sizes(total_units, W, cus) ? order_of(total_units, W, cus, lane, size_of) : kSchedEven;
+    const int order = items_on_chip || !sched_asks_sizes(total_units, W, cus) ? order_of(total_units, W, cus, even_rounds, n_row_groups, lane, size_of) : kSchedEven;
     if (tid == 0) header[1] = order;
     int work = 0;                              // of workgroup tid, so far
     // workgroup tid takes unit idx (if it exists) in round r; no branch around the look-up, so that those of several rounds are
@@ -230,7 +232,6 @@ __global__ __launch_bounds__(kPlanThreads) void attn_plan_kernel(
     const int plain = items_on_chip && rounds > 1 ? max(rounds - kBalancedRounds, 1) : rounds;      // rounds by position
     if (tid < W) {
         const int n_sub = ceil_div(W, cus);
-#pragma unroll 4
         for (int r = 0; r < plain; ++r) take(r, sched_position_in(r, sub, tid - sub * cus, n_sub, W, cus, order));
     }
     for (int r = plain; r < rounds; ++r) {
@@ -282,7 +283,7 @@ __global__ __launch_bounds__(kSmallThreads) void attn_plan_small_kernel(
     const int32_t *__restrict__ ctx_lens, const int32_t *__restrict__ spec_lens, int B, int total_q,
     int max_spec_len, int split_log2, int block_log2, int max_items, int G, int32_t *__restrict__ header,
     int32_t *__restrict__ unit_meta, int32_t *__restrict__ row_rec, int W, int Hkv, int n_row_groups, int rows_per_group,
-    int32_t *__restrict__ sched, int cus, const int32_t *__restrict__ parents, unsigned long long *__restrict__ anc)
+    int32_t *__restrict__ sched, int cus, int even_rounds, const int32_t *__restrict__ parents, unsigned long long *__restrict__ anc)
 {
     if (blockIdx.x > 0) {
         mask_workgroup<kSmallThreads>(spec_lens, B, total_q, max_spec_len, parents, anc);
@@ -372,7 +373,7 @@ __global__ __launch_bounds__(kSmallThreads) void attn_plan_small_kernel(
         const int rg = n_row_groups == 1 ? 0 : idx % n_row_groups, size = item_size[pos];
         return rg < (size >> 8) ? (size & 255) + kUnitFixedBlocks : 0;
     };
-    const int order = order_of(total_units, W, cus, lane, size_of);
+    const int order = order_of(total_units, W, cus, even_rounds, n_row_groups, lane, size_of);
     if (tid == 0) header[1] = order;
     // workgroup w takes unit idx (if it exists) in round r; no branch around the look-up (as above)
     auto take = [&](int r, int w, int idx, bool active) {
@@ -420,6 +421,7 @@ hipError_t launch_attn_plan(const AttnArgs &a)
     const AttnPlan &p = a.plan;
     // tree calls: more workgroups for the ancestor masks, a wavefront per request (see the kernels)
     const bool fused_masks = a.parents != nullptr && a.dims.batch <= kFusedMaskMaxBatch;
+    const int even_rounds = p.row_split ? kEvenRoundsRowSplit : kEvenRounds;
     auto workgroups = [&](int threads) { return dim3(1 + (fused_masks ? ceil_div(a.dims.batch, threads / kWave) : 0)); };
     if (a.sched_w > 0 && a.dims.batch <= kSmallThreads && p.max_items <= kSchedItems && a.sched_cus <= kSmallThreads) {
         hipLaunchKernelGGL(attn_plan_small_kernel, workgroups(kSmallThreads), dim3(kSmallThreads), 0, a.stream, a.ctx_lens,
@@ -428,7 +430,7 @@ hipError_t launch_attn_plan(const AttnArgs &a)
                            a.dims.n_q_heads / a.dims.n_kv_heads, (int32_t *)(a.ws + p.off_header),
                            (int32_t *)(a.ws + p.off_unit_meta), (int32_t *)(a.ws + p.off_row_rec), a.sched_w,
                            a.dims.n_kv_heads, a.n_row_groups, a.rows_per_group, (int32_t *)(a.ws + p.off_sched),
-                           a.sched_cus, a.parents, (unsigned long long *)(a.ws + p.off_anc));
+                           a.sched_cus, even_rounds, a.parents, (unsigned long long *)(a.ws + p.off_anc));
         return hipGetLastError();
     }
     hipLaunchKernelGGL(attn_plan_kernel, workgroups(kPlanThreads), dim3(kPlanThreads), 0, a.stream, a.ctx_lens,
@@ -439,7 +441,7 @@ hipError_t launch_attn_plan(const AttnArgs &a)
                        (int32_t *)(a.ws + p.off_item_req), (int32_t *)(a.ws + p.off_item_order),
                        (int32_t *)(a.ws + p.off_unit_meta), (int32_t *)(a.ws + p.off_row_rec), a.sched_w,
                        a.dims.n_kv_heads, a.n_row_groups, a.rows_per_group, (int32_t *)(a.ws + p.off_sched),
-                       a.sched_cus, (a.parents != nullptr && !fused_masks) ? 1 : 0, a.parents,
+                       a.sched_cus, even_rounds, (a.parents != nullptr && !fused_masks) ? 1 : 0, a.parents,
                        (unsigned long long *)(a.ws + p.off_anc));
     return hipGetLastError();
 }

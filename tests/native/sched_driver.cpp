@@ -15,7 +15,7 @@ int main()
         int size[adaspec::kSchedSamples] = {};
         if (adaspec::sched_asks_sizes(total, W, cus))
             for (int k = 0; k < adaspec::kSchedSamples; ++k) size[k] = work.at(adaspec::sched_sample(k, total, W, cus));
-        const int order = adaspec::sched_order(total, W, cus, size);
+        const int order = adaspec::sched_order(total, W, cus, adaspec::kEvenRounds, size);
         printf("%d", order);
         for (int r = 0; r * W < total; ++r)
             for (int w = 0; w < W; ++w) printf(" %d", adaspec::sched_position(r, w, W, cus, order));

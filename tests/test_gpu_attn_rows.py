@@ -33,7 +33,7 @@ def test_more_than_the_chip_holds(oracle_mod, pkg):  # noqa: F811
     check_attention(step(16, 4, list(ctx), "bf16", hkv=1, acceptance=False), oracle_mod, pkg)
 
 
-@pytest.mark.parametrize("G,k,B,longest", [(16, 2, 5, 128), (16, 3, 5, 192), (13, 4, 130, 320), (7, 6, 400, 96), (16, 3, 600, 64)])
+@pytest.mark.parametrize("G,k,B,longest", [(16, 2, 5, 128), (16, 3, 5, 192), (13, 4, 130, 320), (7, 6, 400, 96), (16, 3, 600, 64), (16, 7, 160, 64)])
 def test_trees(G, k, B, longest, oracle_mod, pkg):  # noqa: F811
     ctx = np.random.default_rng(G + k + B).integers(1, longest + 1, B)
     ctx[:5] = [k + 1, 33, 32, longest, longest - 1]
