@@ -28,9 +28,15 @@
  *   - Outputs are fully overwritten.  Results are deterministic: the same
  *     inputs give bit-identical outputs (no floating-point atomics).
  *   - Host threads: the library keeps no state between calls apart from
- *     one-time device queries.  Calls from several threads are safe as long
- *     as they do not share a workspace.  The calls enqueue kernels only (no allocation, no
- *     memset, no synchronisation), so they can be captured into a HIP graph.
+ *     one-time device queries and a process-wide count of launches (attention
+ *     calls that merge their splits mark flag words in the workspace with a
+ *     number that no other launch is given; no result depends on it).  Calls
+ *     from several threads are safe as long as they do not share a workspace.
+ *     The calls enqueue kernels only (no allocation, no memset, no
+ *     synchronisation), so they can be captured into a HIP graph.  A captured
+ *     launch keeps its number, and every replay leaves its flag words at zero:
+ *     replays may follow each other, and calls between them may use the same
+ *     workspace, as long as all of them are ordered.
  *     The first call of a kernel path on a device does its one-time set-up
  *     (occupancy and device queries; the streaming and two-pass acceptance
  *     paths also raise their kernel's LDS limit): make one call with the same

@@ -27,7 +27,8 @@ struct AttnPlan {
     size_t off_item_order;  // int32[max_items]: items sorted by decreasing length (schedule order)
     size_t off_unit_meta;   // int32[max_items][8] in schedule order: request, split, n_splits, L, n, cu_q, item, 0
     size_t off_row_rec;     // int32[TQ][4] per query row: request, n_splits, first split, row base (j * G)
-    size_t off_sched;       // int32[rounds][W]: unit taken by workgroup w in each round, or -1 (matrix-core kernel)
+    size_t off_sched;       // int32[rounds][W]: unit taken by workgroup w in each round, or -1 (matrix-core kernels; row 0 is not
+                            // read, and only the general plan kernel writes it)
     size_t off_anc;         // uint64[TQ]: tree verification only, ancestor-or-self mask of each query row's node
     size_t off_part_ml;     // float[max_items][Hkv][max_rows][2]  (m in log2 units, l)
     size_t off_part_o;      // float[max_items][Hkv][max_rows][d]

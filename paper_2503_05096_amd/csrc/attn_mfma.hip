@@ -65,9 +65,10 @@ __global__ __launch_bounds__(256, (RT <= 2 ? 2 : 1)) void attn_mfma_kernel(
 
     // ---- work-unit bookkeeping ----------------------------------------------------------------
     // Units are listed longest first and handed out in rounds of W (one unit per workgroup and
-    // round).  Which unit a workgroup takes in a round is a table the plan kernel wrote: it gives
-    // the longest unit of the round to the workgroup with the least work so far.  No atomic is
-    // needed and the next unit is known ahead of time, so its data can be requested early.
+    // round).  Which unit a workgroup takes in the first follows from the order in the header
+    // (sched_position), later ones are a table the plan kernel wrote: by position as well, the last round by
+    // work per compute unit.  No atomic is needed and the next unit is known ahead of time, so its data can
+    // be requested early.
     const int W = gridDim.x, wg = blockIdx.x;
     const int n_rounds = kDirect ? 0 : header[2];
     int round = 0;
