@@ -13,7 +13,7 @@
 // Bound: HBM.  The row split (attn_rows.hip, which keeps the short contexts) shares every block among the four wavefronts, one
 // row tile each, behind a barrier per block: a unit of 8 rows keeps one wavefront busy and three waiting, and the operands of a
 // block are read four times.  Whole calls on MI355X (bf16, 64/8 heads, up to 48 rows), row split / ring: 64 requests of 2048-8192 tokens
-// 259 / 250 us, 48 of 1024-4096 119 / 105, 40 of 4000 160 / 138, 60 of 500 and 4 of 16000 103 / 85, 64 of 300-1000 44.3 / 39.8;
+// 258 / 245 us, 48 of 1024-4096 120 / 106, 40 of 4000 160 / 138, 60 of 500 and 4 of 16000 104 / 83, 64 of 300-1000 44.5 / 37.3;
 // 28/4 heads, 80 of 1000-6000 137 / 126.  A probe that only loads reaches 6.3 TB/s on this pattern through registers or one
 // shared ring and 6.8 TB/s with a ring per wavefront; without the states of the splits the kernel runs at 6.5 TB/s, but
 // every byte of them written costs about as much as five read (52 MB beside 2.1 GB: 327 -> 365 us).
