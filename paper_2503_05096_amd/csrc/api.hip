@@ -124,14 +124,14 @@ AttnKind attn_kind(const adaspec_attn_dims &d)
 // block.  `tokens`: a split of the longest possible request.  The line moves with the number of row tiles and groups (four
 // tiles: a longer chain in the ring), with units > 256, where two workgroups share a compute unit, and for trees, whose masks the
 // ring with four tiles reads from memory.  MI355X, captured calls, bf16, row split / ring:
-//   3 tiles, 64/8 heads, 8 requests of 16-32 tokens 5.9 / 7.1 us, 33-64 6.9 / 8.0, 48-96 7.8 / 8.1, 64-128 8.7 / 8.4, 128-256
-//   12.1 / 10.1; 64 of 96-192 14.1 / 15.1, 128-256 16.4 / 16.4; trees, 64 of 128-256 20.3 / 21.3, 256-512 28.2 / 27.2
-//   4 tiles, 64/8 heads, 8 requests of 16-32 6.2 / 8.3, 64-128 9.0 / 9.3, 96-192 10.3 / 11.3, 128-256 12.2 / 11.7; 64 of 128-256
-//   17.2 / 19.1, 256-512 26.6 / 27.4, 300-600 33.4 / 30.4; trees, 64 of 300-600 32.5 / 34.4, 500-1000 45.9 / 45.5, 128 of 500-1000
-//   80 / 82, 1000-2000 143 / 143
-//   two groups of 4 (72 rows), 64/8 heads, 32 of 128-256 16.3 / 18.3, 256-512 24.8 / 24.3; 250 of 128-256 84.3 / 99.1
+//   3 tiles, 64/8 heads, 8 requests of 16-32 tokens 6.0 / 7.2 us, 32-64 6.9 / 7.8, 48-96 7.8 / 8.1, 64-128 8.7 / 8.3, 128-256
+//   11.9 / 10.0; 64 of 96-192 14.2 / 15.3, 128-256 16.3 / 16.6; trees, 64 of 128-256 19.8 / 21.5, 256-512 28.0 / 28.3
+//   4 tiles, 64/8 heads, 8 requests of 16-32 6.3 / 8.4, 64-128 9.0 / 9.3, 96-192 10.2 / 11.4, 128-256 12.2 / 11.7; 64 of 128-256
+//   17.2 / 19.0, 256-512 26.3 / 27.3, 300-600 32.2 / 30.5; trees, 64 of 300-600 32.4 / 34.4, 500-1000 45.3 / 45.8, 128 of 500-1000
+//   82.4 / 84.4, 1000-2000 145.7 / 144.7
+//   two groups of 4 (72 rows), 64/8 heads, 32 of 128-256 16.3 / 18.0, 256-512 24.4 / 24.5; 250 of 128-256 84.3 / 99.1
 // Requests of several splits have units of any length up to the whole split, so only one or two of them are safe to judge by
-// the longest: 1 of 288 tokens, 56 rows 12.8 / 14.6, 2 of 375 and 525 13.9 / 15.0, 4 of 200-400 15.6 / 15.0.
+// the longest: 1 of 288 tokens, 56 rows 12.8 / 14.6, 2 of 375 and 525 13.9 / 15.0, 4 of up to 288 15.6 / 14.9.
 static bool rows_split_wins(int tiles, int groups, bool tree, int batch, int64_t units, int64_t per_req, int64_t tokens)
 {
     const bool four = tiles > 3, single = groups == 1;
