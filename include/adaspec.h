@@ -403,7 +403,7 @@ int adaspec_check_tree_parents(const int32_t *parents, const int32_t *spec_lens,
  *           evaluated, one workgroup per node, then a small kernel walks the results;
  *   FAST    16-bit logits/probs of one type, V % 8 == 0, V <= 524288, strides % 8 == 0, 16-byte aligned
  *           base pointers: first the statistics of every node (one read of its logits row), then one
- *           workgroup per request walks its tree
+ *           workgroup per request, or a few that share its rows, walks its tree
  *           and reads, at the nodes it reaches only, the logits and draft-probability rows once per
  *           rejected child;
  *   AUTO    FAST when it fits, else VECTOR.

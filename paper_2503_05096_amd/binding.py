@@ -115,50 +115,55 @@ def lib() -> C.CDLL:
             raise ImportError(
                 f"{LIB_PATH} is missing: build it first (python -c 'import __graft_entry__ as g; "
                 "g.build()' or python paper_2503_05096_amd/build.py). There is no fallback path.")
-        # The process must hold ONE HIP runtime.  PyTorch ships its own copy and loads it by path;
-        # the loader shares it with this library only if it is already mapped when the library is
-        # opened (same SONAME).  Opened the other way round, the library would bind to the system
-        # copy and launch kernels through a runtime that knows nothing of torch's streams and memory.
-        import torch  # noqa: F401
-        L = C.CDLL(LIB_PATH)
-        vp = C.c_void_p
-        L.adaspec_verify_attn_workspace_bytes.restype = C.c_size_t
-        L.adaspec_verify_attn_workspace_bytes.argtypes = [C.POINTER(AttnDims)]
-        L.adaspec_verify_attn.restype = C.c_int
-        L.adaspec_verify_attn.argtypes = [vp] * 7 + [C.POINTER(AttnDims), vp, C.c_size_t, vp]
-        L.adaspec_accept_workspace_bytes.restype = C.c_size_t
-        L.adaspec_accept_workspace_bytes.argtypes = [C.POINTER(AcceptDims)]
-        L.adaspec_accept.restype = C.c_int
-        L.adaspec_accept.argtypes = [vp] * 8 + [C.POINTER(AcceptDims), vp, C.c_size_t, vp]
-        L.adaspec_accept_noalloc.restype = C.c_int
-        L.adaspec_accept_noalloc.argtypes = [vp] * 8 + [C.POINTER(AcceptDims), vp]
-        L.adaspec_accept_resolved_path.restype = C.c_int
-        L.adaspec_accept_resolved_path.argtypes = [vp, vp, C.POINTER(AcceptDims)]
-        L.adaspec_verify_attn_tree.restype = C.c_int
-        L.adaspec_verify_attn_tree.argtypes = [vp] * 8 + [C.POINTER(AttnDims), vp, C.c_size_t, vp]
-        L.adaspec_accept_tree.restype = C.c_int
-        L.adaspec_accept_tree.argtypes = [vp] * 10 + [C.POINTER(AcceptDims), vp, C.c_size_t, vp]
-        L.adaspec_kv_compact_path.restype = C.c_int
-        L.adaspec_kv_compact_path.argtypes = [vp] * 7 + [C.POINTER(AttnDims), C.c_int32, vp]
-        L.adaspec_check_accept_inputs.restype = C.c_int
-        L.adaspec_check_accept_inputs.argtypes = [vp, vp, vp, C.POINTER(AcceptDims), vp, vp]
-        L.adaspec_check_tree_parents.restype = C.c_int
-        L.adaspec_check_tree_parents.argtypes = [vp, vp, C.c_int32, C.c_int32, C.c_int32, vp, vp]
-        L.adaspec_check_ragged_inputs.restype = C.c_int
-        L.adaspec_check_ragged_inputs.argtypes = [vp, vp, vp, C.POINTER(AttnDims), vp, vp]
-        L.adaspec_kv_append.restype = C.c_int
-        L.adaspec_kv_append.argtypes = [vp] * 7 + [C.POINTER(AttnDims), vp]
-        L.adaspec_commit.restype = C.c_int
-        L.adaspec_commit.argtypes = [vp] * 10 + [C.POINTER(CommitDims), vp]
-        L.adaspec_draft_sample.restype = C.c_int
-        L.adaspec_draft_sample.argtypes = [vp] * 7 + [C.POINTER(DraftDims), vp, C.c_size_t, vp]
-        L.adaspec_draft_sample_workspace_bytes.restype = C.c_size_t
-        L.adaspec_draft_sample_workspace_bytes.argtypes = [C.POINTER(DraftDims)]
-        L.adaspec_status_string.restype = C.c_char_p
-        L.adaspec_status_string.argtypes = [C.c_int]
-        L.adaspec_version.restype = C.c_int
-        _lib = L
+        _lib = _open(LIB_PATH)
     return _lib
+
+
+def _open(path: str) -> C.CDLL:
+    """The library at `path`, with the C ABI's signatures."""
+    # The process must hold ONE HIP runtime.  PyTorch ships its own copy and loads it by path;
+    # the loader shares it with this library only if it is already mapped when the library is
+    # opened (same SONAME).  Opened the other way round, the library would bind to the system
+    # copy and launch kernels through a runtime that knows nothing of torch's streams and memory.
+    import torch  # noqa: F401
+    L = C.CDLL(path)
+    vp = C.c_void_p
+    L.adaspec_verify_attn_workspace_bytes.restype = C.c_size_t
+    L.adaspec_verify_attn_workspace_bytes.argtypes = [C.POINTER(AttnDims)]
+    L.adaspec_verify_attn.restype = C.c_int
+    L.adaspec_verify_attn.argtypes = [vp] * 7 + [C.POINTER(AttnDims), vp, C.c_size_t, vp]
+    L.adaspec_accept_workspace_bytes.restype = C.c_size_t
+    L.adaspec_accept_workspace_bytes.argtypes = [C.POINTER(AcceptDims)]
+    L.adaspec_accept.restype = C.c_int
+    L.adaspec_accept.argtypes = [vp] * 8 + [C.POINTER(AcceptDims), vp, C.c_size_t, vp]
+    L.adaspec_accept_noalloc.restype = C.c_int
+    L.adaspec_accept_noalloc.argtypes = [vp] * 8 + [C.POINTER(AcceptDims), vp]
+    L.adaspec_accept_resolved_path.restype = C.c_int
+    L.adaspec_accept_resolved_path.argtypes = [vp, vp, C.POINTER(AcceptDims)]
+    L.adaspec_verify_attn_tree.restype = C.c_int
+    L.adaspec_verify_attn_tree.argtypes = [vp] * 8 + [C.POINTER(AttnDims), vp, C.c_size_t, vp]
+    L.adaspec_accept_tree.restype = C.c_int
+    L.adaspec_accept_tree.argtypes = [vp] * 10 + [C.POINTER(AcceptDims), vp, C.c_size_t, vp]
+    L.adaspec_kv_compact_path.restype = C.c_int
+    L.adaspec_kv_compact_path.argtypes = [vp] * 7 + [C.POINTER(AttnDims), C.c_int32, vp]
+    L.adaspec_check_accept_inputs.restype = C.c_int
+    L.adaspec_check_accept_inputs.argtypes = [vp, vp, vp, C.POINTER(AcceptDims), vp, vp]
+    L.adaspec_check_tree_parents.restype = C.c_int
+    L.adaspec_check_tree_parents.argtypes = [vp, vp, C.c_int32, C.c_int32, C.c_int32, vp, vp]
+    L.adaspec_check_ragged_inputs.restype = C.c_int
+    L.adaspec_check_ragged_inputs.argtypes = [vp, vp, vp, C.POINTER(AttnDims), vp, vp]
+    L.adaspec_kv_append.restype = C.c_int
+    L.adaspec_kv_append.argtypes = [vp] * 7 + [C.POINTER(AttnDims), vp]
+    L.adaspec_commit.restype = C.c_int
+    L.adaspec_commit.argtypes = [vp] * 10 + [C.POINTER(CommitDims), vp]
+    L.adaspec_draft_sample.restype = C.c_int
+    L.adaspec_draft_sample.argtypes = [vp] * 7 + [C.POINTER(DraftDims), vp, C.c_size_t, vp]
+    L.adaspec_draft_sample_workspace_bytes.restype = C.c_size_t
+    L.adaspec_draft_sample_workspace_bytes.argtypes = [C.POINTER(DraftDims)]
+    L.adaspec_status_string.restype = C.c_char_p
+    L.adaspec_status_string.argtypes = [C.c_int]
+    L.adaspec_version.restype = C.c_int
+    return L
 
 
 def hip_runtime() -> C.CDLL:
@@ -386,7 +391,7 @@ def accept_tree(target_logits, draft_probs, draft_tokens, parents, uniforms, spe
                 max_spec_len: int, out_tokens=None, out_accept_len=None, out_path=None,
                 out_stride: Optional[int] = None, path: str = "auto", workspace=None, stream=None, timing=None):
     """adaspec_accept_tree; returns (out_tokens [B][out_stride], out_accept_len [B], out_path [B][out_stride]).
-    path: "auto", "vector" (portable per-node kernel) or "fast" (node statistics, then one workgroup per request)."""
+    path: "auto", "vector" (portable per-node kernel) or "fast" (node statistics, then the walk of every request)."""
     if path == "auto" and timing is None:
         r = (_fast or _native()).accept_tree(target_logits, draft_probs, draft_tokens, parents, uniforms, spec_lens,
                                              temperature, max_spec_len, out_tokens, out_accept_len, out_path, out_stride,

@@ -44,24 +44,49 @@ def build_fastcall(verbose: bool = False, out: str = FASTCALL_PATH, defines=()) 
     return out
 
 
+def _sources():
+    return sorted(glob.glob(os.path.join(CSRC, "*.hip")) + glob.glob(os.path.join(CSRC, "*.cpp")))
+
+
+def _object(src: str, tag: str = "") -> str:
+    return os.path.join(BUILD_DIR, os.path.basename(src).replace(".", "_") + tag + ".o")
+
+
+def _compile(src: str, obj: str, defines=(), verbose: bool = False) -> str:
+    cmd = [HIPCC, *FLAGS, *(f"-D{d}" for d in defines), "-I", INCLUDE, "-c", src, "-o", obj]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"hipcc failed on {src}:\n{r.stderr}")
+    return r.stderr
+
+
+def _link(objects, out: str) -> str:
+    r = subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", out, *objects], capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"link failed:\n{r.stderr}")
+    return out
+
+
+def build_impatient(out: str, jobs: int = 8) -> str:
+    """For tests: the library with workgroups that never wait for each other's words (csrc/part_exchange.h) and compute what
+    is missing themselves. Call it after build_library, whose other objects it links."""
+    sources = _sources()
+    waiting = [s for s in sources if '#include "part_exchange.h"' in open(s).read()]
+    with ThreadPoolExecutor(jobs) as ex:
+        list(ex.map(lambda s: _compile(s, _object(s, "_impatient"), ("ADASPEC_PATIENCE=0",)), waiting))
+    return _link([_object(s, "_impatient" if s in waiting else "") for s in sources], out)
+
+
 def build_library(verbose: bool = False, jobs: int = 8) -> str:
     os.makedirs(BUILD_DIR, exist_ok=True)
-    sources = sorted(glob.glob(os.path.join(CSRC, "*.hip")) + glob.glob(os.path.join(CSRC, "*.cpp")))
-    objects = [os.path.join(BUILD_DIR, os.path.basename(s).replace(".", "_") + ".o") for s in sources]
-
-    def compile_one(pair):
-        src, obj = pair
-        cmd = [HIPCC, *FLAGS, "-I", INCLUDE, "-c", src, "-o", obj]
-        if verbose:
-            print(" ".join(cmd), flush=True)
-        r = subprocess.run(cmd, capture_output=True, text=True)
-        if r.returncode != 0:
-            raise RuntimeError(f"hipcc failed on {src}:\n{r.stderr}")
-        return r.stderr
+    sources = _sources()
+    objects = [_object(s) for s in sources]
 
     with ThreadPoolExecutor(jobs) as ex:
         fastcall = ex.submit(build_fastcall, verbose)
-        logs = list(ex.map(compile_one, zip(sources, objects)))
+        logs = list(ex.map(lambda s: _compile(s, _object(s), verbose=verbose), sources))
     try:
         fastcall.result()
     except Exception as e:      # no host compiler, no Python headers: the binding makes its calls in Python then
@@ -74,11 +99,7 @@ def build_library(verbose: bool = False, jobs: int = 8) -> str:
             keep = [l for l in log.splitlines() if "packed-fp32-ops" not in l and l.strip()]
             if keep:
                 print("\n".join(keep))
-    cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB_PATH, *objects]
-    r = subprocess.run(cmd, capture_output=True, text=True)
-    if r.returncode != 0:
-        raise RuntimeError(f"link failed:\n{r.stderr}")
-    return LIB_PATH
+    return _link(objects, LIB_PATH)
 
 
 if __name__ == "__main__":

@@ -254,8 +254,8 @@ hipError_t launch_accept_parts(const AcceptArgs &a, int compute_units);
 // portable form (any types and sizes): a per-node kernel writes (next node or -1, token if the walk stops here)
 // into row_flag / row_cand, a small kernel walks them
 hipError_t launch_accept_tree_nodes(const AcceptArgs &a, const int32_t *parents);
-// 16-bit rows (shapes of the register-resident chain kernel): node statistics, then one workgroup per request
-// walks its tree and writes the outputs (no separate walk kernel)
+// 16-bit rows (shapes of the streaming chain kernel): node statistics, then one workgroup per request, or a few that share
+// its rows, walks its tree and writes the outputs (no separate walk kernel)
 size_t tree_node_stat_bytes(int vocab);
 constexpr size_t kTreeNodeStatMin = 528;
 bool tree_fast_needs_plan(const adaspec_accept_dims &d);   // large batches: row offsets from launch_accept_plan
