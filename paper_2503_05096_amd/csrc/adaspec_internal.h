@@ -164,6 +164,7 @@ struct AttnArgs {
 };
 
 DirectArgs direct_args(const AttnArgs &a);      // (api.hip; every call gives another mark)
+uint64_t next_spread_mark();                    // the same, spread over the 64 bits; never 0
 
 // Upper bound on W for which the workspace holds a schedule table.
 constexpr int kMaxSchedW = 1024;

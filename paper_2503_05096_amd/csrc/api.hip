@@ -265,6 +265,9 @@ static uint64_t next_mark()
     return m != 0 ? m : mark.fetch_add(1, std::memory_order_relaxed);      // (0 is what a merge leaves)
 }
 
+// (times an odd constant: as many different ones, and 0 only from 0)
+uint64_t next_spread_mark() { return next_mark() * 0x9e3779b97f4a7c15ull; }
+
 DirectArgs direct_args(const AttnArgs &a)
 {
     DirectArgs d{a.ctx_lens, a.spec_lens, a.dims.batch, a.dims.max_spec_len, a.dims.total_q, a.plan.per_req, a.plan.split_tokens, nullptr, 0};
@@ -697,28 +700,21 @@ static int validate_draft_dims(const adaspec_draft_dims *d)
     return ADASPEC_OK;
 }
 
-// AUTO of draft sampling, measured on MI355X (us per call; three sweeps / register-resident / in parts):
-//   V = 16384 bf16   1 row  9.1 / 10.8 /  9.7   128 rows 10.0 / 11.6 / 10.9   256 rows 10.8 / 12.3 / 12.2
-//   V = 32768 bf16   1 row 12.2 / 10.6 /  9.9   128 rows 13.7 / 12.1 / 12.8   256 rows 15.8 / 13.8 / 18.1
-//   V = 32768 fp32   1 row 11.0 /   -  /   -   128 rows 13.8 /   -  /   -   256 rows 20.9 /   -  /   -
-//   V = 50272 fp32   1 row 14.1 /   -  /  9.1   144 rows 21.2 /   -  / 22.1   256 rows 33.9 /   -  / 31.5   300 rows 43 / - / 37
-//   V = 50272 bf16   1 row 16.4 / 16.1 / 10.2   128 rows 18.3 / 18.1 / 16.6   192 rows 19.8 / 19.0 / 20.8   300 rows 29 / 34 / 26
-//   V = 65536 bf16   1 row 19.1 / 16.1 / 10.1   128 rows 21.5 / 18.3 / 17.8   144 rows 23.6 / 18.6 / 19.9   192 rows 25 / 19 / 22
-//   V = 81920 bf16   1 row 22.5 / 26.3 /  9.9   144 rows 26.3 / 29.9 / 22.0   256 rows 29.9 / 31.7 / 29.2   300 rows 41 / 55 / 34
-//   V = 131072 bf16  1 row 32.4 / 26.4 / 10.3   192 rows 41.3 / 32.7 / 32.1   256 rows 43.7 / 33.5 / 39.3   300 rows 62 / 57 / 47
-// fp32 rows in parts are measured as AUTO takes them, so not below its line; an earlier version of that form, slower than
-// today's, took 12.0, 16.9 and 22.0 us at V = 32768 and 19.3 (144 rows) and 26.5 (256) at V = 40000 against 17.1 and 26.5.
-// In parts above V = 32768 (fp32 logits, which the single-workgroup kernels need not convert: above 49152), unless 16-bit
-// rows of at most 65536 occupy more than half of the compute units and no more than all of them; else the
-// register-resident kernel above V = 24576 where it fits, else three sweeps.
-constexpr int kDraftFastAbove = 24576, kDraftMediumRow = 65536;
-static bool draft_wants_parts(const adaspec_draft_dims &d)
-{
-    if (d.logits_dtype == ADASPEC_F32) return d.vocab > 49152;
-    const int cus = compute_units();
-    const bool one_wave = d.vocab <= kDraftMediumRow && d.rows > cus / 2 && d.rows <= cus;
-    return d.vocab > 32768 && !one_wave;
-}
+// AUTO of draft sampling, measured on MI355X (us per captured call; three sweeps / register-resident / in parts):
+//   V = 8192 bf16    1 row  7.5 / 11.0 /  6.9   128 rows  8.2 / 11.6 /  7.5   256 rows  8.6 / 11.9 /  7.9   300 rows 11.4 / 18.9 / 10.1
+//     all greedy            5.9 /      /  6.7             6.4 /      /  7.2             7.0 /      /  7.6             9.1 /      /  9.6
+//   V = 16384 bf16   1 row  9.3 / 11.0 /  7.3   128 rows 10.2 / 11.7 /  8.3   256 rows 11.7 / 12.7 /  9.4   300 rows 15.7 / 19.9 / 11.8
+//     all greedy            7.5 /      /  7.0             8.5 /      /  7.9             9.7 /      /  8.9            13.2 /      / 11.4
+//   V = 32768 bf16   1 row 12.7 / 11.0 /  8.2   128 rows 14.6 / 12.9 / 10.7   256 rows 16.0 / 14.1 / 13.1   300 rows 21.9 / 20.8 / 14.8
+//   V = 65536 bf16   1 row 19.5 / 16.5 /  8.7   128 rows 22.6 / 18.6 / 14.6   256 rows 24.9 / 21.2 / 18.4   300 rows 34.9 / 34.7 / 25.0
+//   V = 128256 bf16  1 row 31.8 / 26.4 /  8.8   128 rows 39.1 / 32.1 / 18.9   256 rows 43.0 / 33.5 / 31.7   300 rows 62.8 / 57   / 39.9
+//   V = 12288 fp32   1 row  7.6 /   -  /  7.1   128 rows  9.2 /   -  /  8.2   256 rows 11.9 /   -  / 10.8   300 rows 15.4 /   -  / 12.4
+//     all greedy            6.2 /   -  /  6.6             7.5 /   -  /  7.6            10.4 /   -  / 10.1            13.0 /   -  / 11.7
+//   V = 50272 fp32   1 row 14.3 /   -  /  8.4   128 rows 21.1 /   -  / 16.2   256 rows 34.1 /   -  / 22.0   300 rows 43.2 /   -  / 26.8
+// In parts above V = 12288: below, greedy rows (which the host cannot tell from sampled ones) lose what the others gain.  Without
+// a workspace, or with rows the parts do not take, the register-resident kernel above V = 24576 where it fits, else three sweeps.
+constexpr int kDraftPartsAbove = 12288, kDraftFastAbove = 24576;
+static bool draft_wants_parts(const adaspec_draft_dims &d) { return d.vocab > kDraftPartsAbove; }
 
 // Whether dims may take the form in parts: forced (ADASPEC_PATH_TWO_PASS) for 16-bit logits up to V = 131072; AUTO also
 // for fp32 logits and larger vocabularies.

@@ -1,23 +1,22 @@
 // Draft-side sampling with every row cut into parts: logits and probabilities of any storage types, V % 8 == 0,
 // V <= 524288, 16-byte aligned rows.  What the step computes is stated in draft_sample.hip.
 //
-// One row of V = 128 K elements keeps a compute unit busy for about 30 us (two sweeps of exponentials and the store of the
-// probability row), and a draft step has one row per request: with fewer rows than compute units the single-workgroup
-// kernels leave most of the chip idle for that long.  Here small workgroups (256 threads) share a row, at the price of
-// three kernels:
-//   draft_stats_kernel   (row, part): maximum and normaliser of the part, streamed (row_parts.h); greedy rows: arg-max too
-//   draft_probs_kernel   (row, part of 1024 chunks): the row's (m, Z) from its parts, q_v = 2^((l_v - m) c) / Z rounded once
-//                        and stored, the rounded mass of each wavefront's 256 chunks
-//   draft_pick_kernel    one workgroup per row: the (part, wavefront) pair that holds tau = u * sum(q), then its step, lane
-//                        and element from the stored row; greedy rows: the arg-max of the parts
-// The second kernel re-reads the logits (16-bit rows of a step fit the memory-side cache).  Bound: HBM for large steps, the
-// three launches and their dependent accesses for small ones.  MI355X, whole call, one
-// workgroup per row before: 64 rows of V = 128256 in fp32 43.6 -> 22.4 us, of V = 262144 in bf16 71 -> 25.3 us; 128 rows of
-// V = 128256 in bf16 23.4-24.1 us (26.1 in four parts of 1024 threads).
+// One row of V = 128 K elements keeps a compute unit busy for about 30 us, and a draft step has one row per request, fewer
+// than compute units: rows are shared.  The step is three dependent phases over a row (maximum and normaliser;
+// probabilities out and their mass; the draw).  Workgroup (row, part) of 512 or 1024 threads: reads its part once, into registers, and
+// never again; the parts of a row tell each other their (maximum, normaliser), then the mass of their rounded
+// probabilities (part_exchange.h); the part that holds tau = u * sum(q) finds the element in its registers.  Everything in
+// one launch: what a part needs from the others takes about 1 us where a kernel boundary takes 3 and the row has to be
+// read again.  The probabilities are stored when the mass is out, so that the stores travel during the second exchange.
+//
+// Bound: HBM for large steps (33 MB in, 33 out for 128 rows of V = 128256 bf16), latency for small ones.  MI355X, whole call,
+// three kernels of row parts before: 128 rows of V = 128256 bf16 24.4 -> 18.4 us (3.6 TB/s), in fp32 37.3 -> 24.0, 64 rows in fp32 22.5 -> 17.1,
+// of V = 262144 bf16 24.9 -> 18.7, 300 of V = 128256 47.8 -> 38.5, 8 of V = 524288 17.7 -> 11.0; one row of V = 128256, captured, 9.9 -> 8.8.
 #include <type_traits>
 
 #include "adaspec_internal.h"
 #include "device_utils.h"
+#include "part_exchange.h"
 #include "row_parts.h"
 
 namespace adaspec {
@@ -44,189 +43,434 @@ __device__ __forceinline__ float draft_exponent_scale(float T)     // T == 0 sta
     return T == 0.0f ? 1.4426950408889634f : exponent_scale<LT>(T);
 }
 
-// (m, Z, arg-max or -1) of a row from its parts
-template <class LT>
-__device__ __forceinline__ HalfStat merge_stats(const HalfStat *__restrict__ st, int n_parts, float c)
-{
-    HalfStat s[kStatParts], out;
-    out.m = -INFINITY; out.arg = -1; out.Z = 0.0;
-#pragma unroll
-    for (int p = 0; p < kStatParts; ++p) {
-        s[p].m = -INFINITY; s[p].arg = -1; s[p].Z = 0.0;
-        if (p < n_parts) s[p] = st[p];                       // uniform: scalar loads
-    }
-#pragma unroll
-    for (int p = 0; p < kStatParts; ++p) {
-        out.m = fmaxf(out.m, s[p].m);
-    }
-#pragma unroll
-    for (int p = 0; p < kStatParts; ++p) {
-        if (s[p].m == out.m && s[p].arg >= 0 && (out.arg < 0 || s[p].arg < out.arg)) out.arg = s[p].arg;
-        out.Z += s[p].m > -INFINITY ? s[p].Z * (double)__builtin_amdgcn_exp2f(ref_gap<LT>(s[p].m, out.m, c)) : 0.0;
-    }
-    return out;
-}
+constexpr int kDraftSteps = 8;                       // chunks per thread at most
+constexpr int kDraftMaxParts = 32;                   // two lanes each in the first exchange
+constexpr int kDraftT = 512, kDraftWideT = 1024;     // threads, and elements per thread up to which a row stays whole: see
+constexpr int kDraftWholeElems = 32;                 // launch_draft_parts
+static_assert(kPartsMaxVocab <= kDraftMaxParts * kDraftSteps * kDraftT * 4, "fp32 rows fit");
+// What a part tells the others: (maximum, first element with it) and normaliser, then its mass.  A launch leaves the first two taken back:
+// whoever has all the masses knows that the others have read them.  The mass is taken back where the next launch starts: nobody
+// looks for it before having seen that launch's maximum, which is published after the taking back is in place.
+struct DraftWords { MarkedWord top, Z, mass; };
 
-template <class LT>
-__global__ __launch_bounds__(kQT, kStatWgsPerCu) void draft_stats_kernel(
-    const char *__restrict__ logits, const float *__restrict__ temperature, int V, int n_parts, int64_t lstride_bytes,
-    HalfStat *__restrict__ stats)
+template <class LT, class PT, int NT>
+__global__ __launch_bounds__(NT, 4) void draft_row_kernel(
+    const char *__restrict__ logits, const float *__restrict__ temperature, const float *__restrict__ uniforms,
+    const int32_t *__restrict__ out_rows, char *__restrict__ probs, int32_t *__restrict__ tokens, float *__restrict__ confidence,
+    int V, int n_parts, int part_steps, int64_t lstride_bytes, int64_t pstride_bytes, DraftWords *__restrict__ all_words,
+    unsigned long long mark)
 {
-    __shared__ float s_m[kQW];
-    __shared__ double s_z[kQW];
-    __shared__ int s_i[kQW];
+    // (a part gives the same bits whether its own workgroup computes it or another one: no product is fused into a sum in one
+    // place and not in the other)
+#pragma clang fp contract(off)
+    constexpr int kN = Chunk<LT>::kN, NW = NT / kWave;
+    constexpr bool kKeepsWeights = kN == 8;              // 16-bit logits: the weights; fp32: the logits themselves
+    constexpr int kBytes = ProbChunk<kN, PT>::kBytes;    // probabilities of a chunk
+    __shared__ float s_m[NW];
+    __shared__ double s_z[NW];
+    __shared__ int s_i[NW];
+    __shared__ float s_part_m[kDraftMaxParts];
+    __shared__ int s_part_i[kDraftMaxParts];
+    __shared__ double s_part_z[kDraftMaxParts];          // normalisers, then masses
+    __shared__ float s_row_m, s_row_inv;
+    __shared__ int s_row_arg, s_star, s_wave;            // (s_row_arg: first element with the maximum, or -1)
+    __shared__ double s_tau, s_before;
+    __shared__ double s_mass[NW];                   // of the own part's wavefronts
+    __shared__ unsigned int s_missing;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int r = blockIdx.x / n_parts, h = blockIdx.x % n_parts;
-    const float T = temperature[r], c = draft_exponent_scale<LT>(T);
-    const int row_chunks = V / Chunk<LT>::kN;
-    const __amdgpu_buffer_rsrc_t rl =
-        __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(logits) + (int64_t)r * lstride_bytes, 0, row_chunks * 16, 0x00020000);
-    HalfStat out;
-    if (T == 0.0f) {
-        const PartStream st = stream_part<LT, true, true, kAuxDefault>(rl, row_chunks, n_parts, h, V, c, tid, [] {});
-        out = reduce_norm<LT>(st, c, s_m, s_z, lane, wv);
-        lds_barrier();                                       // s_m is used again
-        const ArgMax b = reduce_argmax(st.best, s_m, s_i, lane, wv);
-        out.arg = b.i < V ? b.i : -1;
-    } else {
-        const PartStream st = stream_part<LT, true, false, kAuxDefault>(rl, row_chunks, n_parts, h, V, c, tid, [] {});
-        out = reduce_norm<LT>(st, c, s_m, s_z, lane, wv);
-    }
-    if (tid == 0) stats[(int64_t)r * kStatParts + h] = out;
-}
+    DraftWords *words = all_words + (int64_t)r * n_parts;
+    if (n_parts > 1 && tid == 0) take_back(&words[h].mass);
 
-template <class LT, class PT>
-__global__ __launch_bounds__(kQT, 8) void draft_probs_kernel(
-    const char *__restrict__ logits, const float *__restrict__ temperature, const int32_t *__restrict__ out_rows,
-    char *__restrict__ probs, int V, int n_stat_parts, int n_parts, int64_t lstride_bytes, int64_t pstride_bytes,
-    const HalfStat *__restrict__ stats, double *__restrict__ mass)
-{
-    constexpr int kN = Chunk<LT>::kN, kBytes = ProbChunk<kN, PT>::kBytes;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int r = blockIdx.x / n_parts, h = blockIdx.x % n_parts;
-    const int row_chunks = V / kN, chunk0 = h * kSumChunks, nchunks = min(row_chunks - chunk0, kSumChunks);
-    const __amdgpu_buffer_rsrc_t rl = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<char *>(logits) + (int64_t)r * lstride_bytes + (int64_t)chunk0 * 16, 0, nchunks * 16, 0x00020000);
-    // wavefront w owns the part's chunks 256 w .. 256 w + 255, lane l of its step it the chunk 64 it + l of those
-    const int my_chunk = wv * (kSumSteps * kWave) + lane;
-    uint4 lg[kSumSteps];
+    // wavefront w holds 64 * part_steps chunks of a part in a row, lane l of its step it the chunk 64 it + l of those
+    const int row_chunks = V / kN, part_chunks = part_steps * NT;
+    const int my_chunk = wv * (part_steps * kWave) + lane;
+    const float T = temperature[r], u = uniforms[r], c = draft_exponent_scale<LT>(T);
+    const bool sampled = T != 0.0f;
+    const char *lrow = logits + (int64_t)r * lstride_bytes;
+    auto part_size = [&](int part) -> int { return max(0, min(row_chunks - part * part_chunks, part_chunks)); };
+    auto part_row = [&](int part) {
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(lrow) + (int64_t)part * part_chunks * 16, 0, part_size(part) * 16, 0x00020000);
+    };
+    auto chunk_index = [&](int part, int it) -> int { return part * part_chunks + my_chunk + it * kWave; };     // in the row
+
+    // What is done with a part is written twice below: for the own one, in registers, and chunk by chunk for parts whose
+    // words do not come.
+    // A thread's weights are relative to a reference near its maximum.  16-bit logits: the scaled reference of its first chunk's
+    // maximum, so that a chunk's weights can be computed when it lands; any reference does, as moving to another one is an
+    // exact factor, unless it is so far off that weights could overflow or vanish.  fp32: the maximum itself.
+    struct Ref { float m, at; };                             // the thread's maximum (-inf: nothing finite) and its reference
+    auto first_ref = [&](float m0) -> float { return m0 > -INFINITY ? scaled_ref(m0, c) : 0.f; };
+    auto ref_of = [&](float m0, float m) -> Ref {
+        const float own = first_ref(m), early = first_ref(m0);
+        return Ref{m, kKeepsWeights && fabsf(own - early) <= 60.f ? early : own};
+    };
+    // exponent that moves a thread's weights to the reference of the maximum m
+    auto thread_gap = [&](Ref t, float m) -> float { return kKeepsWeights ? t.at - scaled_ref(m, c) : (t.m - m) * c; };
+    // a chunk's weights, added up behind z
+    auto add_weights = [&](const uint4 &lv, Ref t, float z, float (&w)[kN]) -> float {
+        float x[kN];
+        Chunk<LT>::unpack(lv, x);
 #pragma unroll
-    for (int it = 0; it < kSumSteps; ++it) lg[it] = part_load16<kAuxDefault>(rl, (uint32_t)my_chunk * 16u, it * (kWave * 16));
-    const float T = temperature[r], c = draft_exponent_scale<LT>(T);
-    const HalfStat row = merge_stats<LT>(stats + (int64_t)r * kStatParts, n_stat_parts, c);
-    const float mc = scaled_ref(row.m, c), invZ = (float)(1.0 / row.Z);   // (a row without any finite logit: q = NaN, as in the other kernels)
-    char *prow = probs + (int64_t)(out_rows ? out_rows[r] : r) * pstride_bytes + (int64_t)chunk0 * kBytes;
-    const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc(prow, 0, nchunks * kBytes, 0x00020000);
-    double total = 0.0;
-#pragma unroll
-    for (int it = 0; it < kSumSteps; ++it) {
-        keep_packed(lg[it]);
-        Chunk<LT>::blank(lg[it], my_chunk + it * kWave >= nchunks);
-        float q[kN];
-        Chunk<LT>::unpack(lg[it], q);
-#pragma unroll
-        for (int e = 0; e < kN; ++e) q[e] = exp_weight<LT>(q[e], row.m, c, mc) * invZ;
-        // (the step's offset in the lane offset, scalar offset 0: see the store in draft_fast.hip)
-        const int at = (my_chunk + it * kWave) * kBytes;
-        if constexpr (std::is_same<PT, F32>::value) {
-#pragma unroll
-            for (int k = 0; k < kN / 4; ++k)
-                __builtin_amdgcn_raw_buffer_store_b128(
-                    u32x4{__float_as_uint(q[4 * k]), __float_as_uint(q[4 * k + 1]), __float_as_uint(q[4 * k + 2]), __float_as_uint(q[4 * k + 3])},
-                    rp, at + 16 * k, 0, 0);
-        } else {
-            uint32_t w[kN / 2];
-#pragma unroll
-            for (int e = 0; e < kN / 2; ++e) {
-                w[e] = round_pair<PT>(q[2 * e], q[2 * e + 1]);
-                q[2 * e] = Pair16<PT>::lo(w[e]);
-                q[2 * e + 1] = Pair16<PT>::hi(w[e]);
-            }
-            if constexpr (kN == 8) {
-                __builtin_amdgcn_raw_buffer_store_b128(u32x4{w[0], w[1], w[2], w[3]}, rp, at, 0, 0);
-            } else {
-                typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-                __builtin_amdgcn_raw_buffer_store_b64(u32x2{w[0], w[1]}, rp, at, 0, 0);
-            }
+        for (int e = 0; e < kN; ++e) {
+            const float v = exp_weight<LT>(x[e], t.m > -INFINITY ? t.m : 0.f, c, t.at);
+            z += v;
+            w[e] = kKeepsWeights ? v : x[e];
         }
+        return z;
+    };
+    // lowest element of a chunk that is its maximum
+    auto first_with = [&](const uint4 &lv, float m, int chunk) -> int {
+        float x[kN];
+        Chunk<LT>::unpack(lv, x);
+        int at = 0;
+#pragma unroll
+        for (int e = kN - 1; e >= 0; --e) at = x[e] == m ? e : at;
+        return chunk * kN + at;
+    };
+    // a chunk's probabilities, rounded, in place; returns their sum.  f moves weights from the thread's reference to the row's
+    // and divides by the normaliser.
+    auto round_probs = [&](float (&w)[kN], float f, float m, float mc, float inv) -> float {
         float acc = 0.f;
 #pragma unroll
-        for (int e = 0; e < kN; ++e) acc += q[e];
-        total += (double)acc;
-    }
-    total = wave_sum(total);
-    if (lane == 0) mass[((int64_t)r * n_parts + h) * kQW + wv] = total;
-}
-
-template <class PT>
-__global__ __launch_bounds__(kQT) void draft_pick_kernel(
-    const char *__restrict__ probs, const float *__restrict__ temperature, const float *__restrict__ uniforms,
-    const int32_t *__restrict__ out_rows, int32_t *__restrict__ tokens, float *__restrict__ confidence, int V, int chunk_elems,
-    int n_stat_parts, int n_parts, int64_t pstride_bytes, const HalfStat *__restrict__ stats, const double *__restrict__ mass)
-{
-    __shared__ PairScratch s_pair;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int r = blockIdx.x;
-    const float T = temperature[r], u = uniforms[r];
-    const char *prow = probs + (int64_t)(out_rows ? out_rows[r] : r) * pstride_bytes;
-    const int n_pairs = n_parts * kQW;
-    double w0 = 0.0, w1 = 0.0;
-    if (T != 0.0f && 2 * tid < n_pairs) {
-        const double2 w = *reinterpret_cast<const double2 *>(mass + (int64_t)r * n_pairs + 2 * tid);
-        w0 = w.x; w1 = w.y;
-    }
-    if (T == 0.0f) {
-        if (tid == 0) {
-            const int arg = merge_stats<PT>(stats + (int64_t)r * kStatParts, n_stat_parts, 1.4426950408889634f).arg;
-            tokens[r] = arg >= 0 ? arg : 0;
-            confidence[r] = arg >= 0 ? load_as_float<PT>(prow, arg) : 0.f;
+        for (int e = 0; e < kN; e += 2) {
+            float q[2];
+#pragma unroll
+            for (int k = 0; k < 2; ++k) q[k] = kKeepsWeights ? w[e + k] * f : exp_weight<LT>(w[e + k], m, c, mc) * inv;
+            if constexpr (!std::is_same<PT, F32>::value) {
+                const uint32_t pair = round_pair<PT>(q[0], q[1]);
+                q[0] = Pair16<PT>::lo(pair); q[1] = Pair16<PT>::hi(pair);
+            }
+            w[e] = q[0]; w[e + 1] = q[1];
+            acc += q[0];
+            acc += q[1];
         }
-        return;
-    }
-    double Q;
-    const double at1 = pair_totals(s_pair, w0 + w1, tid, lane, wv, Q);
-    const double tau = (double)u * Q;
-    const int pair = pick_pair(s_pair, w0, w1, at1, tau, tid, lane, wv);
-    if (pair < 0) {                           // no mass (non-finite input): stay defined
-        if (tid == 0) { tokens[r] = 0; confidence[r] = 0.f; }
-        return;
-    }
-    // this lane's chunk of the stored row: step wv of the pair
-    const int first = (pair / kQW * kSumChunks + ((pair % kQW) * kSumSteps + wv) * kWave + lane) * chunk_elems;
-    auto finish = [&](auto n_tag) {
-        constexpr int N = decltype(n_tag)::value;
-        ProbChunk<N, PT> qc;
-        qc.zero();
-        if (first < V)
-            __builtin_memcpy(qc.w, __builtin_assume_aligned(prow + (int64_t)first * (int)sizeof(typename PT::storage), qc.kBytes < 16 ? 8 : 16), qc.kBytes);
-        float q[N], acc = 0.f;
-        qc.unpack(q);
-#pragma unroll
-        for (int e = 0; e < N; ++e) acc += q[e];
-        double li;
-        bool none;
-        const bool owner = own_point(s_pair, (double)acc, tau, lane, wv, li, none);
-        if (none && tid == 0) { tokens[r] = 0; confidence[r] = 0.f; }
-        if (owner) {
-            const int pick = pick_element<N>(q, li - (double)acc, 1.0, tau);
-            tokens[r] = first + pick;
-            float conf = q[0];
-#pragma unroll
-            for (int e = 1; e < N; ++e) conf = e == pick ? q[e] : conf;
-            confidence[r] = conf;
+        return acc;
+    };
+    // over the workgroup: a part's statistics from its threads' (first half of the way: to LDS)
+    auto leave_stats = [&](Ref t, float z_t, int top) {
+        const float mw = wave_max(t.m);
+        const double zw = wave_sum(t.m > -INFINITY ? (double)(z_t * __builtin_amdgcn_exp2f(thread_gap(t, mw))) : 0.0);
+        if (lane == 0) { s_m[wv] = mw; s_z[wv] = zw; }
+        if (!sampled) {
+            const ArgMax b = wave_argmax(ArgMax{t.m, top});
+            if (lane == 0) s_i[wv] = b.i;
         }
     };
-    if (chunk_elems == 8) finish(std::integral_constant<int, 8>{});
-    else finish(std::integral_constant<int, 4>{});
+    auto take_stats = [&](int part, float &m, double &Z, int &arg) {     // (wavefront 0)
+        const float mw = lane < NW ? s_m[lane] : -INFINITY;
+        m = wave_max(mw);
+        Z = wave_sum(mw > -INFINITY ? s_z[lane & (NW - 1)] * (double)__builtin_amdgcn_exp2f(ref_gap<LT>(mw, m, c)) : 0.0);
+        arg = sampled ? V : wave_argmax(ArgMax{mw, lane < NW ? s_i[lane] : V}).i;
+        if (lane == 0) { s_part_m[part] = m; s_part_i[part] = arg; s_part_z[part] = Z; }
+    };
+    auto row_stats = [&]() {                                             // (wavefront 0, all parts known)
+        const float mp = lane < n_parts ? s_part_m[lane] : -INFINITY, M = wave_max(mp);
+        const double sum = wave_sum(mp > -INFINITY ? s_part_z[lane & 31] * (double)__builtin_amdgcn_exp2f(ref_gap<LT>(mp, M, c)) : 0.0);
+        const int at = s_part_i[lane & 31];
+        const ArgMax b = wave_argmax(lane < n_parts && at < V ? ArgMax{mp, at} : ArgMax{-INFINITY, 0x7fffffff});
+        // (a row without any finite logit: q = NaN, as in the other kernels)
+        if (lane == 0) { s_row_m = M; s_row_inv = (float)(1.0 / sum); s_row_arg = b.i == 0x7fffffff ? -1 : b.i; }
+    };
+    auto thread_factor = [&](Ref t) -> float {
+        return __builtin_amdgcn_exp2f(t.m > -INFINITY ? thread_gap(t, s_row_m) : 0.f) * s_row_inv;
+    };
+
+    // ---- the own part: weights and their sum ----------------------------------------------------------------------
+    float w[kDraftSteps][kN], z_t = 0.f;
+    Ref ref;
+    int top = V;                                             // (greedy rows) first element with the thread's maximum
+    {
+        const __amdgpu_buffer_rsrc_t rl = part_row(h);
+        const int n = part_size(h);
+        uint4 lg[kDraftSteps];
+#pragma unroll
+        for (int it = 0; it < kDraftSteps; ++it) {           // (steps a part does not have: no traffic, -inf)
+            lg[it] = make_uint4(0, 0, 0, 0);
+            if (it < part_steps) lg[it] = part_load16<kAuxDefault>(rl, (uint32_t)my_chunk * 16u, it * (kWave * 16));
+        }
+        auto blank = [&](int it) { Chunk<LT>::blank(lg[it], it >= part_steps || my_chunk + it * kWave >= n); };
+        float m = -INFINITY, m0 = -INFINITY;
+        if constexpr (!kKeepsWeights) {
+#pragma unroll
+            for (int it = 0; it < kDraftSteps; ++it) blank(it);
+            m = thread_max<LT, kDraftSteps>(lg);
+            ref = ref_of(m, m);
+        }
+#pragma unroll
+        for (int it = 0; it < kDraftSteps; ++it) {
+            if constexpr (kKeepsWeights) {
+                blank(it);
+                const float mn = chunk_max<LT>(lg[it], m);
+                if (it == 0) { m0 = mn; ref = Ref{m0, first_ref(m0)}; }
+                if (!sampled && mn > m) top = first_with(lg[it], mn, chunk_index(h, it));
+                m = mn;
+            } else {
+                if (!sampled && top == V && m > -INFINITY && chunk_max<LT>(lg[it], -INFINITY) == m) top = first_with(lg[it], m, chunk_index(h, it));
+            }
+            keep_packed(lg[it]);
+            z_t = add_weights(lg[it], ref, z_t, w[it]);
+            __builtin_amdgcn_sched_barrier(0);               // (one step at a time: registers)
+        }
+        if constexpr (kKeepsWeights) {
+            const float early = ref.at;
+            ref = ref_of(m0, m);
+            if (__ballot(ref.at != early) != 0ull) {         // (logits that far apart, or nothing finite in the first chunk)
+                z_t = 0.f;
+#pragma unroll
+                for (int it = 0; it < kDraftSteps; ++it) {
+                    uint4 v = make_uint4(0, 0, 0, 0);
+                    if (it < part_steps) v = part_load16<kAuxDefault>(rl, (uint32_t)my_chunk * 16u, it * (kWave * 16));
+                    Chunk<LT>::blank(v, it >= part_steps || my_chunk + it * kWave >= n);
+                    z_t = add_weights(v, ref, z_t, w[it]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+        }
+    }
+    leave_stats(ref, z_t, top);
+    lds_barrier();
+    const unsigned int others = (unsigned int)((1ull << n_parts) - 1ull) & ~(1u << h);
+    if (wv == 0) {
+        float m;
+        double Z;
+        int arg;
+        take_stats(h, m, Z, arg);
+        unsigned int missing = 0u;
+        if (n_parts > 1) {
+            if (lane == 0) {
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // (the mass of an earlier launch is taken back)
+                publish_marked(&words[h].top, (unsigned long long)__float_as_uint(m) | ((unsigned long long)(uint32_t)arg << 32), mark);
+                publish_marked(&words[h].Z, word_of(Z), mark);
+            }
+            const int p = lane & 31;                                 // lanes 0..31 the maxima, 32..63 the normalisers
+            const bool other = (others >> p) & 1u;
+            unsigned long long v = 0ull;
+            const unsigned long long got = __ballot(take_marked(lane < 32 ? &words[p].top : &words[p].Z, other, mark, kPatience, v));
+            const unsigned int both = (unsigned int)got & (unsigned int)(got >> 32);
+            if (other && ((both >> p) & 1u)) {
+                if (lane < 32) { s_part_m[p] = __uint_as_float((uint32_t)v); s_part_i[p] = (int)(v >> 32); }
+                else s_part_z[p] = double_of(v);
+            }
+            missing = others & ~both;
+        }
+        if (missing == 0u) row_stats();
+        if (lane == 0) s_missing = missing;
+    }
+    lds_barrier();
+    // (of a part whose statistics did not come in time the mass may be an earlier replay's: not looked at below)
+    const unsigned int late = __builtin_amdgcn_readfirstlane(s_missing);
+    if (late != 0u) {
+        for (unsigned int left = late; left != 0u; left &= left - 1u) {
+            const int part = (int)__builtin_ctz(left);
+            const __amdgpu_buffer_rsrc_t rl = part_row(part);
+            const int n = part_size(part);
+            auto chunk_at = [&](int it) -> uint4 {
+                uint4 v = part_load16<kAuxDefault>(rl, (uint32_t)my_chunk * 16u, it * (kWave * 16));
+                Chunk<LT>::blank(v, my_chunk + it * kWave >= n);
+                return v;
+            };
+            float m = -INFINITY, m0 = -INFINITY, z = 0.f;
+            int first = V;
+            for (int it = 0; it < part_steps; ++it) {
+                const uint4 v = chunk_at(it);
+                const float mn = chunk_max<LT>(v, m);
+                if (it == 0) m0 = mn;
+                if (mn > m) first = first_with(v, mn, chunk_index(part, it));
+                m = mn;
+            }
+            const Ref t = ref_of(m0, m);
+            for (int it = 0; it < part_steps; ++it) {
+                float x[kN];
+                z = add_weights(chunk_at(it), t, z, x);
+            }
+            lds_barrier();
+            leave_stats(t, z, first);
+            lds_barrier();
+            if (wv == 0) {
+                double Z;
+                int arg;
+                take_stats(part, m, Z, arg);
+            }
+        }
+        if (wv == 0) row_stats();
+        lds_barrier();
+    }
+
+    const bool counted = sampled || n_parts > 1;             // (the mass of a whole greedy row tells nobody anything)
+
+    // ---- the probabilities, rounded, and their mass -----------------------------------------------------------
+    const float row_m = s_row_m, row_inv = s_row_inv, mc = scaled_ref(row_m, c);
+    {
+        const float f = thread_factor(ref);
+        double total = 0.0;
+#pragma unroll
+        for (int it = 0; it < kDraftSteps; ++it) {
+            if (it >= part_steps) break;
+            total += (double)round_probs(w[it], f, row_m, mc, row_inv);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (counted) {
+            total = wave_sum(total);
+            if (lane == 0) s_z[wv] = total;
+        }
+    }
+    if (counted) lds_barrier();
+    if (wv == 0 && counted) {
+        const double mass = wave_sum(lane < NW ? s_z[lane] : 0.0);
+        if (lane == 0) {
+            if (n_parts > 1) publish_marked(&words[h].mass, word_of(mass), mark);
+            s_part_z[h] = mass;
+        }
+    }
+    // (the mass is out: the probabilities may follow)
+    {
+        const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc(
+            probs + (int64_t)(out_rows ? out_rows[r] : r) * pstride_bytes + (int64_t)h * part_chunks * kBytes, 0, part_size(h) * kBytes, 0x00020000);
+#pragma unroll
+        for (int it = 0; it < kDraftSteps; ++it) {
+            if (it >= part_steps) break;
+            // (the step's offset in the lane offset, scalar offset 0: see the store in draft_fast.hip)
+            const int at = (my_chunk + it * kWave) * kBytes;
+            uint32_t d[kBytes / 4];
+            if constexpr (std::is_same<PT, F32>::value) {
+#pragma unroll
+                for (int e = 0; e < kN; ++e) d[e] = __float_as_uint(w[it][e]);
+            } else {
+#pragma unroll
+                for (int e = 0; e < kN / 2; ++e) d[e] = round_pair<PT>(w[it][2 * e], w[it][2 * e + 1]);     // (exact)
+            }
+            if constexpr (kBytes == 8) {
+                typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+                __builtin_amdgcn_raw_buffer_store_b64(u32x2{d[0], d[1]}, rp, at, 0, 0);
+            } else {
+#pragma unroll
+                for (int k = 0; k < kBytes / 16; ++k)
+                    __builtin_amdgcn_raw_buffer_store_b128(u32x4{d[4 * k], d[4 * k + 1], d[4 * k + 2], d[4 * k + 3]}, rp, at + 16 * k, 0, 0);
+            }
+        }
+    }
+    // the draw (wavefront 0, all masses known): the part, then the wavefront of it, that holds the point
+    auto draw = [&]() {
+        if (n_parts > 1 && lane == 0) { take_back(&words[h].top); take_back(&words[h].Z); }
+        int star = -1, wave = -1;
+        double before = 0.0, tau = 0.0;
+        if (sampled) {
+            const double at = lane < n_parts ? s_part_z[lane & 31] : 0.0;
+            tau = (double)u * wave_sum(at);
+            star = find_piece(at, 0.0, tau, lane, before);
+            if (star == h) {
+                double ahead;
+                wave = find_piece(lane < NW ? s_mass[lane] : 0.0, before, tau, lane, ahead);
+                before = ahead;
+            }
+        } else if (s_row_arg >= 0) {
+            star = s_row_arg / kN / part_chunks;
+            wave = s_row_arg / kN % part_chunks / (part_steps * kWave);
+        }
+        if (star < 0 && h == 0 && lane == 0) { tokens[r] = 0; confidence[r] = 0.f; }      // no mass (non-finite input): stay defined
+        if (lane == 0) { s_star = star; s_wave = wave; s_before = before; s_tau = tau; }
+    };
+    if (wv == 0) {
+        if (lane < NW) s_mass[lane] = s_z[lane];
+        unsigned int missing = 0u;
+        if (n_parts > 1) {
+            const bool other = (others >> (lane & 31)) & (unsigned int)(lane < 32);
+            unsigned long long v = 0ull;
+            const bool got = take_marked(&words[lane & 31].mass, other && !((late >> (lane & 31)) & 1u), mark, kPatience, v);
+            if (got) s_part_z[lane & 31] = double_of(v);
+            missing = (unsigned int)__ballot(other && !got);
+        }
+        if (missing == 0u) draw();
+        if (lane == 0) s_missing = missing;
+    }
+    lds_barrier();
+    const unsigned int gone = __builtin_amdgcn_readfirstlane(s_missing);
+    if (gone != 0u) {
+        for (unsigned int left = gone; left != 0u; left &= left - 1u) {
+            const int part = (int)__builtin_ctz(left);
+            const __amdgpu_buffer_rsrc_t rl = part_row(part);
+            const int n = part_size(part);
+            auto chunk_at = [&](int it) -> uint4 {
+                uint4 v = part_load16<kAuxDefault>(rl, (uint32_t)my_chunk * 16u, it * (kWave * 16));
+                Chunk<LT>::blank(v, my_chunk + it * kWave >= n);
+                return v;
+            };
+            float m = -INFINITY, m0 = -INFINITY;
+            for (int it = 0; it < part_steps; ++it) {
+                m = chunk_max<LT>(chunk_at(it), m);
+                if (it == 0) m0 = m;
+            }
+            const Ref t = ref_of(m0, m);
+            const float f = thread_factor(t);
+            double total = 0.0;
+            for (int it = 0; it < part_steps; ++it) {
+                float x[kN];
+                add_weights(chunk_at(it), t, 0.f, x);
+                total += (double)round_probs(x, f, row_m, mc, row_inv);
+            }
+            total = wave_sum(total);
+            lds_barrier();
+            if (lane == 0) s_z[wv] = total;
+            lds_barrier();
+            if (wv == 0) {
+                const double mass = wave_sum(lane < NW ? s_z[lane] : 0.0);
+                if (lane == 0) s_part_z[part] = mass;
+            }
+        }
+        if (wv == 0) draw();
+        lds_barrier();
+    }
+    if (s_star != h || s_wave != wv) return;
+
+    // ---- one wavefront of one part: the step, the lane, the element -----------------------------------------
+    const double tau = s_tau;
+    double before = s_before, cum = 0.0;
+    int step = -1, owner = 0, pick = 0;
+    if (sampled) {
+#pragma unroll
+        for (int it = 0; it < kDraftSteps; ++it) {
+            if (it >= part_steps) break;
+            float acc = 0.f;
+#pragma unroll
+            for (int e = 0; e < kN; ++e) acc += w[it][e];
+            const double mine = (double)acc, upto = before + wave_scan_incl(mine, lane);
+            const unsigned long long cross = __ballot(mine > 0.0 && upto > tau), filled = __ballot(mine > 0.0);
+            if (filled) {
+                step = it;
+                owner = cross ? (int)__builtin_ctzll(cross) : 63 - (int)__builtin_clzll(filled);
+                cum = upto - mine;
+            }
+            if (cross) break;
+            before = last_lane(upto);
+        }
+        if (step < 0) {
+            if (lane == 0) { tokens[r] = 0; confidence[r] = 0.f; }
+            return;
+        }
+    } else {
+        const int at = s_row_arg / kN % part_chunks - wv * (part_steps * kWave);
+        step = at / kWave; owner = at % kWave; pick = s_row_arg % kN;
+    }
+#pragma unroll
+    for (int it = 0; it < kDraftSteps; ++it) {
+        if (it != step) continue;
+        if (sampled) pick = pick_element<kN>(w[it], cum, 1.0, tau);
+        float conf = w[it][0];
+#pragma unroll
+        for (int e = 1; e < kN; ++e) conf = e == pick ? w[it][e] : conf;
+        if (lane == owner) { tokens[r] = (h * part_chunks + my_chunk + it * kWave) * kN + pick; confidence[r] = conf; }
+    }
 }
 
 bool draft_parts_supported(const adaspec_draft_dims &d) { return d.vocab % 8 == 0 && d.vocab <= kPartsMaxVocab; }
 
-// workspace: HalfStat[R][kStatParts], then double[R][parts][kQW]
-static size_t stats_bytes(int rows) { return align_up((size_t)rows * kStatParts * sizeof(HalfStat), 256); }
+// DraftWords[R][parts].  A row's share is what it was when rows were swept by three kernels: statistics of eight parts and
+// 32 bytes per 1024 chunks.
+static size_t row_bytes(const adaspec_draft_dims &d) { return kStatParts * sizeof(HalfStat) + (size_t)parts_sum_parts(d.vocab, d.logits_dtype) * kQW * sizeof(double); }
 size_t draft_parts_workspace_bytes(const adaspec_draft_dims &d)
 {
-    return stats_bytes(d.rows) + (size_t)d.rows * parts_sum_parts(d.vocab, d.logits_dtype) * kQW * sizeof(double);
+    return align_up((size_t)d.rows * kStatParts * sizeof(HalfStat), 256) + (size_t)d.rows * parts_sum_parts(d.vocab, d.logits_dtype) * kQW * sizeof(double);
 }
 
 hipError_t launch_draft_parts(const void *logits, const float *temperature, const float *uniforms,
@@ -236,19 +480,27 @@ hipError_t launch_draft_parts(const void *logits, const float *temperature, cons
     if (d.rows == 0) return hipSuccess;
     const int64_t lstride = d.logits_row_stride * (d.logits_dtype == ADASPEC_F32 ? 4 : 2);
     const int64_t pstride = d.probs_row_stride * (d.probs_dtype == ADASPEC_F32 ? 4 : 2);
-    const int n_stat_parts = parts_stat_parts(d.rows, d.vocab, d.logits_dtype, compute_units);
-    const int n_parts = parts_sum_parts(d.vocab, d.logits_dtype);
-    HalfStat *stats = reinterpret_cast<HalfStat *>(ws);
-    double *mass = reinterpret_cast<double *>(ws + stats_bytes(d.rows));
+    // Short rows are not shared: the exchanges take longer than what is saved (captured calls, V = 16384 bf16, 1 / 64 / 128 rows in
+    // parts 8.2 / 9.1 / 9.3 us, whole 7.3 / 8.0 / 8.3; V = 24576 whole 8.7 / 9.5 / 10.4, in parts 8.1 / 9.2 / 9.8).
+    // Else as many parts as there are compute units for: where a compute unit has two of them the second starts 2-3 us later, and
+    // everybody waits for it (V = 16384, 128 rows in 512 parts 11.7, in 256 9.3).  Where 512 threads hold too little for that and
+    // 1024 do not, 1024 (128 rows of V = 128256 19.8 / 18.9, 192 of 65536 18.6 / 15.6; where both could, 512: 1 row 8.8 / 10.8).
+    const int chunks = d.vocab / parts_chunk_elems(d.logits_dtype);
+    auto least_parts = [&](int threads) { return ceil_div(chunks, threads * kDraftSteps); };
+    const bool wide = (int64_t)d.rows * least_parts(kDraftT) > compute_units && (int64_t)d.rows * least_parts(kDraftWideT) <= compute_units;
+    const int threads = wide ? kDraftWideT : kDraftT, steps = ceil_div(chunks, threads), least = least_parts(threads);
+    const int room = (int)(row_bytes(d) / sizeof(DraftWords)), most = room < kDraftMaxParts ? room : kDraftMaxParts;
+    int n_parts = steps * parts_chunk_elems(d.logits_dtype) <= kDraftWholeElems ? 1 : compute_units / d.rows;
+    n_parts = n_parts < least ? least : n_parts > most ? most : n_parts;
+    const int part_steps = ceil_div(steps, n_parts);
+    n_parts = ceil_div(steps, part_steps);
     auto launch = [&](auto lt, auto pt) {
         using LT = decltype(lt);
         using PT = decltype(pt);
-        hipLaunchKernelGGL((draft_stats_kernel<LT>), dim3(d.rows * n_stat_parts), dim3(kQT), 0, stream, (const char *)logits,
-                           temperature, d.vocab, n_stat_parts, lstride, stats);
-        hipLaunchKernelGGL((draft_probs_kernel<LT, PT>), dim3(d.rows * n_parts), dim3(kQT), 0, stream, (const char *)logits,
-                           temperature, out_rows, (char *)probs, d.vocab, n_stat_parts, n_parts, lstride, pstride, stats, mass);
-        hipLaunchKernelGGL((draft_pick_kernel<PT>), dim3(d.rows), dim3(kQT), 0, stream, (const char *)probs, temperature, uniforms,
-                           out_rows, tokens, confidence, d.vocab, Chunk<LT>::kN, n_stat_parts, n_parts, pstride, stats, mass);
+        auto kernel = wide ? draft_row_kernel<LT, PT, kDraftWideT> : draft_row_kernel<LT, PT, kDraftT>;
+        hipLaunchKernelGGL(kernel, dim3(d.rows * n_parts), dim3(threads), 0, stream, (const char *)logits,
+                           temperature, uniforms, out_rows, (char *)probs, tokens, confidence, d.vocab, n_parts, part_steps,
+                           lstride, pstride, reinterpret_cast<DraftWords *>(ws), (unsigned long long)next_spread_mark());
     };
     auto with_p = [&](auto lt) {
         if (d.probs_dtype == ADASPEC_F32) launch(lt, F32{});

@@ -51,4 +51,46 @@ __device__ __forceinline__ unsigned long long take_words(const unsigned long lon
     return w;
 }
 
+// Words that no earlier kernel of the call has cleared: the value, and the value with the launch's mark folded in.  A pair is
+// there if its halves differ by exactly the mark; marks are spread over all 64 bits and never given twice, so that leftovers
+// of whatever kind, or one half of an old pair beside one of a new one, do not look like it.  A captured launch keeps its
+// mark: what one replay leaves must be taken back before the next could read it (see the kernels).
+struct MarkedWord { unsigned long long value, check; };
+__device__ __forceinline__ void publish_marked(MarkedWord *p, unsigned long long v, unsigned long long mark)
+{
+    publish_u64(&p->value, v);
+    publish_u64(&p->check, v ^ mark);
+}
+__device__ __forceinline__ void take_back(MarkedWord *p)
+{
+    publish_u64(&p->value, 0ull);
+    publish_u64(&p->check, 0ull);
+}
+// One wavefront, like take_words; returns whether the lane has its value.
+__device__ __forceinline__ bool take_marked(const MarkedWord *p, bool wanted, unsigned long long mark, int looks, unsigned long long &v)
+{
+    bool there = false;
+    for (int n = 0; n < looks; ++n) {
+        if (wanted && !there) {
+            const unsigned long long a = fetch_u64(&p->value), b = fetch_u64(&p->check);
+            there = (a ^ b) == mark;
+            v = a;
+        }
+        if (__ballot(wanted && !there) == 0ull) break;
+    }
+    return there;
+}
+
+// One wavefront: where a point of a cumulative mass falls.  Lane t brings the mass of the t-th piece, `before` is the running
+// total in front of all of them.  Returns the first piece with mass whose running total exceeds tau, else (rounding left
+// none) the last with mass, else -1; `ahead` = running total in front of it.
+__device__ __forceinline__ int find_piece(double mass, double before, double tau, int lane, double &ahead)
+{
+    const double upto = before + wave_scan_incl(mass, lane);
+    const unsigned long long cross = __ballot(mass > 0.0 && upto > tau), filled = __ballot(mass > 0.0);
+    const int at = cross ? (int)__builtin_ctzll(cross) : (filled ? 63 - (int)__builtin_clzll(filled) : -1);
+    ahead = __shfl(upto - mass, at < 0 ? 0 : at, kWave);
+    return at;
+}
+
 }  // namespace adaspec

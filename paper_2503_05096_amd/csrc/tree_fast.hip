@@ -484,18 +484,11 @@ __global__ __launch_bounds__(kNT, STEPS == 1 ? 8 : 4) void accept_tree_walk_shar
         // Lane p of wavefront 0 looks at part p (no sweep: at step p): the first whose running total exceeds tau, else
         // (rounding left no crossing) the last with mass; then likewise at the (step, wavefront) pairs of the part
         const double tau = (double)sm.u1[u] * Gd;
-        auto find = [&](double at, double before, int &star, double &ahead) {
-            const double upto = before + wave_scan_incl(at, lane);
-            const unsigned long long cross = __ballot(at > 0.0 && upto > tau), filled = __ballot(at > 0.0);
-            star = cross ? (int)__builtin_ctzll(cross) : (filled ? 63 - (int)__builtin_clzll(filled) : -1);
-            ahead = __shfl(upto - at, star < 0 ? 0 : star, kWave);
-        };
         if (wv == 0) {
-            int star, at = -1;
+            int at = -1;
             double ahead, ahead2 = 0.0;
-            find(swept ? (lane < n_parts ? sm.part[tot][lane] : 0.0) : sm.S[u][lane], 0.0, star, ahead);
-            star = max(star, 0);
-            if (swept && star == h) find(sm.pair[tot][lane], ahead, at, ahead2);
+            const int star = max(find_piece(swept ? (lane < n_parts ? sm.part[tot][lane] : 0.0) : sm.S[u][lane], 0.0, tau, lane, ahead), 0);
+            if (swept && star == h) at = find_piece(sm.pair[tot][lane], ahead, tau, lane, ahead2);
             if (lane == 0) { sm.star = star; sm.pair_at = at; sm.before[0] = ahead; sm.before[1] = ahead2; }
         }
         lds_barrier();
@@ -518,9 +511,8 @@ __global__ __launch_bounds__(kNT, STEPS == 1 ? 8 : 4) void accept_tree_walk_shar
             if (lane == 0) sm.pair[tot][wv] = t;
             lds_barrier();
             if (wv == 0) {
-                int at;
                 double ahead2;
-                find(lane < kNW ? sm.pair[tot][lane] : 0.0, sm.before[0], at, ahead2);
+                const int at = find_piece(lane < kNW ? sm.pair[tot][lane] : 0.0, sm.before[0], tau, lane, ahead2);
                 if (lane == 0) { sm.pair_at = at; sm.before[1] = ahead2; }
             }
             lds_barrier();

@@ -54,3 +54,58 @@ def test_tree_walk_without_waiting(B, V, dtype, oracle_mod, pkg, impatient):  # 
         torch.cuda.synchronize()
         return got
     assert all(torch.equal(a, b) for a, b in zip(want, impatient(call)))
+
+
+def _draft_inputs(R, V, dtype, seed, T=None, lead_masked=False):
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    x = 3.0 * torch.randn((R, V), generator=gen, device="cuda")
+    if lead_masked:                                 # nothing finite, or nothing near the maximum, in a thread's first chunk
+        x[::2, :V // 2] = -float("inf")
+        x[1::2] = torch.where(torch.rand((R // 2, V), generator=gen, device="cuda") < 0.5, x[1::2] - 300.0, x[1::2] + 300.0)
+    t = torch.tensor([0.8, 0.0, 1.0, 1e-8], device="cuda").repeat(R)[:R] if T is None else torch.full((R,), T, device="cuda")
+    return x.to(dtype), t, torch.rand(R, generator=gen, device="cuda")
+
+
+# whole rows, parts of every length, a last part that is nearly empty, 1024 threads, the most parts; all pairs of element sizes
+@pytest.mark.parametrize("R,V,ldt,pdt", [(4, 16384, "bfloat16", "bfloat16"), (6, 32776, "bfloat16", "float32"), (5, 128256, "float16", "float16"),
+                                         (128, 128256, "bfloat16", "bfloat16"), (70, 65544, "bfloat16", "float16"), (4, 524288, "float32", "float32"),
+                                         (40, 50184, "float32", "bfloat16"), (2, 262152, "float16", "bfloat16"), (160, 65536, "bfloat16", "bfloat16")])
+@pytest.mark.parametrize("lead_masked", [False, True])
+def test_draft_rows_without_waiting(R, V, ldt, pdt, lead_masked, pkg, impatient):  # noqa: F811
+    import torch
+    x, t, u = _draft_inputs(R, V, getattr(torch, ldt), R + V, lead_masked=lead_masked)
+
+    def call():
+        got = pkg.draft_sample(x, t, u, probs_dtype=getattr(torch, pdt))
+        torch.cuda.synchronize()
+        return got
+    want = call()
+    assert all(torch.equal(a, b) for a, b in zip(want, impatient(call)))
+    q = torch.softmax(x.double() / torch.where(t > 0, t.double(), 1.0)[:, None], dim=1)
+    ulp = {"float32": 2e-5, "float16": 2.0 ** -10, "bfloat16": 2.0 ** -7}[pdt]      # (a step of the stored type, fp32: bar of the draft tests)
+    assert bool(((want[0].double() - q).abs() <= ulp * q + 1e-7).all())
+    assert torch.equal(want[2], want[0].float().gather(1, want[1].long()[:, None])[:, 0])
+    assert torch.equal(want[1][t == 0].long(), x[t == 0].float().argmax(1))
+
+
+@pytest.mark.parametrize("R,V", [(3, 50272), (128, 128256)])
+def test_draft_rows_replayed_from_a_hip_graph(R, V, pkg):  # noqa: F811
+    """A captured launch keeps its mark: every replay, on other inputs, must not find what the one before has left."""
+    import torch
+    sets = [_draft_inputs(R, V, torch.bfloat16, s, 0.8) for s in range(4)]
+    x, t, u = (v.clone() for v in sets[0])
+    want = [[v.clone() for v in pkg.draft_sample(*s)] for s in sets]
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        got = pkg.draft_sample(x, t, u)
+    for turn in range(2):
+        for s, w in zip(sets, want):
+            for dst, src in zip((x, t, u), s):
+                dst.copy_(src)
+            graph.replay()
+            if turn:                                # an eager call in between, with a mark of its own
+                pkg.draft_sample(*sets[0])
+            torch.cuda.synchronize()
+            assert all(torch.equal(a, b) for a, b in zip(got, w))
