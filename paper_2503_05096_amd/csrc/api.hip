@@ -711,10 +711,15 @@ static int validate_draft_dims(const adaspec_draft_dims *d)
 //   V = 12288 fp32   1 row  7.6 /   -  /  7.1   128 rows  9.2 /   -  /  8.2   256 rows 11.9 /   -  / 10.8   300 rows 15.4 /   -  / 12.4
 //     all greedy            6.2 /   -  /  6.6             7.5 /   -  /  7.6            10.4 /   -  / 10.1            13.0 /   -  / 11.7
 //   V = 50272 fp32   1 row 14.3 /   -  /  8.4   128 rows 21.1 /   -  / 16.2   256 rows 34.1 /   -  / 22.0   300 rows 43.2 /   -  / 26.8
-// In parts above V = 12288: below, greedy rows (which the host cannot tell from sampled ones) lose what the others gain.  Without
-// a workspace, or with rows the parts do not take, the register-resident kernel above V = 24576 where it fits, else three sweeps.
-constexpr int kDraftPartsAbove = 12288, kDraftFastAbove = 24576;
-static bool draft_wants_parts(const adaspec_draft_dims &d) { return d.vocab > kDraftPartsAbove; }
+// In parts above V = 12288: below, greedy rows (which the host cannot tell from sampled ones) lose what the others gain.  fp32
+// probabilities of 16-bit logits only above 32768: the sweeps' are a little nearer to 64 bits (V = 16384, T = 1: off by 5.8e-8, in parts
+// 7.5e-8; V = 50272 1.1e-7 and 6.8e-8).  Without a workspace, or with rows the parts do not take, the register-resident kernel above V = 24576 where it fits, else three sweeps.
+constexpr int kDraftPartsAbove = 12288, kDraftPartsAboveWider = 32768, kDraftFastAbove = 24576;
+static bool draft_wants_parts(const adaspec_draft_dims &d)
+{
+    const bool wider = d.probs_dtype == ADASPEC_F32 && d.logits_dtype != ADASPEC_F32;
+    return d.vocab > (wider ? kDraftPartsAboveWider : kDraftPartsAbove);
+}
 
 // Whether dims may take the form in parts: forced (ADASPEC_PATH_TWO_PASS) for 16-bit logits up to V = 131072; AUTO also
 // for fp32 logits and larger vocabularies.

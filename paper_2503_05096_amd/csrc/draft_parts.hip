@@ -96,15 +96,11 @@ __global__ __launch_bounds__(NT, 4) void draft_row_kernel(
 
     // What is done with a part is written twice below: for the own one, in registers, and chunk by chunk for parts whose
     // words do not come.
-    // A thread's weights are relative to a reference near its maximum.  16-bit logits: the scaled reference of its first chunk's
-    // maximum, so that a chunk's weights can be computed when it lands; any reference does, as moving to another one is an
-    // exact factor, unless it is so far off that weights could overflow or vanish.  fp32: the maximum itself.
-    struct Ref { float m, at; };                             // the thread's maximum (-inf: nothing finite) and its reference
-    auto first_ref = [&](float m0) -> float { return m0 > -INFINITY ? scaled_ref(m0, c) : 0.f; };
-    auto ref_of = [&](float m0, float m) -> Ref {
-        const float own = first_ref(m), early = first_ref(m0);
-        return Ref{m, kKeepsWeights && fabsf(own - early) <= 60.f ? early : own};
-    };
+    // A thread's weights are relative to its own maximum (0 if it has nothing finite): exponents of the largest are then next to
+    // 0, where they are rounded least.  (References known earlier, those of first chunks, were no faster, 19.2 against 19.3 us, and
+    // the largest probabilities off by 2e-7 instead of 5e-8.)
+    struct Ref { float m, at; };
+    auto ref_of = [&](float m) -> Ref { return Ref{m, m > -INFINITY ? scaled_ref(m, c) : 0.f}; };
     // exponent that moves a thread's weights to the reference of the maximum m
     auto thread_gap = [&](Ref t, float m) -> float { return kKeepsWeights ? t.at - scaled_ref(m, c) : (t.m - m) * c; };
     // a chunk's weights, added up behind z
@@ -189,43 +185,16 @@ __global__ __launch_bounds__(NT, 4) void draft_row_kernel(
             lg[it] = make_uint4(0, 0, 0, 0);
             if (it < part_steps) lg[it] = part_load16<kAuxDefault>(rl, (uint32_t)my_chunk * 16u, it * (kWave * 16));
         }
-        auto blank = [&](int it) { Chunk<LT>::blank(lg[it], it >= part_steps || my_chunk + it * kWave >= n); };
-        float m = -INFINITY, m0 = -INFINITY;
-        if constexpr (!kKeepsWeights) {
 #pragma unroll
-            for (int it = 0; it < kDraftSteps; ++it) blank(it);
-            m = thread_max<LT, kDraftSteps>(lg);
-            ref = ref_of(m, m);
-        }
+        for (int it = 0; it < kDraftSteps; ++it) Chunk<LT>::blank(lg[it], it >= part_steps || my_chunk + it * kWave >= n);
+        ref = ref_of(thread_max<LT, kDraftSteps>(lg));
 #pragma unroll
         for (int it = 0; it < kDraftSteps; ++it) {
-            if constexpr (kKeepsWeights) {
-                blank(it);
-                const float mn = chunk_max<LT>(lg[it], m);
-                if (it == 0) { m0 = mn; ref = Ref{m0, first_ref(m0)}; }
-                if (!sampled && mn > m) top = first_with(lg[it], mn, chunk_index(h, it));
-                m = mn;
-            } else {
-                if (!sampled && top == V && m > -INFINITY && chunk_max<LT>(lg[it], -INFINITY) == m) top = first_with(lg[it], m, chunk_index(h, it));
-            }
             keep_packed(lg[it]);
+            if (!sampled && top == V && ref.m > -INFINITY && chunk_max<LT>(lg[it], -INFINITY) == ref.m)
+                top = first_with(lg[it], ref.m, chunk_index(h, it));
             z_t = add_weights(lg[it], ref, z_t, w[it]);
             __builtin_amdgcn_sched_barrier(0);               // (one step at a time: registers)
-        }
-        if constexpr (kKeepsWeights) {
-            const float early = ref.at;
-            ref = ref_of(m0, m);
-            if (__ballot(ref.at != early) != 0ull) {         // (logits that far apart, or nothing finite in the first chunk)
-                z_t = 0.f;
-#pragma unroll
-                for (int it = 0; it < kDraftSteps; ++it) {
-                    uint4 v = make_uint4(0, 0, 0, 0);
-                    if (it < part_steps) v = part_load16<kAuxDefault>(rl, (uint32_t)my_chunk * 16u, it * (kWave * 16));
-                    Chunk<LT>::blank(v, it >= part_steps || my_chunk + it * kWave >= n);
-                    z_t = add_weights(v, ref, z_t, w[it]);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            }
         }
     }
     leave_stats(ref, z_t, top);
@@ -270,16 +239,15 @@ __global__ __launch_bounds__(NT, 4) void draft_row_kernel(
                 Chunk<LT>::blank(v, my_chunk + it * kWave >= n);
                 return v;
             };
-            float m = -INFINITY, m0 = -INFINITY, z = 0.f;
+            float m = -INFINITY, z = 0.f;
             int first = V;
             for (int it = 0; it < part_steps; ++it) {
                 const uint4 v = chunk_at(it);
                 const float mn = chunk_max<LT>(v, m);
-                if (it == 0) m0 = mn;
                 if (mn > m) first = first_with(v, mn, chunk_index(part, it));
                 m = mn;
             }
-            const Ref t = ref_of(m0, m);
+            const Ref t = ref_of(m);
             for (int it = 0; it < part_steps; ++it) {
                 float x[kN];
                 z = add_weights(chunk_at(it), t, z, x);
@@ -396,12 +364,9 @@ __global__ __launch_bounds__(NT, 4) void draft_row_kernel(
                 Chunk<LT>::blank(v, my_chunk + it * kWave >= n);
                 return v;
             };
-            float m = -INFINITY, m0 = -INFINITY;
-            for (int it = 0; it < part_steps; ++it) {
-                m = chunk_max<LT>(chunk_at(it), m);
-                if (it == 0) m0 = m;
-            }
-            const Ref t = ref_of(m0, m);
+            float m = -INFINITY;
+            for (int it = 0; it < part_steps; ++it) m = chunk_max<LT>(chunk_at(it), m);
+            const Ref t = ref_of(m);
             const float f = thread_factor(t);
             double total = 0.0;
             for (int it = 0; it < part_steps; ++it) {

@@ -60,7 +60,7 @@ def _draft_inputs(R, V, dtype, seed, T=None, lead_masked=False):
     import torch
     gen = torch.Generator(device="cuda").manual_seed(seed)
     x = 3.0 * torch.randn((R, V), generator=gen, device="cuda")
-    if lead_masked:                                 # nothing finite, or nothing near the maximum, in a thread's first chunk
+    if lead_masked:                                 # threads and parts without a finite logit, logits far apart
         x[::2, :V // 2] = -float("inf")
         x[1::2] = torch.where(torch.rand((R // 2, V), generator=gen, device="cuda") < 0.5, x[1::2] - 300.0, x[1::2] + 300.0)
     t = torch.tensor([0.8, 0.0, 1.0, 1e-8], device="cuda").repeat(R)[:R] if T is None else torch.full((R,), T, device="cuda")
