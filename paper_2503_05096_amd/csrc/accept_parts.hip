@@ -39,9 +39,8 @@
 // rows of it in fp32 39.7 us, 192 rows of V = 262144 bf16 32.3 us.  Masses are published per wavefront (16 bytes per 256 chunks) and
 // not per step and 16-lane row, so that a row of any length fits the final search of one workgroup with two pairs per
 // thread; the four steps of the winning pair are recomputed by one wavefront each.
-#include "adaspec_internal.h"
-#include "device_utils.h"
-#include "row_parts.h"
+#include "accept_head.h"
+#include "part_exchange.h"
 
 namespace adaspec {
 
@@ -62,23 +61,12 @@ static __device__ long long g_stamps[2][kStampGroups][8];
 #define ADASPEC_STAMP(which, k) do { } while (0)
 #endif
 
-// what part 0 of a draft row leaves for the accept test
-struct SlotRec { int x; uint32_t lx_bits, qx_bits, u0_bits; };
-
 // ---- memory that crosses workgroups inside one launch ---------------------------------------------
 // The partial sums of the second pass are written by one workgroup and read by another one of the same
 // launch, possibly on another XCD (each XCD has its own L2).  They travel as relaxed agent-scope atomic
 // stores and loads (write-through / read-through to the level all XCDs share); the writer waits until its
 // stores have been acknowledged before it takes its ticket, and the reader's loads depend on the ticket's
 // return value.  No cache-wide write-back or invalidate is needed, and nobody waits for anybody.
-__device__ __forceinline__ void publish_u64(void *p, unsigned long long v)
-{
-    __hip_atomic_store(reinterpret_cast<unsigned long long *>(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ unsigned long long fetch_u64(const void *p)
-{
-    return __hip_atomic_load(reinterpret_cast<const unsigned long long *>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
 __device__ __forceinline__ void publish_stat(HalfStat *p, float m, int arg, double Z)
 {
     publish_u64(p, (unsigned long long)__float_as_uint(m) | ((unsigned long long)(uint32_t)arg << 32));
@@ -178,8 +166,8 @@ __global__ __launch_bounds__(kQT, kStatWgsPerCu) void accept_rowparts_kernel(
     const int32_t *__restrict__ draft_tokens, const float *__restrict__ uniforms,
     const int32_t *__restrict__ spec_lens, const float *__restrict__ temperature, int B, int V, int total_q,
     int total_draft, int max_spec_len, int n_parts, int64_t lstride, int64_t pstride, int probs_dtype,
-    int32_t *__restrict__ cu_q, int32_t *__restrict__ req_ticket, SlotRec *__restrict__ slot_rec,
-    HalfStat *__restrict__ part_stat)
+    int32_t *__restrict__ cu_q, int32_t *__restrict__ req_ticket, unsigned long long *__restrict__ words, int n_words,
+    SlotRec *__restrict__ slot_rec, HalfStat *__restrict__ part_stat)
 {
     constexpr int kN = Chunk<LT>::kN, kSize = (int)sizeof(typename LT::storage);
     __shared__ int s_tot[kQW];
@@ -190,6 +178,8 @@ __global__ __launch_bounds__(kQT, kStatWgsPerCu) void accept_rowparts_kernel(
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int dr = blockIdx.x / n_parts, h = blockIdx.x % n_parts;      // draft row, part
     ADASPEC_STAMP(0, 0);
+    // the words in which the shared second pass's workgroups tell each other their sums, cleared by the whole grid
+    for (int w = blockIdx.x * kQT + tid; w < n_words; w += gridDim.x * kQT) words[w] = kNoWord;
 
     // ---- which request owns draft row dr: scan of n_i = k_i + 1, four requests per thread --------------
     int kk[4];
@@ -278,40 +268,6 @@ __global__ __launch_bounds__(kQT, kStatWgsPerCu) void accept_rowparts_kernel(
     ADASPEC_STAMP(0, 3);
 }
 
-// (m, Z) of a whole row from its parts' records, or for a greedy request (maximum, arg-max)
-struct RowMerge { float m; double Z; int arg; };
-__device__ __forceinline__ void load_row_parts(const HalfStat *__restrict__ st, int n_parts, HalfStat (&s)[kStatParts])
-{
-#pragma unroll
-    for (int p = 0; p < kStatParts; ++p) {
-        s[p].m = -INFINITY; s[p].arg = -1; s[p].Z = 0.0;
-        if (p < n_parts) s[p] = st[p];
-    }
-}
-template <class LT>
-__device__ __forceinline__ RowMerge merge_row_parts(const HalfStat (&s)[kStatParts], float c, bool greedy)
-{
-    RowMerge out;
-    out.Z = 0.0; out.arg = 0;
-    if (greedy) {
-        ArgMax b{-INFINITY, 0x7fffffff};
-#pragma unroll
-        for (int p = 0; p < kStatParts; ++p)
-            if (s[p].arg >= 0) b = argmax_merge(b, ArgMax{s[p].m, s[p].arg});
-        out.m = b.v;
-        out.arg = b.i == 0x7fffffff ? 0 : b.i;
-        return out;
-    }
-    float m = s[0].m;
-#pragma unroll
-    for (int p = 1; p < kStatParts; ++p) m = fmaxf(m, s[p].m);
-#pragma unroll
-    for (int p = 0; p < kStatParts; ++p)
-        out.Z += s[p].m > -INFINITY ? s[p].Z * (double)__builtin_amdgcn_exp2f(ref_gap<LT>(s[p].m, m, c)) : 0.0;
-    out.m = m;
-    return out;
-}
-
 // ---------------------------------------------------------------------------------------------------
 // Second pass: the deciding row of every request, in parts, and the draw.
 template <class LT, class PT>
@@ -335,66 +291,12 @@ __global__ __launch_bounds__(kQT, sizeof(typename PT::storage) > sizeof(typename
     const int i = blockIdx.x / n_parts, h = blockIdx.x % n_parts;
     ADASPEC_STAMP(1, 0);
 
-    // ---- the request's first rejected draft: wavefront 0 decides, one lane per draft --------------------
-    // The records of the request's first 64 slots are requested before anything else: they need neither
-    // the draft count nor the row offset (slots beyond the count hold leftovers, which are not looked at).
-    // Requested this early they are back before the first workgroups of the launch start streaming rows;
-    // later they would queue behind that traffic.
-    __shared__ int s_dec[3];
-    __shared__ double s_dec_z;
-    SlotRec rec;
-    HalfStat parts[kStatParts];
-    rec.x = 0; rec.lx_bits = rec.qx_bits = rec.u0_bits = 0;
-    if (wv == 0 && lane < max_spec_len) {
-        const int64_t slot = (int64_t)i * max_spec_len + lane;
-        rec = slot_rec[slot];
-        load_row_parts(part_stat + slot * kStatParts, n_stat_parts, parts);
-    }
-    const int start = cu_q[i];
-    const int k = min(max(spec_lens[i], 0), max_spec_len);          // uniform: scalar loads
-    const float T = temperature[i];
-    const bool sampled = T != 0.0f;
-    const float c = sampled ? exponent_scale<LT>(T) : 0.f;
-    if (wv == 0) {
-        int a0 = k;
-        RowMerge row0;                                               // statistics of the deciding row, if a draft
-        row0.m = 0.f; row0.Z = 1.0; row0.arg = 0;
-        for (int j0 = 0; j0 < k; j0 += kWave) {
-            const int jj = j0 + lane;
-            int flag = 1;
-            RowMerge mine;
-            mine.m = 0.f; mine.Z = 1.0; mine.arg = 0;
-            if (jj < k) {
-                if (j0 > 0) {                                        // more drafts than lanes: the next 64 slots
-                    const int64_t slot = (int64_t)i * max_spec_len + jj;
-                    rec = slot_rec[slot];
-                    load_row_parts(part_stat + slot * kStatParts, n_stat_parts, parts);
-                }
-                mine = merge_row_parts<LT>(parts, c, !sampled);
-                if (sampled) {
-                    const float lx = __uint_as_float(rec.lx_bits), qx = __uint_as_float(rec.qx_bits);
-                    const float px = exp_weight<LT>(lx, mine.m, c, scaled_ref(mine.m, c)) * (float)(1.0 / mine.Z);
-                    flag = (qx > 0.f) ? (__uint_as_float(rec.u0_bits) < px / qx) : 1;
-                } else {
-                    flag = rec.x == mine.arg;
-                }
-            }
-            const unsigned long long rej = __ballot(flag == 0);
-            if (rej) {
-                const int src = (int)__builtin_ctzll(rej);
-                a0 = j0 + src;
-                row0.m = __shfl(mine.m, src, kWave);
-                row0.Z = __shfl(mine.Z, src, kWave);
-                row0.arg = __shfl(mine.arg, src, kWave);
-                break;
-            }
-        }
-        if (lane == 0) { s_dec[0] = a0; s_dec[1] = __float_as_int(row0.m); s_dec[2] = row0.arg; s_dec_z = row0.Z; }
-    }
-    lds_barrier();
-    RowMerge row;
-    row.m = __int_as_float(s_dec[1]); row.arg = s_dec[2]; row.Z = s_dec_z;
-    const int a = __builtin_amdgcn_readfirstlane(s_dec[0]);
+    __shared__ DecidingScratch s_dec;
+    const DecidingRow d = deciding_row<LT>(s_dec, i, cu_q, spec_lens, temperature, slot_rec, part_stat, max_spec_len, n_stat_parts, lane, wv);
+    const int start = d.start, k = d.k, a = d.a;
+    const bool sampled = d.sampled;
+    const float c = d.c;
+    const RowMerge row = d.row;
     const int r = start + a;
     const bool bonus = a >= k;
     int32_t *o = out_tokens + (int64_t)i * out_stride;
@@ -600,15 +502,17 @@ hipError_t launch_accept_parts(const AcceptArgs &a, int compute_units)
     const int n_sum_parts = sum_parts(d);
     int32_t *cu_q = (int32_t *)(a.ws + a.plan.off_cu_q);
     int32_t *ticket = (int32_t *)(a.ws + a.plan.off_req_ticket);
+    const SharedParts shared = accept_shared_parts(d, compute_units);
     SlotRec *slot_rec = (SlotRec *)(a.ws + a.plan.off_slot_rec);
     HalfStat *part_stat = (HalfStat *)(a.ws + a.plan.off_part_stat);
     auto first = [&](auto lt) {
-        // (the first pass always runs, at least with one workgroup: it also clears the tickets)
+        // (the first pass always runs, at least with one workgroup: it also clears the tickets and words)
         const int grid = d.total_draft > 0 ? d.total_draft * n_stat_parts : 1;
         hipLaunchKernelGGL((accept_rowparts_kernel<decltype(lt)>), dim3(grid), dim3(kQT), 0, a.stream,
                            (const char *)a.logits, (const char *)a.probs, a.draft_tokens, a.uniforms, a.spec_lens,
                            a.temperature, d.batch, d.vocab, d.total_q, d.total_draft, d.max_spec_len, n_stat_parts,
-                           d.logits_row_stride, d.probs_row_stride, d.probs_dtype, cu_q, ticket, slot_rec, part_stat);
+                           d.logits_row_stride, d.probs_row_stride, d.probs_dtype, cu_q, ticket,
+                           (unsigned long long *)(a.ws + a.plan.off_part), d.batch * shared.n_words, slot_rec, part_stat);
     };
     auto second = [&](auto lt, auto pt) {
         hipLaunchKernelGGL((accept_decide_kernel<decltype(lt), decltype(pt)>), dim3(d.batch * n_sum_parts), dim3(kQT), 0, a.stream,
@@ -620,6 +524,10 @@ hipError_t launch_accept_parts(const AcceptArgs &a, int compute_units)
     };
     auto with_logits = [&](auto lt) {
         first(lt);
+        if (shared.n_parts > 0) {
+            launch_accept_shared(a, shared, n_stat_parts);
+            return;
+        }
         if (d.probs_dtype == ADASPEC_F32) second(lt, F32{});
         else if (d.probs_dtype == ADASPEC_F16) second(lt, F16{});
         else second(lt, BF16{});
