@@ -29,12 +29,13 @@
  *     inputs give bit-identical outputs (no floating-point atomics).
  *   - Host threads: the library keeps no state between calls apart from
  *     one-time device queries and a process-wide count of launches (attention
- *     calls that merge their splits mark flag words in the workspace with a
- *     number that no other launch is given; no result depends on it).  Calls
+ *     calls that merge their splits, and the split form of draft sampling, mark
+ *     words in the workspace with a number that no other launch is given; no
+ *     result depends on it).  Calls
  *     from several threads are safe as long as they do not share a workspace.
  *     The calls enqueue kernels only (no allocation, no memset, no
  *     synchronisation), so they can be captured into a HIP graph.  A captured
- *     launch keeps its number, and every replay leaves its flag words at zero:
+ *     launch keeps its number, and takes its words back before a replay could read them:
  *     replays may follow each other, and calls between them may use the same
  *     workspace, as long as all of them are ordered.
  *     The first call of a kernel path on a device does its one-time set-up
@@ -456,7 +457,7 @@ int adaspec_kv_compact_path(void *k_pages, void *v_pages, const int32_t *block_t
  * ADASPEC_ERR_ALIGN otherwise).
  * Workspace: only the split form uses one (adaspec_draft_sample_workspace_bytes;
  * 256-byte aligned device memory, contents need not be initialised).  With
- * workspace == NULL the call runs a single-kernel form.
+ * workspace == NULL the call runs one of the other forms.
  * ---------------------------------------------------------------------- */
 typedef struct {
     int32_t rows;               /* R >= 0                                      */
@@ -469,12 +470,10 @@ typedef struct {
                                    (16-bit logits, V <= 131072), VECTOR = the
                                    three-sweep kernel, TWO_PASS = the split form
                                    (same shapes as FAST, needs the workspace):
-                                   every row cut into parts over three small
-                                   kernels; AUTO = the split form, of any storage
-                                   types, when a workspace is given and V > 32768
-                                   (fp32 logits: 49152; not for 16-bit rows of at
-                                   most 65536 when they fill more than half of the
-                                   chip one per compute unit); else FAST when it fits and
+                                   long rows shared by workgroups; AUTO = the split
+                                   form, of any storage types, when a workspace is
+                                   given and V > 12288 (fp32 probabilities of 16-bit
+                                   logits: 32768); else FAST when it fits and
                                    V > 24576, else VECTOR */
     int32_t reserved;
     void   *timing_start;       /* optional pair of hipEvent_t (both or neither, NULL = none), recorded */

@@ -44,7 +44,7 @@ __device__ __forceinline__ RowMerge merge_row_parts(const HalfStat (&s)[kStatPar
     return out;
 }
 
-// Second pass for fp32 logits (accept_shared.hip): parts of the deciding rows, chunks per thread in each, words per request that the
+// Second pass for fp32 logits and short rows (accept_shared.hip): parts of the deciding rows, chunks per thread in each, words per request that the
 // first pass clears where the plan has off_part.
 struct SharedParts { int n_parts, part_steps, n_words; };
 SharedParts accept_shared_parts(const adaspec_accept_dims &d, int compute_units);

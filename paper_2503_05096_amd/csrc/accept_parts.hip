@@ -19,8 +19,9 @@
 //       accept test needs besides: the draft token, its logit, its draft probability and the uniform.
 //       Records are stored per SLOT (request, draft position), so the second pass reads them without
 //       knowing where the request's rows start.  Workgroup 0 also writes cu_q and clears the tickets of
-//       the second pass.
-//   accept_decide_kernel     workgroup = (request, part of <= 1024 chunks).  Merges the part
+//       the second pass; the whole grid clears the words of the other one.
+//   accept_decide_kernel     (16-bit rows above V = 12288, large batches; the others: accept_shared.hip)  workgroup = (request, part of
+//       <= 1024 chunks).  Merges the part
 //       statistics of the request's draft rows, applies the accept test to each (one lane per draft), finds
 //       the first rejection -> the deciding row; part 0 writes the accepted drafts, the padding and the
 //       length.  A greedy rejection is decided by the merged arg-max.  Otherwise the workgroup loads its
@@ -35,8 +36,7 @@
 // What the time goes to (MI355X, 510 rows of V = 128256, time stamps): a dependent memory access costs
 // 1.2-1.7 us and the chain has six of them (first pass: lengths -> row; second pass: slot records -> row,
 // then stores acknowledged -> ticket -> partial sums -> the chunks of the draw), the two launches add
-// 1.7 us each, and the rows themselves stream at 5.0-5.5 TB/s.  Whole calls: 510 rows of V = 128256 bf16 38.9 us, 256
-// rows of it in fp32 39.7 us, 192 rows of V = 262144 bf16 32.3 us.  Masses are published per wavefront (16 bytes per 256 chunks) and
+// 1.7 us each, and the rows themselves stream at 5.0-5.5 TB/s.  Whole calls: 510 rows of V = 128256 bf16 38.9 us, 192 rows of V = 262144 bf16 32.3 us.  Masses are published per wavefront (16 bytes per 256 chunks) and
 // not per step and 16-lane row, so that a row of any length fits the final search of one workgroup with two pairs per
 // thread; the four steps of the winning pair are recomputed by one wavefront each.
 #include "accept_head.h"

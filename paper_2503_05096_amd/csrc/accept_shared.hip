@@ -1,5 +1,5 @@
-// Two-pass acceptance in row parts, the second pass for fp32 logits: a few workgroups per request, which share its deciding row,
-// each with its part in registers (the first pass and the second one of 16-bit logits: accept_parts.hip).
+// Two-pass acceptance in row parts, the second pass for fp32 logits and short rows: one or a few workgroups per request, which share its
+// deciding row, each with its part in registers (the first pass, and the second one of longer 16-bit rows: accept_parts.hip).
 //
 // Workgroup (request, part) of 512 threads: the request's deciding row from the first pass's records (accept_head.h), its part of
 // that row and of its draft probabilities into registers, the part's mass to the others and theirs from them
@@ -10,19 +10,19 @@
 // Bound: HBM (64 rejected rows of V = 128256: 66 MB) behind a chain of dependent accesses: records, row, the others' words.
 // accept_decide_kernel takes 16 KB parts, for fp32 rows twice as many as for 16-bit ones (2048 workgroups of 64 requests take 4.8 us to
 // start), sums residual and probability, draws a ticket and reads the winner's chunks again.  MI355X, second pass of 64 requests of
-// V = 128256, accept_decide_kernel / this one: 22.6 / 16.1 us, all bonus rows 21.9 / 14.4, all greedy 6.5 / 8.0 (most workgroups have nothing to
-// do then, and a large one takes longer to start); whole calls 40.5 / 34.4, 25.1 / 17.2, 25.2 / 26.9; 32 of 152064 35.9 / 28.8, 50 of 262144
-// 48.2 / 32.2, 8 of 128256 15.4 / 14.0.  16-bit rows have twice the arithmetic per byte, which here follows the loads where
-// many small workgroups overlap it: 128 requests of V = 128256 39.6 / 41.0, 150 of 32000 21.2 / 25.1, 64 of 262144 33.8 / 33.4, so they stay there.
+// V = 128256 in fp32, accept_decide_kernel / this one: 22.6 / 16.1 us, all bonus rows 21.9 / 14.4; whole calls 40.1 / 33.1, 25.0 / 16.4, all
+// greedy 25.1 / 25.5; 32 of 152064 35.8 / 28.2, 50 of 262144 48.0 / 30.5, 8 of 128256 15.3 / 13.5.  16 bits, V = 4000, captured: 1 request 11.6 / 10.7,
+// 64 13.8 / 11.9, 300 15.6 / 13.7; V = 12000 64 13.7 / 13.1, 300 17.6 / 16.7.
 #include "accept_head.h"
 #include "part_exchange.h"
 
 namespace adaspec {
 
 constexpr int kDecideT = 512;
-constexpr int kDecideSteps = 8;                           // chunks per thread at most
+// chunks per thread at most (probabilities wider than the logits take twice the registers)
+constexpr int decide_steps(int logits_size, int probs_size) { return probs_size > logits_size ? 4 : 8; }
 constexpr int kDecideMaxParts = 32;                       // two lanes each in the exchange
-static_assert(kPartsMaxVocab <= kDecideMaxParts * kDecideT * kDecideSteps * 4, "all rows fit");
+static_assert(kPartsMaxVocab <= kDecideMaxParts * kDecideT * 8 * 4, "fp32 rows fit");
 struct PartWords { unsigned long long mass, top; };
 static_assert(sizeof(PartWords) * kDecideMaxParts <= 4 * sizeof(PartWords) * kSumParts, "the words fit where the plan lays them out");
 
@@ -45,7 +45,7 @@ __device__ __forceinline__ float chunk_masses(const uint4 &lv, const ProbChunk<C
     return acc;
 }
 
-template <class PT>
+template <class LT, class PT>
 __global__ __launch_bounds__(kDecideT, 4) void accept_decide_shared_kernel(
     const char *__restrict__ logits, const char *__restrict__ probs,
     const int32_t *__restrict__ draft_tokens, const float *__restrict__ uniforms,
@@ -57,9 +57,8 @@ __global__ __launch_bounds__(kDecideT, 4) void accept_decide_shared_kernel(
 {
     // (a part gives the same bits whether its own workgroup computes it or another one)
 #pragma clang fp contract(off)
-    using LT = F32;
     constexpr int kN = Chunk<LT>::kN, kLSize = (int)sizeof(typename LT::storage), kPSize = (int)sizeof(typename PT::storage);
-    constexpr int kSteps = kDecideSteps, NW = kDecideT / kWave;
+    constexpr int kSteps = decide_steps(kLSize, kPSize), NW = kDecideT / kWave;
     __shared__ float s_m[NW];
     __shared__ int s_i[NW];
     __shared__ double s_mass[NW], s_own[NW];      // masses of a part's wavefronts; of the own part's
@@ -353,19 +352,24 @@ __global__ __launch_bounds__(kDecideT, 4) void accept_decide_shared_kernel(
 }
 
 // Parts of the deciding rows (0: the call is not for this kernel).  As many as make the fullest compute unit's work the least: turns
-// times (chunks per thread, and two for what a turn costs besides).  64 requests of V = 128256: 8 parts; 150 of V = 32000: three 25.6 us, two
-// 26.5.  From five workgroups per compute unit on the many small ones of accept_decide_kernel fill the chip better (300 requests of
-// V = 50272 35.4 us, here 39.9; 100 of 128256, four, 35.7 / 31.6).
+// times (chunks per thread, and two for what a turn costs besides), and one for an exchange.  fp32, 64 requests of V = 128256: 8
+// parts; 150 of V = 32000: three 25.1 us, two 26.5.  From five workgroups per compute unit on the many small ones of accept_decide_kernel fill the chip better (300 requests
+// of V = 50272 35.4 us, here 39.9; 100 of 128256, four, 35.6 / 29.5).  16-bit rows have twice the arithmetic per byte, which here follows
+// the loads where many small workgroups overlap it, so only short ones come (accept_decide_kernel / here: V = 16000, 300 requests
+// 18.4 / 19.0 us; 128256, 128 39.9 / 40.8; 32000, 150 21.3 / 24.8; 262144, 64 33.2 / 33.2; V = 8000, 1000 29.5 / 34.8).
+constexpr int kSharedShortRow = 12288;
 SharedParts accept_shared_parts(const adaspec_accept_dims &d, int compute_units)
 {
     SharedParts p{0, 0, 0};
-    if (d.logits_dtype != ADASPEC_F32) return p;
-    const int steps = ceil_div(d.vocab / parts_chunk_elems(d.logits_dtype), kDecideT), least = ceil_div(steps, kDecideSteps);
+    const bool f32 = d.logits_dtype == ADASPEC_F32;
+    if (!f32 && (d.vocab > kSharedShortRow || d.batch > 2 * compute_units)) return p;
+    const int most = decide_steps(f32 ? 4 : 2, d.probs_dtype == ADASPEC_F32 ? 4 : 2);
+    const int steps = ceil_div(d.vocab / parts_chunk_elems(d.logits_dtype), kDecideT), least = ceil_div(steps, most);
     if ((int64_t)d.batch * least > 4 * (int64_t)compute_units) return p;
     int64_t best = INT64_MAX;
     for (int n = least; n <= kDecideMaxParts && n <= steps; ++n) {
         const int each = ceil_div(steps, n);
-        const int64_t cost = ((int64_t)d.batch * n + compute_units - 1) / compute_units * (each + 2);
+        const int64_t cost = ((int64_t)d.batch * n + compute_units - 1) / compute_units * (each + 2) + (n > 1 ? 1 : 0);
         if (ceil_div(steps, each) == n && cost < best) {
             best = cost;
             p.n_parts = n;
@@ -379,17 +383,22 @@ SharedParts accept_shared_parts(const adaspec_accept_dims &d, int compute_units)
 void launch_accept_shared(const AcceptArgs &a, const SharedParts &p, int n_stat_parts)
 {
     const adaspec_accept_dims &d = a.dims;
-    auto launch = [&](auto pt) {
-        hipLaunchKernelGGL((accept_decide_shared_kernel<decltype(pt)>), dim3(d.batch * p.n_parts), dim3(kDecideT), 0, a.stream,
+    auto launch = [&](auto lt, auto pt) {
+        hipLaunchKernelGGL((accept_decide_shared_kernel<decltype(lt), decltype(pt)>), dim3(d.batch * p.n_parts), dim3(kDecideT), 0, a.stream,
                            (const char *)a.logits, (const char *)a.probs, a.draft_tokens, a.uniforms, a.spec_lens, a.temperature,
                            d.vocab, d.total_q, d.total_draft, d.max_spec_len, n_stat_parts, p.n_parts, p.part_steps,
                            d.logits_row_stride, d.probs_row_stride, (const int32_t *)(a.ws + a.plan.off_cu_q),
                            (const SlotRec *)(a.ws + a.plan.off_slot_rec), (const HalfStat *)(a.ws + a.plan.off_part_stat),
                            d.out_stride, a.out_tokens, a.out_accept_len, (PartWords *)(a.ws + a.plan.off_part));
     };
-    if (d.probs_dtype == ADASPEC_F32) launch(F32{});
-    else if (d.probs_dtype == ADASPEC_F16) launch(F16{});
-    else launch(BF16{});
+    auto with_p = [&](auto lt) {
+        if (d.probs_dtype == ADASPEC_F32) launch(lt, F32{});
+        else if (d.probs_dtype == ADASPEC_F16) launch(lt, F16{});
+        else launch(lt, BF16{});
+    };
+    if (d.logits_dtype == ADASPEC_F32) with_p(F32{});
+    else if (d.logits_dtype == ADASPEC_F16) with_p(F16{});
+    else with_p(BF16{});
 }
 
 }  // namespace adaspec

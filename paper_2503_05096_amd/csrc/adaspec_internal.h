@@ -207,7 +207,8 @@ struct AcceptPlan {
                             // probability, the accept uniform (form in parts)
     size_t off_part_stat;   // HalfStat[B * max_spec_len][8]: (maximum, normaliser | arg-max) of each part of a draft row
     size_t off_half_stat;   // HalfStat[B][parts]: per part of the deciding row
-    size_t off_part;        // WaveMass[B][parts][4]: masses of the deciding rows, per wavefront of a part
+    size_t off_part;        // WaveMass[B][parts][4]: masses of the deciding rows, per wavefront of a part; or, where a few workgroups share
+                            // the row (accept_shared.hip), PartWords[B][their parts]
     bool parts;             // the workspace holds what the form in parts needs
     size_t off_tree_stat;   // tree acceptance, last: per-node statistics (tree_node_stat_bytes() each)
     size_t total_bytes;
@@ -280,7 +281,7 @@ hipError_t launch_draft_sample(const void *logits, const float *temperature, con
                                const int32_t *out_rows, void *probs, int32_t *tokens, float *confidence,
                                const adaspec_draft_dims &d, hipStream_t stream);
 bool draft_fast_supported(const adaspec_draft_dims &d);
-// every row cut into parts, three kernels (draft_parts.hip)
+// rows shared by workgroups, one kernel (draft_parts.hip)
 bool draft_parts_supported(const adaspec_draft_dims &d);
 size_t draft_parts_workspace_bytes(const adaspec_draft_dims &d);
 hipError_t launch_draft_parts(const void *logits, const float *temperature, const float *uniforms,

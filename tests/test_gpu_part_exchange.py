@@ -10,7 +10,7 @@ from workloads.device import to_device
 from paper_2503_05096_amd import binding, build
 from tests.test_gpu_parity import check_accept
 from tests.test_gpu_tree import _check_tree_accept, pkg  # noqa: F401  (fixture)
-from workloads.verify_step import _store
+from workloads.verify_step import _store, to_f64
 
 pytestmark = pytest.mark.gpu
 IMPATIENT = os.path.join(os.path.dirname(os.path.abspath(__file__)), "native", "libadaspec_impatient.so")
@@ -113,28 +113,29 @@ def test_draft_rows_replayed_from_a_hip_graph(R, V, pkg):  # noqa: F811
             assert all(torch.equal(a, b) for a, b in zip(got, w))
 
 
-def _accept_step(B, V, pdt, seed, equal=False, **kw):
+def _accept_step(B, V, ldt, pdt, seed, equal=False, **kw):
     rng = np.random.default_rng(seed)
     spec = rng.integers(0, 6, B).astype(np.int32)
     T = rng.choice(np.array([0.0, 0.7, 1.0, 1.0], np.float32), B)
-    st = W.make_custom_step(seed, ctx_lens=spec + 1, spec_lens=spec, vocab=V, logits_dtype="f32", temperature=T, attention=False,
+    st = W.make_custom_step(seed, ctx_lens=spec + 1, spec_lens=spec, vocab=V, logits_dtype=ldt, temperature=T, attention=False,
                             logits_sigma=3.0, noise_sigma=1.5, draft_temp=1.2, name=f"accept-exchange-{B}-{V}", **kw)
     if equal:                                       # p == q and tokens that are rejected all the same: no residual mass, drawn from p
         st.target_logits = np.zeros_like(st.target_logits)
-        st.draft_probs = np.full_like(st.draft_probs, np.float32(1.0 / V) * np.float32(1.5))
-    if pdt != "f32":
-        st.draft_probs = _store(st.draft_probs.astype(np.float32), pdt)
+        st.draft_probs = _store(np.full(st.draft_probs.shape, 1.5 / V, np.float32), ldt)
+    if pdt != ldt:
+        st.draft_probs = _store(to_f64(st.draft_probs, ldt).astype(np.float32), pdt)
         st.probs_dtype = pdt
     return st
 
 
 # one part, parts of every length, a last part that is nearly empty, the most parts, more parts than fit the chip at once
-@pytest.mark.parametrize("B,V,pdt", [(5, 2000, "f32"), (64, 128256, "f32"), (150, 32008, "bf16"), (3, 524288, "f16"), (40, 98312, "f32"),
-                                     (1, 128256, "bf16"), (200, 50272, "f32")])
+@pytest.mark.parametrize("B,V,ldt,pdt", [(5, 2000, "f32", "f32"), (64, 128256, "f32", "f32"), (150, 32008, "f32", "bf16"), (3, 524288, "f32", "f16"),
+                                         (40, 98312, "f32", "f32"), (1, 128256, "f32", "bf16"), (200, 50272, "f32", "f32"),
+                                         (6, 12288, "bf16", "bf16"), (70, 8200, "f16", "f32"), (300, 4104, "bf16", "f16")])
 @pytest.mark.parametrize("kind", ["", "masked", "equal"])
-def test_accept_of_fp32_rows_without_waiting(B, V, pdt, kind, oracle_mod, pkg, impatient):  # noqa: F811
+def test_accept_without_waiting(B, V, ldt, pdt, kind, oracle_mod, pkg, impatient):  # noqa: F811
     import torch
-    st = _accept_step(B, V, pdt, 500 + B, equal=kind == "equal", **({"masked_frac": 0.99} if kind == "masked" else {}))
+    st = _accept_step(B, V, ldt, pdt, 500 + B, equal=kind == "equal", **({"masked_frac": 0.99} if kind == "masked" else {}))
     if kind != "equal" or V == 32008:
         check_accept(st, oracle_mod, pkg)
     dev = to_device(st, attention=False)
