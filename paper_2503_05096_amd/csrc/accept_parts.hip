@@ -254,7 +254,7 @@ __global__ __launch_bounds__(kQT, kStatWgsPerCu) void accept_rowparts_kernel(
     };
     ADASPEC_STAMP(0, 2);
     if (T == 0.0f) {
-        const PartStream st = stream_part<LT, false, true, kAuxStream>(rl, row_chunks, n_parts, h, V, 0.f, tid, leave_slot);
+        const PartStream st = stream_part<LT, true, kAuxStream>(rl, row_chunks, n_parts, h, V, 0.f, tid, leave_slot);
         const ArgMax b = reduce_argmax(st.best, s_m, s_i, lane, wv);
         if (tid == 0) {
             HalfStat out; out.m = b.v; out.arg = b.i < V ? b.i : -1; out.Z = 0.0; *my_stat = out;
@@ -262,7 +262,7 @@ __global__ __launch_bounds__(kQT, kStatWgsPerCu) void accept_rowparts_kernel(
         return;
     }
     const float c = exponent_scale<LT>(T);
-    const PartStream st = stream_part<LT, true, false, kAuxStream>(rl, row_chunks, n_parts, h, V, c, tid, leave_slot);
+    const PartStream st = stream_part<LT, false, kAuxStream>(rl, row_chunks, n_parts, h, V, c, tid, leave_slot);
     const HalfStat out = reduce_norm<LT>(st, c, s_m, s_z, lane, wv);
     if (tid == 0) *my_stat = out;
     ADASPEC_STAMP(0, 3);

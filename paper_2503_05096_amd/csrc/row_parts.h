@@ -1,6 +1,7 @@
 // Vocabulary rows cut into PARTS that small workgroups (256 threads) sweep: the pieces shared by the acceptance
-// (accept_parts.hip) and draft sampling (draft_parts.hip).  A row is a sequence of CHUNKS of 16 bytes of logits (8
-// elements of 16 bits, 4 of fp32) with as many probabilities beside them; a STEP is one chunk per thread.
+// (accept_parts.hip, accept_shared.hip), draft sampling (draft_parts.hip) and trees (tree_fast.hip).  A row is a sequence
+// of CHUNKS of 16 bytes of logits (8 elements of 16 bits, 4 of fp32) with as many probabilities beside them; a STEP is
+// one chunk per thread.
 #pragma once
 #include "adaspec_internal.h"
 #include "device_utils.h"
@@ -173,7 +174,7 @@ __device__ __forceinline__ float thread_max(const uint4 (&lg)[STEPS])
 // kStatSteps steps are in flight, each consumed as it lands: a compute unit needs about as long for the exponentials of
 // a row as the memory system needs to deliver it, and only a stream whose arithmetic runs under its own loads gets both
 // done in the time of one.  `issued` runs once the first loads are under way.
-//   kNorm    maximum and normaliser on line, against the thread's running maximum m_run.  Both 16-bit formats are
+//   !kArgMax maximum and normaliser on line, against the thread's running maximum m_run.  Both 16-bit formats are
 //            sign-magnitude: among non-negative values the order of the bit patterns as SIGNED 16-bit integers is the
 //            order of the values and every negative value is a negative integer, so a running packed signed maximum (one
 //            instruction per two elements) is the exact maximum as soon as the thread has seen one value >= +0; until
@@ -181,7 +182,7 @@ __device__ __forceinline__ float thread_max(const uint4 (&lg)[STEPS])
 //            elements per byte) take the float maximum throughout.
 //   kArgMax  arg-max, lowest index on ties (a thread meets its elements in index order)
 struct PartStream { float m_run, zt; ArgMax best; };
-template <class LT, bool kNorm, bool kArgMax, int AUX, class F>
+template <class LT, bool kArgMax, int AUX, class F>
 __device__ __forceinline__ PartStream stream_part(__amdgpu_buffer_rsrc_t rl, int row_chunks, int n_parts, int h, int V, float c,
                                                   int tid, F issued)
 {
@@ -212,10 +213,8 @@ __device__ __forceinline__ PartStream stream_part(__amdgpu_buffer_rsrc_t rl, int
                     for (int e = kN - 1; e >= 0; --e) at = x[e] == mn ? e : at;
                     out.best = ArgMax{mn, chunk * kN + at};
                 }
-            }
-            if constexpr (kNorm) {
-                if constexpr (kArgMax) {
-                } else if constexpr (kN == 4) {
+            } else {
+                if constexpr (kN == 4) {
                     mn = chunk_max<LT>(v, out.m_run);
                 } else {
                     const uint32_t w[4] = {v.x, v.y, v.z, v.w};
