@@ -558,8 +558,8 @@ def main() -> int:
         "mean_accepted_nodes": float(run.alen.float().mean().item()),
         "accept_kernels_ms": acc_tree_ms, "accept_algorithmic_bytes": walk["accept"],
         "accept_frac": gbs(walk["accept"], acc_tree_ms) / HBM_PEAK_GBS,
-        "note": "not part of `value`; tree attention (ancestor masks) + tree acceptance (node statistics, then one "
-                "workgroup per request walks its tree); bytes of the walk form (rows the walk skips not counted); "
+        "note": "not part of `value`; tree attention (ancestor masks) + tree acceptance (node statistics, then the "
+                "walk over each request's tree); bytes of the walk form (rows the walk skips not counted); "
                 "`bench.py --tree 3` gives the full record for this workload"}
     if not args.no_cpu_baseline:
         rec["cpu_baseline"] = cpu_baseline(st)
