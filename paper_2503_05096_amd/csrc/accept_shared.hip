@@ -207,7 +207,7 @@ __global__ __launch_bounds__(kDecideT, 4) void accept_decide_shared_kernel(
     Scale own = draft_scale;
     float own_m = row_m;
     if (bonus && sampled) {
-        leave_max(thread_max<LT, kSteps>(lg));
+        leave_max(thread_max_of_numbers<LT, kSteps>(lg));
         lds_barrier();
         own_m = take_max();
         own = bonus_scale(own_m);

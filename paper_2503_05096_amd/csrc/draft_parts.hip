@@ -99,6 +99,8 @@ __global__ __launch_bounds__(NT, 4) void draft_row_kernel(
     // A thread's weights are relative to its own maximum (0 if it has nothing finite): exponents of the largest are then next to
     // 0, where they are rounded least.  (References known earlier, those of first chunks, were no faster, 19.2 against 19.3 us, and
     // the largest probabilities off by 2e-7 instead of 5e-8.)
+    // A NaN makes its whole row NaN: sums are taken over everybody, also over threads, wavefronts and parts without a finite
+    // logit (theirs are 0 unless they hold one).
     struct Ref { float m, at; };
     auto ref_of = [&](float m) -> Ref { return Ref{m, m > -INFINITY ? scaled_ref(m, c) : 0.f}; };
     // exponent that moves a thread's weights to the reference of the maximum m
@@ -146,7 +148,7 @@ __global__ __launch_bounds__(NT, 4) void draft_row_kernel(
     // over the workgroup: a part's statistics from its threads' (first half of the way: to LDS)
     auto leave_stats = [&](Ref t, float z_t, int top) {
         const float mw = wave_max(t.m);
-        const double zw = wave_sum(t.m > -INFINITY ? (double)(z_t * __builtin_amdgcn_exp2f(thread_gap(t, mw))) : 0.0);
+        const double zw = wave_sum((double)(z_t * __builtin_amdgcn_exp2f(t.m > -INFINITY ? thread_gap(t, mw) : 0.f)));
         if (lane == 0) { s_m[wv] = mw; s_z[wv] = zw; }
         if (!sampled) {
             const ArgMax b = wave_argmax(ArgMax{t.m, top});
@@ -156,13 +158,13 @@ __global__ __launch_bounds__(NT, 4) void draft_row_kernel(
     auto take_stats = [&](int part, float &m, double &Z, int &arg) {     // (wavefront 0)
         const float mw = lane < NW ? s_m[lane] : -INFINITY;
         m = wave_max(mw);
-        Z = wave_sum(mw > -INFINITY ? s_z[lane & (NW - 1)] * (double)__builtin_amdgcn_exp2f(ref_gap<LT>(mw, m, c)) : 0.0);
+        Z = wave_sum(lane < NW ? s_z[lane & (NW - 1)] * (double)__builtin_amdgcn_exp2f(mw > -INFINITY ? ref_gap<LT>(mw, m, c) : 0.f) : 0.0);
         arg = sampled ? V : wave_argmax(ArgMax{mw, lane < NW ? s_i[lane] : V}).i;
         if (lane == 0) { s_part_m[part] = m; s_part_i[part] = arg; s_part_z[part] = Z; }
     };
     auto row_stats = [&]() {                                             // (wavefront 0, all parts known)
         const float mp = lane < n_parts ? s_part_m[lane] : -INFINITY, M = wave_max(mp);
-        const double sum = wave_sum(mp > -INFINITY ? s_part_z[lane & 31] * (double)__builtin_amdgcn_exp2f(ref_gap<LT>(mp, M, c)) : 0.0);
+        const double sum = wave_sum(lane < n_parts ? s_part_z[lane & 31] * (double)__builtin_amdgcn_exp2f(mp > -INFINITY ? ref_gap<LT>(mp, M, c) : 0.f) : 0.0);
         const int at = s_part_i[lane & 31];
         const ArgMax b = wave_argmax(lane < n_parts && at < V ? ArgMax{mp, at} : ArgMax{-INFINITY, 0x7fffffff});
         // (a row without any finite logit: q = NaN, as in the other kernels)
@@ -187,7 +189,7 @@ __global__ __launch_bounds__(NT, 4) void draft_row_kernel(
         }
 #pragma unroll
         for (int it = 0; it < kDraftSteps; ++it) Chunk<LT>::blank(lg[it], it >= part_steps || my_chunk + it * kWave >= n);
-        ref = ref_of(thread_max<LT, kDraftSteps>(lg));
+        ref = ref_of(thread_max_of_numbers<LT, kDraftSteps>(lg));
 #pragma unroll
         for (int it = 0; it < kDraftSteps; ++it) {
             keep_packed(lg[it]);

@@ -168,6 +168,20 @@ __device__ __forceinline__ float thread_max(const uint4 (&lg)[STEPS])
     }
 }
 
+// The same, with NaNs passed over as chunk_max does it (the packed maximum of a thread that holds one is that NaN): for
+// parts that another workgroup may have to compute chunk by chunk, from the same maxima.
+template <class LT, int STEPS>
+__device__ __forceinline__ float thread_max_of_numbers(const uint4 (&lg)[STEPS])
+{
+    float m = thread_max<LT, STEPS>(lg);
+    if (sizeof(typename LT::storage) == 2 && m != m) {
+        m = -INFINITY;
+#pragma unroll
+        for (int it = 0; it < STEPS; ++it) m = chunk_max<LT>(lg[it], m);
+    }
+    return m;
+}
+
 // ---- one part of a row, streamed once ------------------------------------------------------------------------------
 // Part h takes the steps h, h + n_parts, h + 2 n_parts, ... of the row, so that the workgroups of a row sweep it together
 // (neighbouring addresses are in flight at the same time), and reads them past the caches when the row is read only here.

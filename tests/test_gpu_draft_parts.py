@@ -85,3 +85,39 @@ def test_draft_parts_greedy_rows_with_rising_and_equal_maxima(oracle_mod, pkg): 
     for ldt in ("bf16", "f16", "f32"):
         y = x if ldt == "f32" else W.f32_to_bf16_bits(x) if ldt == "bf16" else x.astype(np.float16)
         _check(y, ldt, ldt, T5, U5, oracle_mod, pkg)
+
+
+@pytest.mark.parametrize("V", [16384, 32768, 50184, 128256])
+@pytest.mark.parametrize("ldt", ["bf16", "f16", "f32"])
+def test_draft_rows_with_a_nan(V, ldt, pkg):  # noqa: F811
+    """A NaN among the logits makes its whole row NaN: token 0 and confidence 0, or the arg-max of the rest for a greedy row.
+    NaNs of both signs, beside finite logits of their thread and beside nothing but masked ones; the other rows stay as they are."""
+    import torch
+    dt = {"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16}[ldt]
+    gen = torch.Generator(device="cuda").manual_seed(V)
+    R = 12
+    x = 3.0 * torch.randn((R, V), generator=gen, device="cuda")
+    x[4:8, 2048:V - 2048] = -float("inf")                            # (rows 4-7: threads whose other logits are all masked)
+    x = x.to(dt)
+    t = torch.tensor([0.8, 0.0, 1.0, 0.0], device="cuda").repeat(3)
+    u = torch.rand(R, generator=gen, device="cuda")
+    rest = x.float().clone()
+    clean = [v.clone() for v in pkg.draft_sample(x, t, u)]
+    bits = x.view(torch.int32 if ldt == "f32" else torch.int16)
+    plus, minus = (0x7fffffff, -1) if ldt == "f32" else (0x7fff, -1)
+    for r, (i, pattern) in enumerate([(5, plus), (V // 2 + 3, plus), (V - 1, minus), (V // 3, minus)] * 2):
+        bits[r, i] = pattern
+        rest[r, i] = -float("inf")
+    # beside the largest logit of its row
+    bits[1, (int(rest[1].argmax()) & ~7) + (0 if int(rest[1].argmax()) & 7 else 1)] = plus
+    q, tok, conf = pkg.draft_sample(x, t, u)
+    torch.cuda.synchronize()
+    for r in range(R):
+        if r >= 8:
+            assert torch.equal(q[r], clean[0][r]) and tok[r] == clean[1][r] and conf[r] == clean[2][r]
+            continue
+        assert bool(torch.isnan(q[r]).all()), (r, int(torch.isnan(q[r]).sum()))
+        if float(t[r]) > 0:
+            assert int(tok[r]) == 0 and float(conf[r]) == 0.0
+        else:
+            assert int(tok[r]) == int(rest[r].argmax()) and bool(torch.isnan(conf[r]))

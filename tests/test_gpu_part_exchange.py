@@ -91,6 +91,49 @@ def test_draft_rows_without_waiting(R, V, ldt, pdt, lead_masked, pkg, impatient)
     assert torch.equal(want[1][t == 0].long(), x[t == 0].float().argmax(1))
 
 
+def _bits(t):
+    import torch
+    return t.view({2: torch.int16, 4: torch.int32}[t.element_size()])
+
+
+@pytest.mark.parametrize("V,dtype", [(32776, "bfloat16"), (128256, "float16"), (262152, "bfloat16"), (50184, "float32")])
+def test_draft_rows_with_a_nan_without_waiting(V, dtype, pkg, impatient):  # noqa: F811
+    import torch
+    x, t, u = _draft_inputs(8, V, getattr(torch, dtype), V)
+    x[4:, 4096:V - 4096] = -float("inf")             # (NaNs beside finite logits of their thread, and beside masked ones only)
+    for r, i in enumerate([3, V // 2, V - 1, V // 3] * 2):
+        _bits(x)[r, i] = -1 if r % 2 else 0x7fff * (65537 if dtype == "float32" else 1)
+
+    def call():
+        got = pkg.draft_sample(x, t, u)
+        torch.cuda.synchronize()
+        return got
+    want, got = call(), impatient(call)
+    assert bool(torch.isnan(want[0].float()).all()) and bool(torch.isnan(got[0].float()).all())
+    assert torch.equal(want[1], got[1]) and torch.equal(want[2].nan_to_num(-1.0), got[2].nan_to_num(-1.0))
+
+
+@pytest.mark.parametrize("V,ldt", [(8200, "bf16"), (12288, "f16"), (50272, "f32")])
+def test_accept_bonus_rows_with_a_nan_without_waiting(V, ldt, pkg, impatient):  # noqa: F811
+    """A NaN beside the only finite logits of its part: whoever computes the part must find the same maximum."""
+    import torch
+    dt = {"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16}[ldt]
+    gen = torch.Generator(device="cuda").manual_seed(V)
+    x = (3.0 * torch.randn((6, V), generator=gen, device="cuda")).to(dt)
+    x[:, V // 2:] = -float("inf")
+    x[:, V - 16:V - 8] = 1.0
+    _bits(x)[:, V - 12] = 0x7fff * (65537 if ldt == "f32" else 1)
+    T = torch.tensor([0.7, 1.0, 0.0, 1.0, 1.3, 0.7], device="cuda")
+    zeros = torch.zeros(6, dtype=torch.int32, device="cuda")
+
+    def call():
+        got = pkg.accept(x, torch.zeros((0, V), dtype=dt, device="cuda"), zeros[:0], torch.full((6, 2), 0.999, device="cuda"), zeros, T,
+                         max_spec_len=2, path="auto" if ldt == "f32" else "two_pass")
+        torch.cuda.synchronize()
+        return got
+    assert all(torch.equal(a, b) for a, b in zip(call(), impatient(call)))
+
+
 @pytest.mark.parametrize("R,V", [(3, 50272), (128, 128256)])
 def test_draft_rows_replayed_from_a_hip_graph(R, V, pkg):  # noqa: F811
     """A captured launch keeps its mark: every replay, on other inputs, must not find what the one before has left."""
