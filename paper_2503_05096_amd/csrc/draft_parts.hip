@@ -40,7 +40,8 @@ __device__ __forceinline__ uint32_t round_pair(float a, float b)
 template <class LT>
 __device__ __forceinline__ float draft_exponent_scale(float T)     // T == 0 stands for T = 1
 {
-    return T == 0.0f ? 1.4426950408889634f : exponent_scale<LT>(T);
+    // (T = inf would make it 0: the chunks past the end of a row are -inf, and 0 times that NaN)
+    return T == 0.0f ? 1.4426950408889634f : exponent_scale<LT>(T > 1e38f ? 1e38f : T);
 }
 
 constexpr int kDraftSteps = 8;                       // chunks per thread at most

@@ -121,3 +121,18 @@ def test_draft_rows_with_a_nan(V, ldt, pkg):  # noqa: F811
             assert int(tok[r]) == 0 and float(conf[r]) == 0.0
         else:
             assert int(tok[r]) == int(rest[r].argmax()) and bool(torch.isnan(conf[r]))
+
+
+@pytest.mark.parametrize("V,ldt", [(16384, "bf16"), (16392, "f32"), (32768, "f16"), (131072, "bf16")])
+def test_draft_rows_at_an_infinite_temperature(V, ldt, pkg):  # noqa: F811
+    """T = inf: every token equally likely, whatever the finite logits."""
+    import torch
+    dt = {"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16}[ldt]
+    gen = torch.Generator(device="cuda").manual_seed(V)
+    x = (3.0 * torch.randn((4, V), generator=gen, device="cuda")).to(dt)
+    u = torch.tensor([0.0, 0.25, 0.5, 1.0 - 2.0 ** -24], device="cuda")
+    q, tok, conf = pkg.draft_sample(x, torch.tensor([float("inf"), float("inf"), 3e38, float("inf")], device="cuda"), u)
+    torch.cuda.synchronize()
+    want = torch.tensor(1.0 / V, device="cuda").to(dt).float()
+    assert bool(((q.float() - want).abs() <= {"f32": 2.0 ** -22, "f16": 2.0 ** -10, "bf16": 2.0 ** -7}[ldt] * want + (6e-8 if ldt == "f16" else 0.0)).all())
+    assert bool(((tok.double() - u.double() * V).abs() <= 1e-5 * V + 1).all()) and bool((conf > 0).all())
