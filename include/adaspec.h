@@ -451,6 +451,8 @@ int adaspec_kv_compact_path(void *k_pages, void *v_pages, const int32_t *block_t
  * The row is written to draft_probs row out_rows[r] (row r if out_rows is
  * NULL), so a caller can place it directly into the ragged [TD][V] layout
  * that adaspec_accept reads.
+ * A row may be written where its logits are (same address, same element size);
+ * apart from that draft_probs must not overlap draft_logits.
  *
  * Needs V % 8 == 0, V <= 524288, row strides that are multiples of 8 elements
  * and 16-byte aligned logits / draft_probs (ADASPEC_ERR_UNSUPPORTED or

@@ -761,7 +761,10 @@ int adaspec_draft_sample(const void *draft_logits, const float *temperature, con
         if (workspace_bytes < draft_parts_workspace_bytes(*d)) return ADASPEC_ERR_WORKSPACE;
         split = true;
     } else if (d->path == ADASPEC_PATH_AUTO) {
-        split = split_ok && draft_wants_parts(*d) && workspace &&
+        // (probabilities in the logits' place: a workgroup of the split form would have each row alone; us per captured call, in
+        // parts / register-resident / three sweeps: V = 128256 bf16 1 row 41.1 / 26.9 / 32.4, 128 44.6 / 30.3 / 39.7; 64 of 50272
+        // fp32 38.3 / - / 16.7)
+        split = split_ok && draft_wants_parts(*d) && workspace && (draft_probs != draft_logits || out_rows) &&
                 !(reinterpret_cast<uintptr_t>(workspace) & 255u) && workspace_bytes >= draft_parts_workspace_bytes(*d);
     }
     const bool fast = !split && fast_ok &&

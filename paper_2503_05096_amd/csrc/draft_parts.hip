@@ -54,7 +54,8 @@ static_assert(kPartsMaxVocab <= kDraftMaxParts * kDraftSteps * kDraftT * 4, "fp3
 // looks for it before having seen that launch's maximum, which is published after the taking back is in place.
 struct DraftWords { MarkedWord top, Z, mass; };
 
-template <class LT, class PT, int NT>
+// kInPlace: rows may go where their logits are (what that takes costs the others 0.16 of 18.1 us, so it is left out where it cannot be)
+template <class LT, class PT, int NT, bool kInPlace>
 __global__ __launch_bounds__(NT, 4) void draft_row_kernel(
     const char *__restrict__ logits, const float *__restrict__ temperature, const float *__restrict__ uniforms,
     const int32_t *__restrict__ out_rows, char *__restrict__ probs, int32_t *__restrict__ tokens, float *__restrict__ confidence,
@@ -89,9 +90,13 @@ __global__ __launch_bounds__(NT, 4) void draft_row_kernel(
     const float T = temperature[r], u = uniforms[r], c = draft_exponent_scale<LT>(T);
     const bool sampled = T != 0.0f;
     const char *lrow = logits + (int64_t)r * lstride_bytes;
+    char *prow = probs + (int64_t)(out_rows ? out_rows[r] : r) * pstride_bytes;
     auto part_size = [&](int part) -> int { return max(0, min(row_chunks - part * part_chunks, part_chunks)); };
     auto part_row = [&](int part) {
         return __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(lrow) + (int64_t)part * part_chunks * 16, 0, part_size(part) * 16, 0x00020000);
+    };
+    auto part_probs = [&](int part) {
+        return __builtin_amdgcn_make_buffer_rsrc(prow + (int64_t)part * part_chunks * kBytes, 0, part_size(part) * kBytes, 0x00020000);
     };
     auto chunk_index = [&](int part, int it) -> int { return part * part_chunks + my_chunk + it * kWave; };     // in the row
 
@@ -175,6 +180,156 @@ __global__ __launch_bounds__(NT, 4) void draft_row_kernel(
         return __builtin_amdgcn_exp2f(t.m > -INFINITY ? thread_gap(t, s_row_m) : 0.f) * s_row_inv;
     };
 
+    // a chunk's (rounded) probabilities to memory
+    auto store_chunk = [&](__amdgpu_buffer_rsrc_t rp, int it, const float (&q)[kN]) {
+        // (the step's offset in the lane offset, scalar offset 0: see the store in draft_fast.hip)
+        const int at = (my_chunk + it * kWave) * kBytes;
+        uint32_t d[kBytes / 4];
+        if constexpr (std::is_same<PT, F32>::value) {
+#pragma unroll
+            for (int e = 0; e < kN; ++e) d[e] = __float_as_uint(q[e]);
+        } else {
+#pragma unroll
+            for (int e = 0; e < kN / 2; ++e) d[e] = round_pair<PT>(q[2 * e], q[2 * e + 1]);     // (exact)
+        }
+        if constexpr (kBytes == 8) {
+            typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+            __builtin_amdgcn_raw_buffer_store_b64(u32x2{d[0], d[1]}, rp, at, 0, 0);
+        } else {
+#pragma unroll
+            for (int k = 0; k < kBytes / 16; ++k)
+                __builtin_amdgcn_raw_buffer_store_b128(u32x4{d[4 * k], d[4 * k + 1], d[4 * k + 2], d[4 * k + 3]}, rp, at + 16 * k, 0, 0);
+        }
+    };
+
+    // ---- a part chunk by chunk, by the whole workgroup: what its own workgroup's words would have said, left in LDS ------
+    auto chunk_at = [&](int part, int it) -> uint4 {
+        uint4 v = part_load16<kAuxDefault>(part_row(part), (uint32_t)my_chunk * 16u, it * (kWave * 16));
+        Chunk<LT>::blank(v, my_chunk + it * kWave >= part_size(part));
+        return v;
+    };
+    auto compute_stats = [&](int part) {
+        float m = -INFINITY, z = 0.f;
+        int first = V;
+        for (int it = 0; it < part_steps; ++it) {
+            const uint4 v = chunk_at(part, it);
+            const float mn = chunk_max<LT>(v, m);
+            if (mn > m) first = first_with(v, mn, chunk_index(part, it));
+            m = mn;
+        }
+        const Ref t = ref_of(m);
+        for (int it = 0; it < part_steps; ++it) {
+            float x[kN];
+            z = add_weights(chunk_at(part, it), t, z, x);
+        }
+        lds_barrier();
+        leave_stats(t, z, first);
+        lds_barrier();
+        if (wv == 0) {
+            double Z;
+            int arg;
+            take_stats(part, m, Z, arg);
+        }
+    };
+    auto compute_mass = [&](int part, bool store) {                      // (the row's statistics known)
+        const float row_m = s_row_m, row_inv = s_row_inv, mc = scaled_ref(row_m, c);
+        const __amdgpu_buffer_rsrc_t rp = part_probs(part);
+        float m = -INFINITY;
+        for (int it = 0; it < part_steps; ++it) m = chunk_max<LT>(chunk_at(part, it), m);
+        const Ref t = ref_of(m);
+        const float f = thread_factor(t);
+        double total = 0.0;
+        for (int it = 0; it < part_steps; ++it) {
+            float x[kN];
+            add_weights(chunk_at(part, it), t, 0.f, x);
+            total += (double)round_probs(x, f, row_m, mc, row_inv);
+            if (store) store_chunk(rp, it, x);
+        }
+        total = wave_sum(total);
+        lds_barrier();
+        if (lane == 0) s_z[wv] = total;
+        lds_barrier();
+        if (wv == 0) {
+            const double mass = wave_sum(lane < NW ? s_z[lane] : 0.0);
+            if (lane == 0) s_part_z[part] = mass;
+        }
+    };
+
+    // ---- probabilities that go where the logits are --------------------------------------------------------------------
+    // What a part has overwritten nobody else could compute again if its words did not come in time: one workgroup takes such a
+    // row alone, part by part (a thread stores a chunk it has just read), and draws from what it has stored.
+    if constexpr (kInPlace) {
+        if (n_parts > 1 && prow == lrow) {
+            if (h > 0) return;
+            for (int part = 0; part < n_parts; ++part) compute_stats(part);
+            if (wv == 0) row_stats();
+            lds_barrier();
+            for (int part = 0; part < n_parts; ++part) compute_mass(part, true);
+            if (wv == 0) {
+                double before = 0.0, tau = 0.0;
+                int star = s_row_arg < 0 ? -1 : s_row_arg / kN / part_chunks;
+                if (sampled) {
+                    const double at = lane < n_parts ? s_part_z[lane & 31] : 0.0;
+                    tau = (double)u * wave_sum(at);
+                    star = find_piece(at, 0.0, tau, lane, before);
+                }
+                if (lane == 0) { s_star = star; s_before = before; s_tau = tau; }
+            }
+            __syncthreads();                                 // (the stores are done, too)
+            const int star = s_star;
+            if (star < 0) {                                  // no mass (non-finite input): stay defined
+                if (tid == 0) { tokens[r] = 0; confidence[r] = 0.f; }
+                return;
+            }
+            const __amdgpu_buffer_rsrc_t rp = part_probs(star);
+            auto stored = [&](int it, float (&q)[kN]) -> float {
+                Chunk<PT>::unpack(part_load16<kAuxDefault>(rp, (uint32_t)my_chunk * 16u, it * (kWave * 16)), q);
+                float acc = 0.f;
+#pragma unroll
+                for (int e = 0; e < kN; ++e) acc += q[e];
+                return acc;
+            };
+            float q[kN];
+            if (!sampled) {
+                for (int it = 0; it < part_steps; ++it) {
+                    if (chunk_index(star, it) != s_row_arg / kN) continue;
+                    stored(it, q);
+                    float conf = q[0];
+#pragma unroll
+                    for (int e = 1; e < kN; ++e) conf = e == s_row_arg % kN ? q[e] : conf;
+                    tokens[r] = s_row_arg; confidence[r] = conf;
+                }
+                return;
+            }
+            double total = 0.0, before = 0.0, cum = 0.0;
+            for (int it = 0; it < part_steps; ++it) total += (double)stored(it, q);
+            total = wave_sum(total);
+            if (lane == 0) s_mass[wv] = total;
+            lds_barrier();
+            const double tau = s_tau;
+            if (find_piece(lane < NW ? s_mass[lane & (NW - 1)] : 0.0, s_before, tau, lane, before) != wv) return;
+            int step = -1, owner = 0;
+            for (int it = 0; it < part_steps; ++it) {
+                const double mine = (double)stored(it, q), upto = before + wave_scan_incl(mine, lane);
+                const unsigned long long cross = __ballot(mine > 0.0 && upto > tau), filled = __ballot(mine > 0.0);
+                if (filled) {
+                    step = it;
+                    owner = cross ? (int)__builtin_ctzll(cross) : 63 - (int)__builtin_clzll(filled);
+                    cum = upto - mine;
+                }
+                if (cross) break;
+                before = last_lane(upto);
+            }
+            stored(max(step, 0), q);                         // (the piece has mass: some step has)
+            const int pick = pick_element<kN>(q, cum, 1.0, tau);
+            float conf = q[0];
+#pragma unroll
+            for (int e = 1; e < kN; ++e) conf = e == pick ? q[e] : conf;
+            if (lane == owner) { tokens[r] = chunk_index(star, max(step, 0)) * kN + pick; confidence[r] = conf; }
+            return;
+        }
+    }
+
     // ---- the own part: weights and their sum ----------------------------------------------------------------------
     float w[kDraftSteps][kN], z_t = 0.f;
     Ref ref;
@@ -233,37 +388,7 @@ __global__ __launch_bounds__(NT, 4) void draft_row_kernel(
     // (of a part whose statistics did not come in time the mass may be an earlier replay's: not looked at below)
     const unsigned int late = __builtin_amdgcn_readfirstlane(s_missing);
     if (late != 0u) {
-        for (unsigned int left = late; left != 0u; left &= left - 1u) {
-            const int part = (int)__builtin_ctz(left);
-            const __amdgpu_buffer_rsrc_t rl = part_row(part);
-            const int n = part_size(part);
-            auto chunk_at = [&](int it) -> uint4 {
-                uint4 v = part_load16<kAuxDefault>(rl, (uint32_t)my_chunk * 16u, it * (kWave * 16));
-                Chunk<LT>::blank(v, my_chunk + it * kWave >= n);
-                return v;
-            };
-            float m = -INFINITY, z = 0.f;
-            int first = V;
-            for (int it = 0; it < part_steps; ++it) {
-                const uint4 v = chunk_at(it);
-                const float mn = chunk_max<LT>(v, m);
-                if (mn > m) first = first_with(v, mn, chunk_index(part, it));
-                m = mn;
-            }
-            const Ref t = ref_of(m);
-            for (int it = 0; it < part_steps; ++it) {
-                float x[kN];
-                z = add_weights(chunk_at(it), t, z, x);
-            }
-            lds_barrier();
-            leave_stats(t, z, first);
-            lds_barrier();
-            if (wv == 0) {
-                double Z;
-                int arg;
-                take_stats(part, m, Z, arg);
-            }
-        }
+        for (unsigned int left = late; left != 0u; left &= left - 1u) compute_stats((int)__builtin_ctz(left));
         if (wv == 0) row_stats();
         lds_barrier();
     }
@@ -296,29 +421,11 @@ __global__ __launch_bounds__(NT, 4) void draft_row_kernel(
     }
     // (the mass is out: the probabilities may follow)
     {
-        const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc(
-            probs + (int64_t)(out_rows ? out_rows[r] : r) * pstride_bytes + (int64_t)h * part_chunks * kBytes, 0, part_size(h) * kBytes, 0x00020000);
+        const __amdgpu_buffer_rsrc_t rp = part_probs(h);
 #pragma unroll
         for (int it = 0; it < kDraftSteps; ++it) {
             if (it >= part_steps) break;
-            // (the step's offset in the lane offset, scalar offset 0: see the store in draft_fast.hip)
-            const int at = (my_chunk + it * kWave) * kBytes;
-            uint32_t d[kBytes / 4];
-            if constexpr (std::is_same<PT, F32>::value) {
-#pragma unroll
-                for (int e = 0; e < kN; ++e) d[e] = __float_as_uint(w[it][e]);
-            } else {
-#pragma unroll
-                for (int e = 0; e < kN / 2; ++e) d[e] = round_pair<PT>(w[it][2 * e], w[it][2 * e + 1]);     // (exact)
-            }
-            if constexpr (kBytes == 8) {
-                typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-                __builtin_amdgcn_raw_buffer_store_b64(u32x2{d[0], d[1]}, rp, at, 0, 0);
-            } else {
-#pragma unroll
-                for (int k = 0; k < kBytes / 16; ++k)
-                    __builtin_amdgcn_raw_buffer_store_b128(u32x4{d[4 * k], d[4 * k + 1], d[4 * k + 2], d[4 * k + 3]}, rp, at + 16 * k, 0, 0);
-            }
+            store_chunk(rp, it, w[it]);
         }
     }
     // the draw (wavefront 0, all masses known): the part, then the wavefront of it, that holds the point
@@ -358,34 +465,7 @@ __global__ __launch_bounds__(NT, 4) void draft_row_kernel(
     lds_barrier();
     const unsigned int gone = __builtin_amdgcn_readfirstlane(s_missing);
     if (gone != 0u) {
-        for (unsigned int left = gone; left != 0u; left &= left - 1u) {
-            const int part = (int)__builtin_ctz(left);
-            const __amdgpu_buffer_rsrc_t rl = part_row(part);
-            const int n = part_size(part);
-            auto chunk_at = [&](int it) -> uint4 {
-                uint4 v = part_load16<kAuxDefault>(rl, (uint32_t)my_chunk * 16u, it * (kWave * 16));
-                Chunk<LT>::blank(v, my_chunk + it * kWave >= n);
-                return v;
-            };
-            float m = -INFINITY;
-            for (int it = 0; it < part_steps; ++it) m = chunk_max<LT>(chunk_at(it), m);
-            const Ref t = ref_of(m);
-            const float f = thread_factor(t);
-            double total = 0.0;
-            for (int it = 0; it < part_steps; ++it) {
-                float x[kN];
-                add_weights(chunk_at(it), t, 0.f, x);
-                total += (double)round_probs(x, f, row_m, mc, row_inv);
-            }
-            total = wave_sum(total);
-            lds_barrier();
-            if (lane == 0) s_z[wv] = total;
-            lds_barrier();
-            if (wv == 0) {
-                const double mass = wave_sum(lane < NW ? s_z[lane] : 0.0);
-                if (lane == 0) s_part_z[part] = mass;
-            }
-        }
+        for (unsigned int left = gone; left != 0u; left &= left - 1u) compute_mass((int)__builtin_ctz(left), false);
         if (wv == 0) draw();
         lds_barrier();
     }
@@ -462,10 +542,17 @@ hipError_t launch_draft_parts(const void *logits, const float *temperature, cons
     n_parts = n_parts < least ? least : n_parts > most ? most : n_parts;
     const int part_steps = ceil_div(steps, n_parts);
     n_parts = ceil_div(steps, part_steps);
+    // Whether some row may go where its logits are: without out_rows if both start at one address; with them (their values are on the
+    // device) if the logits lie a whole number of rows behind the first destination.
+    const int64_t apart = (int64_t)(reinterpret_cast<intptr_t>(logits) - reinterpret_cast<intptr_t>(probs));
+    const bool in_place = out_rows ? apart + (d.rows - 1) * lstride >= 0 && (lstride != pstride || apart % pstride == 0) : apart == 0;
     auto launch = [&](auto lt, auto pt) {
         using LT = decltype(lt);
         using PT = decltype(pt);
-        auto kernel = wide ? draft_row_kernel<LT, PT, kDraftWideT> : draft_row_kernel<LT, PT, kDraftT>;
+        auto kernel = wide ? draft_row_kernel<LT, PT, kDraftWideT, false> : draft_row_kernel<LT, PT, kDraftT, false>;
+        if constexpr (sizeof(typename LT::storage) == sizeof(typename PT::storage)) {
+            if (in_place) kernel = wide ? draft_row_kernel<LT, PT, kDraftWideT, true> : draft_row_kernel<LT, PT, kDraftT, true>;
+        }
         hipLaunchKernelGGL(kernel, dim3(d.rows * n_parts), dim3(threads), 0, stream, (const char *)logits,
                            temperature, uniforms, out_rows, (char *)probs, tokens, confidence, d.vocab, n_parts, part_steps,
                            lstride, pstride, reinterpret_cast<DraftWords *>(ws), (unsigned long long)next_spread_mark());

@@ -136,3 +136,33 @@ def test_draft_rows_at_an_infinite_temperature(V, ldt, pkg):  # noqa: F811
     want = torch.tensor(1.0 / V, device="cuda").to(dt).float()
     assert bool(((q.float() - want).abs() <= {"f32": 2.0 ** -22, "f16": 2.0 ** -10, "bf16": 2.0 ** -7}[ldt] * want + (6e-8 if ldt == "f16" else 0.0)).all())
     assert bool(((tok.double() - u.double() * V).abs() <= 1e-5 * V + 1).all()) and bool((conf > 0).all())
+
+
+# whole rows, rows in parts (threads of both sizes, all pairs of equal element size), a last part that is nearly empty, the most parts
+@pytest.mark.parametrize("R,V,dtype", [(4, 16384, "bfloat16"), (6, 32776, "bfloat16"), (5, 50184, "float32"), (70, 65544, "float16"),
+                                       (128, 128256, "bfloat16"), (3, 524288, "float32")])
+@pytest.mark.parametrize("mapped,path", [(False, "auto"), (False, "split"), (True, "auto")])
+def test_draft_rows_in_place(R, V, dtype, mapped, path, pkg):  # noqa: F811
+    """The probabilities may go where the logits are, row by row: the same result as beside them on the path that takes them."""
+    import torch
+    if path == "split" and dtype == "float32":
+        pytest.skip("the split form takes fp32 rows by itself only")
+    beside = path if path == "split" or mapped else "fast" if dtype != "float32" and V > 24576 else "vector"
+    gen = torch.Generator(device="cuda").manual_seed(R + V)
+    x = 3.0 * torch.randn((R, V), generator=gen, device="cuda")
+    x[::3, :V // 2] = -float("inf")
+    x[1, 77] = float("nan")
+    x = x.to(getattr(torch, dtype))
+    t = torch.tensor([0.8, 1.0, 0.0, 1.3], device="cuda").repeat(R)[:R]
+    u = torch.rand(R, generator=gen, device="cuda")
+    want = [v.clone() for v in pkg.draft_sample(x, t, u, path=beside)]
+    buffer = torch.zeros((R + 3, V), dtype=x.dtype, device="cuda")
+    first = 2 if mapped else 0
+    buffer[first:first + R] = x
+    rows = torch.arange(first, first + R, dtype=torch.int32, device="cuda") if mapped else None
+    logits = buffer[first:first + R]
+    _, tok, conf = pkg.draft_sample(logits, t, u, draft_probs=buffer if mapped else logits, out_rows=rows, path=path)
+    torch.cuda.synchronize()
+    assert torch.equal(tok, want[1]) and torch.equal(conf.nan_to_num(-1.0), want[2].nan_to_num(-1.0))
+    assert torch.equal(logits.float().nan_to_num(-1.0), want[0].float().nan_to_num(-1.0))
+    assert bool((buffer[:first] == 0).all()) and bool((buffer[first + R:] == 0).all())
