@@ -24,7 +24,6 @@ constexpr int decide_steps(int logits_size, int probs_size) { return probs_size 
 constexpr int kDecideMaxParts = 32;                       // two lanes each in the exchange
 static_assert(kPartsMaxVocab <= kDecideMaxParts * kDecideT * 8 * 4, "fp32 rows fit");
 struct PartWords { unsigned long long mass, top; };
-static_assert(sizeof(PartWords) * kDecideMaxParts <= 4 * sizeof(PartWords) * kSumParts, "the words fit where the plan lays them out");
 
 // One chunk: r_v = max(0, e_v / Z - q_v), or p_v = e_v / Z itself, with e_v = 2^((l_v - m) c).
 // The sums and the final search both call this, so they see the same numbers.
@@ -366,8 +365,10 @@ SharedParts accept_shared_parts(const adaspec_accept_dims &d, int compute_units)
     const int most = decide_steps(f32 ? 4 : 2, d.probs_dtype == ADASPEC_F32 ? 4 : 2);
     const int steps = ceil_div(d.vocab / parts_chunk_elems(d.logits_dtype), kDecideT), least = ceil_div(steps, most);
     if ((int64_t)d.batch * least > 4 * (int64_t)compute_units) return p;
+    // (words of a request lie where the plan has its masses)
+    const int room = (int)(accept_parts_sum_bytes(d) / (d.batch > 0 ? d.batch : 1) / sizeof(PartWords));
     int64_t best = INT64_MAX;
-    for (int n = least; n <= kDecideMaxParts && n <= steps; ++n) {
+    for (int n = least; n <= kDecideMaxParts && n <= steps && n <= room; ++n) {
         const int each = ceil_div(steps, n);
         const int64_t cost = ((int64_t)d.batch * n + compute_units - 1) / compute_units * (each + 2) + (n > 1 ? 1 : 0);
         if (ceil_div(steps, each) == n && cost < best) {
