@@ -352,23 +352,34 @@ __global__ __launch_bounds__(kDecideT, 4) void accept_decide_shared_kernel(
 
 // Parts of the deciding rows (0: the call is not for this kernel).  As many as make the fullest compute unit's work the least: turns
 // times (chunks per thread, and two for what a turn costs besides), and one for an exchange.  fp32, 64 requests of V = 128256: 8
-// parts; 150 of V = 32000: three 25.1 us, two 26.5.  From five workgroups per compute unit on the many small ones of accept_decide_kernel fill the chip better (300 requests
-// of V = 50272 35.4 us, here 39.9; 100 of 128256, four, 35.6 / 29.5).  16-bit rows have twice the arithmetic per byte, which here follows
+// parts; 150 of V = 32000: three 25.1 us, two 26.5.
+// A compute unit holds two of these workgroups, and the many small ones of accept_decide_kernel fill the chip better than a second
+// turn does (us per captured call, accept_decide_kernel / here, 0-4 drafts, sampled | a third greedy | all greedy: 160 requests of V =
+// 50272 32.8 / 34.7 | 29.7 / 32.2 | 21.4 / 22.8, 200 of 40000 31.3 / 35.6 | 28.9 / 31.7 | 20.7 / 23.3, 300 of 16384 23.5 / 26.5 |
+// 22.0 / 24.0 | 15.3 / 17.3; within one turn 128 of 50272 28.9 / 27.0 | 25.9 / 25.7 | 17.7 / 18.8, 64 of 32000 16.0 / 14.9 | 15.0 /
+// 14.2 | 10.7 / 11.2), except with rows of eight full parts and more (V = 128256, 100: 48.9 / 42.5 | 42.4 / 39.9 | 29.9 / 30.7, 128: 57.3 /
+// 51.4 | 48.7 / 46.3 | 35.1 / 35.3; 100000, 128: 46.8 / 45.8 | 40.7 / 42.6 | 29.2 / 31.7), where a second one still pays.
+// 16-bit probabilities beside fp32 logits leave less to read: very short and long rows only (V = 4096, 64: 11.9 / 11.3 | 11.9 / 11.1 |
+// 9.7 / 9.3; 32000, 100: 18.9 / 20.3 | 17.4 / 19.6 | 12.6 / 13.6; 50272, 64: 21.0 / 20.1 | 18.9 / 19.4 | 13.0 / 13.8; 80000, 64:
+// 26.2 / 22.6 | 22.8 / 21.7 | 15.9 / 16.5).
+// 16-bit rows have twice the arithmetic per byte, which here follows
 // the loads where many small workgroups overlap it, so only short ones come (accept_decide_kernel / here: V = 16000, 300 requests
 // 18.4 / 19.0 us; 128256, 128 39.9 / 40.8; 32000, 150 21.3 / 24.8; 262144, 64 33.2 / 33.2; V = 8000, 1000 29.5 / 34.8).
-constexpr int kSharedShortRow = 12288;
+constexpr int kSharedShortRow = 12288, kSharedManyParts = 8;
+constexpr int kSharedFewSteps = 2, kSharedManySteps = 32;    // rows beside narrower probabilities: at most, more than
 SharedParts accept_shared_parts(const adaspec_accept_dims &d, int compute_units)
 {
     SharedParts p{0, 0, 0};
     const bool f32 = d.logits_dtype == ADASPEC_F32;
-    if (!f32 && (d.vocab > kSharedShortRow || d.batch > 2 * compute_units)) return p;
+    if (!f32 && d.vocab > kSharedShortRow) return p;
     const int most = decide_steps(f32 ? 4 : 2, d.probs_dtype == ADASPEC_F32 ? 4 : 2);
     const int steps = ceil_div(d.vocab / parts_chunk_elems(d.logits_dtype), kDecideT), least = ceil_div(steps, most);
-    if ((int64_t)d.batch * least > 4 * (int64_t)compute_units) return p;
+    if (f32 && d.probs_dtype != ADASPEC_F32 && steps > kSharedFewSteps && steps <= kSharedManySteps) return p;
+    const int64_t workgroups = (int64_t)compute_units * (least >= kSharedManyParts ? 4 : 2);
     // (words of a request lie where the plan has its masses)
     const int room = (int)(accept_parts_sum_bytes(d) / (d.batch > 0 ? d.batch : 1) / sizeof(PartWords));
     int64_t best = INT64_MAX;
-    for (int n = least; n <= kDecideMaxParts && n <= steps && n <= room; ++n) {
+    for (int n = least; n <= kDecideMaxParts && n <= steps && n <= room && n * (int64_t)d.batch <= workgroups; ++n) {
         const int each = ceil_div(steps, n);
         const int64_t cost = ((int64_t)d.batch * n + compute_units - 1) / compute_units * (each + 2) + (n > 1 ? 1 : 0);
         if (ceil_div(steps, each) == n && cost < best) {

@@ -171,9 +171,9 @@ def _accept_step(B, V, ldt, pdt, seed, equal=False, **kw):
     return st
 
 
-# one part, parts of every length, a last part that is nearly empty, the most parts, more parts than fit the chip at once
+# one part, parts of every length, a last part that is nearly empty, the most parts, more parts than fit the chip at once; rows that have gone back to many small workgroups (32008, 50272)
 @pytest.mark.parametrize("B,V,ldt,pdt", [(5, 2000, "f32", "f32"), (64, 128256, "f32", "f32"), (150, 32008, "f32", "bf16"), (3, 524288, "f32", "f16"),
-                                         (40, 98312, "f32", "f32"), (1, 128256, "f32", "bf16"), (200, 50272, "f32", "f32"),
+                                         (40, 98312, "f32", "f32"), (1, 128256, "f32", "bf16"), (200, 50272, "f32", "f32"), (100, 114704, "f32", "f32"),
                                          (6, 12288, "bf16", "bf16"), (70, 8200, "f16", "f32"), (300, 4104, "bf16", "f16")])
 @pytest.mark.parametrize("kind", ["", "masked", "equal"])
 def test_accept_without_waiting(B, V, ldt, pdt, kind, oracle_mod, pkg, impatient):  # noqa: F811
