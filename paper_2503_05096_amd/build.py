@@ -3,7 +3,9 @@
 from __future__ import annotations
 
 import glob
+import hashlib
 import os
+import re
 import subprocess
 import sys
 from concurrent.futures import ThreadPoolExecutor
@@ -69,14 +71,41 @@ def _link(objects, out: str) -> str:
     return out
 
 
-def build_impatient(out: str, jobs: int = 8) -> str:
-    """For tests: the library with workgroups that never wait for each other's words (csrc/part_exchange.h) and compute what
-    is missing themselves. Call it after build_library, whose other objects it links."""
-    sources = _sources()
-    waiting = [s for s in sources if '#include "part_exchange.h"' in open(s).read()]
+def _inputs():
+    return sorted(glob.glob(os.path.join(CSRC, "*")) + glob.glob(os.path.join(INCLUDE, "*")))
+
+
+def source_key(defines=()) -> str:
+    """What the library is made from: a digest of its sources, headers, flags and `defines`."""
+    h = hashlib.sha256(repr((FLAGS, tuple(defines))).encode())
+    for path in _inputs():
+        h.update(os.path.basename(path).encode() + b"\0" + open(path, "rb").read())
+    return h.hexdigest()[:16]
+
+
+def _includes(path: str, header: str) -> bool:
+    """Whether the file includes csrc/`header`, also through other headers of csrc."""
+    names = re.findall(r'#include "([^"]+)"', open(path).read())
+    return header in names or any(_includes(os.path.join(CSRC, n), header) for n in names if os.path.exists(os.path.join(CSRC, n)))
+
+
+def build_variant(out: str, tag: str, defines, header: str, jobs: int = 8) -> str:
+    """The library with `defines` for the sources that include `header`. The other objects are the library's own where
+    they are there and newer than every source."""
+    newest = max(os.path.getmtime(p) for p in _inputs())
+    os.makedirs(BUILD_DIR, exist_ok=True)
+
+    def obj(src):
+        own = _object(src)
+        if _includes(src, header):
+            own = _object(src, "_" + tag)
+            _compile(src, own, defines)
+        elif not os.path.exists(own) or os.path.getmtime(own) < newest:
+            own = _object(src, "_" + tag)
+            _compile(src, own)
+        return own
     with ThreadPoolExecutor(jobs) as ex:
-        list(ex.map(lambda s: _compile(s, _object(s, "_impatient"), ("ADASPEC_PATIENCE=0",)), waiting))
-    return _link([_object(s, "_impatient" if s in waiting else "") for s in sources], out)
+        return _link(list(ex.map(obj, _sources())), out)
 
 
 def build_library(verbose: bool = False, jobs: int = 8) -> str:

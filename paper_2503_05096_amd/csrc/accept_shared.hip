@@ -246,7 +246,7 @@ __global__ __launch_bounds__(kDecideT, 4) void accept_decide_shared_kernel(
             const int p = lane & (kDecideMaxParts - 1);
             const bool other = p < n_parts && p != h;
             const unsigned long long v = take_words(lane < kDecideMaxParts ? &words[p].mass : &words[p].top,
-                                                    other && (lane < kDecideMaxParts ? sampled : bonus), kPatience);
+                                                    other && (lane < kDecideMaxParts ? sampled : bonus));
             const bool there = v != kNoWord || !(lane < kDecideMaxParts ? sampled : bonus);
             const unsigned long long got = __ballot(other && there);
             const unsigned int both = (unsigned int)got & (unsigned int)(got >> 32);

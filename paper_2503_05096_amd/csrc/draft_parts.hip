@@ -373,7 +373,7 @@ __global__ __launch_bounds__(NT, 4) void draft_row_kernel(
             const int p = lane & 31;                                 // lanes 0..31 the maxima, 32..63 the normalisers
             const bool other = (others >> p) & 1u;
             unsigned long long v = 0ull;
-            const unsigned long long got = __ballot(take_marked(lane < 32 ? &words[p].top : &words[p].Z, other, mark, kPatience, v));
+            const unsigned long long got = __ballot(take_marked(lane < 32 ? &words[p].top : &words[p].Z, other, mark, v));
             const unsigned int both = (unsigned int)got & (unsigned int)(got >> 32);
             if (other && ((both >> p) & 1u)) {
                 if (lane < 32) { s_part_m[p] = __uint_as_float((uint32_t)v); s_part_i[p] = (int)(v >> 32); }
@@ -455,7 +455,7 @@ __global__ __launch_bounds__(NT, 4) void draft_row_kernel(
         if (n_parts > 1) {
             const bool other = (others >> (lane & 31)) & (unsigned int)(lane < 32);
             unsigned long long v = 0ull;
-            const bool got = take_marked(&words[lane & 31].mass, other && !((late >> (lane & 31)) & 1u), mark, kPatience, v);
+            const bool got = take_marked(&words[lane & 31].mass, other && !((late >> (lane & 31)) & 1u), mark, v);
             if (got) s_part_z[lane & 31] = double_of(v);
             missing = (unsigned int)__ballot(other && !got);
         }

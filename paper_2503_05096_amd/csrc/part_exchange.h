@@ -7,7 +7,7 @@
 // at once, 1.7 us with 1024, 3 us with 2048, all of which poll the same few lines; and 2048 workgroups take 4.8 us to start,
 // 512 take 1.2.  So rows are shared by FEW workgroups of 1024 threads.
 //
-// Nobody depends on being met: a workgroup looks for the words of the others kPatience times at most and then computes
+// Nobody depends on being met: a workgroup looks for a word of another one ADASPEC_PATIENCE times at most and then computes
 // what is missing itself, with the same instructions on the same inputs and so with the same result.  Whether all parts of
 // a row are resident at once, and in which order they run, decides how long a launch takes and nothing else.
 #pragma once
@@ -17,10 +17,10 @@ namespace adaspec {
 
 // Looks at the others' words, about 0.7 us each.  Parts of a row are neighbours in the grid, so that they start within a few
 // microseconds of each other; the limit matters only where something else holds the compute units.
+// (Tests build the library with other numbers, also with one that differs from word to word.)
 #ifndef ADASPEC_PATIENCE
-#define ADASPEC_PATIENCE 64
+#define ADASPEC_PATIENCE(word) 64
 #endif
-constexpr int kPatience = ADASPEC_PATIENCE;
 
 constexpr unsigned long long kNoWord = ~0ull;         // what an earlier kernel of the call leaves in every word
 
@@ -39,11 +39,12 @@ __device__ __forceinline__ unsigned long long word_of(double x)
 }
 __device__ __forceinline__ double double_of(unsigned long long w) { return __longlong_as_double((long long)w); }
 
-// One wavefront: lane t with `wanted` takes the word at `p`; up to `looks` times, until all are there.  Returns the
+// One wavefront: lane t with `wanted` takes the word at `p`, once all are there or patience has run out.  Returns the
 // lane's word (kNoWord: not there, or not wanted).
-__device__ __forceinline__ unsigned long long take_words(const unsigned long long *p, bool wanted, int looks)
+__device__ __forceinline__ unsigned long long take_words(const unsigned long long *p, bool wanted)
 {
     unsigned long long w = kNoWord;
+    const int looks = ADASPEC_PATIENCE(p);
     for (int n = 0; n < looks; ++n) {
         if (wanted && w == kNoWord) w = fetch_u64(p);
         if (__ballot(wanted && w == kNoWord) == 0ull) break;
@@ -67,9 +68,10 @@ __device__ __forceinline__ void take_back(MarkedWord *p)
     publish_u64(&p->check, 0ull);
 }
 // One wavefront, like take_words; returns whether the lane has its value.
-__device__ __forceinline__ bool take_marked(const MarkedWord *p, bool wanted, unsigned long long mark, int looks, unsigned long long &v)
+__device__ __forceinline__ bool take_marked(const MarkedWord *p, bool wanted, unsigned long long mark, unsigned long long &v)
 {
     bool there = false;
+    const int looks = ADASPEC_PATIENCE(p);
     for (int n = 0; n < looks; ++n) {
         if (wanted && !there) {
             const unsigned long long a = fetch_u64(&p->value), b = fetch_u64(&p->check);

@@ -400,7 +400,7 @@ __global__ __launch_bounds__(kNT, STEPS == 1 ? 8 : 4) void accept_tree_walk_shar
                     if (known == 0ull && n_parts > 1) {         // the own part: the others may be there, or come
                         if (lane == 0) publish_u64(words + h, word_of(mass));
                         const bool other = lane < n_parts && lane != h, waited = other && !((late >> lane) & 1ull);
-                        unsigned long long got = take_words(words + lane, waited, kPatience);
+                        unsigned long long got = take_words(words + lane, waited);
                         if (other && !waited) got = fetch_u64(words + lane);
                         if (other && got != kNoWord) part[lane] = double_of(got);
                         missing = __ballot(other && got == kNoWord);

@@ -1,28 +1,23 @@
 """Workgroups that share a row take each other's sums where they come in time and compute them otherwise
-(csrc/part_exchange.h): a library whose workgroups never wait gives the same results bit for bit."""
-import os
-
+(csrc/part_exchange.h): libraries whose workgroups never wait, or not for some words, give the same results bit for bit."""
 import numpy as np
 import pytest
 
 import workloads as W
 from workloads.device import to_device
-from paper_2503_05096_amd import binding, build
+from paper_2503_05096_amd import binding
+from tests import exchange_builds
 from tests.test_gpu_parity import check_accept
 from tests.test_gpu_tree import _check_tree_accept, pkg  # noqa: F401  (fixture)
 from workloads.verify_step import _store, to_f64
 
 pytestmark = pytest.mark.gpu
-IMPATIENT = os.path.join(os.path.dirname(os.path.abspath(__file__)), "native", "libadaspec_impatient.so")
 
 
-@pytest.fixture
-def impatient(monkeypatch):
-    """Calls go to the library that never waits (through ctypes) until the returned function switches back."""
-    if not os.path.exists(IMPATIENT):
-        build.build_library()
-        build.build_impatient(IMPATIENT)
-    L = binding._open(IMPATIENT)
+@pytest.fixture(params=sorted(exchange_builds.DEFINES))
+def impatient(request, monkeypatch):
+    """Calls go to a library that never waits, or not for some words (through ctypes), until the returned function switches back."""
+    L = binding._open(exchange_builds.ensure(request.param))
 
     def run(call):
         with monkeypatch.context() as m:
@@ -113,6 +108,25 @@ def test_draft_rows_with_a_nan_without_waiting(V, dtype, pkg, impatient):  # noq
     assert torch.equal(want[1], got[1]) and torch.equal(want[2].nan_to_num(-1.0), got[2].nan_to_num(-1.0))
 
 
+@pytest.mark.parametrize("R,V,dtype", [(5, 128256, "bfloat16"), (3, 262144, "float32")])
+def test_draft_rows_in_place_without_waiting(R, V, dtype, pkg, impatient):  # noqa: F811
+    """Rows over their own logits (and, in the same call, one beside them): nobody reads what another workgroup has overwritten."""
+    import torch
+    x, t, u = _draft_inputs(R, V, getattr(torch, dtype), R)
+    want = [v.clone() for v in pkg.draft_sample(x, t, u)]
+    buffer = torch.zeros((R + 2, V), dtype=x.dtype, device="cuda")
+    rows = torch.arange(1, R + 1, dtype=torch.int32, device="cuda")
+    rows[R - 1] = R + 1                                          # (the last row's logits are at row R)
+
+    def call():
+        buffer[1:R + 1] = x
+        got = pkg.draft_sample(buffer[1:R + 1], t, u, draft_probs=buffer, out_rows=rows)
+        torch.cuda.synchronize()
+        return got[0][rows.long()].clone(), got[1], got[2]
+    for got in (call(), impatient(call)):
+        assert all(torch.equal(a, b) for a, b in zip(want, got))
+
+
 @pytest.mark.parametrize("V,ldt", [(8200, "bf16"), (12288, "f16"), (50272, "f32")])
 def test_accept_bonus_rows_with_a_nan_without_waiting(V, ldt, pkg, impatient):  # noqa: F811
     """A NaN beside the only finite logits of its part: whoever computes the part must find the same maximum."""
@@ -154,6 +168,73 @@ def test_draft_rows_replayed_from_a_hip_graph(R, V, pkg):  # noqa: F811
                 pkg.draft_sample(*sets[0])
             torch.cuda.synchronize()
             assert all(torch.equal(a, b) for a, b in zip(got, w))
+
+
+def _replay(call, inputs, sets, want, between):
+    """Captures call() on `inputs` and replays it on every set, with eager calls in between."""
+    import torch
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        got = call()
+    for turn in range(2):
+        for s, w in zip(sets, want):
+            for dst, src in zip(inputs, s):
+                dst.copy_(src)
+            graph.replay()
+            torch.cuda.synchronize()
+            assert all(torch.equal(a, b) for a, b in zip(got, w))
+            if turn:
+                between()
+
+
+@pytest.mark.parametrize("R,V", [(3, 50272), (128, 128256), (20, 262144)])
+def test_draft_rows_replayed_without_waiting(R, V, pkg, impatient):  # noqa: F811
+    """Like the replays above, by workgroups that give up on words, with eager calls of other rows and vocabularies (words laid out
+    otherwise) on the same workspace in between."""
+    import torch
+    sets = [_draft_inputs(R, V, torch.bfloat16, s, 0.8) for s in range(3)]
+    x, t, u = (v.clone() for v in sets[0])
+    want = [[v.clone() for v in pkg.draft_sample(*s)] for s in sets]
+    others = [_draft_inputs(r, v, torch.bfloat16, 9, 1.0) for r, v in ((5, 128256), (70, 65544), (2, 524288))]
+    ws = torch.empty(1 << 22, dtype=torch.uint8, device="cuda")
+    eager = iter(others * 2)
+
+    def between():
+        o = next(eager)
+        pkg.draft_sample(*o, workspace=ws)                       # (its words carry the other library's marks)
+        impatient(lambda: pkg.draft_sample(*o, workspace=ws))
+    torch.cuda.synchronize()
+    _replay(lambda: impatient(lambda: pkg.draft_sample(x, t, u, workspace=ws)), (x, t, u), sets, want, between)
+
+
+@pytest.mark.parametrize("B,V,dtype", [(24, 128256, "f32"), (6, 8200, "bf16")])
+def test_accept_replayed_without_waiting(B, V, dtype, pkg, impatient):  # noqa: F811
+    import torch
+    k = 3
+    T = np.random.default_rng(B).choice(np.array([0.0, 0.7, 1.0, 1.0], np.float32), B)
+    devs = [to_device(W.make_custom_step(40 + s, ctx_lens=[k + 1] * B, spec_lens=[k] * B, vocab=V, logits_dtype=dtype, temperature=T,
+                                         attention=False, logits_sigma=3.0, noise_sigma=1.5, draft_temp=1.2), attention=False) for s in range(2)]
+    sets = [(d.target_logits, d.draft_probs, d.draft_tokens, d.uniforms, d.spec_lens, d.temperature) for d in devs]
+    call = lambda a: pkg.accept(*a, max_spec_len=k)
+    want = [[v.clone() for v in call(s)] for s in sets]
+    inputs = tuple(v.clone() for v in sets[0])
+    torch.cuda.synchronize()
+    _replay(lambda: impatient(lambda: call(inputs)), inputs, sets, want, lambda: None)
+
+
+def test_tree_walk_replayed_without_waiting(pkg, impatient):  # noqa: F811
+    import torch
+    B, V, k = 12, 128256, 4
+    steps = [_tree([k] * B, V, "bf16", np.full(B, 0.9, np.float32)) for _ in range(2)]
+    devs = [to_device(st, attention=False) for st in steps]
+    sets = [(d.target_logits, d.draft_probs, d.draft_tokens, d.parents, d.uniforms, d.spec_lens, d.temperature) for d in devs]
+    sets[1] = tuple(v.clone() for v in sets[1])
+    sets[1][4].copy_(1.0 - sets[1][4])                           # other decisions and other draws
+    call = lambda a: pkg.accept_tree(*a, max_spec_len=k)
+    want = [[v.clone() for v in call(s)] for s in sets]
+    inputs = tuple(v.clone() for v in sets[0])
+    torch.cuda.synchronize()
+    _replay(lambda: impatient(lambda: call(inputs)), inputs, sets, want, lambda: None)
 
 
 def _accept_step(B, V, ldt, pdt, seed, equal=False, **kw):

@@ -460,3 +460,19 @@ def test_tree_accept_with_masked_logits(kpath, oracle_mod, pkg):
     st.draft_probs[:, 2048:12288] = 0
     W.attach_tree(st, max_width=3)
     _check_tree_accept(st, oracle_mod, pkg, kpath=kpath, max_near_tie_frac=0.1)
+
+
+# Batches of which the parts of shared rows would wait for each other's compute units (256 of them: 22 (B parts - 256) > steps *
+# 3 * 256 with parts of up to four steps of 8192): a workgroup per request, over rows of several sweeps and deep walks.
+@pytest.mark.parametrize("B,V,dtype", [(208, 128256, "bf16"), (180, 262144, "f16"), (260, 50272, "bf16")])
+def test_tree_accept_with_a_workgroup_per_request(B, V, dtype, oracle_mod, pkg):
+    import torch
+    assert torch.cuda.get_device_properties(0).multi_processor_count <= 256
+    rng = np.random.default_rng(V)
+    spec = rng.integers(0, 2, size=B).astype(np.int32)
+    spec[::5] = 6
+    st = W.make_custom_step(77 + V, ctx_lens=spec + 1, spec_lens=spec, vocab=V, logits_dtype=dtype, attention=False,
+                            temperature=rng.choice([0.0, 0.7, 1.0, 1.0], size=B), logits_sigma=3.0, noise_sigma=1.5, draft_temp=1.3,
+                            name=f"tree-whole-{V}")
+    W.attach_tree(st, max_width=4)
+    _check_tree_accept(st, oracle_mod, pkg)
