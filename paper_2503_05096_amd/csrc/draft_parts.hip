@@ -108,7 +108,8 @@ __global__ __launch_bounds__(NT, 4) void draft_row_kernel(
     // A NaN makes its whole row NaN: sums are taken over everybody, also over threads, wavefronts and parts without a finite
     // logit (theirs are 0 unless they hold one).
     struct Ref { float m, at; };
-    auto ref_of = [&](float m) -> Ref { return Ref{m, m > -INFINITY ? scaled_ref(m, c) : 0.f}; };
+    const float lowest = lowest_ref<LT>(c);
+    auto ref_of = [&](float m) -> Ref { return Ref{m, m > lowest ? scaled_ref(m, c) : 0.f}; };
     // exponent that moves a thread's weights to the reference of the maximum m
     auto thread_gap = [&](Ref t, float m) -> float { return kKeepsWeights ? t.at - scaled_ref(m, c) : (t.m - m) * c; };
     // a chunk's weights, added up behind z
@@ -117,7 +118,7 @@ __global__ __launch_bounds__(NT, 4) void draft_row_kernel(
         Chunk<LT>::unpack(lv, x);
 #pragma unroll
         for (int e = 0; e < kN; ++e) {
-            const float v = exp_weight<LT>(x[e], t.m > -INFINITY ? t.m : 0.f, c, t.at);
+            const float v = exp_weight<LT>(x[e], t.m > lowest ? t.m : 0.f, c, t.at);
             z += v;
             w[e] = kKeepsWeights ? v : x[e];
         }
@@ -154,7 +155,7 @@ __global__ __launch_bounds__(NT, 4) void draft_row_kernel(
     // over the workgroup: a part's statistics from its threads' (first half of the way: to LDS)
     auto leave_stats = [&](Ref t, float z_t, int top) {
         const float mw = wave_max(t.m);
-        const double zw = wave_sum((double)(z_t * __builtin_amdgcn_exp2f(t.m > -INFINITY ? thread_gap(t, mw) : 0.f)));
+        const double zw = wave_sum((double)(z_t * __builtin_amdgcn_exp2f(t.m > lowest ? thread_gap(t, mw) : 0.f)));
         if (lane == 0) { s_m[wv] = mw; s_z[wv] = zw; }
         if (!sampled) {
             const ArgMax b = wave_argmax(ArgMax{t.m, top});
@@ -164,20 +165,20 @@ __global__ __launch_bounds__(NT, 4) void draft_row_kernel(
     auto take_stats = [&](int part, float &m, double &Z, int &arg) {     // (wavefront 0)
         const float mw = lane < NW ? s_m[lane] : -INFINITY;
         m = wave_max(mw);
-        Z = wave_sum(lane < NW ? s_z[lane & (NW - 1)] * (double)__builtin_amdgcn_exp2f(mw > -INFINITY ? ref_gap<LT>(mw, m, c) : 0.f) : 0.0);
+        Z = wave_sum(lane < NW ? s_z[lane & (NW - 1)] * (double)__builtin_amdgcn_exp2f(mw > lowest ? ref_gap<LT>(mw, m, c) : 0.f) : 0.0);
         arg = sampled ? V : wave_argmax(ArgMax{mw, lane < NW ? s_i[lane] : V}).i;
         if (lane == 0) { s_part_m[part] = m; s_part_i[part] = arg; s_part_z[part] = Z; }
     };
     auto row_stats = [&]() {                                             // (wavefront 0, all parts known)
         const float mp = lane < n_parts ? s_part_m[lane] : -INFINITY, M = wave_max(mp);
-        const double sum = wave_sum(lane < n_parts ? s_part_z[lane & 31] * (double)__builtin_amdgcn_exp2f(mp > -INFINITY ? ref_gap<LT>(mp, M, c) : 0.f) : 0.0);
+        const double sum = wave_sum(lane < n_parts ? s_part_z[lane & 31] * (double)__builtin_amdgcn_exp2f(mp > lowest ? ref_gap<LT>(mp, M, c) : 0.f) : 0.0);
         const int at = s_part_i[lane & 31];
         const ArgMax b = wave_argmax(lane < n_parts && at < V ? ArgMax{mp, at} : ArgMax{-INFINITY, 0x7fffffff});
         // (a row without any finite logit: q = NaN, as in the other kernels)
         if (lane == 0) { s_row_m = M; s_row_inv = (float)(1.0 / sum); s_row_arg = b.i == 0x7fffffff ? -1 : b.i; }
     };
     auto thread_factor = [&](Ref t) -> float {
-        return __builtin_amdgcn_exp2f(t.m > -INFINITY ? thread_gap(t, s_row_m) : 0.f) * s_row_inv;
+        return __builtin_amdgcn_exp2f(t.m > lowest ? thread_gap(t, s_row_m) : 0.f) * s_row_inv;
     };
 
     // a chunk's (rounded) probabilities to memory

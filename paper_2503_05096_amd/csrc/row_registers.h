@@ -43,6 +43,15 @@ __device__ __forceinline__ float row16_sum(float v)
 // where m c is 20 to 100, and nothing took them out of p = weight / sum.
 __device__ __forceinline__ float scaled_ref(float m, float c) { return ceilf(m * c); }
 
+// Maxima at or below this, whose product with c would overflow, count as -inf: sums relative to them would be infinite, and what
+// moves those elsewhere 0.  They are those of threads, wavefronts and parts of which a mask has left nothing, where it wrote bf16's
+// lowest number in place of -inf.
+template <class LT>
+__device__ __forceinline__ float lowest_ref(float c)
+{
+    return sizeof(typename LT::storage) == 2 ? -3.0e38f * __builtin_amdgcn_rcpf(c) : -INFINITY;
+}
+
 // log2(e) / T.  For 16-bit rows no more than 2^22: a reference (or a product m c) from 2^31 on is so coarse that what it
 // leaves of the largest logit's exponent overflows.  Below T = 3.4e-7, where that sets in, 16-bit logits that differ at all
 // differ by a weight of 0, unless all of them are below 1e-2.

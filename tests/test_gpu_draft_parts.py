@@ -166,3 +166,18 @@ def test_draft_rows_in_place(R, V, dtype, mapped, path, pkg):  # noqa: F811
     assert torch.equal(tok, want[1]) and torch.equal(conf.nan_to_num(-1.0), want[2].nan_to_num(-1.0))
     assert torch.equal(logits.float().nan_to_num(-1.0), want[0].float().nan_to_num(-1.0))
     assert bool((buffer[:first] == 0).all()) and bool((buffer[first + R:] == 0).all())
+
+
+@pytest.mark.parametrize("V", [8192, 16384, 32768, 50184, 128256])
+@pytest.mark.parametrize("ldt,path", [("bf16", "auto"), ("bf16", "split"), ("bf16", "fast"), ("bf16", "vector"), ("f16", "auto"), ("f32", "auto")])
+def test_draft_rows_masked_with_the_lowest_number(V, ldt, path, oracle_mod, pkg):  # noqa: F811
+    """Masked by the type's lowest number in place of -inf, alone and in stretches (threads, parts of which nothing else is left): a
+    product of it with log2(e) / T overflows for bf16."""
+    x = _logits(4, V, "f32", seed=8, masked=0.3)
+    x[:, V // 4:V // 2] = -np.inf
+    x[:, V - 256:] = -np.inf
+    x[0, V // 2 + 5] = 3.0                                        # (every row has something left)
+    gone = np.isneginf(x)
+    y = x if ldt == "f32" else W.f32_to_bf16_bits(x) if ldt == "bf16" else x.astype(np.float16)
+    y[gone] = {"f32": np.finfo(np.float32).min, "f16": np.finfo(np.float16).min, "bf16": np.uint16(0xFF7F)}[ldt]
+    _check(y, ldt, ldt, T, U, oracle_mod, pkg, path=path)
