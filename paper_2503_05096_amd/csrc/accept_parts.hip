@@ -110,7 +110,8 @@ template <class LT, int STEPS>
 __device__ __forceinline__ bool part_max_and_norm(uint4 (&lg)[STEPS], float c, float *s_m, double *s_z,
                                                   int lane, int wv, float &m_out, double &z_out)
 {
-    const float mt = thread_max<LT, STEPS>(lg);
+    float mt = thread_max<LT, STEPS>(lg);
+    if (mt <= lowest_ref<LT>(c)) mt = -INFINITY;
     float zt = 0.f;
     if (mt > -INFINITY) {
         const float mtc = scaled_ref(mt, c);

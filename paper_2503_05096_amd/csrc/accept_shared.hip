@@ -129,7 +129,7 @@ __global__ __launch_bounds__(kDecideT, 4) void accept_decide_shared_kernel(
 
     // ---- what a part amounts to: the steps of the way that its own workgroup and, where its words do not come, others
     // share.  A bonus row was not seen by the first pass: its parts are relative to their own maxima.
-    auto leave_max = [&](float m_t) { m_t = wave_max(m_t); if (lane == 0) s_m[wv] = m_t; };
+    auto leave_max = [&](float m_t) { m_t = wave_max(m_t <= lowest_ref<LT>(c) ? -INFINITY : m_t); if (lane == 0) s_m[wv] = m_t; };
     auto take_max = [&]() -> float {
         float m = s_m[0];
 #pragma unroll

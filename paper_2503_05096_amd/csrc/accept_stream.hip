@@ -196,6 +196,7 @@ __global__ __launch_bounds__(kST, 8) void accept_stream_kernel(
 
     // ---- sweep 1: maximum and normaliser on line ----------------------------------------------
     const float c = 1.4426950408889634f / T;
+    const float lowest = lowest_ref<DT>(c);
     float m_run = -INFINITY, zt = 0.f;
     static_assert(kStash % 4 == 0 && (kKeep == 4 || kKeep == 0), "the kept steps are exactly one load group of sweep 1, or none");
     uint4 keep0 = make_uint4(0, 0, 0, 0), keep1 = keep0, keep2 = keep0, keep3 = keep0;   // (named, not an array:
@@ -220,7 +221,7 @@ __global__ __launch_bounds__(kST, 8) void accept_stream_kernel(
             float mn = m_run;
 #pragma unroll
             for (int e = 0; e < 4; ++e) mn = fmaxf(mn, fmaxf(P::lo(w[e]), P::hi(w[e])));
-            if (mn > -INFINITY) {
+            if (mn > lowest) {
                 zt *= __builtin_amdgcn_exp2f((m_run - mn) * c);                     // (-inf - finite) -> 0
                 const float mnc = mn * c;
 #pragma unroll

@@ -204,7 +204,8 @@ __device__ __forceinline__ PartStream stream_part(__amdgpu_buffer_rsrc_t rl, int
     const int steps = (ceil_div(row_chunks, kQT) - h + n_parts - 1) / n_parts;
     const uint32_t tid16 = (uint32_t)tid * 16u;
     PartStream out;
-    out.m_run = -INFINITY; out.zt = 0.f; out.best = ArgMax{-INFINITY, V};
+    const float lowest = lowest_ref<LT>(c);              // (m_run until something above it comes)
+    out.m_run = lowest; out.zt = 0.f; out.best = ArgMax{-INFINITY, V};
     short2v pm = {(short)0x8000, (short)0x8000};
     uint4 lg[kStatSteps];
 #pragma unroll
@@ -241,7 +242,7 @@ __device__ __forceinline__ PartStream stream_part(__amdgpu_buffer_rsrc_t rl, int
                     out.zt *= __builtin_amdgcn_exp2f(ref_gap<LT>(out.m_run, mn, c));      // (-inf - finite) -> 0
                     out.m_run = mn;
                 }
-                if (out.m_run > -INFINITY) {
+                if (out.m_run > lowest) {
                     const float mnc = scaled_ref(out.m_run, c);
                     Chunk<LT>::unpack(v, x);
 #pragma unroll
@@ -253,6 +254,7 @@ __device__ __forceinline__ PartStream stream_part(__amdgpu_buffer_rsrc_t rl, int
             __builtin_amdgcn_sched_barrier(0);       // one step at a time: nothing unpacked ahead of its turn
         }
     }
+    if (!(out.m_run > lowest)) out.m_run = -INFINITY;
     return out;
 }
 

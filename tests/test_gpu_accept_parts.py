@@ -88,3 +88,19 @@ def test_accept_parts_at_temperatures_next_to_zero(ldt, pdt, offset, oracle_mod,
     st = _step(4096, ldt, pdt, spec=[3, 0, 2, 6, 1, 4], temp=[1e-8, 1e-10, 1e-7, 1e-9, 1e-6, 1e-10])
     st.target_logits = _store((to_f64(st.target_logits, ldt) + offset).astype(np.float32), ldt)
     check_accept(st, oracle_mod, pkg)
+
+
+@pytest.mark.parametrize("V", [4096, 8200, 32000, 128256])
+@pytest.mark.parametrize("ldt,pdt,path", [("bf16", "bf16", "auto"), ("bf16", "bf16", "two_pass"), ("bf16", "bf16", "fast"), ("bf16", "bf16", "stream"),
+                                          ("bf16", "f32", "auto"), ("f16", "f16", "auto"), ("f32", "f32", "auto")])
+def test_accept_rows_masked_with_the_lowest_number(ldt, pdt, path, V, oracle_mod, pkg):  # noqa: F811
+    """Masked by the type's lowest number in place of -inf, alone and in stretches (threads, parts of which nothing else is left): a
+    product of it with log2(e) / T overflows for bf16."""
+    st = _step(V, ldt, pdt, spec=[3, 0, 2, 6, 1, 0], temp=[0.8, 1.0, 0.0, 0.5, 0.0, 0.7], masked_frac=0.3)
+    x = to_f64(st.target_logits, ldt)
+    gone = np.isneginf(x)
+    gone[:, V // 4:V // 2] = True
+    gone[:, V - 256:] = True
+    st.target_logits[gone] = {"f32": np.finfo(np.float32).min, "f16": np.finfo(np.float16).min, "bf16": np.uint16(0xFF7F)}[ldt]
+    st.draft_probs[:, V // 4:V // 2] = 0
+    check_accept(st, oracle_mod, pkg, path=path)
