@@ -163,7 +163,7 @@ __global__ __launch_bounds__(kQT, 6) void tree_node_stats_kernel(
         }
         return;
     }
-    const float c = exponent_scale<DT>(T);
+    const float c = exponent_scale<DT>(T), lowest = lowest_ref<DT>(c);
     for (int s = first; s < last; ++s) {
         uint4 nx[kSumSteps];
         load_step(s + 1 < last ? s + 1 : nsteps, nx);            // (another group's step: nothing)
@@ -171,7 +171,8 @@ __global__ __launch_bounds__(kQT, 6) void tree_node_stats_kernel(
         for (int it = 0; it < kSumSteps; ++it) Chunk<DT>::blank(lg[it], s * kStepChunks + it * kQT + tid >= row_chunks);
         // every thread sums against its own maximum; the pairs are merged over the wavefront here, over the
         // wavefronts at the end
-        const float mt = thread_max<DT, kSumSteps>(lg);
+        float mt = thread_max<DT, kSumSteps>(lg);
+        if (mt <= lowest) mt = -INFINITY;
         float zt = 0.f;
         if (mt > -INFINITY) {
             const float mtc = mt * c;

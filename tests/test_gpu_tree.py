@@ -476,3 +476,23 @@ def test_tree_accept_with_a_workgroup_per_request(B, V, dtype, oracle_mod, pkg):
                             name=f"tree-whole-{V}")
     W.attach_tree(st, max_width=4)
     _check_tree_accept(st, oracle_mod, pkg)
+
+
+@pytest.mark.parametrize("dtype,V,kpath", [("bf16", 16384, "fast"), ("bf16", 50272, "fast"), ("bf16", 128256, "fast"), ("f16", 16384, "fast"),
+                                           ("bf16", 16384, "vector")])
+def test_tree_accept_masked_with_the_lowest_number(dtype, V, kpath, oracle_mod, pkg):
+    """Like the masked logits above, with the type's lowest number in place of -inf: a product of it with log2(e) / T overflows for bf16."""
+    rng = np.random.default_rng(33)
+    B = 20
+    spec = rng.integers(0, 9, size=B).astype(np.int32)
+    st = W.make_custom_step(642, ctx_lens=spec + 1, spec_lens=spec, vocab=V, logits_dtype=dtype,
+                            temperature=rng.choice([0.0, 0.8, 1.0, 0.5], size=B), attention=False, noise_sigma=0.5,
+                            masked_frac=0.35, name="tree-masked-lowest")
+    minus_inf, lowest = {"bf16": (np.uint16(0xFF80), np.uint16(0xFF7F)), "f16": (-np.inf, np.finfo(np.float16).min)}[dtype]
+    gone = st.target_logits == minus_inf
+    gone[:, 2048:12288] = True
+    gone[:, V - 512:] = True
+    st.target_logits[gone] = lowest
+    st.draft_probs[:, 2048:12288] = 0
+    W.attach_tree(st, max_width=3)
+    _check_tree_accept(st, oracle_mod, pkg, kpath=kpath, max_near_tie_frac=0.1)
