@@ -43,13 +43,15 @@ __device__ __forceinline__ float row16_sum(float v)
 // where m c is 20 to 100, and nothing took them out of p = weight / sum.
 __device__ __forceinline__ float scaled_ref(float m, float c) { return ceilf(m * c); }
 
-// Maxima at or below this, whose product with c would overflow, count as -inf: sums relative to them would be infinite, and what
-// moves those elsewhere 0.  They are those of threads, wavefronts and parts of which a mask has left nothing, where it wrote bf16's
-// lowest number in place of -inf.
+// Maxima at or below this count as -inf: their product with c, from 2^31 on, is so coarse (or not finite at all) that weights relative
+// to it overflow, and what moves such a sum elsewhere is 0.  They are those of threads, wavefronts and parts of which a mask has
+// left nothing, where it wrote the type's lowest number in place of -inf.
+// (With the largest scale, a power of two, products are exact as long as they are finite.)
+constexpr float kLargestScale = 4194304.f;
 template <class LT>
 __device__ __forceinline__ float lowest_ref(float c)
 {
-    return sizeof(typename LT::storage) == 2 ? -3.0e38f * __builtin_amdgcn_rcpf(c) : -INFINITY;
+    return sizeof(typename LT::storage) == 2 ? (c == kLargestScale ? -3.0e38f : -1.9e9f) * __builtin_amdgcn_rcpf(c) : -INFINITY;
 }
 
 // log2(e) / T.  For 16-bit rows no more than 2^22: a reference (or a product m c) from 2^31 on is so coarse that what it
@@ -59,7 +61,7 @@ template <class LT>
 __device__ __forceinline__ float exponent_scale(float T)
 {
     const float c = 1.4426950408889634f / T;
-    return sizeof(typename LT::storage) == 2 ? fminf(c, 4194304.f) : c;
+    return sizeof(typename LT::storage) == 2 ? fminf(c, kLargestScale) : c;
 }
 
 }  // namespace adaspec

@@ -104,3 +104,8 @@ def test_accept_rows_masked_with_the_lowest_number(ldt, pdt, path, V, oracle_mod
     st.target_logits[gone] = {"f32": np.finfo(np.float32).min, "f16": np.finfo(np.float16).min, "bf16": np.uint16(0xFF7F)}[ldt]
     st.draft_probs[:, V // 4:V // 2] = 0
     check_accept(st, oracle_mod, pkg, path=path)
+    st.temperature[:] = np.array([100.0, 30.0, 0.0, 3.0, 300.0, 50.0], np.float32)      # the product is finite, but coarse
+    check_accept(st, oracle_mod, pkg, path=path)
+    if ldt == "f16":
+        st.temperature[:] = np.array([1e-5, 1e-6, 0.0, 1e-6, 1e-5, 1e-6], np.float32)
+        check_accept(st, oracle_mod, pkg, path=path)

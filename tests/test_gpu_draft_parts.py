@@ -181,3 +181,7 @@ def test_draft_rows_masked_with_the_lowest_number(V, ldt, path, oracle_mod, pkg)
     y = x if ldt == "f32" else W.f32_to_bf16_bits(x) if ldt == "bf16" else x.astype(np.float16)
     y[gone] = {"f32": np.finfo(np.float32).min, "f16": np.finfo(np.float16).min, "bf16": np.uint16(0xFF7F)}[ldt]
     _check(y, ldt, ldt, T, U, oracle_mod, pkg, path=path)
+    if ldt == "bf16" or path == "auto":                           # far from T = 1 the product is finite, but coarse
+        _check(y, ldt, ldt, np.array([100.0, 30.0, 3.0, 300.0], np.float32), U, oracle_mod, pkg, path=path)
+    if ldt == "f16":
+        _check(y, ldt, ldt, np.array([1e-5, 1e-6, 1e-7, 1e-8], np.float32), U, oracle_mod, pkg, path=path)

@@ -496,3 +496,5 @@ def test_tree_accept_masked_with_the_lowest_number(dtype, V, kpath, oracle_mod, 
     st.draft_probs[:, 2048:12288] = 0
     W.attach_tree(st, max_width=3)
     _check_tree_accept(st, oracle_mod, pkg, kpath=kpath, max_near_tie_frac=0.1)
+    st.temperature[:] = rng.choice([0.0, 3.0, 30.0, 100.0], size=B)     # the product is finite, but coarse
+    _check_tree_accept(st, oracle_mod, pkg, kpath=kpath, max_near_tie_frac=0.1)
