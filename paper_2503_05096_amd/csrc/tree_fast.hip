@@ -163,7 +163,9 @@ __global__ __launch_bounds__(kQT, 6) void tree_node_stats_kernel(
         }
         return;
     }
-    const float c = exponent_scale<DT>(T), lowest = lowest_ref<DT>(c);
+    const float c = exponent_scale<DT>(T);
+    // (the same for the workgroup: a scalar register, the vector ones are full)
+    const float lowest = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(lowest_ref<DT>(c))));
     for (int s = first; s < last; ++s) {
         uint4 nx[kSumSteps];
         load_step(s + 1 < last ? s + 1 : nsteps, nx);            // (another group's step: nothing)
@@ -171,10 +173,9 @@ __global__ __launch_bounds__(kQT, 6) void tree_node_stats_kernel(
         for (int it = 0; it < kSumSteps; ++it) Chunk<DT>::blank(lg[it], s * kStepChunks + it * kQT + tid >= row_chunks);
         // every thread sums against its own maximum; the pairs are merged over the wavefront here, over the
         // wavefronts at the end
-        float mt = thread_max<DT, kSumSteps>(lg);
-        if (mt <= lowest) mt = -INFINITY;
+        const float mt = thread_max<DT, kSumSteps>(lg);
         float zt = 0.f;
-        if (mt > -INFINITY) {
+        if (mt > lowest) {
             const float mtc = mt * c;
 #pragma unroll
             for (int it = 0; it < kSumSteps; ++it) {
@@ -188,7 +189,7 @@ __global__ __launch_bounds__(kQT, 6) void tree_node_stats_kernel(
         const float mw = wave_max(mt);
         // (mt c was rounded in the exponents above, which at low temperatures is visible in the sum: the difference is
         // taken out again here)
-        const double zw = wave_sum(mt > -INFINITY ? (double)(zt * __builtin_amdgcn_exp2f((mt - mw) * c - fmaf(mt, c, -(mt * c)))) : 0.0);
+        const double zw = wave_sum(mt > lowest ? (double)(zt * __builtin_amdgcn_exp2f((mt - mw) * c - fmaf(mt, c, -(mt * c)))) : 0.0);
         if (lane == 0) { s_m[s - first][wv] = mw; s_z[s - first][wv] = zw; }
 #pragma unroll
         for (int it = 0; it < kSumSteps; ++it) lg[it] = nx[it];
@@ -809,7 +810,11 @@ hipError_t launch_accept_tree_fast(const AcceptArgs &a, const int32_t *parents, 
     // and sweep, of which the longest chain has up to three.  One workgroup per request / shared, whole call, trees of width 3,
     // V = 128256: 64 of 1-6 drafts 56.1 / 33.2 us, 128 74.0 / 58.9, 155 of 0-2 46.4 / 41.2, 192 of 1-6 90.2 / 82.6, 256 105 / 107,
     // 180 of 0-1 35.4 / 39.8, 233 40.0 / 48.9; V = 50272, 256 of 0-1 24.5 / 29.8, of 0-3 37.5 / 38.2; V = 262144, 64 of 0-3 74.8 / 39.1;
-    // V = 8000, 256 of 1-6 21.4 / 19.6, 1024 of 0-3 48 / 51.
+    // V = 8000, 256 of 1-6 21.4 / 19.6, 1024 of 0-3 48 / 51.  Where all requests are greedy nothing is shared, and the further parts only
+    // start and leave: 64 of V = 128256 21.2 / 20.8, of 262144, whose parts wait, 38.6 / 41.9 (sampled 100 / 60), one request 7.4 / 7.9; a third
+    // greedy, 200 of 1-6 (near the line) 74.3 / 77.6 (all sampled 91.7 / 86.3).
+    // Beside another stream's matrix products, which leave no room for a 1024-thread workgroup with its registers full, every part waits for
+    // a compute unit: 64 of 1-6 drafts 140 / 222 us while 4096^3 products run.
     const int room = (stat_bytes - node_words_at(nsteps)) / 8;
     int part_steps = 1;
     while (part_steps < kWalkSteps && ((int64_t)d.batch * ceil_div(nsteps, part_steps) > compute_units || ceil_div(nsteps, part_steps) > room))
