@@ -475,7 +475,8 @@ typedef struct {
                                    long rows shared by workgroups; AUTO = the split
                                    form, of any storage types, when a workspace is
                                    given and V > 12288 (fp32 probabilities of 16-bit
-                                   logits: 32768); else FAST when it fits and
+                                   logits: 32768; not with draft_probs ==
+                                   draft_logits); else FAST when it fits and
                                    V > 24576, else VECTOR */
     int32_t reserved;
     void   *timing_start;       /* optional pair of hipEvent_t (both or neither, NULL = none), recorded */

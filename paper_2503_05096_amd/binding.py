@@ -552,7 +552,7 @@ def commit(out_tokens, out_accept_len, spec_lens, ctx_lens, *, max_spec_len: int
 def draft_sample(draft_logits, temperature, uniforms, *, probs_dtype=None, draft_probs=None, out_rows=None,
                  draft_tokens=None, confidence=None, path: str = "auto", workspace=None, stream=None, timing=None):
     """adaspec_draft_sample; returns (draft_probs, draft_tokens [R] int32, confidence [R] float32).
-    path "split" (ADASPEC_PATH_TWO_PASS for this call) cuts every row into parts."""
+    path "split" (ADASPEC_PATH_TWO_PASS for this call) shares long rows between workgroups."""
     if path == "auto" and timing is None:
         r = (_fast or _native()).draft_sample(draft_logits, temperature, uniforms, probs_dtype, draft_probs, out_rows,
                                               draft_tokens, confidence, workspace, stream)

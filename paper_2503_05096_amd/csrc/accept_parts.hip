@@ -20,7 +20,7 @@
 //       Records are stored per SLOT (request, draft position), so the second pass reads them without
 //       knowing where the request's rows start.  Workgroup 0 also writes cu_q and clears the tickets of
 //       the second pass; the whole grid clears the words of the other one.
-//   accept_decide_kernel     (16-bit rows above V = 12288, large batches; the others: accept_shared.hip)  workgroup = (request, part of
+//   accept_decide_kernel     (16-bit rows above V = 12288, large batches, some fp32 rows; the others: accept_shared.hip)  workgroup = (request, part of
 //       <= 1024 chunks).  Merges the part
 //       statistics of the request's draft rows, applies the accept test to each (one lane per draft), finds
 //       the first rejection -> the deciding row; part 0 writes the accepted drafts, the padding and the

@@ -708,6 +708,7 @@ static int validate_draft_dims(const adaspec_draft_dims *d)
 //   V = 32768 bf16   1 row 12.7 / 11.0 /  8.2   128 rows 14.6 / 12.9 / 10.7   256 rows 16.0 / 14.1 / 13.1   300 rows 21.9 / 20.8 / 14.8
 //   V = 65536 bf16   1 row 19.5 / 16.5 /  8.7   128 rows 22.6 / 18.6 / 14.6   256 rows 24.9 / 21.2 / 18.4   300 rows 34.9 / 34.7 / 25.0
 //   V = 128256 bf16  1 row 31.8 / 26.4 /  8.8   128 rows 39.1 / 32.1 / 18.9   256 rows 43.0 / 33.5 / 31.7   300 rows 62.8 / 57   / 39.9
+//     one row more than one workgroup of 1024 threads per compute unit holds: 129 rows in parts 23.0, 160 25.5, 192 27.5
 //   V = 12288 fp32   1 row  7.6 /   -  /  7.1   128 rows  9.2 /   -  /  8.2   256 rows 11.9 /   -  / 10.8   300 rows 15.4 /   -  / 12.4
 //     all greedy            6.2 /   -  /  6.6             7.5 /   -  /  7.6            10.4 /   -  / 10.1            13.0 /   -  / 11.7
 //   V = 50272 fp32   1 row 14.3 /   -  /  8.4   128 rows 21.1 /   -  / 16.2   256 rows 34.1 /   -  / 22.0   300 rows 43.2 /   -  / 26.8

@@ -5,17 +5,21 @@
 // share; each XCD has its own L2), a value and "it is there" in the same 8 bytes, so nothing has to be acknowledged first
 // and no cache is written back or invalidated.  MI355X, publish to all seen: 0.6-1.0 us with up to 512 workgroups exchanging
 // at once, 1.7 us with 1024, 3 us with 2048, all of which poll the same few lines; and 2048 workgroups take 4.8 us to start,
-// 512 take 1.2.  So rows are shared by FEW workgroups of 1024 threads.
+// 512 take 1.2.  So rows are shared by FEW workgroups, of 512 or 1024 threads.
 //
 // Nobody depends on being met: a workgroup looks for a word of another one ADASPEC_PATIENCE times at most and then computes
 // what is missing itself, with the same instructions on the same inputs and so with the same result.  Whether all parts of
-// a row are resident at once, and in which order they run, decides how long a launch takes and nothing else.
+// a row are resident at once, and in which order they run, decides how long a launch takes and nothing else.  What that costs: 13 us
+// per exchange for 64 looks in vain, and the parts that are missing (if nobody ever meets, patience 0, captured calls: draft
+// sampling of 128 rows of V = 128256 19 -> 40 us, of 8 of V = 524288 in fp32 14 -> 253; acceptance of 64 fp32 rows 35 -> 102; walks of 64 trees
+// 32 -> 63).  A workgroup that starts when the others have left finds their words where a kernel of the call clears them, and taken back
+// where marks are used.
 #pragma once
 #include "device_utils.h"
 
 namespace adaspec {
 
-// Looks at the others' words, about 0.7 us each.  Parts of a row are neighbours in the grid, so that they start within a few
+// Looks at the others' words, 0.2 us each while nobody writes and up to 0.7 while the others publish.  Parts of a row are neighbours in the grid, so that they start within a few
 // microseconds of each other; the limit matters only where something else holds the compute units.
 // (Tests build the library with other numbers, also with one that differs from word to word.)
 #ifndef ADASPEC_PATIENCE

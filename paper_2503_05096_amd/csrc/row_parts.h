@@ -1,4 +1,5 @@
-// Vocabulary rows cut into PARTS that small workgroups (256 threads) sweep: the pieces shared by the acceptance
+// Vocabulary rows cut into PARTS that small workgroups (256 threads) sweep, or that larger ones (512, 1024) hold in registers: the
+// pieces shared by the acceptance
 // (accept_parts.hip, accept_shared.hip), draft sampling (draft_parts.hip) and trees (tree_fast.hip).  A row is a sequence
 // of CHUNKS of 16 bytes of logits (8 elements of 16 bits, 4 of fp32) with as many probabilities beside them; a STEP is
 // one chunk per thread.

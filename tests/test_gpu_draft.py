@@ -141,7 +141,7 @@ def test_draft_sample_small_vocab_and_planted_ties(oracle_mod, pkg):
     T = np.array([1.0, 0.0, 0.3, 1.0, 0.0, 1.0], np.float32)
     u = rng.random(R).astype(np.float32)
     _check(lg, "f32", "f32", T, u, oracle_mod, pkg)
-    # one chunk only: three of the four parts of the split form are empty
+    # one chunk only: a row of one part, of whose threads one has anything
     _check(W.f32_to_bf16_bits(lg), "bf16", "bf16", T, u, oracle_mod, pkg, path="split")
     _check(lg.astype(np.float16), "f16", "f16", T, u, oracle_mod, pkg, path="split")
 
