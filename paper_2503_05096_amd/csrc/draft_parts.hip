@@ -543,10 +543,11 @@ hipError_t launch_draft_parts(const void *logits, const float *temperature, cons
     n_parts = n_parts < least ? least : n_parts > most ? most : n_parts;
     const int part_steps = ceil_div(steps, n_parts);
     n_parts = ceil_div(steps, part_steps);
-    // Whether some row may go where its logits are: without out_rows if both start at one address; with them (their values are on the
-    // device) if the logits lie a whole number of rows behind the first destination.
+    // Whether some row may go where its logits are (out_rows is on the device): the rows lie where destinations may be and, with equal
+    // strides, whole rows apart.
     const int64_t apart = (int64_t)(reinterpret_cast<intptr_t>(logits) - reinterpret_cast<intptr_t>(probs));
-    const bool in_place = out_rows ? apart + (d.rows - 1) * lstride >= 0 && (lstride != pstride || apart % pstride == 0) : apart == 0;
+    const bool in_place = apart + (d.rows - 1) * lstride >= 0 && (out_rows || apart <= (d.rows - 1) * pstride) &&
+                          (lstride != pstride || apart % pstride == 0);
     auto launch = [&](auto lt, auto pt) {
         using LT = decltype(lt);
         using PT = decltype(pt);

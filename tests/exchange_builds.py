@@ -23,6 +23,7 @@ def ensure(name: str) -> str:
     if not os.path.exists(out):
         for old in glob.glob(os.path.join(NATIVE, f"libadaspec_{name}_*.so")):
             os.remove(old)
-        build.build_variant(out + ".tmp", name, DEFINES[name], "part_exchange.h")
-        os.replace(out + ".tmp", out)
+        made = f"{out}.{os.getpid()}"
+        build.build_variant(made, name, DEFINES[name], "part_exchange.h")
+        os.replace(made, out)
     return out
