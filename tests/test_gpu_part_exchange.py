@@ -108,6 +108,40 @@ def test_draft_rows_with_a_nan_without_waiting(V, dtype, pkg, impatient):  # noq
     assert torch.equal(want[1], got[1]) and torch.equal(want[2].nan_to_num(-1.0), got[2].nan_to_num(-1.0))
 
 
+@pytest.mark.parametrize("V,dtype", [(32776, "bfloat16"), (128256, "bfloat16"), (262152, "float16")])
+def test_draft_rows_masked_with_the_lowest_number_without_waiting(V, dtype, pkg, impatient):  # noqa: F811
+    import torch
+    x, t, u = _draft_inputs(8, V, getattr(torch, dtype), V + 1)
+    x[:, V // 4:V // 2] = torch.finfo(x.dtype).min
+    x[:, V - 512:] = torch.finfo(x.dtype).min
+
+    def call():
+        got = pkg.draft_sample(x, t, u)
+        torch.cuda.synchronize()
+        return got
+    want = call()
+    assert bool(torch.isfinite(want[0].float()).all()) and bool((want[2][t > 0] > 0).all())
+    assert all(torch.equal(a, b) for a, b in zip(want, impatient(call)))
+
+
+@pytest.mark.parametrize("V,ldt", [(8200, "bf16"), (12288, "bf16"), (128256, "f32")])
+def test_accept_rows_masked_with_the_lowest_number_without_waiting(V, ldt, oracle_mod, pkg, impatient):  # noqa: F811
+    import torch
+    st = _accept_step(20, V, ldt, ldt, 700 + V)
+    lowest = np.uint16(0xFF7F) if ldt == "bf16" else np.finfo(np.float32).min
+    st.target_logits[:, V // 4:3 * V // 4] = lowest
+    st.target_logits[:, V - 512:] = lowest
+    check_accept(st, oracle_mod, pkg)
+    dev = to_device(st, attention=False)
+
+    def call():
+        got = pkg.accept(dev.target_logits, dev.draft_probs, dev.draft_tokens, dev.uniforms, dev.spec_lens, dev.temperature,
+                         max_spec_len=st.max_spec_len)
+        torch.cuda.synchronize()
+        return got
+    assert all(torch.equal(a, b) for a, b in zip(call(), impatient(call)))
+
+
 @pytest.mark.parametrize("R,V,dtype", [(5, 128256, "bfloat16"), (3, 262144, "float32")])
 def test_draft_rows_in_place_without_waiting(R, V, dtype, pkg, impatient):  # noqa: F811
     """Rows over their own logits (and, in the same call, one beside them): nobody reads what another workgroup has overwritten."""
